@@ -440,191 +440,253 @@ __global__ void __launch_bounds__(256) fill_zero(T* __restrict__ p, long count) 
 }
 
 // Gauss-Jordan inverse of one NB x NB diagonal block, no pivoting, blocked by
-// 16.  The block is held as 8 x 8 tiles of 16 x 16 in MFMA accumulator layout:
-// wave w (of 4) owns tile rows 2w and 2w+1.  Step s takes
-// the 16 x 16 pivot tile P = M(s,s) and applies
+// 16.  The block is held as 8 x 8 tiles of 16 x 16 in MFMA accumulator layout;
+// wave w (of 8) owns tile row w.  Step s takes the 16 x 16 pivot tile
+// P = M(s,s) and applies
 //   M(s,s) <- P^-1,   M(s,j) <- P^-1 M(s,j),   M(i,s) <- -M(i,s) P^-1,
 //   M(i,j) <- M(i,j) - M(i,s) P^-1 M(s,j)                 (i, j != s),
 // i.e. the scalar in-place Gauss-Jordan update with a 16 x 16 pivot; after
-// the 8 steps M = A^-1.  P is inverted inside one wave by 16 scalar
-// Gauss-Jordan steps with each lane holding four entries of one row (the
-// pivot row's entries and the pivot column's entry are broadcast with lane
-// shuffles, no barriers; 2.3x faster than one column per lane with lane
-// reads, whose results had to pass through scalar registers); the row products (one tile column
-// per wave) and the rank-16 updates run on the matrix cores, each wave
-// loading its tile-row operand once per step and each tile-column operand
-// once for all its tiles.  Two workgroup barriers per step.
+// the 8 steps M = A^-1.  The 16 scalar steps of a pivot tile are a serial
+// chain (about 3.5k cycles alone), and the updates' 2 NB^3 flops bind one CU's
+// matrix cores for 4.1k cycles per step, so the two run side by side: a ninth
+// wave forms pivot tile s + 1 from the tiles of step s (two products of its
+// own) and inverts it while the others update theirs.  Inside a pivot tile the
+// pivot row is broadcast over the lane groups and the pivot column along each
+// group by lane permutations of the vector pipe, with no LDS round trip on
+// the chain.  128 x 128 FP64 alone: 48.4 -> 35 us per launch against four waves with
+// the pivot's shuffles through LDS between the updates; the rest of the
+// distance is the FP64 vector operations of the pivot waiting behind 64-cycle
+// MFMAs of the waves on the same SIMD.
 // Diagonal dominance of K makes every pivot order stable, so no pivoting is
 // needed; the scalar pivots are the same Schur-complement diagonals as in
 // unblocked elimination and are checked against the singularity threshold.
-constexpr int GJ_WAVES = 4;    // two tile rows per wave; at 254 VGPRs a wave fits on a SIMD beside one GEMM wave
-constexpr int GJ_THREADS = 64 * GJ_WAVES;
+constexpr int GJ_THREADS = 64 * (NB / 16 + 1);
 
-// 1/x: hardware reciprocal refined by Newton steps to full precision
+// 1/x: the hardware reciprocal refined to full precision; with e = 1 - x r
+// the relative error of r, r (1 + e + e^2) leaves e^3
 __device__ __forceinline__ double recip_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = r * (2.0 - x * r);
-  r = r * (2.0 - x * r);
-  return r;
+  const double r = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
 __device__ __forceinline__ float recip_nr(float x) {
   float r = __builtin_amdgcn_rcpf(x);
   return r * (2.0f - x * r);
 }
 
-// value of x in lane `lane` (uniform), broadcast to the wave
-__device__ __forceinline__ double lane_read(double x, int lane) {
-  const long long v = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane(static_cast<int>(v), lane);
-  const int hi = __builtin_amdgcn_readlane(static_cast<int>(v >> 32), lane);
-  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+// 32-bit lane permutations behind the pivot chain: the value of lane Q of each
+// group of 16 lanes, and the 16 lanes of group G in every group
+template <int Q>
+__device__ __forceinline__ unsigned bcast_col32(unsigned x) {
+  return __builtin_amdgcn_update_dpp(x, x, 0x150 + Q, 0xf, 0xf, true);  // row_newbcast:Q
 }
-__device__ __forceinline__ float lane_read(float x, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+template <int G>
+__device__ __forceinline__ unsigned bcast_group32(unsigned x) {
+  const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);  // [0]: lanes 0-31 twice, [1]: 32-63 twice
+  const unsigned y = h[G >> 1];
+  const auto r = __builtin_amdgcn_permlane16_swap(y, y, false, false);  // [0]: even groups twice, [1]: odd ones
+  return r[G & 1];
+}
+template <int Q>
+__device__ __forceinline__ double bcast_col(double x) {
+  const unsigned long long v = __double_as_longlong(x);
+  const unsigned long long lo = bcast_col32<Q>(static_cast<unsigned>(v)), hi = bcast_col32<Q>(static_cast<unsigned>(v >> 32));
+  return __longlong_as_double(static_cast<long long>((hi << 32) | lo));
+}
+template <int Q>
+__device__ __forceinline__ float bcast_col(float x) { return __uint_as_float(bcast_col32<Q>(__float_as_uint(x))); }
+template <int G>
+__device__ __forceinline__ double bcast_group(double x) {
+  const unsigned long long v = __double_as_longlong(x);
+  const unsigned long long lo = bcast_group32<G>(static_cast<unsigned>(v)), hi = bcast_group32<G>(static_cast<unsigned>(v >> 32));
+  return __longlong_as_double(static_cast<long long>((hi << 32) | lo));
+}
+template <int G>
+__device__ __forceinline__ float bcast_group(float x) { return __uint_as_float(bcast_group32<G>(__float_as_uint(x))); }
+
+// w - (column Q of v, broadcast along each group of 16 lanes) * rj
+template <int Q>
+__device__ __forceinline__ void sub_col_times(double (&w)[4], const double (&v)[4], double rj) {
+  // one instruction per element: the broadcast is the multiply-add's own lane
+  // permutation (the waits cover the lane permutations before and after it)
+  __asm__("s_nop 1\n\t"
+          "v_fmac_f64_dpp %0, -%4, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %1, -%5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %2, -%6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+          "v_fmac_f64_dpp %3, -%7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+          "s_nop 1"
+          : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3])
+          : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(rj), "n"(Q));
+}
+template <int Q>
+__device__ __forceinline__ void sub_col_times(float (&w)[4], const float (&v)[4], float rj) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) w[r] = fma(-bcast_col<Q>(v[r]), rj, w[r]);
 }
 
-// orders this wave's LDS writes before its later LDS reads
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// In-place Gauss-Jordan steps Q..15 of a 16 x 16 tile held by one wave in
+// accumulator layout (v[r] = P(orow(l, r), l % 16)); every lane must be active.
+// row is row Q in every lane group, piv = P(Q, Q) and d its reciprocal.  The
+// chain through the 16 reciprocals binds the tile: step Q forms the next
+// pivot and starts its reciprocal from three broadcast entries before the
+// tile itself is updated, and carries the next row along instead of
+// broadcasting it again.
+template <class T, int Q>
+__device__ __forceinline__ void pivot_steps(T (&v)[4], T row, T piv, T d, int l, T& pivots) {
+  // row q sits in lane group grp(q), register reg(q)
+  constexpr auto grp = [](int q) { return sizeof(T) == 8 ? (q & 3) : (q >> 2); };
+  constexpr auto reg = [](int q) { return sizeof(T) == 8 ? (q >> 2) : (q & 3); };
+  const int li = l & 15, lg = l >> 4;
+  T rown = T(0), c = T(0), pn = T(0), dn = T(0);
+  if constexpr (Q < 15) {
+    rown = bcast_group<grp(Q + 1)>(v[reg(Q + 1)]);  // P(Q + 1, li) before this step
+    c = bcast_col<Q>(rown);
+    pn = fma(-c, bcast_col<Q + 1>(row) * d, bcast_col<Q + 1>(rown));
+    dn = recip_nr(pn);
+  }
+  pivots = l == Q ? piv : pivots;
+  const bool own = li == Q;
+  const T rj = own ? d : row * d;  // the new pivot row
+  T w[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) w[r] = own ? T(0) : v[r];
+  sub_col_times<Q>(w, v, rj);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = w[r];
+  v[reg(Q)] = lg == grp(Q) ? rj : w[reg(Q)];
+  if constexpr (Q < 15) pivot_steps<T, Q + 1>(v, fma(-c, rj, own ? T(0) : rown), pn, dn, l, pivots);
 }
 
-template <class T, int NW>
-__device__ __forceinline__ void gj_body(const T* __restrict__ A, long lda, T* __restrict__ out, Scalars* sc) {
+// In-place inverse of such a tile; pivots receives pivot q in lane q.
+template <class T>
+__device__ __forceinline__ void pivot_inverse(T (&v)[4], int l, T& pivots) {
+  const T row = bcast_group<0>(v[0]), piv = bcast_col<0>(row);
+  pivot_steps<T, 0>(v, row, piv, recip_nr(piv), l, pivots);
+}
+
+template <class T>
+struct GjShared {
+  static constexpr int BT = 16;
+  T sC[NB][BT + 2];    // tile column s before the step
+  T sRo[BT][NB + 2];   // tile row s before the step
+  T sR[BT][NB + 2];    // tile row s after it
+  T sP[BT][BT + 1];    // inverse of the pivot tile
+  T sD[BT][BT + 1];    // diagonal tile s + 1 before the step
+};
+
+template <class T>
+__device__ __forceinline__ void gj_body(const T* __restrict__ A, long lda, T* __restrict__ out, Scalars* sc,
+                                        GjShared<T>& sh) {
   typedef typename Mfma<T>::v4 v4;
   constexpr int BT = 16;
   constexpr int NT = NB / BT;
-  constexpr int RPW = NT / NW;        // tile rows per wave
-  static_assert(RPW * NW == NT, "NW must divide 8");
-  constexpr int LC = BT + 2;
-  constexpr int LR = NB + 2;
-  __shared__ T sC[2][NB][LC];
-  __shared__ T sRo[BT][LR];
-  __shared__ T sR[BT][LR];
-  __shared__ T sP[BT][BT + 1];
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int li = l & 15, lg = l >> 4;
-  v4 m[RPW][NT];
+  if (w == NT) {  // the pivot wave; its dependent operations go first
+    __builtin_amdgcn_s_setprio(3);
+    const double tiny = sizeof(T) == 8 ? 1e-11 : 1e-5;
+    int singular = 0;
+    T v[4];
 #pragma unroll
-  for (int rr = 0; rr < RPW; ++rr)
+    for (int r = 0; r < 4; ++r) v[r] = A[static_cast<long>(Mfma<T>::orow(l, r)) * lda + li];
+    for (int s = 0;; ++s) {
+      T pivots = T(1);
+      pivot_inverse(v, l, pivots);
 #pragma unroll
-    for (int bj = 0; bj < NT; ++bj)
+      for (int r = 0; r < 4; ++r) sh.sP[Mfma<T>::orow(l, r)][li] = v[r];
+      __syncthreads();  // the step begins
+      if (s + 1 < NT) {
+        // the next pivot tile: M(s+1, s+1) - M(s+1, s) P^-1 M(s, s+1)
+        v4 t = v4{0, 0, 0, 0}, d;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        m[rr][bj][r] = A[static_cast<long>((w * RPW + rr) * BT + Mfma<T>::orow(l, r)) * lda + bj * BT + li];
-  const double tiny = sizeof(T) == 8 ? 1e-11 : 1e-5;
-  int singular = 0;
-#pragma unroll 1
-  for (int s = 0; s < NT; ++s) {
-    const int cb = s & 1;
-    const int sw = s / RPW, srr = s % RPW;  // owner wave of tile row s, its local row
+        for (int kk = 0; kk < 4; ++kk)
+          t = Mfma<T>::mma(sh.sP[li][Mfma<T>::orow(l, kk)], sh.sRo[Mfma<T>::orow(l, kk)][(s + 1) * BT + li], t);
 #pragma unroll
-    for (int rr = 0; rr < RPW; ++rr) {
-      const int bi = w * RPW + rr;
+        for (int r = 0; r < 4; ++r) d[r] = sh.sD[Mfma<T>::orow(l, r)][li];
 #pragma unroll
-      for (int bj = 0; bj < NT; ++bj) {
-        if (bj == s)
+        for (int kk = 0; kk < 4; ++kk)
+          d = Mfma<T>::mma(-sh.sC[(s + 1) * BT + li][Mfma<T>::orow(l, kk)], t[kk], d);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) sC[cb][bi * BT + Mfma<T>::orow(l, r)][li] = m[rr][bj][r];
-        if (bi == s)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sRo[Mfma<T>::orow(l, r)][bj * BT + li] = m[rr][bj][r];
+        for (int r = 0; r < 4; ++r) v[r] = d[r];
       }
+      const double ap = fabs(static_cast<double>(pivots));
+      singular |= !(ap > tiny && ap < 1e300);
+      __syncthreads();  // the new tile row s is complete; the old row and column have been read
+      if (s + 1 == NT) break;
     }
-    if (w == sw) {
-      wave_lds_sync();
-      // lane (i, q4) = (l % 16, l / 16) holds P(i, 4 q4 .. 4 q4 + 3); each
-      // scalar step broadcasts the pivot row's entries of the lane's four
-      // columns and the pivot column's entry of its row with lane shuffles
-      const int i = li, q4 = lg;
-      T v[4];
+    if (singular) raise_status(&sc->status, RAD_ESINGULAR);
+    return;
+  }
+  v4 m[NT];  // tile row w
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = sRo[i][s * BT + 4 * q4 + u];
+  for (int bj = 0; bj < NT; ++bj)
 #pragma unroll
-      for (int q = 0; q < BT; ++q) {
-        const int qq = q >> 2, qu = q & 3;
-        T r[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) r[u] = __shfl(v[u], q + 16 * q4);  // P(q, 4 q4 + u)
-        const T pc = __shfl(v[qu], i + 16 * qq);                          // P(i, q)
-        const T piv = lane_read(v[qu], q + 16 * qq);                      // P(q, q)
-        T d = recip_nr(piv);
-        if (!(fabs(static_cast<double>(piv)) > tiny) || !(fabs(static_cast<double>(d)) < 1e300)) {
-          singular = 1;
-          d = T(0);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int j = 4 * q4 + u;
-          const T rj = (j == q) ? d : r[u] * d;  // the new pivot row
-          if (i == q) v[u] = rj;
-          else v[u] = fma(-pc, rj, j == q ? T(0) : v[u]);
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) sP[i][4 * q4 + u] = v[u];
-    }
-    __syncthreads();
-    // new tile row s, spread over the waves: R(s, j) = P^-1 Ro(s, j), R(s, s) = P^-1
-    {
-      T pa[4];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) pa[kk] = sP[li][4 * kk + lg];
-#pragma unroll
-      for (int jj = 0; jj < RPW; ++jj) {
-        const int bj = w * RPW + jj;
-        if (bj == s) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sR[Mfma<T>::orow(l, r)][bj * BT + li] = sP[Mfma<T>::orow(l, r)][li];
-        } else {
-          v4 acc = v4{0, 0, 0, 0};
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk) acc = Mfma<T>::mma(pa[kk], sRo[4 * kk + lg][bj * BT + li], acc);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) sR[Mfma<T>::orow(l, r)][bj * BT + li] = acc[r];
-        }
-      }
-    }
-    __syncthreads();
-    // rank-16 update of the other tile rows; tile column s becomes -M(i,s) P^-1;
-    // tile row s takes R(s, :)
-    T av[RPW][4];
-#pragma unroll
-    for (int rr = 0; rr < RPW; ++rr)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) av[rr][kk] = -sC[cb][(w * RPW + rr) * BT + li][4 * kk + lg];
+    for (int r = 0; r < 4; ++r) m[bj][r] = A[static_cast<long>(w * BT + Mfma<T>::orow(l, r)) * lda + bj * BT + li];
+  // tile column q, tile row q and the diagonal tile q + 1 for step q
+  auto stage = [&](int q) {
 #pragma unroll
     for (int bj = 0; bj < NT; ++bj) {
-      T bv[4];
+      if (bj == q)
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) bv[kk] = sR[4 * kk + lg][bj * BT + li];
+        for (int r = 0; r < 4; ++r) sh.sC[w * BT + Mfma<T>::orow(l, r)][li] = m[bj][r];
+      if (w == q)
 #pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) {
-        if (w * RPW + rr == s) {
+        for (int r = 0; r < 4; ++r) sh.sRo[Mfma<T>::orow(l, r)][bj * BT + li] = m[bj][r];
+      if (bj == q + 1 && w == q + 1)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) m[rr][bj][r] = sR[Mfma<T>::orow(l, r)][bj * BT + li];
-          continue;
+        for (int r = 0; r < 4; ++r) sh.sD[Mfma<T>::orow(l, r)][li] = m[bj][r];
+    }
+  };
+  stage(0);
+#pragma unroll 1
+  for (int s = 0; s < NT; ++s) {
+    __syncthreads();
+    // the new tile row s, one tile per wave: R(s, j) = P^-1 Ro(s, j), R(s, s) = P^-1
+    T av[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) av[kk] = -sh.sC[w * BT + li][4 * kk + lg];
+    if (w == s) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sh.sR[Mfma<T>::orow(l, r)][w * BT + li] = sh.sP[Mfma<T>::orow(l, r)][li];
+    } else {
+      v4 acc = v4{0, 0, 0, 0};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        acc = Mfma<T>::mma(sh.sP[li][4 * kk + lg], sh.sRo[4 * kk + lg][w * BT + li], acc);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sh.sR[Mfma<T>::orow(l, r)][w * BT + li] = acc[r];
+    }
+    __syncthreads();
+    // rank-16 update of the other tile rows; tile column s becomes -M(w, s) P^-1
+    if (w == s) {
+#pragma unroll
+      for (int bj = 0; bj < NT; ++bj)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[bj][r] = sh.sR[Mfma<T>::orow(l, r)][bj * BT + li];
+    } else {
+#pragma unroll
+      for (int b2 = 0; b2 < NT; b2 += 2) {
+        if (b2 == s) m[b2] = v4{0, 0, 0, 0};
+        if (b2 + 1 == s) m[b2 + 1] = v4{0, 0, 0, 0};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          m[b2] = Mfma<T>::mma(av[kk], sh.sR[4 * kk + lg][b2 * BT + li], m[b2]);
+          m[b2 + 1] = Mfma<T>::mma(av[kk], sh.sR[4 * kk + lg][(b2 + 1) * BT + li], m[b2 + 1]);
         }
-        if (bj == s) m[rr][bj] = v4{0, 0, 0, 0};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) m[rr][bj] = Mfma<T>::mma(av[rr][kk], bv[kk], m[rr][bj]);
       }
     }
+    stage(s + 1);
   }
 #pragma unroll
-  for (int rr = 0; rr < RPW; ++rr)
+  for (int bj = 0; bj < NT; ++bj)
 #pragma unroll
-    for (int bj = 0; bj < NT; ++bj)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        out[((w * RPW + rr) * BT + Mfma<T>::orow(l, r)) * NB + bj * BT + li] = m[rr][bj][r];
-  if (singular) raise_status(&sc->status, RAD_ESINGULAR);
+    for (int r = 0; r < 4; ++r) out[(w * BT + Mfma<T>::orow(l, r)) * NB + bj * BT + li] = m[bj][r];
 }
 template <class T>
 __global__ void __launch_bounds__(GJ_THREADS)
 gj_inverse(const T* __restrict__ A, long lda, T* __restrict__ out, Scalars* sc) {
-  gj_body<T, GJ_WAVES>(A, lda, out, sc);
+  __shared__ GjShared<T> sh;
+  gj_body<T>(A, lda, out, sc, sh);
 }
 
 // many diagonal blocks (of different problems) in one launch
@@ -638,8 +700,9 @@ struct GjJob {
 
 template <class T>
 __global__ void __launch_bounds__(GJ_THREADS) gj_batched(const GjJob<T>* __restrict__ jobs) {
+  __shared__ GjShared<T> sh;
   const GjJob<T> jb = jobs[blockIdx.x];
-  gj_body<T, GJ_WAVES>(jb.A, jb.lda, jb.out, jb.sc);
+  gj_body<T>(jb.A, jb.lda, jb.out, jb.sc, sh);
 }
 
 // ----------------------------------------------------- panel inverses ---
