@@ -190,15 +190,9 @@ hipError_t factor_update_emu(const EmuWork& ew, const Fact<double>& f, int c0, i
 // side stream s2 meanwhile.  Panel p+1's row-block forward substitution waits
 // for that part (event), and the call joins s2 back into s at the end.  The
 // arithmetic and its order per element are the same as without the split.
-//
-// xs (nullable, np x NB elements): scratch for the L-block products
-// X = A21 D^-1.  With it they are written out of place and copied back, so
-// they take 64 x 64 tiles (two column tiles per row block, four times the
-// workgroups of the in-place 128 x 128 form) on the chain of diagonal blocks;
-// both forms round identically.
 template <class T>
 hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc, hipStream_t s,
-                          const EmuWork* ew = nullptr, T* xs = nullptr) {
+                          const EmuWork* ew = nullptr) {
   const long ldk = f.ldk;
   T* kf = f.kf;
   SideStream* ss = nullptr;
@@ -222,17 +216,8 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
       const int r1 = k0 + NB;
       if (r1 >= f.np) break;
       T* x = kf + static_cast<long>(r1) * ldk + k0;
-      GemmArgs<T> a = gemm_args<T>(x, ldk, f.np - r1, NB, T(1), T(0));
-      if (xs) {
-        gemm_add_segment<T>(a, dk, NB, xs, NB, NB);
-        RAD_GEMM(a, false);
-        hipLaunchKernelGGL(copy_nb_cols<T>, dim3(static_cast<unsigned>(ceil_div(f.np - r1, 16))), dim3(256), 0, s,
-                           xs, static_cast<long>(NB), x, ldk, f.np - r1);
-      } else {
-        gemm_add_segment<T>(a, dk, NB, x, ldk, NB);
-        a.inplace = 1;  // X overwrites the A21 it reads
-        RAD_GEMM(a, false);
-      }
+      e = lblock_run<T>(x, ldk, dk, f.np - r1, s);
+      if (e != hipSuccess) return e;
       if (r1 < c1) {
         GemmArgs<T> u = update_args<T>(x, ldk, f.np - r1, NB);
         gemm_add_segment<T>(u, kf + static_cast<long>(k0) * ldk + r1, ldk, kf + static_cast<long>(r1) * ldk + r1,
@@ -339,14 +324,18 @@ hipError_t forward_only(const Fact<T>& f, T* Y, long ldy, int wy, hipStream_t s)
   return hipSuccess;
 }
 
-// W_p = U_pp^-1 and V_p = L_pp^-1 of every panel (seven launches).
+// W_p = U_pp^-1 and V_p = L_pp^-1 of every panel (at most seven launches).
 template <class T>
 hipError_t panel_inverses(const Fact<T>& f, T* tmp, long ldt, hipStream_t s) {
   TriJob<T> j{f.kf, f.ldk, f.dinv, f.np, f.W, f.V, f.ldw, tmp, ldt};
   hipLaunchKernelGGL(tri_init<T>, dim3(f.np), dim3(256), 0, s, j);
-  for (int b = NB; b < NB2; b *= 2)
-    for (int stage = 0; stage < 2; ++stage)
-      hipLaunchKernelGGL(tri_level<T>, dim3(tri_level_blocks(f.P2, b)), dim3(256), 0, s, j, b, stage);
+  for (int b = NB; b < NB2 && b < f.np; b *= 2)  // pairs of b-wide blocks exist
+    for (int stage = 0; stage < 2; ++stage) {
+      if (tri_level_blocks(f.P2, b, 64) < GEMM_TILE32_BELOW)
+        hipLaunchKernelGGL((tri_level<T, 32>), dim3(tri_level_blocks(f.P2, b, 32)), dim3(256), 0, s, j, b, stage);
+      else
+        hipLaunchKernelGGL((tri_level<T, 64>), dim3(tri_level_blocks(f.P2, b, 64)), dim3(256), 0, s, j, b, stage);
+    }
   return hipGetLastError();
 }
 
@@ -550,8 +539,7 @@ struct GebWork {
   double* part; // grad_eps partial sums (adjoint)
   EmuWork emu;  // digit buffers (RAD_PREC_FP64_I8)
   void* scr;    // (T) two panels of right-hand sides (2 NB2 x ldy), shared with
-                // the panel-inverse products (tri_tmp_elems, ld ldt) and the
-                // factorization's L-block products (np x NB)
+                // the panel-inverse products (tri_tmp_elems, ld ldt)
   long ldt;
   size_t bytes;
   bool ok;
@@ -661,7 +649,7 @@ extern "C" int32_t rad_gebhart_ref(const double* F, int64_t n, int64_t ldf, cons
     double* Y = static_cast<double*>(w.y);
     hipLaunchKernelGGL(geb_form<double>, dim3(f.np), dim3(256), 0, s, F, static_cast<long>(ldf), ni, eps,
                        rho, f.kf, f.ldk, f.np, Y, w.ldy, w.sc);
-    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, ni + 1, w.sc, s, ew, static_cast<double*>(w.scr)));
+    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, ni + 1, w.sc, s, ew));
     RAD_HIP_CHECK(panel_inverses<double>(f, static_cast<double*>(w.scr), w.ldt, s));
     RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, ni + 1, static_cast<double*>(w.scr), w.ldy, s, ew));
     hipLaunchKernelGGL((copy_block<double, double>), dim3(ni), dim3(256), 0, s, Y, w.ldy, ni, B,
@@ -671,7 +659,7 @@ extern "C" int32_t rad_gebhart_ref(const double* F, int64_t n, int64_t ldf, cons
     float* Y = static_cast<float*>(w.y);
     hipLaunchKernelGGL(geb_form<float>, dim3(f.np), dim3(256), 0, s, F, static_cast<long>(ldf), ni, eps,
                        rho, f.kf, f.ldk, f.np, Y, w.ldy, w.sc);
-    RAD_HIP_CHECK(factor_forward<float>(f, Y, w.ldy, ni + 1, w.sc, s, nullptr, static_cast<float*>(w.scr)));
+    RAD_HIP_CHECK(factor_forward<float>(f, Y, w.ldy, ni + 1, w.sc, s));
     RAD_HIP_CHECK(panel_inverses<float>(f, static_cast<float*>(w.scr), w.ldt, s));
     RAD_HIP_CHECK(back_solve<float>(f, Y, w.ldy, ni + 1, static_cast<float*>(w.scr), w.ldy, s));
     if (ir_max > 0) {
@@ -761,7 +749,7 @@ extern "C" int32_t rad_steady_temperature(const double* Y, int64_t n, int64_t ld
   hipLaunchKernelGGL(scalars_init, dim3(1), dim3(64), 0, s, w.sc);
   hipLaunchKernelGGL(ss_form, dim3(f.np), dim3(256), 0, s, Y, static_cast<long>(ldy), ni, weight, Q,
                      static_cast<long>(ldq), mi, t_fixed, xs, sigma, f.kf, f.ldk, f.np, X, w.ldy, w.sc);
-  RAD_HIP_CHECK(factor_forward<double>(f, X, w.ldy, SS_RHS, w.sc, s, ew, static_cast<double*>(w.scr)));
+  RAD_HIP_CHECK(factor_forward<double>(f, X, w.ldy, SS_RHS, w.sc, s, ew));
   RAD_HIP_CHECK(panel_inverses<double>(f, static_cast<double*>(w.scr), w.ldt, s));
   RAD_HIP_CHECK(back_solve<double>(f, X, w.ldy, SS_RHS, static_cast<double*>(w.scr), w.ldy, s, ew));
   hipLaunchKernelGGL(ss_output, dim3(static_cast<unsigned>(ceil_div(n * m, 256))), dim3(256), 0, s, X, w.ldy, ni,
@@ -852,7 +840,7 @@ extern "C" int32_t rad_enforce_lsq(const double* F, int64_t n, int64_t ldf, cons
     hipLaunchKernelGGL(fill_zero<int>, dim3(1), dim3(64), 0, s, l.negatives, 1L);
     hipLaunchKernelGGL(lsq_schur, dim3(static_cast<unsigned>(ceil_div(f.np, LSQ_RB))), dim3(256), 0, s, F,
                        static_cast<long>(ldf), ni, omega, l.mask[cur], f.kf, f.ldk, f.np, Y, w.ldy);
-    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, LSQ_RHS, w.sc, s, ew, static_cast<double*>(w.scr)));
+    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, LSQ_RHS, w.sc, s, ew));
     RAD_HIP_CHECK(panel_inverses<double>(f, static_cast<double*>(w.scr), w.ldt, s));
     RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, LSQ_RHS, static_cast<double*>(w.scr), w.ldy, s, ew));
     hipLaunchKernelGGL(lsq_update, ugrid, dim3(256), 0, s, F, static_cast<long>(ldf), ni, omega, l.mask[cur], Y,

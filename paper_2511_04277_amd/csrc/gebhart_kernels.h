@@ -795,13 +795,11 @@ __host__ __device__ inline bool tri_level_args(const TriJob<T>& j, int b, int st
   return true;
 }
 
-// Grid: panels x pairs x 2 matrices x (b/64)^2 tiles of 64 x 64 (the joins
-// are short latency-bound products, so the smaller tile spreads them over
-// four times the CUs).
-constexpr int TRI_TS = 64;
-template <class T>
-__global__ void __launch_bounds__(256, 4) tri_level(TriJob<T> j, int b, int stage) {
-  const int tpg = (b / TRI_TS) * (b / TRI_TS);
+// Grid: panels x pairs x 2 matrices x (b/TS)^2 tiles of TS x TS (the joins
+// are short latency-bound products, so small tiles spread them over the CUs).
+template <class T, int TS>
+__global__ void __launch_bounds__(256, TS == 64 ? 4 : 2) tri_level(TriJob<T> j, int b, int stage) {
+  const int tpg = (b / TS) * (b / TS);
   const int nq = NB2 / (2 * b);
   int blk = blockIdx.x;
   const int tile = blk % tpg;
@@ -810,13 +808,91 @@ __global__ void __launch_bounds__(256, 4) tri_level(TriJob<T> j, int b, int stag
   blk /= 2;
   GemmArgs<T> g;
   if (!tri_level_args<T>(j, b, stage, blk / nq, blk % nq, mat, g)) return;
-  const int ntx = (g.N[0] + TRI_TS - 1) / TRI_TS, nty = (g.M + TRI_TS - 1) / TRI_TS;
+  const int ntx = (g.N[0] + TS - 1) / TS, nty = (g.M + TS - 1) / TS;
   if (tile >= ntx * nty) return;
-  gemm_tile<T, false, TRI_TS>(g, tile % ntx, tile / ntx);
+  if constexpr (TS == 64) {
+    gemm_tile<T, false, 64>(g, tile % ntx, tile / ntx);
+  } else {
+    __shared__ Tile32<T, false> sh;
+    gemm_tile32<T, false>(g, tile % ntx, tile / ntx, sh);
+  }
 }
 
-inline unsigned tri_level_blocks(int P2, int b) {
-  return static_cast<unsigned>(P2) * (NB2 / (2 * b)) * 2 * (b / TRI_TS) * (b / TRI_TS);
+inline unsigned tri_level_blocks(int P2, int b, int ts) {
+  return static_cast<unsigned>(P2) * (NB2 / (2 * b)) * 2 * (b / ts) * (b / ts);
+}
+
+// L block X = A21 D^-1 of one diagonal block, in place: rows [0, 16 RB grid)
+// of A21 (NB columns).  A workgroup owns whole rows, so it may overwrite them
+// once they are staged: no scratch copy of X and no launch to copy it back
+// (one product in scratch and the copy took 16 us a block, this 6 us at up to
+// 4096 rows).  Wave w forms columns 32 w .. 32 w + 31; its D^-1 operand (the
+// same for every workgroup, so it comes from L2) is loaded into registers
+// whole, in flight together with the staging of A21.  The products of an
+// output run in gemm_tile's order, so both round alike.
+template <class T, int RB>
+__global__ void __launch_bounds__(256, 2)
+lblock_inplace(T* __restrict__ A, long lda, const T* __restrict__ D) {
+  typedef typename Mfma<T>::v4 v4;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int KC = GemmCfg<T>::KC, PV = 16 / sizeof(T), R = 16 * RB;
+  __shared__ T sA[R][NB + 2];
+  const int t = threadIdx.x, l = t & 63, li = l & 15, lg = l >> 4, wc = (t >> 6) * 32;
+  T* a0 = A + static_cast<long>(blockIdx.x) * R * lda;
+  constexpr int NV = R * NB / PV / 256;
+  vec ra[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int p = t + 256 * q;
+    ra[q] = *reinterpret_cast<const vec*>(a0 + static_cast<long>(p / (NB / PV)) * lda + (p % (NB / PV)) * PV);
+  }
+  T fb[NB / 4][2];
+#pragma unroll
+  for (int q = 0; q < NB / 4; ++q) {
+    const int k = q / (KC / 4) * KC + lg * (KC / 4) + q % (KC / 4);
+#pragma unroll
+    for (int y = 0; y < 2; ++y) fb[q][y] = D[k * NB + wc + 16 * y + li];
+  }
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int p = t + 256 * q;
+    *reinterpret_cast<vec*>(&sA[p / (NB / PV)][(p % (NB / PV)) * PV]) = ra[q];
+  }
+  __syncthreads();  // every row is staged: its place in A may be overwritten
+  v4 acc[RB][2];
+#pragma unroll
+  for (int x = 0; x < RB; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y) acc[x][y] = v4{0, 0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < NB / 4; ++q) {
+    const int k = q / (KC / 4) * KC + lg * (KC / 4) + q % (KC / 4);
+#pragma unroll
+    for (int x = 0; x < RB; ++x) {
+      const T fa = sA[16 * x + li][k];
+#pragma unroll
+      for (int y = 0; y < 2; ++y) acc[x][y] = Mfma<T>::mma(fa, fb[q][y], acc[x][y]);
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < RB; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        a0[static_cast<long>(16 * x + Mfma<T>::orow(l, r)) * lda + wc + 16 * y + li] = acc[x][y][r];
+}
+
+// rows: a multiple of NB.  Past 4096 rows (one workgroup per CU at 16 rows)
+// 32 rows per workgroup halve the reads of D^-1.
+template <class T>
+inline hipError_t lblock_run(T* A, long lda, const T* D, int rows, hipStream_t s) {
+  ProfScope prof(s, gemm_prof_kind<T>(false), 2.0 * rows * NB * NB, sizeof(T) * (2.0 * rows + NB) * NB);
+  if (rows > 4096)
+    hipLaunchKernelGGL((lblock_inplace<T, 2>), dim3(static_cast<unsigned>(rows / 32)), dim3(256), 0, s, A, lda, D);
+  else
+    hipLaunchKernelGGL((lblock_inplace<T, 1>), dim3(static_cast<unsigned>(rows / 16)), dim3(256), 0, s, A, lda, D);
+  return hipGetLastError();
 }
 
 // dst rows [0, rows) <- src, columns < cols (same precision)
@@ -835,18 +911,6 @@ copy_rows(const T* __restrict__ src, long lds, T* __restrict__ dst, long ldd, in
       if (j < cols) dst[i * ldd + j] = v[u];
     }
   }
-}
-
-// dst rows [0, rows) <- src, NB columns; 16 rows per workgroup, each thread
-// 8 consecutive entries
-template <class T>
-__global__ void __launch_bounds__(256)
-copy_nb_cols(const T* __restrict__ src, long lds, T* __restrict__ dst, long ldd, int rows) {
-  const long r = static_cast<long>(blockIdx.x) * 16 + (threadIdx.x >> 4);
-  if (r >= rows) return;
-  const int c = (threadIdx.x & 15) * (NB / 16);
-#pragma unroll
-  for (int j = 0; j < NB / 16; ++j) dst[r * ldd + c + j] = src[r * lds + c + j];
 }
 
 // dst (D, rows < n, cols <= n) <- src (S)

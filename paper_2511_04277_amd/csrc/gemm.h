@@ -302,6 +302,105 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T>& g, int bx, int by) 
       }
 }
 
+// One 32 x 32 output tile for products with too few 64 x 64 tiles to fill the
+// chip (the K = 128 updates of the factorization chain, the solves of small
+// models): four times the workgroups, each wave one 16 x 16 block.  A lone
+// tile is bound by latency, so a whole 128-deep K stage of both operands is
+// loaded at once (one memory round trip instead of one per 16 k) and the next
+// stage's loads run under the products.  The products of an output run in the
+// same order as in gemm_tile, so every tile shape rounds alike.
+// K must be a multiple of GEMM_KS (contract of gemm_tile otherwise).
+constexpr int GEMM_KS = 128;
+
+template <class T, bool TRANS_A>
+struct Tile32 {
+  static constexpr int TS = 32, KS = GEMM_KS;
+  // rows of 16-byte aligned runs; 36 elements shift the rows that one fragment
+  // read touches by half the banks
+  static constexpr int LA = TRANS_A ? TS + 4 : KS + 2, RA = TRANS_A ? KS : TS;
+  static constexpr int LB = TS + 4;
+  T a[RA][LA];
+  T b[KS][LB];
+};
+
+template <class T, bool TRANS_A>
+__device__ __forceinline__ void gemm_tile32(const GemmArgs<T>& g, int bx, int by, Tile32<T, TRANS_A>& sh) {
+  typedef typename Mfma<T>::v4 v4;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int TS = 32, KS = GEMM_KS, KC = GemmCfg<T>::KC, PV = 16 / sizeof(T);
+  constexpr int NV = TS * KS / PV / 256;  // 16-byte pieces of each slab per thread
+  const int nt0 = g.N[0] > 0 ? (g.N[0] + TS - 1) / TS : 0;
+  int ct = bx;
+  int seg = 0;
+  if (ct >= nt0) {
+    seg = 1;
+    ct -= nt0;
+  }
+  const T* __restrict__ A = g.A;
+  const T* __restrict__ Bm = g.B[seg];
+  T* __restrict__ Cm = g.C[seg];
+  const long lda = g.lda, ldb = g.ldb[seg], ldc = g.ldc[seg];
+  const int N = g.N[seg], M = g.M, K = g.K;
+  const int m0 = by * TS, n0 = ct * TS;
+  const int t = threadIdx.x, l = t & 63, li = l & 15, lg = l >> 4;
+  const int wr = (t >> 7) * 16, wc = ((t >> 6) & 1) * 16;
+  const int mb = (m0 / GEMM_TILE) * GEMM_TILE;
+  const int kbeg = g.tri == 1 ? mb : 0;
+  const int kend = g.tri == 2 ? min(K, mb + GEMM_TILE) : K;
+  vec ra[NV], rb[NV];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int p = t + 256 * q;
+      if (!TRANS_A)
+        ra[q] = *reinterpret_cast<const vec*>(A + static_cast<long>(m0 + p / (KS / PV)) * lda + k0 + (p % (KS / PV)) * PV);
+      else
+        ra[q] = *reinterpret_cast<const vec*>(A + static_cast<long>(k0 + p / (TS / PV)) * lda + m0 + (p % (TS / PV)) * PV);
+      rb[q] = *reinterpret_cast<const vec*>(Bm + static_cast<long>(k0 + p / (TS / PV)) * ldb + n0 + (p % (TS / PV)) * PV);
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int p = t + 256 * q;
+      constexpr int AP = TRANS_A ? TS / PV : KS / PV;
+      *reinterpret_cast<vec*>(&sh.a[p / AP][(p % AP) * PV]) = ra[q];
+      *reinterpret_cast<vec*>(&sh.b[p / (TS / PV)][(p % (TS / PV)) * PV]) = rb[q];
+    }
+  };
+  if (kbeg < kend) load(kbeg);
+  T cv[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    // clamped address: no bounds branch around the load
+    const int i = min(m0 + wr + Mfma<T>::orow(l, r), M - 1), j = min(n0 + wc + li, N - 1);
+    cv[r] = g.beta != T(0) ? Cm[static_cast<long>(i) * ldc + j] : T(0);
+  }
+  v4 acc = v4{0, 0, 0, 0};
+  for (int k0 = kbeg; k0 < kend; k0 += KS) {
+    if (k0 > kbeg) __syncthreads();  // the previous stage has been read
+    store();
+    __syncthreads();
+    if (k0 + KS < kend) load(k0 + KS);
+#pragma unroll
+    for (int c = 0; c < KS / KC; ++c)
+#pragma unroll
+      for (int s = 0; s < KC / 4; ++s) {
+        const int k = c * KC + lg * (KC / 4) + s;
+        const T fa = TRANS_A ? sh.a[k][wr + li] : sh.a[wr + li][k];
+        acc = Mfma<T>::mma(fa, sh.b[k][wc + li], acc);
+      }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = m0 + wr + Mfma<T>::orow(l, r), j = n0 + wc + li;
+    if (i < M && j < N) {
+      const T ax = g.alpha * acc[r];
+      Cm[static_cast<long>(i) * ldc + j] = g.beta != T(0) ? fma(g.beta, cv[r], ax) : ax;
+    }
+  }
+}
+
 // Tile order.  The hardware hands workgroup k of a launch to XCD k % 8, and
 // each XCD has its own L2.  The dispatch index is first remapped so that each
 // XCD owns a contiguous range of logical tiles, then the logical tiles are
@@ -339,6 +438,17 @@ __global__ void __launch_bounds__(256, TS == GEMM_TILE ? 2 : 4) gemm_lds(GemmArg
   gemm_tile<T, TRANS_A, TS>(g, bx, by);
 }
 
+template <class T, bool TRANS_A>
+__global__ void __launch_bounds__(256, 2) gemm_lds32(GemmArgs<T> g) {
+  __shared__ Tile32<T, TRANS_A> sh;
+  const int nt0 = g.N[0] > 0 ? (g.N[0] + 31) / 32 : 0;
+  const int nt1 = (g.nseg > 1 && g.N[1] > 0) ? (g.N[1] + 31) / 32 : 0;
+  const int ntx = nt0 + nt1, nty = (g.M + 31) / 32;
+  int bx, by;
+  grouped_tile(xcd_contiguous(blockIdx.x, ntx * nty), ntx, nty, g.tri ? nty : TILE_GROUP, bx, by);
+  gemm_tile32<T, TRANS_A>(g, bx, by, sh);
+}
+
 // Runtime choice of the tile: a product with fewer than small_tile_below
 // 128 x 128 tiles (precision index 0 = FP64, 1 = FP32) runs with 64 x 64
 // tiles.  Set by rad_tuning_set (tuning.cpp), chosen by the autotuner.
@@ -347,6 +457,14 @@ struct GemmTuning {
   int side_chunk_tiles;  // row chunks of the side-stream trailing update (0: one launch)
 };
 GemmTuning& gemm_tuning();
+
+// Products with fewer 64 x 64 tiles than this take 32 x 32 tiles.  One 64 x 64
+// tile per CU needs 10.4 us at K = 128 and 48 us at K = 1024 however few there
+// are; in 32 x 32 tiles the same product takes 4.8-5.3 us and 19-21 us up to
+// 64 tiles, 7.2 us and 33 us (against 11.2 and 50 us) at 128 tiles, and 12.4 us
+// and 60 us (against 11.7 and 52 us) at 196, where the operands' extra reads
+// outweigh the idle CUs.
+constexpr int GEMM_TILE32_BELOW = 160;
 
 // Host: number of 128 x 128 tiles of a product (fills g.ntile).
 template <class T>
@@ -401,6 +519,15 @@ inline hipError_t launch_gemm(const GemmArgs<T>& a0, bool trans_a, hipStream_t s
   const int big = gemm_tiles<T>(a);
   if (big == 0) return hipSuccess;
   ProfScope prof(s, gemm_prof_kind<T>(trans_a), gemm_flops(a), gemm_bytes(a));
+  const int tiles64 = tiles_x<T, 64>(a) * ((a.M + 63) / 64);
+  if (!a.inplace && a.K % GEMM_KS == 0 && tiles64 < GEMM_TILE32_BELOW) {
+    const unsigned grid = static_cast<unsigned>(tiles_x<T, 32>(a)) * static_cast<unsigned>((a.M + 31) / 32);
+    if (trans_a)
+      hipLaunchKernelGGL((gemm_lds32<T, true>), dim3(grid), dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL((gemm_lds32<T, false>), dim3(grid), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   const bool small = !a.inplace && big < gemm_tuning().small_tile_below[sizeof(T) == 8 ? 0 : 1];
   if (small) {
     const unsigned grid = static_cast<unsigned>(tiles_x<T, 64>(a)) * static_cast<unsigned>((a.M + 63) / 64);
