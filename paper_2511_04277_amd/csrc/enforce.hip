@@ -34,6 +34,7 @@ struct EnfLayout {
   double* blkmax;
   double* finred;
   double* partial;
+  EnfArrivals* arr;
   size_t bytes;
   bool ok;
 };
@@ -46,8 +47,9 @@ EnfLayout enf_layout(void* work, size_t work_bytes, int64_t n) {
   l.scale = cv.take<double>(static_cast<size_t>(n));
   l.inv_area = cv.take<double>(static_cast<size_t>(n));
   l.blkmax = cv.take<double>(static_cast<size_t>(t * (t + 1)));
-  l.finred = cv.take<double>(static_cast<size_t>(3 * fin_blocks(n)));
+  l.finred = cv.take<double>(static_cast<size_t>(std::max<int64_t>(3 * fin_blocks(n), 8 * t)));
   l.partial = cv.take<double>(static_cast<size_t>((t + 1) * n));
+  l.arr = cv.take<EnfArrivals>(1);
   l.bytes = cv.used;
   l.ok = cv.ok;
   return l;
@@ -86,6 +88,70 @@ int32_t enforce_check_args(const char* who, double* F, int64_t n, int64_t ldf, c
   return RAD_OK;
 }
 
+// Tile pairs that the current device holds at once with per_cu = 1 or 2
+// workgroups per CU (0: no cooperative launches), looked up once per device.
+long resident_limit(int per_cu) {
+  static std::atomic<long> limit[64][2];  // limit + 1; 0: not looked up yet
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  long v = limit[dev][per_cu - 1].load(std::memory_order_relaxed);
+  if (v == 0) {
+    int coop = 0, cus = 0, per = 0;
+    const bool ok =
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        (per_cu == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, enf_resident<1>, ENF_THREADS, 0)
+                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, enf_resident<2>, ENF_THREADS, 0)) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    v = 1 + (ok ? static_cast<long>(cus) * std::min(per, per_cu) : 0L);
+    limit[dev][per_cu - 1].store(v, std::memory_order_relaxed);
+  }
+  return v - 1;
+}
+
+// Whether the stream is being captured (or cannot be asked): a cooperative
+// launch is not recorded into graphs.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+// One sweep and one finalize launch per iteration, F streamed through.
+int32_t enforce_streamed(const EnfInst& in, double tol, int32_t max_iter, hipStream_t s) {
+  // tol mode: launch iterations in batches; a converged flag makes the rest
+  // of a batch exit at once, so the stop is exact without a sync per step.
+  const int batch = tol > 0.0 ? 8 : max_iter;
+  int launched = 0;
+  while (launched < max_iter) {
+    int nb = std::min(batch, max_iter - launched);
+    for (int k = 0; k < nb; ++k) {
+      int it = launched + k;
+      {
+        ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, 16.0 * static_cast<double>(in.n) * (in.n + 1));
+        hipLaunchKernelGGL(enf_sweep, dim3(static_cast<unsigned>(in.pairs)), dim3(ENF_THREADS), 0, s, in,
+                           it == 0 ? 1 : 0);
+      }
+      hipLaunchKernelGGL(enf_finalize, dim3(static_cast<unsigned>(fin_blocks(in.n))), dim3(256), 0, s, in, tol);
+    }
+    RAD_HIP_CHECK(hipGetLastError());
+    launched += nb;
+    if (tol > 0.0 && launched < max_iter) {
+      int conv = 0, st = 0;
+      RAD_HIP_CHECK(hipMemcpyAsync(&conv, &in.ctrl->converged, sizeof(int), hipMemcpyDeviceToHost, s));
+      RAD_HIP_CHECK(hipMemcpyAsync(&st, &in.ctrl->status, sizeof(int), hipMemcpyDeviceToHost, s));
+      RAD_HIP_CHECK(hipStreamSynchronize(s));
+      if (conv || st < 0) break;
+    }
+  }
+  hipLaunchKernelGGL(enf_apply_scale, dim3(static_cast<unsigned>(in.n)), dim3(256), 0, s, in);
+  RAD_HIP_CHECK(hipGetLastError());
+  return RAD_OK;
+}
+
 // The iteration itself, on scratch laid out by enf_layout (either the
 // caller's workspace or the library's static scratch).
 int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const double* area,
@@ -110,34 +176,33 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.blkmax = l.blkmax;
   in.finred = l.finred;
   in.ctrl = l.ctrl;
+  in.arr = l.arr;
   hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
   hipLaunchKernelGGL(enf_inv_area, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, in);
-  // tol mode: launch iterations in batches; a converged flag makes the rest
-  // of a batch exit at once, so the stop is exact without a sync per step.
-  const int batch = tol > 0.0 ? 8 : max_iter;
-  int launched = 0;
-  while (launched < max_iter) {
-    int nb = std::min(batch, max_iter - launched);
-    for (int k = 0; k < nb; ++k) {
-      int it = launched + k;
-      {
-        ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, 16.0 * static_cast<double>(n) * (n + 1));
-        hipLaunchKernelGGL(enf_sweep, dim3(static_cast<unsigned>(pairs)), dim3(ENF_THREADS), 0, s, in,
-                           it == 0 ? 1 : 0);
+  // one tile needs no co-operation; a resident grid does, which a capture does
+  // not record (the iteration bound keeps the arrival counters in range)
+  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(2) && max_iter <= (1 << 20) && !capturing(s));
+  if (resident) {
+    ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, 16.0 * static_cast<double>(n) * (n + 1));
+    if (pairs == 1) {
+      hipLaunchKernelGGL(enf_single, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
+    } else {
+      hipLaunchKernelGGL(enf_arrivals_init, dim3(1), dim3(64), 0, s, l.arr);
+      void* args[] = {&in, &tol, &max_iter};
+      const void* k = pairs <= resident_limit(1) ? reinterpret_cast<const void*>(enf_resident<1>)
+                                                 : reinterpret_cast<const void*>(enf_resident<2>);
+      const hipError_t e = hipLaunchCooperativeKernel(k,
+                                                      dim3(static_cast<unsigned>(pairs)), dim3(ENF_THREADS), args, 0, s);
+      if (e != hipSuccess) {  // nothing was enqueued: one launch per step instead
+        (void)hipGetLastError();
+        resident = false;
       }
-      hipLaunchKernelGGL(enf_finalize, dim3(static_cast<unsigned>(fin_blocks(n))), dim3(256), 0, s, in, tol);
-    }
-    RAD_HIP_CHECK(hipGetLastError());
-    launched += nb;
-    if (tol > 0.0 && launched < max_iter) {
-      int conv = 0, st = 0;
-      RAD_HIP_CHECK(hipMemcpyAsync(&conv, &l.ctrl->converged, sizeof(int), hipMemcpyDeviceToHost, s));
-      RAD_HIP_CHECK(hipMemcpyAsync(&st, &l.ctrl->status, sizeof(int), hipMemcpyDeviceToHost, s));
-      RAD_HIP_CHECK(hipStreamSynchronize(s));
-      if (conv || st < 0) break;
     }
   }
-  hipLaunchKernelGGL(enf_apply_scale, dim3(static_cast<unsigned>(n)), dim3(256), 0, s, in);
+  if (!resident) {
+    const int32_t rc = enforce_streamed(in, tol, max_iter, s);
+    if (rc != RAD_OK) return rc;
+  }
   RAD_HIP_CHECK(hipGetLastError());
   if (!stats) return RAD_OK;
   EnfCtrl h;

@@ -23,6 +23,14 @@ struct EnfCtrl {
 };
 
 
+// Arrival counters of the resident kernel, each on a cache line of its own:
+// tile pairs of the current iterations per 64-row block, and finished blocks.
+constexpr int ENF_RES_TILES = 64;  // most 64-row blocks of a resident model
+struct EnfArrivals {
+  int block[ENF_RES_TILES][32];
+  int done;
+};
+
 // One enforcement problem as the kernels see it.
 struct EnfInst {
   double* F;
@@ -38,6 +46,7 @@ struct EnfInst {
   double* blkmax;           // 2 per tile pair: max |eta_ij - eta_ji|, max eta
   double* finred;           // 3 per finalize block: closure defect, the two maxima
   EnfCtrl* ctrl;
+  EnfArrivals* arr;         // resident kernel only
 };
 
 constexpr int ERW = ET / ENW;  // tile rows per wave
@@ -84,6 +93,144 @@ __device__ __forceinline__ double kappa_c(double fij, double fji, double ci, dou
   r = r * __builtin_fma(-s, r, 2.0);
   r = r * __builtin_fma(-s, r, 2.0);
   return s > 0.0 ? b * r : 0.5;
+}
+
+// Loads and stores at the level that all XCDs share (no cache of one XCD
+// holds the value), for what workgroups of one launch exchange.
+template <class T>
+__device__ __forceinline__ T agent_load(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One iteration of a tile pair held in registers: own tile (I, J) in a, partner
+// tile (J, I) in b (see enf_sweep_tile); rowc holds the rows' constants and the
+// previous closure scale.  put() is called once the new own tile is in a and
+// the new partner tile in sB; sums() in wave 0 at the end, with the sums of
+// own row l and of partner row l in lane l and the pair's maxima in lane 0.
+// WIDE: registers to spare, so the pairs of a thread are computed side by side
+// (their chains of dependent operations bind a workgroup alone on its CU).
+template <bool DIAG, bool EDGE, bool HALF, bool WIDE, class Put, class Sums>
+__device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, double (&a)[ERW],
+                                              const double (&b)[ERW], double (*sB)[ETP], double (*rowc)[ET], int& bad,
+                                              Put put, Sums sums) {
+#pragma clang fp contract(off)
+  const int n = in.n;
+  const bool half = HALF;
+  const int r0 = I * ET, c0 = J * ET;
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int jg = c0 + l;
+  const int ig = r0 + l;
+  // scaled by the positive finite 1 / s (1 on the first sweep); negative or
+  // non-finite inputs stay so and are caught where the pair is formed
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) {
+    const int i = r0 + w + ENW * k;
+    double v = a[k];
+    if (EDGE && !(i < n && jg < n)) v = 0.0;
+    a[k] = v * rowc[3][w + ENW * k];
+  }
+  // partner tile into LDS: sB[jl][il] = F(c0 + jl, r0 + il)
+  if (!DIAG) {
+#pragma unroll
+    for (int k = 0; k < ERW; ++k) {
+      const int jr = c0 + w + ENW * k;
+      double v = b[k];
+      if (EDGE && !(jr < n && ig < n)) v = 0.0;
+      sB[w + ENW * k][l] = v * rowc[7][w + ENW * k];
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < ERW; ++k) sB[w + ENW * k][l] = a[k];
+  }
+  __syncthreads();
+
+  // reciprocity on each unordered pair {i, j}, i != j, exactly once
+  double rmax = 0.0, emax = 0.0, sb = 0.0;
+  // constants of row c0 + l (the partner's row; on a diagonal tile the own rows)
+  const double aj = rowc[DIAG ? 0 : 4][l], iaj = rowc[DIAG ? 1 : 5][l];
+  const double cj = rowc[DIAG ? 2 : 6][l];
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) {
+    const int il = w + ENW * k;
+    const double ai = rowc[0][il];
+    if (DIAG) {
+      if (l == il) {                               // the diagonal keeps its value
+        emax = fmax(emax, ai * a[k]);
+        bad |= !(a[k] >= 0.0) || !(a[k] <= 1.0e300);
+      }
+      if (l <= il) continue;                       // handled by the owner of (l, il)
+    }
+    const double iai = rowc[1][il];
+    const double fij = a[k], fji = sB[l][il];
+    bad |= !(fij >= 0.0) || !(fij <= 1.0e300) || !(fji >= 0.0) || !(fji <= 1.0e300);
+    const double eij = ai * fij, eji = aj * fji;
+    rmax = fmax(rmax, fabs(eij - eji));
+    emax = fmax(emax, fmax(eij, eji));
+    const double kp = half ? 0.5 : kappa_c(fij, fji, rowc[2][il], cj);
+    const double eh = kp * eij + (1.0 - kp) * eji;
+    const double bji = eh * iaj;
+    a[k] = eh * iai;
+    sB[l][il] = bji;
+    sb += bji;
+    // fold this pair into the running maxima and the error flag now: left to
+    // itself the compiler keeps every pair's terms live and reduces them as a
+    // tree after the loop, which doubles the registers of the kernel
+    if (!WIDE) __asm__ volatile("" : "+v"(rmax), "+v"(emax), "+v"(bad), "+v"(sb));
+  }
+  __syncthreads();
+  if (DIAG) {
+#pragma unroll
+    for (int k = 0; k < ERW; ++k)
+      if (l < w + ENW * k) a[k] = sB[w + ENW * k][l];  // written by the owner of the mirror
+  }
+
+  put();
+  __syncthreads();
+  // own tile transposed into LDS, then each thread sums ERW entries of row l
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) sB[l][w + ENW * k] = a[k];
+  for (int off = 32; off > 0; off >>= 1) {
+    rmax = fmax(rmax, __shfl_xor(rmax, off));
+    emax = fmax(emax, __shfl_xor(emax, off));
+  }
+  __syncthreads();
+  double sa = 0.0;
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) sa += sB[w + ENW * k][l];
+  __syncthreads();
+  // the transposed tile has been summed: LDS rows 2.. take this wave's
+  // partial sums of the partner's row l and of the own row l, rows 0 and 1
+  // the wave maxima
+  sB[2 + w][l] = sb;
+  sB[2 + ENW + w][l] = sa;
+  if (l == 0) {
+    sB[0][w] = rmax;
+    sB[1][w] = emax;
+  }
+  __syncthreads();
+  if (w == 0) {
+    double s_own = 0.0, s_par = 0.0;
+#pragma unroll
+    for (int q = 0; q < ENW; ++q) {
+      s_own += sB[2 + ENW + q][l];
+      s_par += sB[2 + q][l];
+    }
+    double x = 0.0, y = 0.0;
+    if (l == 0) {
+      x = sB[0][0];
+      y = sB[1][0];
+      for (int q = 1; q < ENW; ++q) {
+        x = fmax(x, sB[0][q]);
+        y = fmax(y, sB[1][q]);
+      }
+    }
+    sums(s_own, s_par, x, y);
+  }
 }
 
 // One workgroup per tile pair (I, J), I <= J, of 64 x 64 tiles.  Lane l of
@@ -154,136 +301,40 @@ __device__ __forceinline__ void enf_sweep_tile(const EnfInst& in, long pair, int
     rowc[q + 3][rl] = first ? 1.0 : inv_scale[i];
   }
   __syncthreads();
-  // scaled by the positive finite 1 / s (1 on the first sweep); negative or
-  // non-finite inputs stay so and are caught where the pair is formed
+  enf_pair_step<DIAG, EDGE, HALF, false>(
+      in, I, J, a, b, sB, rowc, bad,
+      [&]() {
+        // own tile back to F
 #pragma unroll
-  for (int k = 0; k < ERW; ++k) {
-    const int i = r0 + w + ENW * k;
-    double v = a[k];
-    if (EDGE && !(i < n && jg < n)) v = 0.0;
-    a[k] = v * rowc[3][w + ENW * k];
-  }
-  // partner tile into LDS: sB[jl][il] = F(c0 + jl, r0 + il)
-  if (!DIAG) {
+        for (int k = 0; k < ERW; ++k) {
+          const int i = r0 + w + ENW * k;
+          if (!EDGE || (i < n && jg < n)) row_st(F + static_cast<long>(i) * ldf, jg, a[k]);
+        }
+        if (!DIAG) {  // partner tile back to F
 #pragma unroll
-    for (int k = 0; k < ERW; ++k) {
-      const int jr = c0 + w + ENW * k;
-      double v = b[k];
-      if (EDGE && !(jr < n && ig < n)) v = 0.0;
-      sB[w + ENW * k][l] = v * rowc[7][w + ENW * k];
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < ERW; ++k) sB[w + ENW * k][l] = a[k];
-  }
-  __syncthreads();
-
-  // reciprocity on each unordered pair {i, j}, i != j, exactly once
-  double rmax = 0.0, emax = 0.0, sb = 0.0;
-  // constants of row c0 + l (the partner's row; on a diagonal tile the own rows)
-  const double aj = rowc[DIAG ? 0 : 4][l], iaj = rowc[DIAG ? 1 : 5][l];
-  const double cj = rowc[DIAG ? 2 : 6][l];
-#pragma unroll
-  for (int k = 0; k < ERW; ++k) {
-    const int il = w + ENW * k;
-    const double ai = rowc[0][il];
-    if (DIAG) {
-      if (l == il) {                               // the diagonal keeps its value
-        emax = fmax(emax, ai * a[k]);
-        bad |= !(a[k] >= 0.0) || !(a[k] <= 1.0e300);
-      }
-      if (l <= il) continue;                       // handled by the owner of (l, il)
-    }
-    const double iai = rowc[1][il];
-    const double fij = a[k], fji = sB[l][il];
-    bad |= !(fij >= 0.0) || !(fij <= 1.0e300) || !(fji >= 0.0) || !(fji <= 1.0e300);
-    const double eij = ai * fij, eji = aj * fji;
-    rmax = fmax(rmax, fabs(eij - eji));
-    emax = fmax(emax, fmax(eij, eji));
-    const double kp = half ? 0.5 : kappa_c(fij, fji, rowc[2][il], cj);
-    const double eh = kp * eij + (1.0 - kp) * eji;
-    const double bji = eh * iaj;
-    a[k] = eh * iai;
-    sB[l][il] = bji;
-    sb += bji;
-    // fold this pair into the running maxima and the error flag now: left to
-    // itself the compiler keeps every pair's terms live and reduces them as a
-    // tree after the loop, which doubles the registers of the kernel
-    __asm__ volatile("" : "+v"(rmax), "+v"(emax), "+v"(bad), "+v"(sb));
-  }
-  __syncthreads();
-  if (DIAG) {
-#pragma unroll
-    for (int k = 0; k < ERW; ++k)
-      if (l < w + ENW * k) a[k] = sB[w + ENW * k][l];  // written by the owner of the mirror
-  }
-
-  // own tile back to F
-#pragma unroll
-  for (int k = 0; k < ERW; ++k) {
-    const int i = r0 + w + ENW * k;
-    if (!EDGE || (i < n && jg < n)) row_st(F + static_cast<long>(i) * ldf, jg, a[k]);
-  }
-  if (!DIAG) {  // partner tile back to F
-    const int ig = r0 + l;
-#pragma unroll
-    for (int k = 0; k < ERW; ++k) {
-      const int jr = c0 + w + ENW * k;
-      if (!EDGE || (jr < n && ig < n)) row_st(F + static_cast<long>(jr) * ldf, ig, sB[w + ENW * k][l]);
-    }
-  }
-  __syncthreads();
-  // own tile transposed into LDS, then each thread sums ERW entries of row l
-#pragma unroll
-  for (int k = 0; k < ERW; ++k) sB[l][w + ENW * k] = a[k];
-  for (int off = 32; off > 0; off >>= 1) {
-    rmax = fmax(rmax, __shfl_xor(rmax, off));
-    emax = fmax(emax, __shfl_xor(emax, off));
-  }
-  __syncthreads();
-  double sa = 0.0;
-#pragma unroll
-  for (int k = 0; k < ERW; ++k) sa += sB[w + ENW * k][l];
-  __syncthreads();
-  // the transposed tile has been summed: LDS rows 2.. take this wave's
-  // partial sums of the partner's row l and of the own row l, rows 0 and 1
-  // the wave maxima
-  sB[2 + w][l] = sb;
-  sB[2 + ENW + w][l] = sa;
-  if (l == 0) {
-    sB[0][w] = rmax;
-    sB[1][w] = emax;
-  }
-  __syncthreads();
-  if (w == 0) {
-    double s_own = 0.0, s_par = 0.0;
-#pragma unroll
-    for (int q = 0; q < ENW; ++q) {
-      s_own += sB[2 + ENW + q][l];
-      s_par += sB[2 + q][l];
-    }
-    const int t = in.t;
-    double* __restrict__ partial = in.partial;
-    if (!EDGE || r0 + l < n) partial[static_cast<long>(J) * n + r0 + l] = s_own;
-    if (!DIAG && (!EDGE || c0 + l < n)) partial[static_cast<long>(I) * n + c0 + l] = s_par;
-    if (DIAG && (!EDGE || r0 + l < n)) {  // the space column of the tile's rows rides with the diagonal tile
-      double* sp = F + static_cast<long>(r0 + l) * ldf + n;
-      double v = *sp;
-      bad |= !(v >= 0.0) || !(v <= 1.0e300);
-      v *= rowc[3][l];
-      *sp = v;
-      partial[static_cast<long>(t) * n + r0 + l] = v;
-    }
-    if (l == 0) {
-      double x = sB[0][0], y = sB[1][0];
-      for (int q = 1; q < ENW; ++q) {
-        x = fmax(x, sB[0][q]);
-        y = fmax(y, sB[1][q]);
-      }
-      in.blkmax[2 * pair] = x;
-      in.blkmax[2 * pair + 1] = y;
-    }
-  }
+          for (int k = 0; k < ERW; ++k) {
+            const int jr = c0 + w + ENW * k;
+            if (!EDGE || (jr < n && ig < n)) row_st(F + static_cast<long>(jr) * ldf, ig, sB[w + ENW * k][l]);
+          }
+        }
+      },
+      [&](double s_own, double s_par, double x, double y) {
+        double* __restrict__ partial = in.partial;
+        if (!EDGE || r0 + l < n) partial[static_cast<long>(J) * n + r0 + l] = s_own;
+        if (!DIAG && (!EDGE || c0 + l < n)) partial[static_cast<long>(I) * n + c0 + l] = s_par;
+        if (DIAG && (!EDGE || r0 + l < n)) {  // the space column of the tile's rows rides with the diagonal tile
+          double* sp = F + static_cast<long>(r0 + l) * ldf + n;
+          double v = *sp;
+          bad |= !(v >= 0.0) || !(v <= 1.0e300);
+          v *= rowc[3][l];
+          *sp = v;
+          partial[static_cast<long>(in.t) * n + r0 + l] = v;
+        }
+        if (l == 0) {
+          in.blkmax[2 * pair] = x;
+          in.blkmax[2 * pair + 1] = y;
+        }
+      });
   if (bad) raise_status(&in.ctrl->status, RAD_ENONFINITE);
 }
 
@@ -486,6 +537,299 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
   enf_finalize_body(in, m.local, (in.n + FIN_ROWS - 1) / FIN_ROWS, tol);
 }
 
+
+// ---- all iterations in one launch, F on chip ---------------------------------
+// A pair's two tiles fit the registers of its workgroup, so a model whose tile
+// pairs are all resident at once (two workgroups per CU: n <= 1984 on 256
+// CUs) is read and written once, and between iterations only row sums travel:
+// a workgroup stores its rows' partial sums and counts itself in for its two
+// row blocks; the last of a block's t workgroups adds the block's sums, stores
+// the closure scales and counts the block done; when all t blocks are done
+// every workgroup goes on.  Bound by the latency of that exchange through the
+// memory that all XCDs share (five dependent round trips).  Needs a cooperative
+// launch unless the grid is one workgroup.  Same operations in the same order
+// as enf_sweep, enf_finalize and enf_apply_scale, so the same bits.
+
+// The sums of row block rb (64 rows), by its last workgroup; finred receives
+// the closure defect, the pair maxima and whether an error was seen.
+__device__ __forceinline__ void enf_resident_finalize(const EnfInst& in, int rb, double* finred, double (*sB)[ETP]) {
+  const int n = in.n, t = in.t, w = threadIdx.x >> 6, l = threadIdx.x & 63, i = rb * ET + l;
+  const int ic = min(i, n - 1);
+  static_assert(ENW == FIN_LANES, "wave w sums part w of every row");
+  double s = 0.0;
+  for (int q = w; q <= t; q += 4 * FIN_LANES) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = agent_load(in.partial + static_cast<long>(min(q + u * FIN_LANES, t)) * n + ic);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q + u * FIN_LANES <= t) s += v[u];
+  }
+  double rm = 0.0, em = 0.0;
+  int st = 0;
+  if (w == 0) {
+    st = agent_load(&in.ctrl->status) < 0;  // of the block's workgroups at least
+    const long p0 = static_cast<long>(rb) * t - static_cast<long>(rb) * (rb - 1) / 2;  // pair (rb, rb)
+    if (l < t - rb) {
+      rm = agent_load(in.blkmax + 2 * (p0 + l));
+      em = agent_load(in.blkmax + 2 * (p0 + l) + 1);
+    }
+  }
+  sB[w][l] = s;
+  __syncthreads();
+  if (w == 0) {
+    double d = 0.0;
+    if (i < n) {
+      s = ((sB[0][l] + sB[1][l]) + (sB[2][l] + sB[3][l])) + ((sB[4][l] + sB[5][l]) + (sB[6][l] + sB[7][l]));
+      if (!(s > 0.0) && !st) {  // a row sum after an input error means nothing
+        raise_status(&in.ctrl->status, RAD_EZEROROW);
+        st = 1;
+      }
+      agent_store(in.scale + i, 1.0 / s);
+      d = fabs(s - 1.0);
+    }
+    double x[4] = {d, rm, em, static_cast<double>(st)};
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      for (int off = 32; off > 0; off >>= 1) x[c] = fmax(x[c], __shfl_xor(x[c], off));
+    if (l < 4) agent_store(finred + 4 * rb + l, l == 0 ? x[0] : l == 1 ? x[1] : l == 2 ? x[2] : x[3]);
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores are done before the block is
+    if (l == 0) atomicAdd(&in.arr->done, 1);
+  }
+  __syncthreads();
+}
+
+template <bool DIAG, bool EDGE, bool HALF, bool WIDE>
+__device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int J, double tol, int max_iter,
+                                                  double (*sB)[ETP], double (*rowc)[ET]) {
+#pragma clang fp contract(off)
+  __shared__ int last[2];
+  const long ldf = in.ldf;
+  const int n = in.n, t = in.t;
+  const int r0 = I * ET, c0 = J * ET;
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int jg = c0 + l, ig = r0 + l;
+  const int jgc = (EDGE && jg >= n) ? n - 1 : jg, igc = (EDGE && ig >= n) ? n - 1 : ig;
+  double a[ERW], b[ERW], space = 0.0;
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) {
+    const int i = r0 + w + ENW * k;
+    a[k] = row_ld(in.F + static_cast<long>((EDGE && i >= n) ? n - 1 : i) * ldf, jgc);
+  }
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) {
+    const int jr = c0 + w + ENW * k;
+    b[k] = DIAG ? 0.0 : row_ld(in.F + static_cast<long>((EDGE && jr >= n) ? n - 1 : jr) * ldf, igc);
+  }
+  if (DIAG && w == 0) space = in.F[static_cast<long>(igc) * ldf + n];
+  const int crow = (tid < ET ? r0 : c0) + l, cq = tid < ET ? 0 : 4;  // the row of this thread's constants
+  const int crc = (EDGE && crow >= n) ? n - 1 : crow;
+  if (tid < (DIAG ? ET : 2 * ET)) {
+    const double ai = in.area[crc];
+    rowc[cq + 0][l] = ai;
+    rowc[cq + 1][l] = in.inv_area[crc];
+    rowc[cq + 2][l] = HALF ? 0.0 : ai * ai / in.nrays[crc];
+    rowc[cq + 3][l] = 1.0;
+  }
+  __syncthreads();
+  const int pair = static_cast<int>(blockIdx.x);
+  int iters = 0, converged = 0, stop = 0;
+  double x[4] = {};  // closure defect, pair maxima, error seen
+  while (iters < max_iter && !converged && !stop) {
+    int bad = 0;
+    enf_pair_step<DIAG, EDGE, HALF, WIDE>(
+        in, I, J, a, b, sB, rowc, bad,
+        [&]() {
+          if (!DIAG)
+#pragma unroll
+            for (int k = 0; k < ERW; ++k) b[k] = sB[w + ENW * k][l];
+        },
+        [&](double s_own, double s_par, double rm, double em) {
+          if (DIAG) {
+            bad |= (!EDGE || ig < n) && (!(space >= 0.0) || !(space <= 1.0e300));
+            space *= rowc[3][l];
+          }
+          if (!EDGE || ig < n) agent_store(in.partial + static_cast<long>(J) * n + ig, s_own);
+          if (!DIAG && (!EDGE || jg < n)) agent_store(in.partial + static_cast<long>(I) * n + jg, s_par);
+          if (DIAG && (!EDGE || ig < n)) agent_store(in.partial + static_cast<long>(t) * n + ig, space);
+          if (l == 0) {
+            agent_store(in.blkmax + 2 * pair, rm);
+            agent_store(in.blkmax + 2 * pair + 1, em);
+          }
+        });
+    if (bad) raise_status(&in.ctrl->status, RAD_ENONFINITE);
+    // double-buffered: a workgroup may still read the last iteration's entries
+    double* finred = in.finred + (iters & 1) * 4 * t;
+    const int epoch = iters + 1;
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores (and its error) are done before its workgroup counts itself in
+    __syncthreads();
+    if (tid == 0) {
+      const int ci = atomicAdd(&in.arr->block[I][0], 1);
+      const int cj = DIAG ? 0 : atomicAdd(&in.arr->block[J][0], 1);
+      last[0] = ci + 1 == t * epoch;
+      last[1] = !DIAG && cj + 1 == t * epoch;
+    }
+    __syncthreads();
+    if (last[0]) enf_resident_finalize(in, I, finred, sB);
+    if (!DIAG && last[1]) enf_resident_finalize(in, J, finred, sB);
+    if (tid == 0)
+      while (agent_load(&in.arr->done) < t * epoch) __builtin_amdgcn_s_sleep(1);
+    __syncthreads();
+    // every wave of every workgroup takes the same decision from the same values
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = l < t ? agent_load(finred + 4 * l + c) : 0.0;
+    if (tid < (DIAG ? ET : 2 * ET)) rowc[cq + 3][l] = agent_load(in.scale + crc);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      for (int off = 32; off > 0; off >>= 1) x[c] = fmax(x[c], __shfl_xor(x[c], off));
+    __syncthreads();
+    stop = x[3] > 0.0;
+    if (stop) break;
+    ++iters;
+    converged = tol > 0.0 && x[0] <= tol;
+  }
+  if (pair == 0 && tid == 0) {
+    in.ctrl->iters = iters;
+    in.ctrl->converged = converged;
+    in.ctrl->last_defect = x[0];
+    in.ctrl->last_recip = x[2] > 0.0 ? x[1] / x[2] : 0.0;
+  }
+  if (stop || iters == 0) return;
+  // F once, with the last closure scale (rowc[3], rowc[7])
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) {
+    const int i = r0 + w + ENW * k;
+    if (!EDGE || (i < n && jg < n)) row_st(in.F + static_cast<long>(i) * ldf, jg, a[k] * rowc[3][w + ENW * k]);
+  }
+  if (!DIAG)
+#pragma unroll
+    for (int k = 0; k < ERW; ++k) {
+      const int jr = c0 + w + ENW * k;
+      if (!EDGE || (jr < n && ig < n)) row_st(in.F + static_cast<long>(jr) * ldf, ig, b[k] * rowc[7][w + ENW * k]);
+    }
+  if (DIAG && w == 0 && (!EDGE || ig < n)) in.F[static_cast<long>(ig) * ldf + n] = space * rowc[3][l];
+}
+
+template <bool HALF, bool WIDE>
+__device__ __forceinline__ void enf_resident_pair(const EnfInst& in, int I, int J, double tol, int max_iter,
+                                                  double (*sB)[ETP], double (*rowc)[ET]) {
+  const bool edge = (J + 1) * ET > in.n;
+  if (I == J) {
+    if (edge) enf_resident_tile<true, true, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
+    else enf_resident_tile<true, false, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
+  } else {
+    if (edge) enf_resident_tile<false, true, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
+    else enf_resident_tile<false, false, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
+  }
+}
+
+// PER_CU: workgroups per CU the registers allow, 1 or 2
+template <int PER_CU>
+__global__ void __launch_bounds__(ENF_THREADS, 2 * PER_CU) enf_resident(EnfInst in, double tol, int max_iter) {
+  __shared__ double sB[ET][ETP];
+  __shared__ double rowc[8][ET];
+  int I, J;
+  pair_from_index(blockIdx.x, in.t, I, J);
+  I = __builtin_amdgcn_readfirstlane(I);
+  J = __builtin_amdgcn_readfirstlane(J);
+  if (in.mode == RAD_KAPPA_HALF) enf_resident_pair<true, PER_CU == 1>(in, I, J, tol, max_iter, sB, rowc);
+  else enf_resident_pair<false, PER_CU == 1>(in, I, J, tol, max_iter, sB, rowc);
+}
+
+// One tile (n <= 64): the exchange stays in the workgroup too.
+template <bool EDGE, bool HALF>
+__device__ __forceinline__ void enf_single_tile(const EnfInst& in, double tol, int max_iter, double (*sB)[ETP],
+                                                double (*rowc)[ET]) {
+#pragma clang fp contract(off)
+  __shared__ double dec[4];
+  const long ldf = in.ldf;
+  const int n = in.n, tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int lc = (EDGE && l >= n) ? n - 1 : l;
+  double a[ERW], space = in.F[static_cast<long>(lc) * ldf + n];
+  const double b[ERW] = {};
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) {
+    const int i = w + ENW * k;
+    a[k] = row_ld(in.F + static_cast<long>((EDGE && i >= n) ? n - 1 : i) * ldf, lc);
+  }
+  if (w == 0) {
+    const double ai = in.area[lc];
+    rowc[0][l] = ai;
+    rowc[1][l] = in.inv_area[lc];
+    rowc[2][l] = HALF ? 0.0 : ai * ai / in.nrays[lc];
+    rowc[3][l] = 1.0;
+  }
+  if (agent_load(&in.ctrl->status) < 0) return;  // a bad area, found by an earlier launch
+  __syncthreads();
+  int iters = 0, converged = 0, stop = 0;
+  while (iters < max_iter && !converged) {
+    int bad = 0;
+    enf_pair_step<true, EDGE, HALF, true>(
+        in, 0, 0, a, b, sB, rowc, bad, []() {},
+        [&](double s_own, double, double rm, double em) {
+          double d = 0.0, zero = 0.0;
+          if (!EDGE || l < n) {
+            bad |= !(space >= 0.0) || !(space <= 1.0e300);
+            space *= rowc[3][l];
+            const double s = s_own + space;
+            zero = s > 0.0 ? 0.0 : 1.0;
+            rowc[3][l] = 1.0 / s;
+            d = fabs(s - 1.0);
+          }
+          for (int off = 32; off > 0; off >>= 1) {
+            d = fmax(d, __shfl_xor(d, off));
+            zero = fmax(zero, __shfl_xor(zero, off));
+          }
+          if (l == 0) {
+            dec[0] = d;
+            dec[1] = rm;
+            dec[2] = em;
+            dec[3] = zero;
+          }
+        });
+    const int input_error = __syncthreads_or(bad);
+    if (input_error || dec[3] > 0.0) {
+      if (tid == 0) raise_status(&in.ctrl->status, input_error ? RAD_ENONFINITE : RAD_EZEROROW);
+      stop = 1;
+      break;
+    }
+    ++iters;
+    converged = tol > 0.0 && dec[0] <= tol;
+  }
+  if (tid == 0 && iters > 0) {
+    in.ctrl->iters = iters;
+    in.ctrl->converged = converged;
+    in.ctrl->last_defect = dec[0];
+    in.ctrl->last_recip = dec[2] > 0.0 ? dec[1] / dec[2] : 0.0;
+  }
+  if (stop) return;
+#pragma unroll
+  for (int k = 0; k < ERW; ++k) {
+    const int i = w + ENW * k;
+    if (!EDGE || (i < n && l < n)) row_st(in.F + static_cast<long>(i) * ldf, l, a[k] * rowc[3][i]);
+  }
+  if (w == 0 && (!EDGE || l < n)) in.F[static_cast<long>(l) * ldf + n] = space * rowc[3][l];
+}
+
+__global__ void __launch_bounds__(ENF_THREADS, 2) enf_single(EnfInst in, double tol, int max_iter) {
+  __shared__ double sB[ET][ETP];
+  __shared__ double rowc[8][ET];
+  if (in.mode == RAD_KAPPA_HALF) {
+    if (in.n < ET) enf_single_tile<true, true>(in, tol, max_iter, sB, rowc);
+    else enf_single_tile<false, true>(in, tol, max_iter, sB, rowc);
+  } else {
+    if (in.n < ET) enf_single_tile<true, false>(in, tol, max_iter, sB, rowc);
+    else enf_single_tile<false, false>(in, tol, max_iter, sB, rowc);
+  }
+}
+
+__global__ void __launch_bounds__(64) enf_arrivals_init(EnfArrivals* arr) {
+  arr->block[threadIdx.x][0] = 0;
+  if (threadIdx.x == 0) arr->done = 0;
+}
+static_assert(ENF_RES_TILES == 64, "one counter per thread, one finred entry per lane");
 
 __device__ __forceinline__ void enf_apply_scale_body(const EnfInst& in, long row) {
   if (in.ctrl->status < 0 || in.ctrl->iters == 0) return;
