@@ -797,7 +797,10 @@ void build_tables(rad_batch_plan* P, char* base, TableBuilder& tb) {
   P->back.clear();
   P->fwd.clear();
   P->resid.clear();
-  // enforcement instances
+  // enforcement instances; one iteration sweeps them all, so their bytes together
+  // decide whether F may stay in the last-level cache
+  double f_bytes = 0.0;
+  for (int i = 0; i < P->count; ++i) f_bytes += 8.0 * static_cast<double>(P->inst[i].n) * (P->inst[i].n + 1);
   std::vector<EnfInst> ei;
   std::vector<long> pair_start(1, 0), fblk_start(1, 0), fin_start(1, 0), row_start(1, 0);
   for (int i = 0; i < P->count; ++i) {
@@ -813,6 +816,7 @@ void build_tables(rad_batch_plan* P, char* base, TableBuilder& tb) {
     e.inv_area = reinterpret_cast<double*>(base + o.inv_area);
     e.nrays = s.n_rays;
     e.mode = P->kappa;
+    e.nt = enf_nontemporal(s.F, e.ldf, f_bytes);
     e.scale = reinterpret_cast<double*>(base + o.scale);
     e.partial = reinterpret_cast<double*>(base + o.partial);
     e.blkmax = reinterpret_cast<double*>(base + o.blkmax);

@@ -171,6 +171,7 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.inv_area = l.inv_area;
   in.nrays = n_rays;
   in.mode = kappa_mode;
+  in.nt = enf_nontemporal(F, in.ldf, 8.0 * static_cast<double>(n) * (n + 1));
   in.scale = l.scale;
   in.partial = l.partial;
   in.blkmax = l.blkmax;

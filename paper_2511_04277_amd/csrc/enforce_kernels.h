@@ -41,6 +41,7 @@ struct EnfInst {
   const double* inv_area;   // 1 / A_i (workspace)
   const double* nrays;      // null for kappa = 1/2
   int mode;
+  int nt;                   // sweeps use nontemporal accesses
   double* scale;            // 1 / s_i of the last closure step
   double* partial;          // (t + 1) x n partial row sums
   double* blkmax;           // 2 per tile pair: max |eta_ij - eta_ji|, max eta
@@ -68,13 +69,28 @@ __device__ __forceinline__ gchar* uniform_ptr(const double* p) {
   const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
   return reinterpret_cast<gchar*>((static_cast<unsigned long long>(hi) << 32) | lo);
 }
-// F streams through once per sweep (it is larger than the last-level cache
-// at the sizes that matter), so its loads and stores are nontemporal.
+// NT: nontemporal, past the last-level cache (see enf_nontemporal).
+template <bool NT = true>
 __device__ __forceinline__ double row_ld(const double* row, unsigned col) {
-  return __builtin_nontemporal_load(reinterpret_cast<const gdouble*>(uniform_ptr(row) + col * 8u));
+  const gdouble* p = reinterpret_cast<const gdouble*>(uniform_ptr(row) + col * 8u);
+  return NT ? __builtin_nontemporal_load(p) : *p;
 }
+template <bool NT = true>
 __device__ __forceinline__ void row_st(double* row, unsigned col, double v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<gdouble*>(uniform_ptr(row) + col * 8u));
+  gdouble* p = reinterpret_cast<gdouble*>(uniform_ptr(row) + col * 8u);
+  if (NT) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// Whether sweeps over matrices of bytes in total go past the last-level cache
+// (256 MB).  Up to about its size F stays there between sweeps: 105 -> 85 us an
+// iteration at n = 5200 (216 MB, rows on 128-byte lines), 68 -> 59 us at 4048.
+// Rows off the 128-byte lines share a line between two tiles, which
+// nontemporal accesses fetch and write twice: 704 -> 615 us at n = 12288 and
+// 320 -> 268 us at 8192 without them.  Aligned and larger, they win: 238 us
+// against 252 at 8192, 523 against 546 at 12288.
+inline bool enf_nontemporal(const double* F, long ldf, double bytes) {
+  return reinterpret_cast<uintptr_t>(F) % 128 == 0 && ldf % 16 == 0 && bytes > 256.0e6;
 }
 
 // kappa of eq. 3.25 from the pair (f_ij, f_ji) and c = A^2 / N of both faces:
@@ -245,7 +261,7 @@ __device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, d
 // All sums run in a fixed order (bitwise reproducible).  DIAG: I == J (each
 // unordered pair once, the diagonal kept, the space column carried along);
 // EDGE: the tile pair crosses n (clamped loads, masked stores).
-template <bool DIAG, bool EDGE, bool HALF>
+template <bool DIAG, bool EDGE, bool HALF, bool NT>
 __device__ __forceinline__ void enf_sweep_tile(const EnfInst& in, long pair, int I, int J, int first,
                                                double (*sB)[ETP], double (*rowc)[ET]) {
 #pragma clang fp contract(off)
@@ -276,14 +292,14 @@ __device__ __forceinline__ void enf_sweep_tile(const EnfInst& in, long pair, int
   for (int k = 0; k < ERW; ++k) {
     const int i = r0 + w + ENW * k;
     const int ic = (EDGE && i >= n) ? n - 1 : i;
-    a[k] = row_ld(F + static_cast<long>(ic) * ldf, jgc);
+    a[k] = row_ld<NT>(F + static_cast<long>(ic) * ldf, jgc);
   }
   if (!DIAG) {
 #pragma unroll
     for (int k = 0; k < ERW; ++k) {
       const int jr = c0 + w + ENW * k;
       const int jrc = (EDGE && jr >= n) ? n - 1 : jr;
-      b[k] = row_ld(F + static_cast<long>(jrc) * ldf, igc);
+      b[k] = row_ld<NT>(F + static_cast<long>(jrc) * ldf, igc);
     }
   }
   // per-row constants: area, 1 / area, A^2 / N and the previous closure
@@ -308,13 +324,13 @@ __device__ __forceinline__ void enf_sweep_tile(const EnfInst& in, long pair, int
 #pragma unroll
         for (int k = 0; k < ERW; ++k) {
           const int i = r0 + w + ENW * k;
-          if (!EDGE || (i < n && jg < n)) row_st(F + static_cast<long>(i) * ldf, jg, a[k]);
+          if (!EDGE || (i < n && jg < n)) row_st<NT>(F + static_cast<long>(i) * ldf, jg, a[k]);
         }
         if (!DIAG) {  // partner tile back to F
 #pragma unroll
           for (int k = 0; k < ERW; ++k) {
             const int jr = c0 + w + ENW * k;
-            if (!EDGE || (jr < n && ig < n)) row_st(F + static_cast<long>(jr) * ldf, ig, sB[w + ENW * k][l]);
+            if (!EDGE || (jr < n && ig < n)) row_st<NT>(F + static_cast<long>(jr) * ldf, ig, sB[w + ENW * k][l]);
           }
         }
       },
@@ -338,6 +354,19 @@ __device__ __forceinline__ void enf_sweep_tile(const EnfInst& in, long pair, int
   if (bad) raise_status(&in.ctrl->status, RAD_ENONFINITE);
 }
 
+template <bool HALF, bool NT>
+__device__ __forceinline__ void enf_sweep_pair(const EnfInst& in, long pair, int I, int J, int first,
+                                               double (*sB)[ETP], double (*rowc)[ET]) {
+  const bool edge = (J + 1) * ET > in.n;
+  if (I == J) {
+    if (edge) enf_sweep_tile<true, true, HALF, NT>(in, pair, I, J, first, sB, rowc);
+    else enf_sweep_tile<true, false, HALF, NT>(in, pair, I, J, first, sB, rowc);
+  } else {
+    if (edge) enf_sweep_tile<false, true, HALF, NT>(in, pair, I, J, first, sB, rowc);
+    else enf_sweep_tile<false, false, HALF, NT>(in, pair, I, J, first, sB, rowc);
+  }
+}
+
 __device__ __forceinline__ void enf_sweep_body(const EnfInst& in, long pair, int first) {
   if (in.ctrl->converged || in.ctrl->status < 0) return;
   __shared__ double sB[ET][ETP];
@@ -346,23 +375,12 @@ __device__ __forceinline__ void enf_sweep_body(const EnfInst& in, long pair, int
   pair_from_index(pair, in.t, I, J);
   I = __builtin_amdgcn_readfirstlane(I);  // workgroup-uniform: keeps tile addressing scalar
   J = __builtin_amdgcn_readfirstlane(J);
-  const bool edge = (I + 1) * ET > in.n || (J + 1) * ET > in.n;
   if (in.mode == RAD_KAPPA_HALF) {
-    if (I == J) {
-      if (edge) enf_sweep_tile<true, true, true>(in, pair, I, J, first, sB, rowc);
-      else enf_sweep_tile<true, false, true>(in, pair, I, J, first, sB, rowc);
-    } else {
-      if (edge) enf_sweep_tile<false, true, true>(in, pair, I, J, first, sB, rowc);
-      else enf_sweep_tile<false, false, true>(in, pair, I, J, first, sB, rowc);
-    }
+    if (in.nt) enf_sweep_pair<true, true>(in, pair, I, J, first, sB, rowc);
+    else enf_sweep_pair<true, false>(in, pair, I, J, first, sB, rowc);
   } else {
-    if (I == J) {
-      if (edge) enf_sweep_tile<true, true, false>(in, pair, I, J, first, sB, rowc);
-      else enf_sweep_tile<true, false, false>(in, pair, I, J, first, sB, rowc);
-    } else {
-      if (edge) enf_sweep_tile<false, true, false>(in, pair, I, J, first, sB, rowc);
-      else enf_sweep_tile<false, false, false>(in, pair, I, J, first, sB, rowc);
-    }
+    if (in.nt) enf_sweep_pair<false, true>(in, pair, I, J, first, sB, rowc);
+    else enf_sweep_pair<false, false>(in, pair, I, J, first, sB, rowc);
   }
 }
 
