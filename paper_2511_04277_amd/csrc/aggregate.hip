@@ -17,43 +17,51 @@ namespace {
 constexpr int CSR_CHUNK = 1024;   // indices per rank block
 constexpr int AGG_THREADS = 256;
 
-// Stable counting sort of the group map in three passes.  (1) One block per
-// chunk of CSR_CHUNK indices: each index's rank among equal ids earlier in
-// its chunk, and the chunk's count per group.  (2) One block: per group, the
+// Stable counting sort of the group map in three passes.  (1) Per chunk of
+// CSR_CHUNK indices: each index's rank among equal ids earlier in its chunk,
+// and the chunk's count per group.  (2) One block: per group, the
 // offset of each chunk's run (chunks in order) and the group offsets (scan
 // over groups).  (3) Scatter: index i goes to
 // offs[g_i] + chunk_off[chunk][g_i] + rank_i, so members appear in
 // increasing index order and every later sum runs in a fixed order.
-__global__ void __launch_bounds__(CSR_CHUNK)
+// A block ranks 64 indices; its four waves each compare them with a quarter of
+// the chunk's earlier ids (one block of 1024 threads per chunk left most CUs
+// idle: 26 -> 5 us at n = 8192).
+constexpr int CSR_SUB = 64;
+__global__ void __launch_bounds__(256)
 csr_rank(const int* __restrict__ group, int n, int g, int* __restrict__ rank, int* __restrict__ cnt,
          int* __restrict__ status) {
   __shared__ __align__(16) int chunk[CSR_CHUNK];
-  const int c = blockIdx.x, tid = threadIdx.x;
-  const int i = c * CSR_CHUNK + tid;
-  int gi = i < n ? group[i] : -1;
+  __shared__ int part[4][CSR_SUB];
+  const int c = blockIdx.x / (CSR_CHUNK / CSR_SUB), sub = blockIdx.x % (CSR_CHUNK / CSR_SUB);
+  const int base = c * CSR_CHUNK, own = sub * CSR_SUB;  // this block ranks chunk[own .. own + 63]
+  const int tid = threadIdx.x, l = tid & 63, w = tid >> 6;
+  for (int q = tid; q < own + CSR_SUB; q += 256) chunk[q] = base + q < n ? group[base + q] : -1;
+  __syncthreads();
+  int gi = chunk[own + l];
+  const int i = base + own + l;
   if (i < n && (gi < 0 || gi >= g)) {
-    atomicMin(status, RAD_EINVAL);
+    if (w == 0) atomicMin(status, RAD_EINVAL);
     gi = -1;
   }
-  chunk[tid] = gi;
-  __syncthreads();
-  if (gi < 0) return;
-  // equal ids before tid in the chunk; the loop bound (a multiple of 64) is
-  // the same for every lane of a wave (no divergence), four ids per LDS read
-  // and four reads in flight
-  const int qend = (tid | 63) + 1;
+  // equal ids before index own + l: wave w takes the ids of [16 w, 16 w + 16)
+  // of every 64, four ids per LDS read and four reads in flight
   int r = 0;
-  for (int q0 = 0; q0 < qend; q0 += 16) {
+  for (int q0 = 16 * w; q0 <= own + 16 * w; q0 += 64) {
     int4 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const int4*>(&chunk[q0 + 4 * u]);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int q = q0 + 4 * u;
-      r += (v[u].x == gi && q < tid) + (v[u].y == gi && q + 1 < tid) + (v[u].z == gi && q + 2 < tid) +
-           (v[u].w == gi && q + 3 < tid);
+      const int q = q0 + 4 * u, t = own + l;
+      r += (v[u].x == gi && q < t) + (v[u].y == gi && q + 1 < t) + (v[u].z == gi && q + 2 < t) +
+           (v[u].w == gi && q + 3 < t);
     }
   }
+  part[w][l] = r;
+  __syncthreads();
+  if (w > 0 || gi < 0 || i >= n) return;
+  r = (part[0][l] + part[1][l]) + (part[2][l] + part[3][l]);
   rank[i] = r;
   atomicMax(&cnt[static_cast<long>(c) * g + gi], r + 1);  // the chunk's count of gi (cnt starts at zero)
 }
@@ -156,7 +164,18 @@ agg_reduce(const double* __restrict__ X, long ldx, int n, const double* __restri
 // column groups' gathers hit LDS instead of scattered HBM lines.  Thread t
 // owns the outputs H = t, t + AGGL_THREADS, ... (at most HPT of them) in
 // registers; every sum runs in the same member order as agg_reduce, so both
-// give the same bits.  Used when a row of X fits in AGGL_MAX_LDS.
+// give the same bits.  What a thread's outputs gather does not change from row
+// to row, so the column groups' ranges and (up to eight outputs per thread)
+// their first members stay in registers, and the next row's loads run under
+// the gathers: 8192 faces to 2048 (537 MB) 187 -> 108 us against loading the
+// ranges and members again for every row and output.  Used when a row of X fits in
+// AGGL_MAX_LDS.
+// MODE: what becomes of the sums.
+constexpr int AGG_SUMS = 0;        // Y = sums (divided by the group weight if divide)
+constexpr int AGG_RATIO = 1;       // Y[0] = sums under w[0] / sums under w[1] (eq. C.4; where
+                                   // those are zero the ratio of the group weights)
+constexpr int AGG_FRACTIONS = 2;   // unit weights; Y[0] (n x (n+1)) = X_ij / the sum of its group pair
+                                   // (0 where that is 0), from a second, cached read of G's rows
 constexpr int AGGL_THREADS = 512;
 constexpr size_t AGGL_MAX_LDS = 150 * 1024;
 
@@ -169,108 +188,201 @@ struct AggOut {
   double* gw[2];       // group weights (nullable)
 };
 
-template <int HPT, int NWT>
-__global__ void __launch_bounds__(AGGL_THREADS)
-agg_reduce_lds(const double* __restrict__ X, long ldx, int n, const int* __restrict__ offs,
-               const int* __restrict__ members, int g, AggOut o, long ldy, int divide) {
+template <int HPT, int NWT, int MODE>
+__global__ void __launch_bounds__(AGGL_THREADS, HPT <= 8 ? 4 : 2)
+agg_reduce_lds(const double* __restrict__ X, long ldx, int n, const int* __restrict__ group,
+               const int* __restrict__ offs, const int* __restrict__ members, int g, AggOut o, long ldy, int divide) {
   extern __shared__ double xrow[];  // n + 1
-  const int G = blockIdx.x;
+  constexpr int CM = HPT <= 2 ? 16 : HPT <= 4 ? 4 : HPT <= 8 ? 2 : 0;  // members kept per output
+  constexpr int PF = HPT >= 8 && NWT == 2 ? (HPT > 16 ? 4 : 12) : 16;  // entries of the next row in flight per thread
+  const int G = blockIdx.x, tid = threadIdx.x;
   const int rb = offs[G], re = offs[G + 1];
-  double acc[NWT][HPT];
+  // column groups of the thread's outputs: first member index and count, and
+  // the first members, 16 bits each (a row that fits the LDS has fewer entries)
+  static_assert(AGGL_MAX_LDS / sizeof(double) < 65536, "indices of 16 bits");
+  unsigned rc[HPT], cm[HPT][CM / 2 + 1];
 #pragma unroll
-  for (int t = 0; t < NWT; ++t)
+  for (int k = 0; k < HPT; ++k) {
+    const int H = min(tid + k * AGGL_THREADS, g - 1);
+    const int cb = offs[H], cn = offs[H + 1] - cb;
+    rc[k] = static_cast<unsigned>(cb) | static_cast<unsigned>(cn) << 16;
+  }
+#pragma unroll
+  for (int k = 0; k < HPT; ++k) {
+    const int cb = rc[k] & 0xffff, cn = rc[k] >> 16;
+#pragma unroll
+    for (int u = 0; u < CM; u += 2) {
+      // clamped addresses; entries past the group are not used as an index
+      const unsigned m0 = members[max(0, min(cb + u, cb + cn - 1))], m1 = members[max(0, min(cb + u + 1, cb + cn - 1))];
+      cm[k][u / 2] = (u < cn ? m0 : 0u) | (u + 1 < cn ? m1 : 0u) << 16;
+    }
+  }
+  double acc[NWT][HPT], accs[NWT], wsum[NWT];  // accs: the space column
+#pragma unroll
+  for (int t = 0; t < NWT; ++t) {
+    accs[t] = wsum[t] = 0.0;
 #pragma unroll
     for (int k = 0; k < HPT; ++k) acc[t][k] = 0.0;
-  double wsum[NWT];
+  }
+  // entries of a row in pieces of AGGL_THREADS; the last piece of a row ends
+  // with it (overlapping the one before), so no lane needs a bounds test
+  const int lane = min(tid, n), last = max(0, n + 1 - AGGL_THREADS);
+  double v[PF];
+  auto load = [&](int i) {
+    const double* row = X + static_cast<long>(i) * ldx;
 #pragma unroll
-  for (int t = 0; t < NWT; ++t) wsum[t] = 0.0;
+    for (int u = 0; u < PF; ++u)
+      if (u * AGGL_THREADS <= n) {
+        const double* p = row + min(u * AGGL_THREADS, last);
+        v[u] = MODE == AGG_FRACTIONS ? p[lane] : __builtin_nontemporal_load(p + lane);
+      }
+  };
+  int i = rb < re ? members[rb] : 0;
+  if (rb < re) load(i);
   for (int a = rb; a < re; ++a) {
-    const int i = members[a];
     double wi[NWT];
 #pragma unroll
     for (int t = 0; t < NWT; ++t) {
-      wi[t] = o.w[t][i];
+      wi[t] = MODE == AGG_FRACTIONS ? 1.0 : o.w[t][i];
       wsum[t] += wi[t];
     }
-    const double* row = X + static_cast<long>(i) * ldx;
+    const int inext = a + 1 < re ? members[a + 1] : i;
     __syncthreads();  // the previous row's gathers are done
-    // eight loads per thread in flight (addresses clamped to the row, so no
-    // load waits behind a bounds branch)
-    for (int j0 = 0; j0 <= n; j0 += 8 * AGGL_THREADS) {
-      double v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        v[u] = __builtin_nontemporal_load(row + min(j0 + u * AGGL_THREADS + static_cast<int>(threadIdx.x), n));
+    for (int u = 0; u < PF; ++u)
+      if (u * AGGL_THREADS <= n) xrow[min(u * AGGL_THREADS, last) + lane] = v[u];
+    const double* row = X + static_cast<long>(i) * ldx;
+    for (int j0 = PF * AGGL_THREADS; j0 <= n; j0 += 8 * AGGL_THREADS) {  // rows longer than the registers hold
+      double x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = row[min(j0 + u * AGGL_THREADS + tid, n)];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int j = j0 + u * AGGL_THREADS + static_cast<int>(threadIdx.x);
-        if (j <= n) xrow[j] = v[u];
+        const int j = j0 + u * AGGL_THREADS + tid;
+        if (j <= n) xrow[j] = x[u];
       }
     }
+    i = inext;
+    if (a + 1 < re) load(i);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < HPT; ++k) {
-      const int H = threadIdx.x + k * AGGL_THREADS;
-      if (H < g) {
-        const int cb = offs[H], ce = offs[H + 1];
-        double sv = 0.0;
-        for (int b0 = cb; b0 < ce; b0 += 4) {  // four index loads in flight, sums in member order
-          int m[4];
+      // (opaque here, or the unpacked addresses of every output are kept across
+      // the rows and spill)
+      __asm__ volatile("" : "+v"(rc[k]));
 #pragma unroll
-          for (int u = 0; u < 4; ++u) m[u] = members[min(b0 + u, ce - 1)];
+      for (int u = 0; u < CM / 2; ++u) __asm__ volatile("" : "+v"(cm[k][u]));
+      const int cb = rc[k] & 0xffff, cn = rc[k] >> 16;
+      double sv = 0.0;
 #pragma unroll
-          for (int u = 0; u < 4; ++u)
-            if (b0 + u < ce) sv += xrow[m[u]];
+      for (int u = 0; u < CM; ++u) {
+        const double x = xrow[u % 2 ? cm[k][u / 2] >> 16 : cm[k][u / 2] & 0xffff];
+        if (u < cn) sv += x;
+      }
+      for (int b0 = CM; b0 < cn; b0 += 4) {  // four index loads in flight, sums in member order
+        int m[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) m[u] = members[cb + min(b0 + u, cn - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (b0 + u < cn) sv += xrow[m[u]];
+      }
+#pragma unroll
+      for (int t = 0; t < NWT; ++t) acc[t][k] += wi[t] * sv;
+    }
+#pragma unroll
+    for (int t = 0; t < NWT; ++t) accs[t] += wi[t] * xrow[n];
+  }
+  if constexpr (MODE == AGG_SUMS) {
+#pragma unroll
+    for (int t = 0; t < NWT; ++t) {
+#pragma unroll
+      for (int k = 0; k < HPT; ++k) {
+        const int H = tid + k * AGGL_THREADS;
+        if (H < g) o.Y[t][static_cast<long>(G) * ldy + H] = divide ? acc[t][k] / wsum[t] : acc[t][k];
+      }
+      if (tid == 0) {
+        o.Y[t][static_cast<long>(G) * ldy + g] = divide ? accs[t] / wsum[t] : accs[t];
+        if (o.gw[t]) o.gw[t][G] = wsum[t];
+      }
+    }
+  } else if constexpr (MODE == AGG_RATIO) {
+    const double mean = wsum[0] / wsum[NWT - 1];
+#pragma unroll
+    for (int k = 0; k < HPT; ++k) {
+      const int H = tid + k * AGGL_THREADS;
+      const double d = acc[NWT - 1][k];
+      if (H < g) o.Y[0][static_cast<long>(G) * ldy + H] = d != 0.0 ? acc[0][k] / d : mean;
+    }
+    if (tid == 0) o.Y[0][static_cast<long>(G) * ldy + g] = accs[NWT - 1] != 0.0 ? accs[0] / accs[NWT - 1] : mean;
+  } else {
+    __syncthreads();  // the last row's gathers are done
+#pragma unroll
+    for (int k = 0; k < HPT; ++k) {
+      const int H = tid + k * AGGL_THREADS;
+      if (H < g) xrow[H] = acc[0][k];
+    }
+    if (tid == 0) xrow[g] = accs[0];
+    __syncthreads();
+    for (int a = rb; a < re; ++a) {
+      const int r = members[a];
+      const double* xr = X + static_cast<long>(r) * ldx;
+      double* yr = o.Y[0] + static_cast<long>(r) * ldy;
+      // eight columns per thread with their loads in flight together
+      for (int b0 = tid; b0 <= n; b0 += 8 * AGGL_THREADS) {
+        int hv[8];
+        double fv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int b = min(b0 + u * AGGL_THREADS, n);
+          hv[u] = group[min(b, n - 1)];
+          fv[u] = xr[b];
         }
 #pragma unroll
-        for (int t = 0; t < NWT; ++t) acc[t][k] += wi[t] * sv;
-      } else if (H == g) {
-#pragma unroll
-        for (int t = 0; t < NWT; ++t) acc[t][k] += wi[t] * xrow[n];
+        for (int u = 0; u < 8; ++u) {
+          const int b = b0 + u * AGGL_THREADS;
+          if (b > n) break;
+          const int H = b < n ? hv[u] : g;
+          const double den = (H >= 0 && H <= g) ? xrow[H] : 0.0;
+          __builtin_nontemporal_store(den != 0.0 ? fv[u] / den : 0.0, yr + b);
+        }
       }
     }
   }
-#pragma unroll
-  for (int t = 0; t < NWT; ++t) {
-#pragma unroll
-    for (int k = 0; k < HPT; ++k) {
-      const int H = threadIdx.x + k * AGGL_THREADS;
-      if (H <= g) o.Y[t][static_cast<long>(G) * ldy + H] = divide ? acc[t][k] / wsum[t] : acc[t][k];
-    }
-    if (o.gw[t] && threadIdx.x == 0) o.gw[t][G] = wsum[t];
-  }
 }
 
-// agg_reduce_lds when the row fits in LDS and the outputs in registers, else
-// agg_reduce (once per weighting)
-template <int NWT>
-void launch_agg_n(const double* X, long ldx, int n, const AggOut& o, const int* offs, const int* members, int g,
-                  long ldy, int divide, hipStream_t s) {
+// agg_reduce_lds if the row fits in LDS and the outputs in registers; false if
+// not (nothing is launched then).
+template <int HPT, int NWT, int MODE>
+bool launch_agg_hpt(const double* X, long ldx, int n, const int* group, const AggOut& o, const int* offs,
+                    const int* members, int g, long ldy, int divide, hipStream_t s) {
   const size_t lds = static_cast<size_t>(n + 1) * sizeof(double);
-  const int hpt = (g + AGGL_THREADS) / AGGL_THREADS;  // ceil((g + 1) / AGGL_THREADS)
-  if (lds <= AGGL_MAX_LDS && hpt <= 32) {
-    // dynamic LDS beyond the default 64 KB has to be allowed per kernel
-    auto allow = [](const void* fn) {
-      return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(AGGL_MAX_LDS)) ==
-             hipSuccess;
-    };
-    const void* fn = hpt <= 4    ? reinterpret_cast<const void*>(&agg_reduce_lds<4, NWT>)
-                     : hpt <= 16 ? reinterpret_cast<const void*>(&agg_reduce_lds<16, NWT>)
-                                 : reinterpret_cast<const void*>(&agg_reduce_lds<32, NWT>);
-    if (lds <= 64 * 1024 || allow(fn)) {
-      if (hpt <= 4)
-        hipLaunchKernelGGL((agg_reduce_lds<4, NWT>), dim3(static_cast<unsigned>(g)), dim3(AGGL_THREADS), lds, s, X,
-                           ldx, n, offs, members, g, o, ldy, divide);
-      else if (hpt <= 16)
-        hipLaunchKernelGGL((agg_reduce_lds<16, NWT>), dim3(static_cast<unsigned>(g)), dim3(AGGL_THREADS), lds, s, X,
-                           ldx, n, offs, members, g, o, ldy, divide);
-      else
-        hipLaunchKernelGGL((agg_reduce_lds<32, NWT>), dim3(static_cast<unsigned>(g)), dim3(AGGL_THREADS), lds, s, X,
-                           ldx, n, offs, members, g, o, ldy, divide);
-      return;
-    }
-    (void)hipGetLastError();  // the attribute was refused: the gather form below
+  if (lds > 64 * 1024 &&  // dynamic LDS beyond the default 64 KB has to be allowed per kernel
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&agg_reduce_lds<HPT, NWT, MODE>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(AGGL_MAX_LDS)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
   }
+  hipLaunchKernelGGL((agg_reduce_lds<HPT, NWT, MODE>), dim3(static_cast<unsigned>(g)), dim3(AGGL_THREADS), lds, s, X,
+                     ldx, n, group, offs, members, g, o, ldy, divide);
+  return true;
+}
+template <int NWT, int MODE>
+bool launch_agg_lds(const double* X, long ldx, int n, const int* group, const AggOut& o, const int* offs,
+                    const int* members, int g, long ldy, int divide, hipStream_t s) {
+  const int hpt = (g + AGGL_THREADS - 1) / AGGL_THREADS;
+  if (static_cast<size_t>(n + 1) * sizeof(double) > AGGL_MAX_LDS || hpt > 32) return false;
+  if (hpt <= 2) return launch_agg_hpt<2, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
+  if (hpt <= 4) return launch_agg_hpt<4, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
+  if (hpt <= 8) return launch_agg_hpt<8, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
+  if (hpt <= 16) return launch_agg_hpt<16, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
+  return launch_agg_hpt<32, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
+}
+
+// the sums of rows too long for LDS, once per weighting
+template <int NWT>
+void launch_agg_gather(const double* X, long ldx, int n, const AggOut& o, const int* offs, const int* members, int g,
+                       long ldy, int divide, hipStream_t s) {
   dim3 grid(static_cast<unsigned>(ceil_div(g + 1, AGG_THREADS)), static_cast<unsigned>(g));
   for (int t = 0; t < NWT; ++t)
     hipLaunchKernelGGL(agg_reduce, grid, dim3(AGG_THREADS), 0, s, X, ldx, n, o.w[t], offs, members, g, o.Y[t], ldy,
@@ -279,10 +391,14 @@ void launch_agg_n(const double* X, long ldx, int n, const AggOut& o, const int* 
 
 void launch_agg(const double* X, long ldx, int n, const double* w, const int* offs, const int* members, int g,
                 double* Y, long ldy, double* gw, int divide, hipStream_t s) {
-  launch_agg_n<1>(X, ldx, n, AggOut{{w, nullptr}, {Y, nullptr}, {gw, nullptr}}, offs, members, g, ldy, divide, s);
+  const AggOut o{{w, nullptr}, {Y, nullptr}, {gw, nullptr}};
+  if (!launch_agg_lds<1, AGG_SUMS>(X, ldx, n, nullptr, o, offs, members, g, ldy, divide, s))
+    launch_agg_gather<1>(X, ldx, n, o, offs, members, g, ldy, divide, s);
 }
 
-__global__ void __launch_bounds__(256) zero_ints(int* __restrict__ p, long count) {
+// status and the chunk counts
+__global__ void __launch_bounds__(256) csr_init(int* __restrict__ status, int* __restrict__ p, long count) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *status = 0;
   for (long q = blockIdx.x * static_cast<long>(blockDim.x) + threadIdx.x; q < count;
        q += static_cast<long>(gridDim.x) * blockDim.x)
     p[q] = 0;
@@ -333,47 +449,6 @@ vf_fraction(const double* __restrict__ F, long ldf, int nf, const int* __restric
   }
 }
 
-// The same quotients with one workgroup per node G: its row of D is staged
-// in LDS once, then the rows of G's faces stream through (coalesced loads
-// and stores; the column-to-node map is read coalesced and stays in cache,
-// the gathers hit LDS).  Used when g + 1 doubles fit in VF_LDS_BYTES.
-constexpr size_t VF_LDS_BYTES = 64 * 1024;
-
-__global__ void __launch_bounds__(256)
-vf_fraction_lds(const double* __restrict__ F, long ldf, int nf, const int* __restrict__ group, int g,
-                const int* __restrict__ offs, const int* __restrict__ members, const double* __restrict__ D,
-                long ldd, double* __restrict__ R, long ldr) {
-  extern __shared__ double drow[];  // g + 1
-  const int G = blockIdx.x;
-  for (int h = threadIdx.x; h <= g; h += blockDim.x) drow[h] = D[static_cast<long>(G) * ldd + h];
-  __syncthreads();
-  for (int m = offs[G]; m < offs[G + 1]; ++m) {
-    const int a = members[m];
-    const double* frow = F + static_cast<long>(a) * ldf;
-    double* rrow = R + static_cast<long>(a) * ldr;
-    // eight columns per thread with their loads in flight together
-    // (addresses clamped into the row; selects on computed values only)
-    for (int b0 = 0; b0 <= nf; b0 += 8 * 256) {
-      int hv[8];
-      double fv[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int b = min(b0 + u * 256 + static_cast<int>(threadIdx.x), nf);
-        hv[u] = group[min(b, nf - 1)];
-        fv[u] = __builtin_nontemporal_load(frow + b);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int b = b0 + u * 256 + static_cast<int>(threadIdx.x);
-        if (b > nf) break;
-        const int H = b < nf ? hv[u] : g;
-        const double den = (H >= 0 && H <= g) ? drow[H] : 0.0;
-        rrow[b] = den != 0.0 ? fv[u] / den : 0.0;
-      }
-    }
-  }
-}
-
 // eq. C.4: eps_GH = (sum_{a in G} eps_a S_a sum_{b in H} B_ab) / (sum_{a in G} S_a sum_{b in H} B_ab);
 // a pair without exchange gets the node's area-mean emissivity.
 __global__ void __launch_bounds__(256)
@@ -407,30 +482,16 @@ __global__ void __launch_bounds__(256) fill_ones(double* __restrict__ p, int n) 
   if (a < n) p[a] = 1.0;
 }
 
-// CSR of the group map (members of each group in face order), shared by the reductions of one call
+// CSR of the group map (members of each group in index order), shared by the reductions of one call
 void agg_build(const int32_t* group, int n, int g, const AggLayout& l, hipStream_t s) {
   const long ncnt = static_cast<long>(l.nch) * g;
-  hipLaunchKernelGGL(zero_ints, dim3(1), dim3(64), 0, s, l.status, 1L);
-  hipLaunchKernelGGL(zero_ints, dim3(static_cast<unsigned>(std::min<long>(ceil_div(ncnt, 256), 4096))), dim3(256), 0,
-                     s, l.cnt, ncnt);
-  hipLaunchKernelGGL(csr_rank, dim3(static_cast<unsigned>(l.nch)), dim3(CSR_CHUNK), 0, s, group, n, g, l.rank,
-                     l.cnt, l.status);
+  hipLaunchKernelGGL(csr_init, dim3(static_cast<unsigned>(std::min<long>(ceil_div(ncnt, 256), 4096))), dim3(256), 0,
+                     s, l.status, l.cnt, ncnt);
+  hipLaunchKernelGGL(csr_rank, dim3(static_cast<unsigned>(ceil_div(n, CSR_SUB))), dim3(256), 0, s, group, n, g,
+                     l.rank, l.cnt, l.status);
   hipLaunchKernelGGL(csr_offsets, dim3(1), dim3(1024), 0, s, l.cnt, l.nch, g, l.offs, l.status);
   hipLaunchKernelGGL(csr_scatter, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, group, n, g,
                      l.rank, l.cnt, l.offs, l.members);
-}
-
-void agg_sums(const double* X, long ldx, int n, const double* w, const AggLayout& l, int g, double* Y, long ldy,
-              double* gw, hipStream_t s) {
-  ProfScope prof(s, RAD_PROF_AGGREGATE, 0.0, 8.0 * static_cast<double>(n) * (n + 1));
-  launch_agg(X, ldx, n, w, l.offs, l.members, g, Y, ldy, gw, 0, s);
-}
-
-// the same sums under two weightings in one pass over X
-void agg_sums2(const double* X, long ldx, int n, const double* w0, const double* w1, const AggLayout& l, int g,
-               double* Y0, double* Y1, long ldy, double* gw0, double* gw1, hipStream_t s) {
-  ProfScope prof(s, RAD_PROF_AGGREGATE, 0.0, 8.0 * static_cast<double>(n) * (n + 1));
-  launch_agg_n<2>(X, ldx, n, AggOut{{w0, w1}, {Y0, Y1}, {gw0, gw1}}, l.offs, l.members, g, ldy, 0, s);
 }
 
 int read_status(const int* dev, hipStream_t s, int* out) {
@@ -496,15 +557,7 @@ extern "C" int32_t rad_aggregate_nodes(const double* X, int64_t n, int64_t ldx,
               "rad_aggregate_nodes: workspace too small or not 256-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int ni = static_cast<int>(n), gi = static_cast<int>(g);
-  const long ncnt = static_cast<long>(l.nch) * g;
-  hipLaunchKernelGGL(zero_ints, dim3(1), dim3(64), 0, s, l.status, 1L);
-  hipLaunchKernelGGL(zero_ints, dim3(static_cast<unsigned>(std::min<long>(ceil_div(ncnt, 256), 4096))), dim3(256), 0,
-                     s, l.cnt, ncnt);
-  hipLaunchKernelGGL(csr_rank, dim3(static_cast<unsigned>(l.nch)), dim3(CSR_CHUNK), 0, s, group, ni, gi, l.rank,
-                     l.cnt, l.status);
-  hipLaunchKernelGGL(csr_offsets, dim3(1), dim3(1024), 0, s, l.cnt, l.nch, gi, l.offs, l.status);
-  hipLaunchKernelGGL(csr_scatter, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, group, ni, gi,
-                     l.rank, l.cnt, l.offs, l.members);
+  agg_build(group, ni, gi, l, s);
   {
     ProfScope prof(s, RAD_PROF_AGGREGATE, 0.0, 8.0 * static_cast<double>(n) * (n + 1));
     launch_agg(X, static_cast<long>(ldx), ni, weight, l.offs, l.members, gi, Y, static_cast<long>(ldy),
@@ -546,19 +599,21 @@ extern "C" int32_t rad_view_fractions(const double* F, int64_t nf, int64_t ldf, 
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int ni = static_cast<int>(nf), gi = static_cast<int>(g);
   agg_build(group, ni, gi, t.agg, s);
-  hipLaunchKernelGGL(fill_ones, dim3(static_cast<unsigned>(ceil_div(nf, 256))), dim3(256), 0, s, t.w, ni);
-  agg_sums(F, static_cast<long>(ldf), ni, t.w, t.agg, gi, t.d0, t.ldd, nullptr, s);
-  const size_t lds = static_cast<size_t>(g + 1) * sizeof(double);
-  if (lds <= VF_LDS_BYTES) {
+  {
+    ProfScope prof(s, RAD_PROF_AGGREGATE, 0.0, 8.0 * static_cast<double>(nf) * (nf + 1));
     // (rows of faces whose node id is out of range are left unwritten; the
     // call reports that error when stats are requested)
-    hipLaunchKernelGGL(vf_fraction_lds, dim3(static_cast<unsigned>(g)), dim3(256), lds, s, F, static_cast<long>(ldf),
-                       ni, group, gi, t.agg.offs, t.agg.members, t.d0, t.ldd, R, static_cast<long>(ldr));
-  } else {
-    hipLaunchKernelGGL(vf_fraction, dim3(static_cast<unsigned>(ceil_div(nf + 1, 256)),
-                                         static_cast<unsigned>(std::min<int64_t>(nf, 32768))),
-                       dim3(256), 0, s, F, static_cast<long>(ldf), ni, group, gi, t.d0, t.ldd, R,
-                       static_cast<long>(ldr));
+    const AggOut o{{nullptr, nullptr}, {R, nullptr}, {nullptr, nullptr}};
+    if (!launch_agg_lds<1, AGG_FRACTIONS>(F, static_cast<long>(ldf), ni, group, o, t.agg.offs, t.agg.members, gi,
+                                          static_cast<long>(ldr), 0, s)) {
+      hipLaunchKernelGGL(fill_ones, dim3(static_cast<unsigned>(ceil_div(nf, 256))), dim3(256), 0, s, t.w, ni);
+      launch_agg_gather<1>(F, static_cast<long>(ldf), ni, AggOut{{t.w, nullptr}, {t.d0, nullptr}, {nullptr, nullptr}},
+                           t.agg.offs, t.agg.members, gi, t.ldd, 0, s);
+      hipLaunchKernelGGL(vf_fraction, dim3(static_cast<unsigned>(ceil_div(nf + 1, 256)),
+                                           static_cast<unsigned>(std::min<int64_t>(nf, 32768))),
+                         dim3(256), 0, s, F, static_cast<long>(ldf), ni, group, gi, t.d0, t.ldd, R,
+                         static_cast<long>(ldr));
+    }
   }
   RAD_HIP_CHECK(hipGetLastError());
   if (!stats) return RAD_OK;
@@ -599,9 +654,18 @@ extern "C" int32_t rad_node_emissivity(const double* B, int64_t nf, int64_t ldb,
   agg_build(group, ni, gi, t.agg, s);
   hipLaunchKernelGGL(face_weights, dim3(static_cast<unsigned>(ceil_div(nf, 256))), dim3(256), 0, s, eps, area, ni,
                      t.w, t.agg.status);
-  agg_sums2(B, static_cast<long>(ldb), ni, t.w, area, t.agg, gi, t.d0, t.d1, t.ldd, t.gw0, t.gw1, s);
-  hipLaunchKernelGGL(ne_ratio, dim3(static_cast<unsigned>(ceil_div(g + 1, 256)), static_cast<unsigned>(std::min<int64_t>(g, 32768))), dim3(256),
-                     0, s, t.d0, t.d1, t.ldd, t.gw0, t.gw1, gi, E, static_cast<long>(lde));
+  {
+    ProfScope prof(s, RAD_PROF_AGGREGATE, 0.0, 8.0 * static_cast<double>(nf) * (nf + 1));
+    const AggOut o{{t.w, area}, {E, nullptr}, {nullptr, nullptr}};
+    if (!launch_agg_lds<2, AGG_RATIO>(B, static_cast<long>(ldb), ni, nullptr, o, t.agg.offs, t.agg.members, gi,
+                                      static_cast<long>(lde), 0, s)) {
+      launch_agg_gather<2>(B, static_cast<long>(ldb), ni, AggOut{{t.w, area}, {t.d0, t.d1}, {t.gw0, t.gw1}},
+                           t.agg.offs, t.agg.members, gi, t.ldd, 0, s);
+      hipLaunchKernelGGL(ne_ratio, dim3(static_cast<unsigned>(ceil_div(g + 1, 256)),
+                                        static_cast<unsigned>(std::min<int64_t>(g, 32768))),
+                         dim3(256), 0, s, t.d0, t.d1, t.ldd, t.gw0, t.gw1, gi, E, static_cast<long>(lde));
+    }
+  }
   RAD_HIP_CHECK(hipGetLastError());
   if (!stats) return RAD_OK;
   int st = 0;

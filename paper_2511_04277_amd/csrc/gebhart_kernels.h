@@ -1031,7 +1031,16 @@ ref_closure(const double* __restrict__ B, long ldb, int n, double* __restrict__ 
   double s = 0.0;
   if (row < n) {
     const double* __restrict__ b = B + static_cast<long>(row) * ldb;
-    for (int j = l; j <= n; j += 64) s += b[j];
+    // eight loads per lane in flight (addresses clamped into the row); the sum
+    // still runs over the columns in increasing order
+    for (int j0 = l; j0 <= n; j0 += 8 * 64) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = b[min(j0 + 64 * u, n)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (j0 + 64 * u <= n) s += v[u];
+    }
   }
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
   if (l == 0) red[w] = (row < n) ? fabs(s - 1.0) : 0.0;
