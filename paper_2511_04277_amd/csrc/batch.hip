@@ -39,7 +39,7 @@ struct rad_batch_plan {
   std::vector<ProbOff> po;
   size_t tables_off = 0;
   // launch schedule (table offsets relative to the tables block)
-  struct Launch { int kind; int trans; int ts; unsigned grid; size_t off, off2; int count; double flops, bytes; };
+  struct Launch { int kind; int trans; unsigned grid; size_t off, off2; int count; double flops, bytes; };
   std::vector<Launch> factor, back, fwd, resid;
   size_t off_enf = 0, off_fblk = 0, off_row = 0, off_pd = 0, off_nprow = 0, off_nrow = 0;
   size_t off_pair_map = 0, off_fin_map = 0;
@@ -51,7 +51,7 @@ namespace rad {
 namespace {
 
 enum { L_GJ = 0, L_GEMM = 1, L_COPY = 2, L_TRI_INIT = 3, L_EMU_EXP_KC = 4, L_EMU_EXP_RC = 5, L_EMU_SPLIT_KC = 6,
-       L_EMU_SPLIT_RC = 7, L_EMU_GEMM = 8 };
+       L_EMU_SPLIT_RC = 7, L_EMU_GEMM = 8, L_LBLOCK = 9 };
 
 // One operand of the int8-emulated products of a batched launch (the digits
 // and exponents of each problem's operands have buffers of their own): the
@@ -112,11 +112,27 @@ b_copy_jobs(const CopyJob<T>* __restrict__ jobs, const long* __restrict__ start,
   for (int c = threadIdx.x; c < j.cols; c += blockDim.x) j.dst[i * j.ldd + c] = j.src[i * j.lds + c];
 }
 
+// the L blocks of one step of many problems: start[q] = first workgroup of job q
 template <class T>
-__global__ void __launch_bounds__(256)
+struct LblockJob {
+  T* A;
+  long lda;
+  const T* D;
+};
+template <class T, int RB>
+__global__ void __launch_bounds__(256, 2)
+lblock_batched(const LblockJob<T>* __restrict__ jobs, const long* __restrict__ start, int count) {
+  __shared__ LblockShared<T, RB> sh;
+  const int q = find_segment(start, count, blockIdx.x);
+  const LblockJob<T> j = jobs[q];
+  lblock_rows<T, RB>(j.A + (blockIdx.x - start[q]) * (16 * RB) * j.lda, j.lda, j.D, sh);
+}
+
+template <class T>
+__global__ void __launch_bounds__(256, 2)
 b_tri_init(const TriJob<T>* __restrict__ jobs, const long* __restrict__ start, int count) {
   const int q = find_segment(start, count, blockIdx.x);
-  tri_init_row<T>(jobs[q], static_cast<int>(blockIdx.x - start[q]));
+  tri_init_block<T>(jobs[q], static_cast<int>(blockIdx.x - start[q]));
 }
 
 struct ProbDesc {
@@ -270,36 +286,11 @@ b_apply_correction(const ProbDesc* __restrict__ pd, const long* __restrict__ sta
   block_max(m, &d.sc->max_d);
 }
 
-// persistent grouped GEMM: workgroups walk the concatenated tile list of
-// TS x TS tiles
-template <class T, bool TRANS_A, int TS>
-__global__ void __launch_bounds__(256, TS == GEMM_TILE ? 2 : 4)
-gemm_grouped_persistent(const GemmArgs<T>* __restrict__ probs, const int* __restrict__ tile_start, int nprob) {
-  // Tiles are taken in list order, so consecutive tiles go to different
-  // XCDs: the problems of a launch differ widely in K, and giving each XCD a
-  // contiguous range (as for one product) would load some XCDs with all the
-  // large problems.
-  const int total = tile_start[nprob];
-  for (int b = blockIdx.x; b < total; b += gridDim.x) {
-    const int t = b;
-    int lo = 0, hi = nprob - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (tile_start[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    const GemmArgs<T>& g = probs[lo];
-    int ntx = 0;
-    for (int q = 0; q < g.nseg; ++q) ntx += g.N[q] > 0 ? (g.N[q] + TS - 1) / TS : 0;
-    int bx, by;
-    grouped_tile(t - tile_start[lo], ntx, (g.M + TS - 1) / TS, TILE_GROUP, bx, by);
-    gemm_tile<T, TRANS_A, TS, false>(g, bx, by);
-  }
-}
-
-// The same walk with one 64 x 64 tile per workgroup (grid = all tiles, so the
-// hardware hands them out in list order, round robin over the XCDs): without
-// the persistent loop the tile keeps its C values in registers across the K
-// loop, as the single-product kernel does.
+// Grouped GEMM over the concatenated tile list of a launch's products, one
+// 64 x 64 tile per workgroup.  The hardware hands the tiles out in list order,
+// round robin over the XCDs: the products differ widely in K, and giving each
+// XCD a contiguous range (as for one product) would load some XCDs with all
+// the large ones.
 template <class T, bool TRANS_A>
 __global__ void __launch_bounds__(256, 4)
 gemm_grouped_tiles(const GemmArgs<T>* __restrict__ probs, const int* __restrict__ tile_start, int nprob) {
@@ -314,13 +305,7 @@ gemm_grouped_tiles(const GemmArgs<T>* __restrict__ probs, const int* __restrict_
   for (int q = 0; q < g.nseg; ++q) ntx += g.N[q] > 0 ? (g.N[q] + 63) / 64 : 0;
   int bx, by;
   grouped_tile(t - tile_start[lo], ntx, (g.M + 63) / 64, TILE_GROUP, bx, by);
-  gemm_tile<T, TRANS_A, 64, true>(g, bx, by);
-}
-
-// resident workgroups of the persistent kernel: two 128-tiles per CU; the
-// 64-tile launches take one workgroup per tile
-inline unsigned grouped_grid(int ts, int tiles) {
-  return ts == GEMM_TILE ? std::min<unsigned>(static_cast<unsigned>(tiles), 2 * 256) : static_cast<unsigned>(tiles);
+  gemm_tile<T, TRANS_A, 64>(g, bx, by);
 }
 
 // ------------------------------------------------------------- host side ---
@@ -336,18 +321,15 @@ struct TableBuilder {
 };
 
 // One grouped GEMM launch over the products a (cleared).  Grouped launches
-// take 64 x 64 tiles unless a product is in place: their persistent grids
-// hold many problems' tiles at once, where the smaller tile balances better
-// (measured on the 64-model batch: 100.5 ms per step vs 107.4 ms with the
-// single-product rule).  False if there is no work.
+// take 64 x 64 tiles: they hold many problems' tiles at once, where the
+// smaller tile balances better (measured on the 64-model batch: 100.5 ms per
+// step vs 107.4 ms with the single-product rule).  False if there is no work.
 template <class U>
 bool gemm_launch(TableBuilder* tb, std::vector<GemmArgs<U>>& a, bool trans, rad_batch_plan::Launch& L) {
   int t128 = 0;
-  bool inplace = false;
   double flops = 0.0, bytes = 0.0;
   for (auto& g : a) {
     t128 += gemm_tiles<U>(g);
-    inplace = inplace || g.inplace;
     flops += gemm_flops(g);
     bytes += gemm_bytes(g);
   }
@@ -355,24 +337,20 @@ bool gemm_launch(TableBuilder* tb, std::vector<GemmArgs<U>>& a, bool trans, rad_
     a.clear();
     return false;
   }
-  const int ts = inplace ? GEMM_TILE : 64;
   std::vector<int> st(a.size() + 1, 0);
   for (size_t k = 0; k < a.size(); ++k) {
     const GemmArgs<U>& g = a[k];
-    const int n = (g.M <= 0 || g.K <= 0) ? 0
-                  : (ts == GEMM_TILE ? gemm_tiles<U>(a[k]) : tiles_x<U, 64>(g) * ((g.M + 63) / 64));
-    st[k + 1] = st[k] + n;
+    st[k + 1] = st[k] + ((g.M <= 0 || g.K <= 0) ? 0 : tiles_x<U, 64>(g) * ((g.M + 63) / 64));
   }
   L = rad_batch_plan::Launch{};
   L.kind = L_GEMM;
   L.trans = trans ? 1 : 0;
-  L.ts = ts;
   L.flops = flops;
   L.bytes = bytes;
   L.count = static_cast<int>(a.size());
   L.off = tb->add(a.data(), a.size());
   L.off2 = tb->add(st.data(), st.size());
-  L.grid = grouped_grid(ts, st.back());
+  L.grid = static_cast<unsigned>(st.back());
   a.clear();
   return true;
 }
@@ -483,6 +461,25 @@ struct Sched {
     rad_batch_plan::Launch L;
     if (gemm_launch<T>(tb, a, trans, L)) out.push_back(L);
   }
+  void emit_lblock(std::vector<rad_batch_plan::Launch>& out, std::vector<LblockJob<T>>& j, std::vector<long>& rows) {
+    if (j.empty()) return;
+    long total = 0;
+    for (long r : rows) total += r;
+    rad_batch_plan::Launch L{};
+    L.trans = total > LBLOCK_ROWS16 ? 1 : 0;  // 32 rows per workgroup
+    std::vector<long> st(1, 0);
+    for (long r : rows) st.push_back(st.back() + r / (L.trans ? 32 : 16));
+    L.kind = L_LBLOCK;
+    L.count = static_cast<int>(j.size());
+    L.grid = static_cast<unsigned>(st.back());
+    L.off = tb->add(j.data(), j.size());
+    L.off2 = tb->add(st.data(), st.size());
+    L.flops = 2.0 * total * NB * NB;
+    L.bytes = sizeof(T) * (2.0 * total + static_cast<double>(NB) * j.size()) * NB;
+    out.push_back(L);
+    j.clear();
+    rows.clear();
+  }
   void emit_gj(std::vector<rad_batch_plan::Launch>& out, std::vector<GjJob<T>>& j) {
     if (j.empty()) return;
     rad_batch_plan::Launch L{};
@@ -503,6 +500,8 @@ struct Sched {
   // factorization with fused forward elimination (same order as factor_forward)
   void factor() {
     std::vector<GjJob<T>> gj;
+    std::vector<LblockJob<T>> lb;
+    std::vector<long> rows;
     std::vector<GemmArgs<T>> g;
     const int mp = max_panels();
     for (int pan = 0; pan < mp; ++pan) {
@@ -517,19 +516,17 @@ struct Sched {
                                 dinv(q) + static_cast<long>(k0) * NB, sc(q)});
         }
         emit_gj(P->factor, gj);
-        for (int q = 0; q < P->nprob; ++q) {  // X = A21 D^{-1}
+        for (int q = 0; q < P->nprob; ++q) {  // L blocks
           const auto& o = P->po[q];
           const int c0 = pan * NB2;
           if (c0 >= o.np) continue;
           const int c1 = std::min(c0 + NB2, o.np), k0 = c0 + kk * NB, r1 = k0 + NB;
           if (k0 >= c1 || r1 >= o.np) continue;
           T* x = kf(q) + static_cast<long>(r1) * o.ldk + k0;
-          GemmArgs<T> a = gemm_args<T>(x, o.ldk, o.np - r1, NB, T(1), T(0));
-          gemm_add_segment<T>(a, dinv(q) + static_cast<long>(k0) * NB, NB, x, o.ldk, NB);
-          a.inplace = 1;  // X overwrites the A21 it reads
-          g.push_back(a);
+          lb.push_back(LblockJob<T>{x, o.ldk, dinv(q) + static_cast<long>(k0) * NB});
+          rows.push_back(o.np - r1);
         }
-        emit_gemm(P->factor, g, false);
+        emit_lblock(P->factor, lb, rows);
         for (int q = 0; q < P->nprob; ++q) {  // panel update
           const auto& o = P->po[q];
           const int c0 = pan * NB2;
@@ -627,7 +624,7 @@ struct Sched {
     std::vector<long> rs(1, 0);
     for (int q = 0; q < P->nprob; ++q) {
       jobs.push_back(tri_job(q));
-      rs.push_back(rs.back() + P->po[q].np);
+      rs.push_back(rs.back() + tri_init_blocks(P->po[q].np));
     }
     emit_rows(P->factor, L_TRI_INIT, tb->add(jobs.data(), jobs.size()), rs, P->nprob);
     std::vector<GemmArgs<T>> g;
@@ -926,6 +923,14 @@ hipError_t run_launches(const std::vector<rad_batch_plan::Launch>& ls, const cha
       hipLaunchKernelGGL(b_tri_init<T>, dim3(L.grid), dim3(256), 0, s,
                          reinterpret_cast<const TriJob<T>*>(tables + L.off),
                          reinterpret_cast<const long*>(tables + L.off2), L.count);
+    } else if (L.kind == L_LBLOCK) {
+      ProfScope prof(s, gemm_prof_kind<T>(false), L.flops, L.bytes);
+      const LblockJob<T>* jobs = reinterpret_cast<const LblockJob<T>*>(tables + L.off);
+      const long* st = reinterpret_cast<const long*>(tables + L.off2);
+      if (L.trans)
+        hipLaunchKernelGGL((lblock_batched<T, 2>), dim3(L.grid), dim3(256), 0, s, jobs, st, L.count);
+      else
+        hipLaunchKernelGGL((lblock_batched<T, 1>), dim3(L.grid), dim3(256), 0, s, jobs, st, L.count);
     } else if (L.kind == L_GJ) {
       ProfScope prof(s, RAD_PROF_DIAG_INVERSE, 2.0 * NB * NB * NB * L.count, 0.0);
       hipLaunchKernelGGL(gj_batched<T>, dim3(L.grid), dim3(GJ_THREADS), 0, s,
@@ -934,19 +939,10 @@ hipError_t run_launches(const std::vector<rad_batch_plan::Launch>& ls, const cha
       ProfScope prof(s, gemm_prof_kind<T>(L.trans != 0), L.flops, L.bytes);
       const GemmArgs<T>* a = reinterpret_cast<const GemmArgs<T>*>(tables + L.off);
       const int* ts = reinterpret_cast<const int*>(tables + L.off2);
-      if (L.ts == GEMM_TILE) {
-        if (L.trans)
-          hipLaunchKernelGGL((gemm_grouped_persistent<T, true, GEMM_TILE>), dim3(L.grid), dim3(256), 0, s, a, ts,
-                             L.count);
-        else
-          hipLaunchKernelGGL((gemm_grouped_persistent<T, false, GEMM_TILE>), dim3(L.grid), dim3(256), 0, s, a, ts,
-                             L.count);
-      } else {
-        if (L.trans)
-          hipLaunchKernelGGL((gemm_grouped_tiles<T, true>), dim3(L.grid), dim3(256), 0, s, a, ts, L.count);
-        else
-          hipLaunchKernelGGL((gemm_grouped_tiles<T, false>), dim3(L.grid), dim3(256), 0, s, a, ts, L.count);
-      }
+      if (L.trans)
+        hipLaunchKernelGGL((gemm_grouped_tiles<T, true>), dim3(L.grid), dim3(256), 0, s, a, ts, L.count);
+      else
+        hipLaunchKernelGGL((gemm_grouped_tiles<T, false>), dim3(L.grid), dim3(256), 0, s, a, ts, L.count);
     }
   }
   return hipGetLastError();

@@ -328,7 +328,7 @@ hipError_t forward_only(const Fact<T>& f, T* Y, long ldy, int wy, hipStream_t s)
 template <class T>
 hipError_t panel_inverses(const Fact<T>& f, T* tmp, long ldt, hipStream_t s) {
   TriJob<T> j{f.kf, f.ldk, f.dinv, f.np, f.W, f.V, f.ldw, tmp, ldt};
-  hipLaunchKernelGGL(tri_init<T>, dim3(f.np), dim3(256), 0, s, j);
+  hipLaunchKernelGGL(tri_init<T>, dim3(tri_init_blocks(f.np)), dim3(256), 0, s, j);
   for (int b = NB; b < NB2 && b < f.np; b *= 2)  // pairs of b-wide blocks exist
     for (int stage = 0; stage < 2; ++stage) {
       if (tri_level_blocks(f.P2, b, 64) < GEMM_TILE32_BELOW)

@@ -439,28 +439,37 @@ __global__ void __launch_bounds__(256) fill_zero(T* __restrict__ p, long count) 
     p[q] = T(0);
 }
 
-// Gauss-Jordan inverse of one NB x NB diagonal block, no pivoting, blocked by
-// 16.  The block is held as 8 x 8 tiles of 16 x 16 in MFMA accumulator layout;
-// wave w (of 8) owns tile row w.  Step s takes the 16 x 16 pivot tile
-// P = M(s,s) and applies
-//   M(s,s) <- P^-1,   M(s,j) <- P^-1 M(s,j),   M(i,s) <- -M(i,s) P^-1,
-//   M(i,j) <- M(i,j) - M(i,s) P^-1 M(s,j)                 (i, j != s),
-// i.e. the scalar in-place Gauss-Jordan update with a 16 x 16 pivot; after
-// the 8 steps M = A^-1.  The 16 scalar steps of a pivot tile are a serial
-// chain (about 3.5k cycles alone), and the updates' 2 NB^3 flops bind one CU's
-// matrix cores for 4.1k cycles per step, so the two run side by side: a ninth
-// wave forms pivot tile s + 1 from the tiles of step s (two products of its
-// own) and inverts it while the others update theirs.  Inside a pivot tile the
-// pivot row is broadcast over the lane groups and the pivot column along each
-// group by lane permutations of the vector pipe, with no LDS round trip on
-// the chain.  128 x 128 FP64 alone: 48.4 -> 35 us per launch against four waves with
-// the pivot's shuffles through LDS between the updates; the rest of the
-// distance is the FP64 vector operations of the pivot waiting behind 64-cycle
-// MFMAs of the waves on the same SIMD.
+// Inverse of one NB x NB diagonal block D = [A11 A12; A21 A22] (halves of HB),
+// no pivoting.  The chain of diagonal blocks needs the product with D^-1, not
+// D^-1 itself, so only what that product takes is formed on the chain:
+//   I1 = A11^-1,  T = I1 A12,  I2 = (A22 - A21 T)^-1,
+// kept as [I1 T; A21 I2] in the block's place in dinv; the L blocks are formed
+// from it half by half (lblock_rows), and the launch that starts the panel
+// inverses makes it D^-1 for all blocks at once (tri_init_block).
+// Blocked by 16: the block is 8 x 8 tiles of 16 x 16 in MFMA accumulator
+// layout, and wave w's registers hold tile row w.  Step s takes the pivot tile
+// P = M(s,s), R(s,j) = P^-1 M(s,j) (R(s,s) = P^-1) and
+//   M(i,j) <- M(i,j) - M(i,s) R(s,j),  M(i,s) <- -M(i,s) R(s,s),
+// the scalar in-place Gauss-Jordan update with a 16 x 16 pivot: in the upper
+// half's steps for the rows below s only (the rows above take their updates,
+// in the same order, while the lower half is inverted), in the lower half's
+// for its own rows.  The 16 scalar steps of a pivot tile are a serial chain
+// (about 4k cycles) that bounds the kernel; a wave of its own forms pivot tile
+// s + 1 from the tiles of step s (two products) and inverts it while the
+// others update theirs.  Its FP64 vector operations would wait behind the
+// 64-cycle MFMAs of waves on the same SIMD, so it has a SIMD to itself: waves
+// 0, 4, 8 of a workgroup share one, and the eight rows are on the other three.
+// The steps are unrolled: with tile columns picked at run time the rows took
+// 5k to 7k cycles a step instead of 2k to 4k, and bound it.  128 x 128 FP64
+// 21.4 us alone (35 us as one full inverse on four SIMDs), FP32 13.0 us.
+// Inside a pivot tile the pivot row is broadcast over the lane groups and the
+// pivot column along each group by lane permutations of the vector pipe, with
+// no LDS round trip on the chain.
 // Diagonal dominance of K makes every pivot order stable, so no pivoting is
 // needed; the scalar pivots are the same Schur-complement diagonals as in
 // unblocked elimination and are checked against the singularity threshold.
-constexpr int GJ_THREADS = 64 * (NB / 16 + 1);
+constexpr int HB = NB / 2;
+constexpr int GJ_THREADS = 64 * 11;
 
 // 1/x: the hardware reciprocal refined to full precision; with e = 1 - x r
 // the relative error of r, r (1 + e + e^2) leaves e^3
@@ -564,123 +573,199 @@ __device__ __forceinline__ void pivot_inverse(T (&v)[4], int l, T& pivots) {
   pivot_steps<T, 0>(v, row, piv, recip_nr(piv), l, pivots);
 }
 
+constexpr int GJ_LD = NB + 16;  // four rows of 16 FP64 operands in two passes over the banks
 template <class T>
 struct GjShared {
   static constexpr int BT = 16;
-  T sC[NB][BT + 2];    // tile column s before the step
-  T sRo[BT][NB + 2];   // tile row s before the step
-  T sR[BT][NB + 2];    // tile row s after it
-  T sP[BT][BT + 1];    // inverse of the pivot tile
-  T sD[BT][BT + 1];    // diagonal tile s + 1 before the step
+  T sC[NB][BT + 2];      // tile column s before the step
+  T sRo[BT][GJ_LD];      // tile row s before the step
+  T sR[2][BT][GJ_LD];    // tile row s after it, of two steps
+  T sU[2][BT][GJ_LD];    // the upper rows' own pass: the row it takes
+  T sP[BT][BT + 1];      // inverse of the pivot tile
+  T sD[BT][BT + 1];      // diagonal tile s + 1 before the step
 };
 
+// The pivot wave: inverts pivot tile s, and forms tile s + 1 from the tiles of step s.
 template <class T>
-__device__ __forceinline__ void gj_body(const T* __restrict__ A, long lda, T* __restrict__ out, Scalars* sc,
-                                        GjShared<T>& sh) {
+__device__ __forceinline__ void gj_pivots(const T* __restrict__ A, long lda, Scalars* sc, GjShared<T>& sh) {
   typedef typename Mfma<T>::v4 v4;
-  constexpr int BT = 16;
-  constexpr int NT = NB / BT;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-  const int li = l & 15, lg = l >> 4;
-  if (w == NT) {  // the pivot wave; its dependent operations go first
-    __builtin_amdgcn_s_setprio(3);
-    const double tiny = sizeof(T) == 8 ? 1e-11 : 1e-5;
-    int singular = 0;
-    T v[4];
+  constexpr int BT = 16, NT = NB / BT;
+  const int l = threadIdx.x & 63, li = l & 15;
+  __builtin_amdgcn_s_setprio(3);  // its dependent operations go first
+  const double tiny = sizeof(T) == 8 ? 1e-11 : 1e-5;
+  int singular = 0;
+  T v[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = A[static_cast<long>(Mfma<T>::orow(l, r)) * lda + li];
-    for (int s = 0;; ++s) {
-      T pivots = T(1);
-      pivot_inverse(v, l, pivots);
+  for (int r = 0; r < 4; ++r) v[r] = A[static_cast<long>(Mfma<T>::orow(l, r)) * lda + li];
+#pragma unroll 1
+  for (int s = 0;; ++s) {
+    T pivots = T(1);
+    pivot_inverse(v, l, pivots);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sh.sP[Mfma<T>::orow(l, r)][li] = v[r];
-      __syncthreads();  // the step begins
-      if (s + 1 < NT) {
-        // the next pivot tile: M(s+1, s+1) - M(s+1, s) P^-1 M(s, s+1)
-        v4 t = v4{0, 0, 0, 0}, d;
+    for (int r = 0; r < 4; ++r) sh.sP[Mfma<T>::orow(l, r)][li] = v[r];
+    __syncthreads();  // the step begins
+    if (s + 1 < NT) {
+      // the next pivot tile: M(s+1, s+1) - M(s+1, s) P^-1 M(s, s+1)
+      v4 t = v4{0, 0, 0, 0}, d;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          t = Mfma<T>::mma(sh.sP[li][Mfma<T>::orow(l, kk)], sh.sRo[Mfma<T>::orow(l, kk)][(s + 1) * BT + li], t);
+      for (int kk = 0; kk < 4; ++kk)
+        t = Mfma<T>::mma(sh.sP[li][Mfma<T>::orow(l, kk)], sh.sRo[Mfma<T>::orow(l, kk)][(s + 1) * BT + li], t);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) d[r] = sh.sD[Mfma<T>::orow(l, r)][li];
+      for (int r = 0; r < 4; ++r) d[r] = sh.sD[Mfma<T>::orow(l, r)][li];
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          d = Mfma<T>::mma(-sh.sC[(s + 1) * BT + li][Mfma<T>::orow(l, kk)], t[kk], d);
+      for (int kk = 0; kk < 4; ++kk)
+        d = Mfma<T>::mma(-sh.sC[(s + 1) * BT + li][Mfma<T>::orow(l, kk)], t[kk], d);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = d[r];
-      }
-      const double ap = fabs(static_cast<double>(pivots));
-      singular |= !(ap > tiny && ap < 1e300);
-      __syncthreads();  // the new tile row s is complete; the old row and column have been read
-      if (s + 1 == NT) break;
+      for (int r = 0; r < 4; ++r) v[r] = d[r];
     }
-    if (singular) raise_status(&sc->status, RAD_ESINGULAR);
-    return;
+    const double ap = fabs(static_cast<double>(pivots));
+    singular |= !(ap > tiny && ap < 1e300);
+    __syncthreads();  // the new tile row s is complete; the old row and column have been read
+    if (s + 1 == NT) break;
   }
-  v4 m[NT];  // tile row w
+  if (singular) raise_status(&sc->status, RAD_ESINGULAR);
+}
+
+// Tile row w, of the upper or the lower half, through the eight steps.
+template <class T, bool UPPER>
+__device__ __forceinline__ void gj_row(const T* __restrict__ A, long lda, T* __restrict__ out, int w,
+                                       GjShared<T>& sh) {
+  typedef typename Mfma<T>::v4 v4;
+  constexpr int BT = 16, NT = NB / BT, NH = NT / 2;
+  const int l = threadIdx.x & 63, li = l & 15, lg = l >> 4;
+  v4 m[NT];
 #pragma unroll
   for (int bj = 0; bj < NT; ++bj)
 #pragma unroll
     for (int r = 0; r < 4; ++r) m[bj][r] = A[static_cast<long>(w * BT + Mfma<T>::orow(l, r)) * lda + bj * BT + li];
-  // tile column q, tile row q and the diagonal tile q + 1 for step q
-  auto stage = [&](int q) {
+  auto put = [&](T* d, int ld, const v4& x) {
 #pragma unroll
-    for (int bj = 0; bj < NT; ++bj) {
-      if (bj == q)
+    for (int r = 0; r < 4; ++r) d[Mfma<T>::orow(l, r) * ld + li] = x[r];
+  };
+  auto put_row = [&](T(*d)[GJ_LD], int b0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sh.sC[w * BT + Mfma<T>::orow(l, r)][li] = m[bj][r];
-      if (w == q)
+    for (int bj = b0; bj < NT; ++bj) put(&d[0][bj * BT], GJ_LD, m[bj]);
+  };
+  auto get_row = [&](const T(*d)[GJ_LD], int b0) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sh.sRo[Mfma<T>::orow(l, r)][bj * BT + li] = m[bj][r];
-      if (bj == q + 1 && w == q + 1)
+    for (int bj = b0; bj < NT; ++bj)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) sh.sD[Mfma<T>::orow(l, r)][li] = m[bj][r];
+      for (int r = 0; r < 4; ++r) m[bj][r] = d[Mfma<T>::orow(l, r)][bj * BT + li];
+  };
+  auto store = [&](int b0, int b1) {
+#pragma unroll
+    for (int bj = b0; bj < b1; ++bj) put(out + static_cast<long>(w) * BT * NB + bj * BT, NB, m[bj]);
+  };
+  // tile columns [b0, b1) += a (this row's part of a tile column, negated) times a tile row
+  auto rank16 = [&](const T(&a)[4], const T(*row)[GJ_LD], int b0, int b1) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int bj = b0; bj < b1; ++bj) m[bj] = Mfma<T>::mma(a[kk], row[4 * kk + lg][bj * BT + li], m[bj]);
+  };
+  auto column = [&](T(&a)[4]) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) a[kk] = -sh.sC[w * BT + li][4 * kk + lg];
+  };
+  // tile w of the new tile row s: R(s, j) = P^-1 Ro(s, j), R(s, s) = P^-1
+  auto new_row = [&](int s) {
+    T* d = &sh.sR[s & 1][0][w * BT];
+    if (w == s) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d[Mfma<T>::orow(l, r) * GJ_LD + li] = sh.sP[Mfma<T>::orow(l, r)][li];
+    } else {
+      v4 x = v4{0, 0, 0, 0};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) x = Mfma<T>::mma(sh.sP[li][4 * kk + lg], sh.sRo[4 * kk + lg][w * BT + li], x);
+      put(d, GJ_LD, x);
     }
   };
-  stage(0);
-#pragma unroll 1
-  for (int s = 0; s < NT; ++s) {
-    __syncthreads();
-    // the new tile row s, one tile per wave: R(s, j) = P^-1 Ro(s, j), R(s, s) = P^-1
-    T av[4];
+  put(&sh.sC[w * BT][0], BT + 2, m[0]);
+  if constexpr (UPPER) {
+    if (w == 0) put_row(sh.sRo, 0);
+    if (w == 1) put(&sh.sD[0][0], BT + 1, m[1]);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) av[kk] = -sh.sC[w * BT + li][4 * kk + lg];
-    if (w == s) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sh.sR[Mfma<T>::orow(l, r)][w * BT + li] = sh.sP[Mfma<T>::orow(l, r)][li];
-    } else {
-      v4 acc = v4{0, 0, 0, 0};
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-        acc = Mfma<T>::mma(sh.sP[li][4 * kk + lg], sh.sRo[4 * kk + lg][w * BT + li], acc);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sh.sR[Mfma<T>::orow(l, r)][w * BT + li] = acc[r];
-    }
-    __syncthreads();
-    // rank-16 update of the other tile rows; tile column s becomes -M(w, s) P^-1
-    if (w == s) {
-#pragma unroll
-      for (int bj = 0; bj < NT; ++bj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) m[bj][r] = sh.sR[Mfma<T>::orow(l, r)][bj * BT + li];
-    } else {
-#pragma unroll
-      for (int b2 = 0; b2 < NT; b2 += 2) {
-        if (b2 == s) m[b2] = v4{0, 0, 0, 0};
-        if (b2 + 1 == s) m[b2 + 1] = v4{0, 0, 0, 0};
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-          m[b2] = Mfma<T>::mma(av[kk], sh.sR[4 * kk + lg][b2 * BT + li], m[b2]);
-          m[b2 + 1] = Mfma<T>::mma(av[kk], sh.sR[4 * kk + lg][(b2 + 1) * BT + li], m[b2 + 1]);
-        }
+    for (int s = 0; s < NH; ++s) {
+      __syncthreads();
+      T av[4];
+      column(av);
+      new_row(s);
+      __syncthreads();
+      if (w == s) get_row(sh.sR[s & 1], 0);
+      if (w > s) {
+        m[s] = v4{0, 0, 0, 0};
+        rank16(av, sh.sR[s & 1], 0, NT);
+      }
+      if (s + 1 < NH) {
+        put(&sh.sC[w * BT][0], BT + 2, m[s + 1]);
+        if (w == s + 1) put_row(sh.sRo, 0);
+        if (s + 2 < NH && w == s + 2) put(&sh.sD[0][0], BT + 1, m[s + 2 < NT ? s + 2 : 0]);
       }
     }
-    stage(s + 1);
+    // what the rows lack: rows 1, 2, 3 taken from those above them
+#pragma unroll
+    for (int p = 1; p < NH; ++p) {
+      put(&sh.sC[w * BT][0], BT + 2, m[p]);
+      if (w == p) put_row(sh.sU[p & 1], 0);
+      __syncthreads();
+      T av[4];
+      column(av);
+      __syncthreads();
+      if (w < p) {
+        m[p] = v4{0, 0, 0, 0};
+        rank16(av, sh.sU[p & 1], 0, NT);
+      }
+    }
+    store(0, NT);
+    __syncthreads();
+    __syncthreads();
+  } else {
+    store(0, NH);  // A21 stays as it is
+    T av[4], avp[4];
+#pragma unroll
+    for (int s = 0; s < NT; ++s) {
+      __syncthreads();
+      column(av);
+      new_row(s);
+      __syncthreads();
+      if (s < NH) {
+        if (s + 1 < NH) rank16(av, sh.sR[s & 1], s + 1, NH);
+        if (s == 1 || s == 2) rank16(avp, sh.sR[(s - 1) & 1], NH, NT);
+        if (s >= 2) rank16(av, sh.sR[s & 1], NH, NT);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) avp[kk] = av[kk];
+      } else if (w == s) {
+        get_row(sh.sR[s & 1], NH);
+      } else {
+        m[s] = v4{0, 0, 0, 0};
+        rank16(av, sh.sR[s & 1], NH, NT);
+      }
+      if (s + 1 < NT) {
+        put(&sh.sC[w * BT][0], BT + 2, m[s + 1 < NT ? s + 1 : 0]);
+        if (s + 1 >= NH && w == s + 1) put_row(sh.sRo, NH);
+        if (s + 2 >= NH && s + 2 < NT && w == s + 2) put(&sh.sD[0][0], BT + 1, m[s + 2 < NT ? s + 2 : 0]);
+      }
+    }
+    store(NH, NT);
   }
-#pragma unroll
-  for (int bj = 0; bj < NT; ++bj)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) out[(w * BT + Mfma<T>::orow(l, r)) * NB + bj * BT + li] = m[bj][r];
+}
+
+template <class T>
+__device__ __forceinline__ void gj_body(const T* __restrict__ A, long lda, T* __restrict__ out, Scalars* sc,
+                                        GjShared<T>& sh) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (wave == 0) {
+    gj_pivots<T>(A, lda, sc, sh);
+  } else if ((wave & 3) == 0) {  // on the pivot wave's SIMD: no work
+    for (int s = 0; s < 2 * (NB / 16); ++s) __syncthreads();
+  } else {
+    // tile rows of waves 1, 2, 3, 5, 6, 7, 9, 10, so that the three SIMDs share the updates
+    const int w = (0x64753210 >> (4 * (wave - 1 - wave / 4))) & 15;
+    if (w < NB / 32)
+      gj_row<T, true>(A, lda, out, w, sh);
+    else
+      gj_row<T, false>(A, lda, out, w, sh);
+  }
 }
 template <class T>
 __global__ void __launch_bounds__(GJ_THREADS)
@@ -726,23 +811,87 @@ struct TriJob {
   long ldt;
 };
 
-// W_p = blockdiag(D_k^-1), V_p = I (zero elsewhere, padded columns included);
-// row r of the padded matrix (all panels stacked)
+// Workgroups that start the panel inverses of a model of np padded rows: the
+// strips of the diagonal blocks' inverses, then one row each.
+constexpr int TRI_STRIPS = HB / 16;
+__host__ __device__ inline int tri_init_blocks(int np) { return np / NB * TRI_STRIPS + np; }
+
+// W_p = blockdiag(D_k^-1), V_p = I (zero elsewhere, padded columns included).
+// D^-1 = [B11 B12; B21 B22] comes from [I1 T; A21 I2] (see gj_row) by
+//   B21 = -I2 (A21 I1),  B11 = I1 - T B21,  B12 = -T I2,  B22 = I2;
+// column strips of 16 are independent of each other, so a strip of each half
+// makes one workgroup (wave w forms rows 16 w .. of each quarter), in the same
+// launch as the rows of zeros and ones.
 template <class T>
-__device__ __forceinline__ void tri_init_row(const TriJob<T>& j, int r) {
-  const int p = r / NB2, rl = r % NB2, kb = rl / NB;
-  T* wr = j.W + (static_cast<long>(p) * NB2 + rl) * j.ldw;
-  T* vr = j.V + (static_cast<long>(p) * NB2 + rl) * j.ldw;
-  const T* drow = j.dinv + (static_cast<long>(r / NB) * NB + rl % NB) * NB;
-  for (int c = threadIdx.x; c < j.ldw; c += blockDim.x) {
-    wr[c] = (c / NB == kb && c < NB2) ? drow[c % NB] : T(0);
-    vr[c] = (c == rl) ? T(1) : T(0);
+__device__ __forceinline__ void tri_init_block(const TriJob<T>& j, int b) {
+  typedef typename Mfma<T>::v4 v4;
+  constexpr int BT = 16, KK = HB / 4;
+  __shared__ T x[HB][BT + 2];
+  const int strips = j.np / NB * TRI_STRIPS;
+  if (b >= strips) {
+    const int r = b - strips, p = r / NB2, rl = r % NB2, kb = rl / NB;
+    T* wr = j.W + (static_cast<long>(p) * NB2 + rl) * j.ldw;
+    T* vr = j.V + (static_cast<long>(p) * NB2 + rl) * j.ldw;
+    for (int c = threadIdx.x; c < j.ldw; c += blockDim.x) {
+      if (c / NB != kb || c >= NB2) wr[c] = T(0);
+      vr[c] = (c == rl) ? T(1) : T(0);
+    }
+    return;
   }
+  const int k = b / TRI_STRIPS, c0 = b % TRI_STRIPS * BT;  // block, first column in each half
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+  const int li = l & 15, lg = l >> 4, row = w * BT;
+  const T* D = j.dinv + static_cast<long>(k) * NB * NB;
+  const int rl = k * NB % NB2;
+  T* W = j.W + (static_cast<long>(k * NB / NB2) * NB2 + rl) * j.ldw + rl;
+  // this wave's rows of T, A21 and I2, and the strips of I1 and I2
+  T ft[KK], fa[KK], fi[KK], s1[KK], s2[KK];
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    fa[kk] = D[(HB + row + li) * NB + 4 * kk + lg];
+    s1[kk] = D[(4 * kk + lg) * NB + c0 + li];
+    fi[kk] = D[(HB + row + li) * NB + HB + 4 * kk + lg];
+    ft[kk] = D[(row + li) * NB + HB + 4 * kk + lg];
+    s2[kk] = D[(HB + 4 * kk + lg) * NB + HB + c0 + li];
+  }
+  v4 i1, i2;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    i1[r] = D[(row + Mfma<T>::orow(l, r)) * NB + c0 + li];
+    i2[r] = D[(HB + row + Mfma<T>::orow(l, r)) * NB + HB + c0 + li];
+  }
+  auto put = [&](int i0, int j0, const v4& v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) W[static_cast<long>(i0 + row + Mfma<T>::orow(l, r)) * j.ldw + j0 + c0 + li] = v[r];
+  };
+  auto keep = [&](const v4& v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[row + Mfma<T>::orow(l, r)][li] = v[r];
+  };
+  const v4 zero = v4{0, 0, 0, 0};
+  v4 u = zero, b12 = zero, b21 = zero;
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) u = Mfma<T>::mma(fa[kk], s1[kk], u);
+  keep(u);
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) b12 = Mfma<T>::mma(-ft[kk], s2[kk], b12);
+  put(0, HB, b12);
+  put(HB, HB, i2);
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) b21 = Mfma<T>::mma(-fi[kk], x[4 * kk + lg][li], b21);
+  put(HB, 0, b21);
+  __syncthreads();
+  keep(b21);
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) i1 = Mfma<T>::mma(-ft[kk], x[4 * kk + lg][li], i1);
+  put(0, 0, i1);
 }
 
 template <class T>
-__global__ void __launch_bounds__(256) tri_init(TriJob<T> j) {
-  tri_init_row<T>(j, blockIdx.x);
+__global__ void __launch_bounds__(256, 2) tri_init(TriJob<T> j) {
+  tri_init_block<T>(j, blockIdx.x);
 }
 
 // Operands of one join at level b: panel p, pair q, matrix mat (0 W, 1 V),
@@ -822,23 +971,26 @@ inline unsigned tri_level_blocks(int P2, int b, int ts) {
   return static_cast<unsigned>(P2) * (NB2 / (2 * b)) * 2 * (b / ts) * (b / ts);
 }
 
-// L block X = A21 D^-1 of one diagonal block, in place: rows [0, 16 RB grid)
-// of A21 (NB columns).  A workgroup owns whole rows, so it may overwrite them
-// once they are staged: no scratch copy of X and no launch to copy it back
-// (one product in scratch and the copy took 16 us a block, this 6 us at up to
-// 4096 rows).  Wave w forms columns 32 w .. 32 w + 31; its D^-1 operand (the
-// same for every workgroup, so it comes from L2) is loaded into registers
-// whole, in flight together with the staging of A21.  The products of an
-// output run in gemm_tile's order, so both round alike.
+// L block X = P D^-1 of one diagonal block, in place: 16 RB rows of P (NB
+// columns) from [I1 T; A21 I2] (see gj_row):
+//   Xb = (Pb - Pa T) I2,   Xa = (Pa - Xb A21) I1.
+// A workgroup owns whole rows, so it may overwrite them once they are staged:
+// no scratch copy of X and no launch to copy it back.  Wave w forms columns
+// 16 w .. 16 w + 15 of each half; its operands of D (the same for every
+// workgroup, so they come from L2) are loaded into registers whole, in flight
+// together with the staging of P.
 template <class T, int RB>
-__global__ void __launch_bounds__(256, 2)
-lblock_inplace(T* __restrict__ A, long lda, const T* __restrict__ D) {
+struct LblockShared {
+  T p[16 * RB][NB + 2];
+  T x[16 * RB][HB + 2];
+};
+template <class T, int RB>
+__device__ __forceinline__ void lblock_rows(T* __restrict__ a0, long lda, const T* __restrict__ D,
+                                            LblockShared<T, RB>& sh) {
   typedef typename Mfma<T>::v4 v4;
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
-  constexpr int KC = GemmCfg<T>::KC, PV = 16 / sizeof(T), R = 16 * RB;
-  __shared__ T sA[R][NB + 2];
-  const int t = threadIdx.x, l = t & 63, li = l & 15, lg = l >> 4, wc = (t >> 6) * 32;
-  T* a0 = A + static_cast<long>(blockIdx.x) * R * lda;
+  constexpr int PV = 16 / sizeof(T), R = 16 * RB, KK = HB / 4;
+  const int t = threadIdx.x, l = t & 63, li = l & 15, lg = l >> 4, wc = (t >> 6) * 16;
   constexpr int NV = R * NB / PV / 256;
   vec ra[NV];
 #pragma unroll
@@ -846,49 +998,78 @@ lblock_inplace(T* __restrict__ A, long lda, const T* __restrict__ D) {
     const int p = t + 256 * q;
     ra[q] = *reinterpret_cast<const vec*>(a0 + static_cast<long>(p / (NB / PV)) * lda + (p % (NB / PV)) * PV);
   }
-  T fb[NB / 4][2];
+  T f[4][KK];  // columns wc + li of T, I2, A21, I1
 #pragma unroll
-  for (int q = 0; q < NB / 4; ++q) {
-    const int k = q / (KC / 4) * KC + lg * (KC / 4) + q % (KC / 4);
+  for (int h = 0; h < 4; ++h)
 #pragma unroll
-    for (int y = 0; y < 2; ++y) fb[q][y] = D[k * NB + wc + 16 * y + li];
-  }
+    for (int kk = 0; kk < KK; ++kk) {
+      const int i0 = (h == 1 || h == 2) ? HB : 0, j0 = h < 2 ? HB : 0;
+      f[h][kk] = D[(i0 + 4 * kk + lg) * NB + j0 + wc + li];
+    }
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
     const int p = t + 256 * q;
-    *reinterpret_cast<vec*>(&sA[p / (NB / PV)][(p % (NB / PV)) * PV]) = ra[q];
+    *reinterpret_cast<vec*>(&sh.p[p / (NB / PV)][(p % (NB / PV)) * PV]) = ra[q];
   }
   __syncthreads();  // every row is staged: its place in A may be overwritten
-  v4 acc[RB][2];
+  v4 x[RB];
 #pragma unroll
-  for (int x = 0; x < RB; ++x)
+  for (int y = 0; y < RB; ++y) {  // Pb - Pa T
 #pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = v4{0, 0, 0, 0};
+    for (int r = 0; r < 4; ++r) x[y][r] = sh.p[16 * y + Mfma<T>::orow(l, r)][HB + wc + li];
 #pragma unroll
-  for (int q = 0; q < NB / 4; ++q) {
-    const int k = q / (KC / 4) * KC + lg * (KC / 4) + q % (KC / 4);
-#pragma unroll
-    for (int x = 0; x < RB; ++x) {
-      const T fa = sA[16 * x + li][k];
-#pragma unroll
-      for (int y = 0; y < 2; ++y) acc[x][y] = Mfma<T>::mma(fa, fb[q][y], acc[x][y]);
-    }
+    for (int kk = 0; kk < KK; ++kk) x[y] = Mfma<T>::mma(-sh.p[16 * y + li][4 * kk + lg], f[0][kk], x[y]);
   }
 #pragma unroll
-  for (int x = 0; x < RB; ++x)
+  for (int y = 0; y < RB; ++y)  // own columns of Pb, which no other wave reads before the barrier
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+    for (int r = 0; r < 4; ++r) sh.p[16 * y + Mfma<T>::orow(l, r)][HB + wc + li] = x[y][r];
+  __syncthreads();
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        a0[static_cast<long>(16 * x + Mfma<T>::orow(l, r)) * lda + wc + 16 * y + li] = acc[x][y][r];
+  for (int y = 0; y < RB; ++y) {  // Xb
+    x[y] = v4{0, 0, 0, 0};
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) x[y] = Mfma<T>::mma(sh.p[16 * y + li][HB + 4 * kk + lg], f[1][kk], x[y]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      sh.x[16 * y + Mfma<T>::orow(l, r)][wc + li] = x[y][r];
+      a0[static_cast<long>(16 * y + Mfma<T>::orow(l, r)) * lda + HB + wc + li] = x[y][r];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int y = 0; y < RB; ++y) {  // Pa - Xb A21
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[y][r] = sh.p[16 * y + Mfma<T>::orow(l, r)][wc + li];
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) x[y] = Mfma<T>::mma(-sh.x[16 * y + li][4 * kk + lg], f[2][kk], x[y]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sh.p[16 * y + Mfma<T>::orow(l, r)][wc + li] = x[y][r];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int y = 0; y < RB; ++y) {  // Xa
+    x[y] = v4{0, 0, 0, 0};
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) x[y] = Mfma<T>::mma(sh.p[16 * y + li][4 * kk + lg], f[3][kk], x[y]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      a0[static_cast<long>(16 * y + Mfma<T>::orow(l, r)) * lda + wc + li] = x[y][r];
+  }
+}
+template <class T, int RB>
+__global__ void __launch_bounds__(256, 2) lblock_inplace(T* __restrict__ A, long lda, const T* __restrict__ D) {
+  __shared__ LblockShared<T, RB> sh;
+  lblock_rows<T, RB>(A + static_cast<long>(blockIdx.x) * (16 * RB) * lda, lda, D, sh);
 }
 
 // rows: a multiple of NB.  Past 4096 rows (one workgroup per CU at 16 rows)
-// 32 rows per workgroup halve the reads of D^-1.
+// 32 rows per workgroup halve the reads of D.
+constexpr long LBLOCK_ROWS16 = 4096;
 template <class T>
 inline hipError_t lblock_run(T* A, long lda, const T* D, int rows, hipStream_t s) {
   ProfScope prof(s, gemm_prof_kind<T>(false), 2.0 * rows * NB * NB, sizeof(T) * (2.0 * rows + NB) * NB);
-  if (rows > 4096)
+  if (rows > LBLOCK_ROWS16)
     hipLaunchKernelGGL((lblock_inplace<T, 2>), dim3(static_cast<unsigned>(rows / 32)), dim3(256), 0, s, A, lda, D);
   else
     hipLaunchKernelGGL((lblock_inplace<T, 1>), dim3(static_cast<unsigned>(rows / 16)), dim3(256), 0, s, A, lda, D);

@@ -51,8 +51,6 @@ struct GemmArgs {
   int tri;             // shape of op(A) by 128-blocks: 0 full, 1 block upper (rows of
                        // block b read k >= 128 b), 2 block lower (k < 128 (b + 1));
                        // the skipped entries must be zero
-  int inplace;         // 1: C overwrites the rows of op(A) it reads (N <= 128): one
-                       // column tile per row block, so only 128 x 128 tiles are safe
   int nseg;
   int ntile[2];        // 128-wide column tiles per segment
   int N[2];
@@ -196,13 +194,13 @@ __device__ __forceinline__ void lds_stage_store(T (*sA)[(ASlab<T, TRANS_A, TS>::
 // row-tile index by.  With 64 x 64 tiles each lane loads its C values into
 // registers before the K loop (the registers fit four workgroups per CU), so
 // the epilogue does not wait on them: 4-12 % faster on the K = 128 panel
-// updates, bitwise the same results (CPRE; persistent kernels, whose tile
-// loop would spill the extra registers, keep the plain epilogue).
-template <class T, bool TRANS_A, int TS = GEMM_TILE, bool CPRE = (TS == 64)>
+// updates, bitwise the same results (CPRE).
+template <class T, bool TRANS_A, int TS = GEMM_TILE>
 __device__ __forceinline__ void gemm_tile(const GemmArgs<T>& g, int bx, int by) {
   typedef typename Mfma<T>::v4 v4;
   constexpr int KC = GemmCfg<T>::KC, E = slab_ept<T, TS>();
   constexpr int NBR = TS / 32;   // 16 x 16 blocks per wave side
+  constexpr bool CPRE = TS == 64;
   __shared__ T sA[2][ASlab<T, TRANS_A, TS>::R][ASlab<T, TRANS_A, TS>::C];
   __shared__ T sB[2][KC][TS + GemmCfg<T>::PB];
   const int nt0 = (g.nseg > 0 && g.N[0] > 0) ? (g.N[0] + TS - 1) / TS : 0;
@@ -520,7 +518,7 @@ inline hipError_t launch_gemm(const GemmArgs<T>& a0, bool trans_a, hipStream_t s
   if (big == 0) return hipSuccess;
   ProfScope prof(s, gemm_prof_kind<T>(trans_a), gemm_flops(a), gemm_bytes(a));
   const int tiles64 = tiles_x<T, 64>(a) * ((a.M + 63) / 64);
-  if (!a.inplace && a.K % GEMM_KS == 0 && tiles64 < GEMM_TILE32_BELOW) {
+  if (a.K % GEMM_KS == 0 && tiles64 < GEMM_TILE32_BELOW) {
     const unsigned grid = static_cast<unsigned>(tiles_x<T, 32>(a)) * static_cast<unsigned>((a.M + 31) / 32);
     if (trans_a)
       hipLaunchKernelGGL((gemm_lds32<T, true>), dim3(grid), dim3(256), 0, s, a);
@@ -528,7 +526,7 @@ inline hipError_t launch_gemm(const GemmArgs<T>& a0, bool trans_a, hipStream_t s
       hipLaunchKernelGGL((gemm_lds32<T, false>), dim3(grid), dim3(256), 0, s, a);
     return hipGetLastError();
   }
-  const bool small = !a.inplace && big < gemm_tuning().small_tile_below[sizeof(T) == 8 ? 0 : 1];
+  const bool small = big < gemm_tuning().small_tile_below[sizeof(T) == 8 ? 0 : 1];
   if (small) {
     const unsigned grid = static_cast<unsigned>(tiles_x<T, 64>(a)) * static_cast<unsigned>((a.M + 63) / 64);
     if (trans_a)
