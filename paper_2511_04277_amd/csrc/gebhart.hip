@@ -181,17 +181,36 @@ hipError_t factor_update_emu(const EmuWork& ew, const Fact<double>& f, int c0, i
   return hipSuccess;
 }
 
-// LDU factorization of K in place; Y (if given, n+1 columns) is eliminated too.
+// W_p = U_pp^-1 and V_p = L_pp^-1 of every panel (at most seven launches).
+template <class T>
+hipError_t panel_inverses(const Fact<T>& f, T* tmp, long ldt, hipStream_t s) {
+  TriJob<T> j{f.kf, f.ldk, f.dinv, f.np, f.W, f.V, f.ldw, tmp, ldt};
+  hipLaunchKernelGGL(tri_init<T>, dim3(tri_init_blocks(f.np)), dim3(256), 0, s, j);
+  for (int b = NB; b < NB2 && b < f.np; b *= 2)  // pairs of b-wide blocks exist
+    for (int stage = 0; stage < 2; ++stage) {
+      if (tri_level_blocks(f.P2, b, 64) < GEMM_TILE32_BELOW)
+        hipLaunchKernelGGL((tri_level<T, 32>), dim3(tri_level_blocks(f.P2, b, 32)), dim3(256), 0, s, j, b, stage);
+      else
+        hipLaunchKernelGGL((tri_level<T, 64>), dim3(tri_level_blocks(f.P2, b, 64)), dim3(256), 0, s, j, b, stage);
+    }
+  return hipGetLastError();
+}
+
+// LDU factorization of K in place and its panel inverses; Y (if given, wy
+// columns) is eliminated too.  tmp: scratch of the panel inverses.
 //
 // Look-ahead: the update of panel p's trailing matrix is split.  Its first
 // 1024 columns (panel p+1) are updated on the caller's stream s, so panel
 // p+1's chain of diagonal inverses and narrow updates can start at once; the
 // rest of the trailing matrix and the right-hand sides are updated on the
 // side stream s2 meanwhile.  Panel p+1's row-block forward substitution waits
-// for that part (event), and the call joins s2 back into s at the end.  The
-// arithmetic and its order per element are the same as without the split.
+// for that part (event).  Past the last panel only the right-hand sides are
+// left, up to seven short products in a row: they run on s2 beside the panel
+// inverses (as many short launches), and the call joins s2 back into s at the
+// end.  The arithmetic and its order per element are the same as without the
+// split.  A single diagonal block has no side work: no events.
 template <class T>
-hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc, hipStream_t s,
+hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc, T* tmp, long ldt, hipStream_t s,
                           const EmuWork* ew = nullptr) {
   const long ldk = f.ldk;
   T* kf = f.kf;
@@ -199,9 +218,11 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
   hipError_t e = side_stream(&ss);
   if (e != hipSuccess) return e;
   // without look-ahead the far updates stay on s (the event waits are then no-ops)
-  hipStream_t s2 = lookahead_enabled() ? ss->s2 : s;
-  e = stream_wait(s2, s, ss->ev[0]);  // s2 starts after the caller's earlier work
-  if (e != hipSuccess) return e;
+  hipStream_t s2 = lookahead_enabled() && f.np > NB ? ss->s2 : s;
+  if (f.np > NB2 && s2 != s) {
+    e = stream_wait(s2, s, ss->ev[0]);  // s2 starts after the caller's earlier work
+    if (e != hipSuccess) return e;
+  }
   for (int c0 = 0; c0 < f.np; c0 += NB2) {
     const int c1 = std::min(c0 + NB2, f.np);
     const int c2 = std::min(c1 + NB2, f.np);
@@ -225,6 +246,20 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
         RAD_GEMM(u, false);
       }
     }
+    if (c1 == f.np) {
+      if (s2 != s) {
+        e = stream_wait(s2, s, ss->ev[0]);
+        if (e != hipSuccess) return e;
+      }
+      for (int k0 = c0; Y && k0 + NB < c1; k0 += NB) {
+        const int r1 = k0 + NB;
+        GemmArgs<T> u = update_args<T>(kf + static_cast<long>(r1) * ldk + k0, ldk, c1 - r1, NB);
+        gemm_add_segment<T>(u, Y + static_cast<long>(k0) * ldy, ldy, Y + static_cast<long>(r1) * ldy, ldy, wy);
+        e = launch_gemm(u, false, s2);
+        if (e != hipSuccess) return e;
+      }
+      break;
+    }
     // the previous panel's far update must have reached this panel's rows
     // before they are eliminated (its first row chunks; event ev[3])
     if (c0 > 0) {
@@ -235,11 +270,10 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
     for (int k0 = c0; k0 + NB < c1; k0 += NB) {
       const int r1 = k0 + NB;
       GemmArgs<T> u = update_args<T>(kf + static_cast<long>(r1) * ldk + k0, ldk, c1 - r1, NB);
-      if (c1 < f.np)
-        gemm_add_segment<T>(u, kf + static_cast<long>(k0) * ldk + c1, ldk, kf + static_cast<long>(r1) * ldk + c1,
-                            ldk, f.np - c1);
+      gemm_add_segment<T>(u, kf + static_cast<long>(k0) * ldk + c1, ldk, kf + static_cast<long>(r1) * ldk + c1,
+                          ldk, f.np - c1);
       if (Y) gemm_add_segment<T>(u, Y + static_cast<long>(k0) * ldy, ldy, Y + static_cast<long>(r1) * ldy, ldy, wy);
-      if (u.nseg) RAD_GEMM(u, false);
+      RAD_GEMM(u, false);
     }
     // the rest of the previous panel's far update must be done before the
     // next panel's columns take this panel's update
@@ -249,12 +283,12 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
     }
     // (3) everything below and right of the panel: K = panel-width GEMMs,
     // the next panel's columns on s, the rest on s2
-    if (c1 < f.np && ew) {
+    if (ew) {
       if constexpr (std::is_same<T, double>::value) {
         e = factor_update_emu(*ew, f, c0, c1, c2, Y, ldy, wy, s, s2, ss);
         if (e != hipSuccess) return e;
       }
-    } else if (c1 < f.np) {
+    } else {
       GemmArgs<T> u = update_args<T>(kf + static_cast<long>(c1) * ldk + c0, ldk, f.np - c1, c1 - c0);
       gemm_add_segment<T>(u, kf + static_cast<long>(c0) * ldk + c1, ldk, kf + static_cast<long>(c1) * ldk + c1,
                           ldk, c2 - c1);
@@ -298,8 +332,12 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
       }
     }
   }
-  e = stream_wait(s, s2, ss->ev[1]);  // join
+  e = panel_inverses<T>(f, tmp, ldt, s);
   if (e != hipSuccess) return e;
+  if (s2 != s) {
+    e = stream_wait(s, s2, ss->ev[1]);  // join
+    if (e != hipSuccess) return e;
+  }
   return hipGetLastError();
 }
 
@@ -324,21 +362,6 @@ hipError_t forward_only(const Fact<T>& f, T* Y, long ldy, int wy, hipStream_t s)
   return hipSuccess;
 }
 
-// W_p = U_pp^-1 and V_p = L_pp^-1 of every panel (at most seven launches).
-template <class T>
-hipError_t panel_inverses(const Fact<T>& f, T* tmp, long ldt, hipStream_t s) {
-  TriJob<T> j{f.kf, f.ldk, f.dinv, f.np, f.W, f.V, f.ldw, tmp, ldt};
-  hipLaunchKernelGGL(tri_init<T>, dim3(tri_init_blocks(f.np)), dim3(256), 0, s, j);
-  for (int b = NB; b < NB2 && b < f.np; b *= 2)  // pairs of b-wide blocks exist
-    for (int stage = 0; stage < 2; ++stage) {
-      if (tri_level_blocks(f.P2, b, 64) < GEMM_TILE32_BELOW)
-        hipLaunchKernelGGL((tri_level<T, 32>), dim3(tri_level_blocks(f.P2, b, 32)), dim3(256), 0, s, j, b, stage);
-      else
-        hipLaunchKernelGGL((tri_level<T, 64>), dim3(tri_level_blocks(f.P2, b, 64)), dim3(256), 0, s, j, b, stage);
-    }
-  return hipGetLastError();
-}
-
 // Panel products of the back and transposed solves.  Y_p <- op(M_p) Y_p goes
 // through one of two scratch panels S[0], S[1] (alternating); the update of
 // the other rows reads the product straight from the scratch, and the copy
@@ -352,6 +375,7 @@ struct PanelSweep {
   hipStream_t s, s2;
   SideStream* ss;
   int idx = 0;
+  bool side = false;  // copies on s2 that s has not joined
   T* cur = nullptr;
 
   hipError_t init(T* scr, long ld, hipStream_t st) {
@@ -366,7 +390,7 @@ struct PanelSweep {
   }
   // product of panel rows c0..c0+L into the next scratch panel; returns it in cur
   hipError_t product(const T* Mp, long ldm, bool trans, int tri, int c0, int L, const T* Y, long ldy, int wy) {
-    if (idx >= 2) {
+    if (idx >= 2 && side) {
       hipError_t e = hipStreamWaitEvent(s, ss->ev[1], 0);
       if (e != hipSuccess) return e;
     }
@@ -377,14 +401,24 @@ struct PanelSweep {
     gemm_add_segment<T>(a, Y + static_cast<long>(c0) * ldy, ldy, cur, lds, wy);
     return launch_gemm(a, trans, s);
   }
-  // copy of the current product into Y_p, on the side stream
-  hipError_t copy_back(int c0, int L, T* Y, long ldy, int wy) {
-    hipError_t e = stream_wait(s2, s, ss->ev[0]);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(copy_rows<T>, dim3(L), dim3(256), 0, s2, cur, lds, Y + static_cast<long>(c0) * ldy, ldy, wy);
-    return hipEventRecord(ss->ev[1], s2);
+  // copy of the current product into Y_p, on the side stream; after the last
+  // product of a sweep there is nothing beside it, and it stays on s
+  hipError_t copy_back(int c0, int L, T* Y, long ldy, int wy, bool last) {
+    hipStream_t st = last ? s : s2;
+    if (st != s) {
+      hipError_t e = stream_wait(st, s, ss->ev[0]);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(copy_rows<T>, dim3(L), dim3(256), 0, st, cur, lds, Y + static_cast<long>(c0) * ldy, ldy, wy);
+    if (st == s) return hipSuccess;
+    side = true;
+    return hipEventRecord(ss->ev[1], st);
   }
-  hipError_t join() { return stream_wait(s, s2, ss->ev[2]); }
+  hipError_t join() {
+    if (!side) return hipSuccess;
+    side = false;
+    return stream_wait(s, s2, ss->ev[2]);
+  }
 };
 
 // The factor operand of a panel's emulated update in the back and transposed
@@ -439,7 +473,7 @@ hipError_t back_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, long lds
     }
     e = ps.product(Wp, f.ldw, false, 1, c0, c1 - c0, Y, ldy, wy);
     if (e != hipSuccess) return e;
-    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy);
+    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy, c0 == 0);
     if (e != hipSuccess) return e;
     if (c0 > 0 && ew) {
       if constexpr (std::is_same<T, double>::value) {
@@ -478,7 +512,7 @@ hipError_t transposed_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, lo
     }
     e = ps.product(Wp, f.ldw, true, 2, c0, c1 - c0, Y, ldy, wy);
     if (e != hipSuccess) return e;
-    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy);
+    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy, c1 == f.np);
     if (e != hipSuccess) return e;
     if (c1 < f.np && ew) {
       if constexpr (std::is_same<T, double>::value) {
@@ -510,7 +544,7 @@ hipError_t transposed_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, lo
     }
     e = ps.product(Vp, f.ldw, true, 1, c0, c1 - c0, Y, ldy, wy);
     if (e != hipSuccess) return e;
-    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy);
+    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy, c0 == 0);
     if (e != hipSuccess) return e;
     if (c0 > 0 && ew) {
       if constexpr (std::is_same<T, double>::value) {
@@ -649,8 +683,7 @@ extern "C" int32_t rad_gebhart_ref(const double* F, int64_t n, int64_t ldf, cons
     double* Y = static_cast<double*>(w.y);
     hipLaunchKernelGGL(geb_form<double>, dim3(f.np), dim3(256), 0, s, F, static_cast<long>(ldf), ni, eps,
                        rho, f.kf, f.ldk, f.np, Y, w.ldy, w.sc);
-    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, ni + 1, w.sc, s, ew));
-    RAD_HIP_CHECK(panel_inverses<double>(f, static_cast<double*>(w.scr), w.ldt, s));
+    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, ni + 1, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
     RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, ni + 1, static_cast<double*>(w.scr), w.ldy, s, ew));
     hipLaunchKernelGGL((copy_block<double, double>), dim3(ni), dim3(256), 0, s, Y, w.ldy, ni, B,
                        static_cast<long>(ldb));
@@ -659,8 +692,7 @@ extern "C" int32_t rad_gebhart_ref(const double* F, int64_t n, int64_t ldf, cons
     float* Y = static_cast<float*>(w.y);
     hipLaunchKernelGGL(geb_form<float>, dim3(f.np), dim3(256), 0, s, F, static_cast<long>(ldf), ni, eps,
                        rho, f.kf, f.ldk, f.np, Y, w.ldy, w.sc);
-    RAD_HIP_CHECK(factor_forward<float>(f, Y, w.ldy, ni + 1, w.sc, s));
-    RAD_HIP_CHECK(panel_inverses<float>(f, static_cast<float*>(w.scr), w.ldt, s));
+    RAD_HIP_CHECK(factor_forward<float>(f, Y, w.ldy, ni + 1, w.sc, static_cast<float*>(w.scr), w.ldt, s));
     RAD_HIP_CHECK(back_solve<float>(f, Y, w.ldy, ni + 1, static_cast<float*>(w.scr), w.ldy, s));
     if (ir_max > 0) {
       zero<double>(w.x, static_cast<long>(f.np) * w.ldx, s);
@@ -749,8 +781,7 @@ extern "C" int32_t rad_steady_temperature(const double* Y, int64_t n, int64_t ld
   hipLaunchKernelGGL(scalars_init, dim3(1), dim3(64), 0, s, w.sc);
   hipLaunchKernelGGL(ss_form, dim3(f.np), dim3(256), 0, s, Y, static_cast<long>(ldy), ni, weight, Q,
                      static_cast<long>(ldq), mi, t_fixed, xs, sigma, f.kf, f.ldk, f.np, X, w.ldy, w.sc);
-  RAD_HIP_CHECK(factor_forward<double>(f, X, w.ldy, SS_RHS, w.sc, s, ew));
-  RAD_HIP_CHECK(panel_inverses<double>(f, static_cast<double*>(w.scr), w.ldt, s));
+  RAD_HIP_CHECK(factor_forward<double>(f, X, w.ldy, SS_RHS, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
   RAD_HIP_CHECK(back_solve<double>(f, X, w.ldy, SS_RHS, static_cast<double*>(w.scr), w.ldy, s, ew));
   hipLaunchKernelGGL(ss_output, dim3(static_cast<unsigned>(ceil_div(n * m, 256))), dim3(256), 0, s, X, w.ldy, ni,
                      mi, t_fixed, T, static_cast<long>(ldt), w.sc);
@@ -840,8 +871,7 @@ extern "C" int32_t rad_enforce_lsq(const double* F, int64_t n, int64_t ldf, cons
     hipLaunchKernelGGL(fill_zero<int>, dim3(1), dim3(64), 0, s, l.negatives, 1L);
     hipLaunchKernelGGL(lsq_schur, dim3(static_cast<unsigned>(ceil_div(f.np, LSQ_RB))), dim3(256), 0, s, F,
                        static_cast<long>(ldf), ni, omega, l.mask[cur], f.kf, f.ldk, f.np, Y, w.ldy);
-    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, LSQ_RHS, w.sc, s, ew));
-    RAD_HIP_CHECK(panel_inverses<double>(f, static_cast<double*>(w.scr), w.ldt, s));
+    RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, LSQ_RHS, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
     RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, LSQ_RHS, static_cast<double*>(w.scr), w.ldy, s, ew));
     hipLaunchKernelGGL(lsq_update, ugrid, dim3(256), 0, s, F, static_cast<long>(ldf), ni, omega, l.mask[cur], Y,
                        w.ldy, nnr, l.mask[1 - cur], Fout, static_cast<long>(ldo), l.negatives);
