@@ -304,7 +304,9 @@ gemm_grouped_tiles(const GemmArgs<T>* __restrict__ probs, const int* __restrict_
   int ntx = 0;
   for (int q = 0; q < g.nseg; ++q) ntx += g.N[q] > 0 ? (g.N[q] + 63) / 64 : 0;
   int bx, by;
-  grouped_tile(t - tile_start[lo], ntx, (g.M + 63) / 64, TILE_GROUP, bx, by);
+  const int nty = (g.M + 63) / 64;
+  grouped_tile(t - tile_start[lo], ntx, nty, g.tri ? nty : TILE_GROUP, bx, by);
+  if (g.tri) by = tri_row(by, bx, nty);  // an XCD gets every eighth tile: all depths alike
   gemm_tile<T, TRANS_A, 64>(g, bx, by);
 }
 

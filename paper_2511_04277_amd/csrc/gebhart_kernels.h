@@ -811,39 +811,33 @@ struct TriJob {
   long ldt;
 };
 
-// Workgroups that start the panel inverses of a model of np padded rows: the
-// strips of the diagonal blocks' inverses, then one row each.
+// Workgroups that start the panel inverses of a model of np padded rows.
 constexpr int TRI_STRIPS = HB / 16;
-__host__ __device__ inline int tri_init_blocks(int np) { return np / NB * TRI_STRIPS + np; }
+__host__ __device__ inline int tri_init_blocks(int np) { return np / NB * TRI_STRIPS; }
 
-// W_p = blockdiag(D_k^-1), V_p = I (zero elsewhere, padded columns included).
+// The diagonal blocks of W_p and V_p: D_k^-1 and I.  The blocks on their other
+// side are never read (the products with them take op(A) and B as triangular by
+// blocks) and stay unwritten.
 // D^-1 = [B11 B12; B21 B22] comes from [I1 T; A21 I2] (see gj_row) by
 //   B21 = -I2 (A21 I1),  B11 = I1 - T B21,  B12 = -T I2,  B22 = I2;
 // column strips of 16 are independent of each other, so a strip of each half
-// makes one workgroup (wave w forms rows 16 w .. of each quarter), in the same
-// launch as the rows of zeros and ones.
+// makes one workgroup (wave w forms rows 16 w .. of each quarter).
 template <class T>
 __device__ __forceinline__ void tri_init_block(const TriJob<T>& j, int b) {
   typedef typename Mfma<T>::v4 v4;
   constexpr int BT = 16, KK = HB / 4;
   __shared__ T x[HB][BT + 2];
-  const int strips = j.np / NB * TRI_STRIPS;
-  if (b >= strips) {
-    const int r = b - strips, p = r / NB2, rl = r % NB2, kb = rl / NB;
-    T* wr = j.W + (static_cast<long>(p) * NB2 + rl) * j.ldw;
-    T* vr = j.V + (static_cast<long>(p) * NB2 + rl) * j.ldw;
-    for (int c = threadIdx.x; c < j.ldw; c += blockDim.x) {
-      if (c / NB != kb || c >= NB2) wr[c] = T(0);
-      vr[c] = (c == rl) ? T(1) : T(0);
-    }
-    return;
-  }
   const int k = b / TRI_STRIPS, c0 = b % TRI_STRIPS * BT;  // block, first column in each half
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
   const int li = l & 15, lg = l >> 4, row = w * BT;
   const T* D = j.dinv + static_cast<long>(k) * NB * NB;
   const int rl = k * NB % NB2;
-  T* W = j.W + (static_cast<long>(k * NB / NB2) * NB2 + rl) * j.ldw + rl;
+  const long diag = (static_cast<long>(k * NB / NB2) * NB2 + rl) * j.ldw + rl;
+  T* W = j.W + diag;
+  for (int e = threadIdx.x; e < NB * NB / TRI_STRIPS; e += 256) {
+    const int i = NB / TRI_STRIPS * (b % TRI_STRIPS) + e / NB, c = e % NB;
+    j.V[diag + static_cast<long>(i) * j.ldw + c] = i == c ? T(1) : T(0);
+  }
   // this wave's rows of T, A21 and I2, and the strips of I1 and I2
   T ft[KK], fa[KK], fi[KK], s1[KK], s2[KK];
 #pragma unroll
@@ -920,9 +914,11 @@ __host__ __device__ inline bool tri_level_args(const TriJob<T>& j, int b, int st
       g.lda = ldk; g.M = b; g.K = bb; g.alpha = T(1);
       g.B[0] = Wp + static_cast<long>(o + b) * ldw + (o + b); g.ldb[0] = ldw;
       g.C[0] = tq; g.ldc[0] = j.ldt; g.N[0] = bb;
+      g.btri = 1;
     } else {
       g.A = Wp + static_cast<long>(o) * ldw + o;
       g.lda = ldw; g.M = b; g.K = b; g.alpha = T(-1);
+      g.tri = 1;
       g.B[0] = tq; g.ldb[0] = j.ldt;
       g.C[0] = Wp + static_cast<long>(o) * ldw + (o + b); g.ldc[0] = ldw; g.N[0] = bb;
     }
@@ -932,9 +928,11 @@ __host__ __device__ inline bool tri_level_args(const TriJob<T>& j, int b, int st
       g.lda = ldk; g.M = bb; g.K = b; g.alpha = T(1);
       g.B[0] = Vp + static_cast<long>(o) * ldw + o; g.ldb[0] = ldw;
       g.C[0] = tq; g.ldc[0] = j.ldt; g.N[0] = b;
+      g.btri = 2;
     } else {
       g.A = Vp + static_cast<long>(o + b) * ldw + (o + b);
       g.lda = ldw; g.M = bb; g.K = bb; g.alpha = T(-1);
+      g.tri = 2;
       g.B[0] = tq; g.ldb[0] = j.ldt;
       g.C[0] = Vp + static_cast<long>(o + b) * ldw + o; g.ldc[0] = ldw; g.N[0] = b;
     }

@@ -50,7 +50,9 @@ struct GemmArgs {
   T alpha, beta;
   int tri;             // shape of op(A) by 128-blocks: 0 full, 1 block upper (rows of
                        // block b read k >= 128 b), 2 block lower (k < 128 (b + 1));
-                       // the skipped entries must be zero
+                       // the skipped entries count as zero and are not read
+  int btri;            // shape of B by 128-blocks: 0 full, 1 block upper (columns of
+                       // block b read k < 128 (b + 1)), 2 block lower (k >= 128 b)
   int nseg;
   int ntile[2];        // 128-wide column tiles per segment
   int N[2];
@@ -248,8 +250,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T>& g, int bx, int by) 
   // K range of this row tile: a triangular op(A) is zero by 128-blocks, so
   // the row tile skips the blocks left (upper) or right (lower) of its block
   const int mb = (m0 / GEMM_TILE) * GEMM_TILE;
-  const int kbeg = g.tri == 1 ? mb : 0;
-  const int kend = g.tri == 2 ? min(K, mb + GEMM_TILE) : K;
+  int kbeg = g.tri == 1 ? mb : 0;
+  int kend = g.tri == 2 ? min(K, mb + GEMM_TILE) : K;
+  const int nb = (n0 / GEMM_TILE) * GEMM_TILE;
+  if (g.btri == 1) kend = min(kend, nb + GEMM_TILE);
+  if (g.btri == 2) kbeg = max(kbeg, nb);
   const int nch = kend > kbeg ? (kend - kbeg + KC - 1) / KC : 0;
   if (nch > 0) {
     lds_stage_load<T, TRANS_A, TS>(A, lda, Bm, ldb, m0, n0, kbeg, ra0, rb0);
@@ -343,8 +348,11 @@ __device__ __forceinline__ void gemm_tile32(const GemmArgs<T>& g, int bx, int by
   const int t = threadIdx.x, l = t & 63, li = l & 15, lg = l >> 4;
   const int wr = (t >> 7) * 16, wc = ((t >> 6) & 1) * 16;
   const int mb = (m0 / GEMM_TILE) * GEMM_TILE;
-  const int kbeg = g.tri == 1 ? mb : 0;
-  const int kend = g.tri == 2 ? min(K, mb + GEMM_TILE) : K;
+  int kbeg = g.tri == 1 ? mb : 0;
+  int kend = g.tri == 2 ? min(K, mb + GEMM_TILE) : K;
+  const int nb = (n0 / GEMM_TILE) * GEMM_TILE;
+  if (g.btri == 1) kend = min(kend, nb + GEMM_TILE);
+  if (g.btri == 2) kbeg = max(kbeg, nb);
   vec ra[NV], rb[NV];
   auto load = [&](int k0) {
 #pragma unroll
@@ -512,6 +520,15 @@ inline double gemm_flops(const GemmArgs<T>& a) {
       const int kb = a.tri == 1 ? m0 : 0, ke = a.tri == 2 ? std::min(a.K, m0 + GEMM_TILE) : a.K;
       mk += static_cast<double>(rows) * std::max(0, ke - kb);
     }
+  }
+  if (a.btri != 0) {  // one segment; op(A) full
+    double nk = 0.0;
+    for (int n0 = 0; n0 < a.N[0]; n0 += GEMM_TILE) {
+      const int cols = std::min(GEMM_TILE, a.N[0] - n0);
+      const int kb = a.btri == 2 ? n0 : 0, ke = a.btri == 1 ? std::min(a.K, n0 + GEMM_TILE) : a.K;
+      nk += static_cast<double>(cols) * std::max(0, ke - kb);
+    }
+    return 2.0 * a.M * nk;
   }
   return 2.0 * mk * ncols;
 }
