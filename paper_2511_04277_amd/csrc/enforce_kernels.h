@@ -423,14 +423,15 @@ constexpr int FIN_ROWS = 256 / FIN_LANES;  // rows per 256-thread block
 // the finalize blocks' maxima, run by the instance's last finalize block.
 __device__ __forceinline__ void enf_decide_body(const EnfInst& in, double tol) {
   EnfCtrl* ctrl = in.ctrl;
-  if (ctrl->converged || ctrl->status < 0) return;
   const int nf = (in.n + FIN_ROWS - 1) / FIN_ROWS;
+  const int status = agent_load(&ctrl->status);
   double d = 0.0, rm = 0.0, em = 0.0;
   for (int b = threadIdx.x; b < nf; b += blockDim.x) {
-    d = fmax(d, in.finred[3 * b]);
-    rm = fmax(rm, in.finred[3 * b + 1]);
-    em = fmax(em, in.finred[3 * b + 2]);
+    d = fmax(d, agent_load(in.finred + 3 * b));
+    rm = fmax(rm, agent_load(in.finred + 3 * b + 1));
+    em = fmax(em, agent_load(in.finred + 3 * b + 2));
   }
+  if (status < 0) return;
   __shared__ double fr[3][4];
   for (int off = 32; off > 0; off >>= 1) {
     d = fmax(d, __shfl_xor(d, off));
@@ -465,9 +466,12 @@ __device__ __forceinline__ void enf_decide_body(const EnfInst& in, double tol) {
 // combine as ((0 + 1) + (2 + 3)) + ((4 + 5) + (6 + 7)) (fixed order).  Thread
 // t takes part t / 32 of row t % 32, so each load instruction of a wave reads
 // two 256-byte runs of consecutive rows of one partial.  Each block's maxima
-// go to finred; the block that finishes last (a counter in the control
-// block, one atomic per block) reduces them and decides.
-
+// go to finred; the block that finishes last (a counter in the control block,
+// one atomic per block) reduces them and decides.  A launch is a chain of round
+// trips, so everything a block reads is requested at once, and the maxima
+// pass through the memory that all XCDs share by themselves: fences around the
+// counter, which write back and drop whole caches, and loads in turn made a
+// launch take 11 us at n = 8192 and 16 us in a batch of 16 models (8.5 and 6.3).
 __device__ __forceinline__ void enf_finalize_body(const EnfInst& in, int blk, int nblocks, double tol) {
   const int n = in.n, t = in.t;
   const double* __restrict__ partial = in.partial;
@@ -475,25 +479,27 @@ __device__ __forceinline__ void enf_finalize_body(const EnfInst& in, int blk, in
   const double* __restrict__ blkmax = in.blkmax;
   const long nblk = in.pairs;
   EnfCtrl* ctrl = in.ctrl;
-  if (ctrl->converged || ctrl->status < 0) return;
   __shared__ double ps[FIN_LANES][FIN_ROWS];
   const int part = threadIdx.x / FIN_ROWS;
   const int r = threadIdx.x % FIN_ROWS;
   const int i = blk * FIN_ROWS + r;
-  double s = 0.0;
-  if (i < n) {
-    const double* __restrict__ col = partial + i;
-    int q = part;
-    // eight loads in flight; the sum still runs over q in increasing order
-    for (; q + 7 * FIN_LANES <= t; q += 8 * FIN_LANES) {
-      double v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = col[static_cast<long>(q + u * FIN_LANES) * n];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; q <= t; q += FIN_LANES) s += col[static_cast<long>(q) * n];
+  const bool stop = ctrl->converged || ctrl->status < 0;
+  const double* __restrict__ col = partial + min(i, n - 1);
+  double rm = 0.0, em = 0.0, s = 0.0;
+  const long tid = static_cast<long>(blk) * blockDim.x + threadIdx.x;
+  for (long b = tid; b < nblk; b += static_cast<long>(nblocks) * blockDim.x) {
+    rm = fmax(rm, blkmax[2 * b]);
+    em = fmax(em, blkmax[2 * b + 1]);
   }
+  for (int q = part; q <= t; q += 8 * FIN_LANES) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = col[static_cast<long>(min(q + u * FIN_LANES, t)) * n];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (q + u * FIN_LANES <= t) s += v[u];
+  }
+  if (stop) return;
   ps[part][r] = s;
   __syncthreads();
   double d = 0.0;
@@ -503,13 +509,7 @@ __device__ __forceinline__ void enf_finalize_body(const EnfInst& in, int blk, in
     scale[i] = 1.0 / s;
     d = fabs(s - 1.0);
   }
-  double rm = 0.0, em = 0.0;
-  const long tid = static_cast<long>(blk) * blockDim.x + threadIdx.x;
-  for (long b = tid; b < nblk; b += static_cast<long>(nblocks) * blockDim.x) {
-    rm = fmax(rm, blkmax[2 * b]);
-    em = fmax(em, blkmax[2 * b + 1]);
-  }
-  // block maxima to finred (the decide kernel reduces the blocks; no atomics)
+  // block maxima to finred
   __shared__ double fr[3][4];
   for (int off = 32; off > 0; off >>= 1) {
     d = fmax(d, __shfl_xor(d, off));
@@ -528,14 +528,13 @@ __device__ __forceinline__ void enf_finalize_body(const EnfInst& in, int blk, in
     for (int c = 0; c < 3; ++c) {
       double x = fr[c][0];
       for (int q = 1; q < 4; ++q) x = fmax(x, fr[c][q]);
-      in.finred[3 * static_cast<long>(blk) + c] = x;
+      agent_store(in.finred + 3 * static_cast<long>(blk) + c, x);
     }
-    __threadfence();  // the maxima are visible before the block counts itself done
+    __builtin_amdgcn_s_waitcnt(0);  // the maxima are there before the block counts itself done
     last = atomicAdd(&ctrl->done, 1) == nblocks - 1;
   }
   __syncthreads();
   if (last) {
-    __threadfence();
     if (threadIdx.x == 0) ctrl->done = 0;
     enf_decide_body(in, tol);
   }
