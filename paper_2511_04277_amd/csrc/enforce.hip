@@ -178,8 +178,10 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.finred = l.finred;
   in.ctrl = l.ctrl;
   in.arr = l.arr;
-  hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
-  hipLaunchKernelGGL(enf_inv_area, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, in);
+  if (pairs > 1) {
+    hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
+    hipLaunchKernelGGL(enf_inv_area, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, in);
+  }
   // one tile needs no co-operation; a resident grid does, which a capture does
   // not record (the iteration bound keeps the arrival counters in range)
   bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(2) && max_iter <= (1 << 20) && !capturing(s));

@@ -754,92 +754,174 @@ __global__ void __launch_bounds__(ENF_THREADS, 2 * PER_CU) enf_resident(EnfInst 
   else enf_resident_pair<false, PER_CU == 1>(in, I, J, tol, max_iter, sB, rowc);
 }
 
-// One tile (n <= 64): the exchange stays in the workgroup too.
-template <bool EDGE, bool HALF>
-__device__ __forceinline__ void enf_single_tile(const EnfInst& in, double tol, int max_iter, double (*sB)[ETP],
-                                                double (*rowc)[ET]) {
+__device__ __forceinline__ void enf_init_body(EnfCtrl* ctrl) {
+  {
+    ctrl->status = 0;
+    ctrl->converged = 0;
+    ctrl->iters = 0;
+    ctrl->done = 0;
+    ctrl->last_defect = ctrl->last_recip = 0.0;
+  }
+}
+
+// One tile (n <= 64), one workgroup: F stays in its registers for all
+// iterations and the exchange in its LDS.  An iteration is one serial chain, so
+// it is kept short: each thread holds whole unordered pairs {i, j} (four at
+// n = 64, one up to n = 32; both entries), with no transposes, a ballot decides
+// on convergence, and the maxima of the statistics are reduced after the last
+// iteration only.  SINGLE_US us an iteration at n = 32, SINGLE_US64 at n = 64 (3.9 and
+// 4.9 with the streamed sweep's tile step).  Every product and the order of
+// every sum are the sweep's and the finalize's, so the bits are.  The control
+// block and the areas' check, launches of their own elsewhere, are here too.
+constexpr int ESP = ET * (ET - 1) / 2 / ENF_THREADS + 1;  // pairs per thread, at most
+
+template <bool HALF>
+__device__ __forceinline__ void enf_single_body(const EnfInst& in, double tol, int max_iter, double (*sF)[ETP],
+                                                double (*part)[ET], double (*rowc)[ET], int* flags) {
 #pragma clang fp contract(off)
-  __shared__ double dec[4];
   const long ldf = in.ldf;
   const int n = in.n, tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
-  const int lc = (EDGE && l >= n) ? n - 1 : l;
-  double a[ERW], space = in.F[static_cast<long>(lc) * ldf + n];
-  const double b[ERW] = {};
+  if (tid == 0) enf_init_body(in.ctrl);
+  const bool own = tid < n;  // this thread has a row's diagonal and space entries
+  bool bad_area = false;
+  double diag = 0.0, space = 0.0;
+  if (own) {
+    const double ai = in.area[tid];
+    bad_area = !(ai > 0.0 && ai <= 1.0e300);
+    rowc[0][tid] = ai;
+    rowc[1][tid] = 1.0 / ai;
+    rowc[2][tid] = HALF ? 0.0 : ai * ai / in.nrays[tid];
+    rowc[3][tid] = 1.0;
+    diag = in.F[static_cast<long>(tid) * ldf + tid];
+    space = in.F[static_cast<long>(tid) * ldf + n];
+  }
+  const int npair = n * (n - 1) / 2;
+  int pi[ESP], pj[ESP];
+  double fij[ESP], fji[ESP];
 #pragma unroll
-  for (int k = 0; k < ERW; ++k) {
-    const int i = w + ENW * k;
-    a[k] = row_ld(in.F + static_cast<long>((EDGE && i >= n) ? n - 1 : i) * ldf, lc);
+  for (int m = 0; m < ESP; ++m) {
+    // row-wise: pair p of rows i < j; rows n - 1, n - 2, .. hold n - 1, n - 2, .. pairs from the end
+    const int p = tid + ENF_THREADS * m, back = npair - 1 - min(p, npair - 1);
+    int r = static_cast<int>((sqrtf(8.0f * static_cast<float>(max(back, 0)) + 1.0f) - 1.0f) * 0.5f);
+    r += (r + 1) * (r + 2) / 2 <= back;
+    r -= r * (r + 1) / 2 > back;
+    pi[m] = max(n - 2 - r, 0);
+    pj[m] = n - 1 - max(back - r * (r + 1) / 2, 0);
+    fij[m] = fji[m] = 0.0;
+    if (p < npair) {
+      fij[m] = in.F[static_cast<long>(pi[m]) * ldf + pj[m]];
+      fji[m] = in.F[static_cast<long>(pj[m]) * ldf + pi[m]];
+    }
   }
-  if (w == 0) {
-    const double ai = in.area[lc];
-    rowc[0][l] = ai;
-    rowc[1][l] = in.inv_area[lc];
-    rowc[2][l] = HALF ? 0.0 : ai * ai / in.nrays[lc];
-    rowc[3][l] = 1.0;
+  if (tid < 3) flags[tid] = 0;
+  if (__syncthreads_or(bad_area)) {
+    if (tid == 0) raise_status(&in.ctrl->status, RAD_EINVAL);
+    return;
   }
-  if (agent_load(&in.ctrl->status) < 0) return;  // a bad area, found by an earlier launch
-  __syncthreads();
+  const double area = own ? rowc[0][tid] : 0.0;
   int iters = 0, converged = 0, stop = 0;
+  double rmax = 0.0, emax = 0.0, d = 0.0;
   while (iters < max_iter && !converged) {
-    int bad = 0;
-    enf_pair_step<true, EDGE, HALF, true>(
-        in, 0, 0, a, b, sB, rowc, bad, []() {},
-        [&](double s_own, double, double rm, double em) {
-          double d = 0.0, zero = 0.0;
-          if (!EDGE || l < n) {
-            bad |= !(space >= 0.0) || !(space <= 1.0e300);
-            space *= rowc[3][l];
-            const double s = s_own + space;
-            zero = s > 0.0 ? 0.0 : 1.0;
-            rowc[3][l] = 1.0 / s;
-            d = fabs(s - 1.0);
-          }
-          for (int off = 32; off > 0; off >>= 1) {
-            d = fmax(d, __shfl_xor(d, off));
-            zero = fmax(zero, __shfl_xor(zero, off));
-          }
-          if (l == 0) {
-            dec[0] = d;
-            dec[1] = rm;
-            dec[2] = em;
-            dec[3] = zero;
-          }
-        });
-    const int input_error = __syncthreads_or(bad);
-    if (input_error || dec[3] > 0.0) {
-      if (tid == 0) raise_status(&in.ctrl->status, input_error ? RAD_ENONFINITE : RAD_EZEROROW);
-      stop = 1;
+    // of this iteration: a wave ahead may be in the next while another reads it
+    int* error = flags + 1 + (iters & 1);
+    bool bad = false;
+    rmax = 0.0;
+    emax = 0.0;
+    if (own) {
+      const double sc = rowc[3][tid];
+      diag *= sc;  // the diagonal keeps its value
+      space *= sc;
+      bad = !(diag >= 0.0) || !(diag <= 1.0e300) || !(space >= 0.0) || !(space <= 1.0e300);
+      emax = area * diag;
+      sF[tid][tid] = diag;
+    }
+#pragma unroll
+    for (int m = 0; m < ESP; ++m) {
+      if (tid + ENF_THREADS * m >= npair) break;
+      const int i = pi[m], j = pj[m];
+      const double x = fij[m] * rowc[3][i], y = fji[m] * rowc[3][j];
+      bad |= !(x >= 0.0) || !(x <= 1.0e300) || !(y >= 0.0) || !(y <= 1.0e300);
+      const double eij = rowc[0][i] * x, eji = rowc[0][j] * y;
+      rmax = fmax(rmax, fabs(eij - eji));
+      emax = fmax(emax, fmax(eij, eji));
+      const double kp = HALF ? 0.5 : kappa_c(x, y, rowc[2][i], rowc[2][j]);
+      const double eh = kp * eij + (1.0 - kp) * eji;
+      fij[m] = eh * rowc[1][i];
+      fji[m] = eh * rowc[1][j];
+      sF[i][j] = fij[m];
+      sF[j][i] = fji[m];
+    }
+    if (__ballot(bad) != 0 && l == 0) *error = RAD_ENONFINITE;
+    __syncthreads();
+    double s = 0.0;  // every 8th entry of row l, from w
+    if (l < n)
+      for (int c = w; c < n; c += ENW) s += sF[l][c];
+    part[w][l] = s;
+    __syncthreads();
+    if (w == 0) {
+      s = 0.0;
+#pragma unroll
+      for (int q = 0; q < ENW; ++q) s += part[q][l];
+      s += space;
+      const bool zero = own && !(s > 0.0);
+      d = own ? fabs(s - 1.0) : 0.0;
+      if (own) rowc[3][l] = 1.0 / s;
+      const bool all = __ballot(d <= tol) == ~0ull;
+      if (__ballot(zero) != 0 && l == 0 && *error == 0) *error = RAD_EZEROROW;
+      if (l == 0) flags[0] = tol > 0.0 && all;
+    }
+    __syncthreads();
+    stop = *error;
+    if (stop != 0) {
+      if (tid == 0) raise_status(&in.ctrl->status, stop);
       break;
     }
     ++iters;
-    converged = tol > 0.0 && dec[0] <= tol;
+    converged = flags[0];
   }
+  for (int off = 32; off > 0; off >>= 1) {
+    rmax = fmax(rmax, __shfl_xor(rmax, off));
+    emax = fmax(emax, __shfl_xor(emax, off));
+    d = fmax(d, __shfl_xor(d, off));
+  }
+  __syncthreads();  // part has been read
+  if (l == 0) {
+    part[0][w] = rmax;
+    part[1][w] = emax;
+  }
+  __syncthreads();
   if (tid == 0 && iters > 0) {
+    for (int q = 1; q < ENW; ++q) {
+      rmax = fmax(rmax, part[0][q]);
+      emax = fmax(emax, part[1][q]);
+    }
     in.ctrl->iters = iters;
     in.ctrl->converged = converged;
-    in.ctrl->last_defect = dec[0];
-    in.ctrl->last_recip = dec[2] > 0.0 ? dec[1] / dec[2] : 0.0;
+    in.ctrl->last_defect = d;
+    in.ctrl->last_recip = emax > 0.0 ? rmax / emax : 0.0;
   }
-  if (stop) return;
+  if (stop != 0 || iters == 0) return;
 #pragma unroll
-  for (int k = 0; k < ERW; ++k) {
-    const int i = w + ENW * k;
-    if (!EDGE || (i < n && l < n)) row_st(in.F + static_cast<long>(i) * ldf, l, a[k] * rowc[3][i]);
+  for (int m = 0; m < ESP; ++m)
+    if (tid + ENF_THREADS * m < npair) {
+      in.F[static_cast<long>(pi[m]) * ldf + pj[m]] = fij[m] * rowc[3][pi[m]];
+      in.F[static_cast<long>(pj[m]) * ldf + pi[m]] = fji[m] * rowc[3][pj[m]];
+    }
+  if (own) {
+    in.F[static_cast<long>(tid) * ldf + tid] = diag * rowc[3][tid];
+    in.F[static_cast<long>(tid) * ldf + n] = space * rowc[3][tid];
   }
-  if (w == 0 && (!EDGE || l < n)) in.F[static_cast<long>(l) * ldf + n] = space * rowc[3][l];
 }
 
 __global__ void __launch_bounds__(ENF_THREADS, 2) enf_single(EnfInst in, double tol, int max_iter) {
-  __shared__ double sB[ET][ETP];
-  __shared__ double rowc[8][ET];
-  if (in.mode == RAD_KAPPA_HALF) {
-    if (in.n < ET) enf_single_tile<true, true>(in, tol, max_iter, sB, rowc);
-    else enf_single_tile<false, true>(in, tol, max_iter, sB, rowc);
-  } else {
-    if (in.n < ET) enf_single_tile<true, false>(in, tol, max_iter, sB, rowc);
-    else enf_single_tile<false, false>(in, tol, max_iter, sB, rowc);
-  }
+  __shared__ double sF[ET][ETP];
+  __shared__ double part[ENW][ET], rowc[4][ET];
+  __shared__ int flags[3];  // converged, the error of two iterations in turn
+  if (in.mode == RAD_KAPPA_HALF)
+    enf_single_body<true>(in, tol, max_iter, sF, part, rowc, flags);
+  else
+    enf_single_body<false>(in, tol, max_iter, sF, part, rowc, flags);
 }
 
 __global__ void __launch_bounds__(64) enf_arrivals_init(EnfArrivals* arr) {
@@ -880,16 +962,6 @@ __global__ void __launch_bounds__(256)
 enf_inv_area_batched(const EnfInst* __restrict__ ins, const long* __restrict__ blk_start, int count) {
   const int k = find_segment(blk_start, count, blockIdx.x);
   enf_inv_area_body(ins[k], static_cast<int>(blockIdx.x - blk_start[k]) * blockDim.x + threadIdx.x);
-}
-
-__device__ __forceinline__ void enf_init_body(EnfCtrl* ctrl) {
-  {
-    ctrl->status = 0;
-    ctrl->converged = 0;
-    ctrl->iters = 0;
-    ctrl->done = 0;
-    ctrl->last_defect = ctrl->last_recip = 0.0;
-  }
 }
 
 __global__ void enf_init(EnfCtrl* ctrl) {
