@@ -34,7 +34,7 @@ struct EnfLayout {
   double* blkmax;
   double* finred;
   double* partial;
-  EnfArrivals* arr;
+  EnfWord* xch;
   size_t bytes;
   bool ok;
 };
@@ -47,9 +47,9 @@ EnfLayout enf_layout(void* work, size_t work_bytes, int64_t n) {
   l.scale = cv.take<double>(static_cast<size_t>(n));
   l.inv_area = cv.take<double>(static_cast<size_t>(n));
   l.blkmax = cv.take<double>(static_cast<size_t>(t * (t + 1)));
-  l.finred = cv.take<double>(static_cast<size_t>(std::max<int64_t>(3 * fin_blocks(n), 8 * t)));
+  l.finred = cv.take<double>(static_cast<size_t>(3 * fin_blocks(n)));
   l.partial = cv.take<double>(static_cast<size_t>((t + 1) * n));
-  l.arr = cv.take<EnfArrivals>(1);
+  l.xch = cv.take<EnfWord>(t > 1 && t <= ENF_RES_TILES ? static_cast<size_t>(enf_xch_words(t)) : 0);
   l.bytes = cv.used;
   l.ok = cv.ok;
   return l;
@@ -177,20 +177,24 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.blkmax = l.blkmax;
   in.finred = l.finred;
   in.ctrl = l.ctrl;
-  in.arr = l.arr;
+  in.xch = l.xch;
+  // one tile needs no co-operation; a resident grid does, which a capture does
+  // not record
+  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(2) && !capturing(s));
   if (pairs > 1) {
     hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
-    hipLaunchKernelGGL(enf_inv_area, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, in);
+    const long words = resident ? enf_xch_words(t) : 0;
+    if (resident)
+      hipLaunchKernelGGL(enf_resident_init, dim3(static_cast<unsigned>(ceil_div(std::max<long>(n, words / 8), 256))),
+                         dim3(256), 0, s, in);
+    else
+      hipLaunchKernelGGL(enf_inv_area, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, in);
   }
-  // one tile needs no co-operation; a resident grid does, which a capture does
-  // not record (the iteration bound keeps the arrival counters in range)
-  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(2) && max_iter <= (1 << 20) && !capturing(s));
   if (resident) {
     ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, 16.0 * static_cast<double>(n) * (n + 1));
     if (pairs == 1) {
       hipLaunchKernelGGL(enf_single, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
     } else {
-      hipLaunchKernelGGL(enf_arrivals_init, dim3(1), dim3(64), 0, s, l.arr);
       void* args[] = {&in, &tol, &max_iter};
       const void* k = pairs <= resident_limit(1) ? reinterpret_cast<const void*>(enf_resident<1>)
                                                  : reinterpret_cast<const void*>(enf_resident<2>);

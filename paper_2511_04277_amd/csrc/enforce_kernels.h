@@ -23,13 +23,12 @@ struct EnfCtrl {
 };
 
 
-// Arrival counters of the resident kernel, each on a cache line of its own:
-// tile pairs of the current iterations per 64-row block, and finished blocks.
-constexpr int ENF_RES_TILES = 64;  // most 64-row blocks of a resident model
-struct EnfArrivals {
-  int block[ENF_RES_TILES][32];
-  int done;
-};
+// What the workgroups of the resident kernel exchange, in words: row sums
+// (two iterations in turn x row block x column block x 64), closure scales and
+// row blocks' states (four iterations in turn), then three maxima and a counter.
+constexpr int ENF_RES_TILES = 32;  // most 64-row blocks of a resident model
+typedef unsigned long long EnfWord;
+__host__ __device__ constexpr long enf_xch_words(long t) { return 2 * t * t * ET + 4 * t * ET + 4 * t + 4; }
 
 // One enforcement problem as the kernels see it.
 struct EnfInst {
@@ -47,7 +46,7 @@ struct EnfInst {
   double* blkmax;           // 2 per tile pair: max |eta_ij - eta_ji|, max eta
   double* finred;           // 3 per finalize block: closure defect, the two maxima
   EnfCtrl* ctrl;
-  EnfArrivals* arr;         // resident kernel only
+  EnfWord* xch;             // resident kernel only: enf_xch_words(t)
 };
 
 constexpr int ERW = ET / ENW;  // tile rows per wave
@@ -129,10 +128,12 @@ __device__ __forceinline__ void agent_store(T* p, T v) {
 // own row l and of partner row l in lane l and the pair's maxima in lane 0.
 // WIDE: registers to spare, so the pairs of a thread are computed side by side
 // (their chains of dependent operations bind a workgroup alone on its CU).
-template <bool DIAG, bool EDGE, bool HALF, bool WIDE, class Put, class Sums>
+// MAXIMA: the workgroup's maxima go to sums; otherwise rmax and emax are left
+// per thread.
+template <bool DIAG, bool EDGE, bool HALF, bool WIDE, bool MAXIMA, class Put, class Sums>
 __device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, double (&a)[ERW],
                                               const double (&b)[ERW], double (*sB)[ETP], double (*rowc)[ET], int& bad,
-                                              Put put, Sums sums) {
+                                              double& rmax, double& emax, Put put, Sums sums) {
 #pragma clang fp contract(off)
   const int n = in.n;
   const bool half = HALF;
@@ -166,7 +167,8 @@ __device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, d
   __syncthreads();
 
   // reciprocity on each unordered pair {i, j}, i != j, exactly once
-  double rmax = 0.0, emax = 0.0, sb = 0.0;
+  double sb = 0.0;
+  rmax = emax = 0.0;
   // constants of row c0 + l (the partner's row; on a diagonal tile the own rows)
   const double aj = rowc[DIAG ? 0 : 4][l], iaj = rowc[DIAG ? 1 : 5][l];
   const double cj = rowc[DIAG ? 2 : 6][l];
@@ -210,10 +212,11 @@ __device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, d
   // own tile transposed into LDS, then each thread sums ERW entries of row l
 #pragma unroll
   for (int k = 0; k < ERW; ++k) sB[l][w + ENW * k] = a[k];
-  for (int off = 32; off > 0; off >>= 1) {
-    rmax = fmax(rmax, __shfl_xor(rmax, off));
-    emax = fmax(emax, __shfl_xor(emax, off));
-  }
+  if constexpr (MAXIMA)
+    for (int off = 32; off > 0; off >>= 1) {
+      rmax = fmax(rmax, __shfl_xor(rmax, off));
+      emax = fmax(emax, __shfl_xor(emax, off));
+    }
   __syncthreads();
   double sa = 0.0;
 #pragma unroll
@@ -224,7 +227,7 @@ __device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, d
   // the wave maxima
   sB[2 + w][l] = sb;
   sB[2 + ENW + w][l] = sa;
-  if (l == 0) {
+  if (MAXIMA && l == 0) {
     sB[0][w] = rmax;
     sB[1][w] = emax;
   }
@@ -236,16 +239,20 @@ __device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, d
       s_own += sB[2 + ENW + q][l];
       s_par += sB[2 + q][l];
     }
-    double x = 0.0, y = 0.0;
-    if (l == 0) {
-      x = sB[0][0];
-      y = sB[1][0];
-      for (int q = 1; q < ENW; ++q) {
-        x = fmax(x, sB[0][q]);
-        y = fmax(y, sB[1][q]);
+    if constexpr (MAXIMA) {
+      double x = 0.0, y = 0.0;
+      if (l == 0) {
+        x = sB[0][0];
+        y = sB[1][0];
+        for (int q = 1; q < ENW; ++q) {
+          x = fmax(x, sB[0][q]);
+          y = fmax(y, sB[1][q]);
+        }
       }
+      sums(s_own, s_par, x, y);
+    } else {
+      sums(s_own, s_par);
     }
-    sums(s_own, s_par, x, y);
   }
 }
 
@@ -317,8 +324,9 @@ __device__ __forceinline__ void enf_sweep_tile(const EnfInst& in, long pair, int
     rowc[q + 3][rl] = first ? 1.0 : inv_scale[i];
   }
   __syncthreads();
-  enf_pair_step<DIAG, EDGE, HALF, false>(
-      in, I, J, a, b, sB, rowc, bad,
+  double rmax, emax;
+  enf_pair_step<DIAG, EDGE, HALF, false, true>(
+      in, I, J, a, b, sB, rowc, bad, rmax, emax,
       [&]() {
         // own tile back to F
 #pragma unroll
@@ -559,68 +567,52 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 // A pair's two tiles fit the registers of its workgroup, so a model whose tile
 // pairs are all resident at once (two workgroups per CU: n <= 1984 on 256
 // CUs) is read and written once, and between iterations only row sums travel:
-// a workgroup stores its rows' partial sums and counts itself in for its two
-// row blocks; the last of a block's t workgroups adds the block's sums, stores
-// the closure scales and counts the block done; when all t blocks are done
-// every workgroup goes on.  Bound by the latency of that exchange through the
-// memory that all XCDs share (five dependent round trips).  Needs a cooperative
-// launch unless the grid is one workgroup.  Same operations in the same order
-// as enf_sweep, enf_finalize and enf_apply_scale, so the same bits.
+// a workgroup stores its rows' partial sums, the diagonal workgroup of a row
+// block adds the block's t + 1 sums and stores the closure scales and the
+// block's state, and every workgroup goes on once it has its two blocks' scales
+// and all t states.  Bound by the latency of that exchange through the memory
+// that all XCDs share, so the data are their own signal: a word holds ENF_EMPTY
+// until its value is stored, and a reader loads until it is not.  Two one-way
+// trips an iteration; with counters that announce the data there were five
+// dependent round trips (n = 1081: 10.5 us an iteration, now 6; n = 1900: 16.5, now 8.8).
+//
+// Buffers are used in turn and emptied by the diagonal workgroup of their row
+// block.  Row sums (two in turn): it empties what it has read at iteration k, and
+// that is done before it stores the scales of k + 1 (a wave's wait for its loads
+// covers its earlier stores), which every writer of iteration k + 2 has seen.
+// Scales and states (four): having read the sums of iteration k, whose writers
+// have all seen every state of k - 1 and so every workgroup those of k - 2, it
+// empties those of k - 2 for iteration k + 2, before it stores those of k + 1.
+//
+// Needs a cooperative launch: a workgroup that waits holds its place, and every
+// word that it waits for is stored by a workgroup that is resident too, in the
+// same iteration, whether or not an error was seen.  Same operations in the
+// same order as enf_sweep, enf_finalize and enf_apply_scale, so the same bits.
+constexpr EnfWord ENF_NAN = 0x7ff8000000000000ull;    // any NaN that is stored
+constexpr EnfWord ENF_EMPTY = 0x7ff8c0ffee000001ull;  // so no sum or scale is one of these
+constexpr EnfWord ENF_ERROR = 0x7ff8c0ffee000002ull;  // in place of a sum: an input error was seen
+enum : EnfWord { ENF_OPEN = 0, ENF_CLOSED = 1, ENF_FAILED = 2 };  // state of a row block
 
-// The sums of row block rb (64 rows), by its last workgroup; finred receives
-// the closure defect, the pair maxima and whether an error was seen.
-__device__ __forceinline__ void enf_resident_finalize(const EnfInst& in, int rb, double* finred, double (*sB)[ETP]) {
-  const int n = in.n, t = in.t, w = threadIdx.x >> 6, l = threadIdx.x & 63, i = rb * ET + l;
-  const int ic = min(i, n - 1);
-  static_assert(ENW == FIN_LANES, "wave w sums part w of every row");
-  double s = 0.0;
-  for (int q = w; q <= t; q += 4 * FIN_LANES) {
-    double v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = agent_load(in.partial + static_cast<long>(min(q + u * FIN_LANES, t)) * n + ic);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (q + u * FIN_LANES <= t) s += v[u];
+__device__ __forceinline__ EnfWord enf_word(double x) {
+  return x == x ? static_cast<EnfWord>(__double_as_longlong(x)) : ENF_NAN;
+}
+__device__ __forceinline__ double enf_value(EnfWord v) { return __longlong_as_double(static_cast<long long>(v)); }
+
+// One word per lane of an active wave, once no active lane's is empty.
+__device__ __forceinline__ EnfWord enf_await(const EnfWord* p) {
+  EnfWord v = agent_load(p);
+  while (__ballot(v == ENF_EMPTY) != 0) {
+    __builtin_amdgcn_s_sleep(1);
+    v = agent_load(p);
   }
-  double rm = 0.0, em = 0.0;
-  int st = 0;
-  if (w == 0) {
-    st = agent_load(&in.ctrl->status) < 0;  // of the block's workgroups at least
-    const long p0 = static_cast<long>(rb) * t - static_cast<long>(rb) * (rb - 1) / 2;  // pair (rb, rb)
-    if (l < t - rb) {
-      rm = agent_load(in.blkmax + 2 * (p0 + l));
-      em = agent_load(in.blkmax + 2 * (p0 + l) + 1);
-    }
-  }
-  sB[w][l] = s;
-  __syncthreads();
-  if (w == 0) {
-    double d = 0.0;
-    if (i < n) {
-      s = ((sB[0][l] + sB[1][l]) + (sB[2][l] + sB[3][l])) + ((sB[4][l] + sB[5][l]) + (sB[6][l] + sB[7][l]));
-      if (!(s > 0.0) && !st) {  // a row sum after an input error means nothing
-        raise_status(&in.ctrl->status, RAD_EZEROROW);
-        st = 1;
-      }
-      agent_store(in.scale + i, 1.0 / s);
-      d = fabs(s - 1.0);
-    }
-    double x[4] = {d, rm, em, static_cast<double>(st)};
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      for (int off = 32; off > 0; off >>= 1) x[c] = fmax(x[c], __shfl_xor(x[c], off));
-    if (l < 4) agent_store(finred + 4 * rb + l, l == 0 ? x[0] : l == 1 ? x[1] : l == 2 ? x[2] : x[3]);
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores are done before the block is
-    if (l == 0) atomicAdd(&in.arr->done, 1);
-  }
-  __syncthreads();
+  return v;
 }
 
 template <bool DIAG, bool EDGE, bool HALF, bool WIDE>
 __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int J, double tol, int max_iter,
                                                   double (*sB)[ETP], double (*rowc)[ET]) {
 #pragma clang fp contract(off)
-  __shared__ int last[2];
+  __shared__ int error, dec[2];  // an input error in this workgroup; all closed, any failed
   const long ldf = in.ldf;
   const int n = in.n, t = in.t;
   const int r0 = I * ET, c0 = J * ET;
@@ -628,6 +620,13 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int jg = c0 + l, ig = r0 + l;
   const int jgc = (EDGE && jg >= n) ? n - 1 : jg, igc = (EDGE && ig >= n) ? n - 1 : ig;
+  EnfWord* const xpart = in.xch;
+  EnfWord* const xscale = xpart + 2L * t * t * ET;
+  EnfWord* const xstate = xscale + 4L * t * ET;
+  EnfWord* const xmax = xstate + 4L * t;
+  // slot of row block r, column block c in iteration k
+  auto slot = [&](int k, int r, int c) { return xpart + ((static_cast<long>(k & 1) * t + r) * t + c) * ET + l; };
+  if (agent_load(&in.ctrl->status) < 0) return;  // a bad area, found by an earlier launch: for every workgroup alike
   double a[ERW], b[ERW], space = 0.0;
 #pragma unroll
   for (int k = 0; k < ERW; ++k) {
@@ -649,68 +648,127 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
     rowc[cq + 2][l] = HALF ? 0.0 : ai * ai / in.nrays[crc];
     rowc[cq + 3][l] = 1.0;
   }
+  if (tid == 0) error = 0;
   __syncthreads();
-  const int pair = static_cast<int>(blockIdx.x);
   int iters = 0, converged = 0, stop = 0;
-  double x[4] = {};  // closure defect, pair maxima, error seen
-  while (iters < max_iter && !converged && !stop) {
+  double rmax = 0.0, emax = 0.0, d = 0.0;
+  while (iters < max_iter && !converged) {
     int bad = 0;
-    enf_pair_step<DIAG, EDGE, HALF, WIDE>(
-        in, I, J, a, b, sB, rowc, bad,
+    enf_pair_step<DIAG, EDGE, HALF, WIDE, false>(
+        in, I, J, a, b, sB, rowc, bad, rmax, emax,
         [&]() {
           if (!DIAG)
 #pragma unroll
             for (int k = 0; k < ERW; ++k) b[k] = sB[w + ENW * k][l];
+          if (__ballot(bad) != 0 && l == 0) error = 1;
         },
-        [&](double s_own, double s_par, double rm, double em) {
+        [&](double s_own, double s_par) {
           if (DIAG) {
-            bad |= (!EDGE || ig < n) && (!(space >= 0.0) || !(space <= 1.0e300));
+            if (!EDGE || ig < n) bad |= !(space >= 0.0) || !(space <= 1.0e300);
             space *= rowc[3][l];
-          }
-          if (!EDGE || ig < n) agent_store(in.partial + static_cast<long>(J) * n + ig, s_own);
-          if (!DIAG && (!EDGE || jg < n)) agent_store(in.partial + static_cast<long>(I) * n + jg, s_par);
-          if (DIAG && (!EDGE || ig < n)) agent_store(in.partial + static_cast<long>(t) * n + ig, space);
-          if (l == 0) {
-            agent_store(in.blkmax + 2 * pair, rm);
-            agent_store(in.blkmax + 2 * pair + 1, em);
+            if (__ballot(bad) != 0 && l == 0) error = 1;
+            rowc[4][l] = s_own;
+            rowc[5][l] = space;
+          } else {
+            const bool e = error != 0;
+            agent_store(slot(iters, I, J), e ? ENF_ERROR : enf_word(s_own));
+            agent_store(slot(iters, J, I), e ? ENF_ERROR : enf_word(s_par));
           }
         });
     if (bad) raise_status(&in.ctrl->status, RAD_ENONFINITE);
-    // double-buffered: a workgroup may still read the last iteration's entries
-    double* finred = in.finred + (iters & 1) * 4 * t;
-    const int epoch = iters + 1;
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's stores (and its error) are done before its workgroup counts itself in
-    __syncthreads();
-    if (tid == 0) {
-      const int ci = atomicAdd(&in.arr->block[I][0], 1);
-      const int cj = DIAG ? 0 : atomicAdd(&in.arr->block[J][0], 1);
-      last[0] = ci + 1 == t * epoch;
-      last[1] = !DIAG && cj + 1 == t * epoch;
+    if (DIAG) {
+      // wave w sums every 8th partial sum of row l, the last one the space column's
+      __syncthreads();
+      static_assert(ENW == FIN_LANES, "wave w sums part w of every row");
+      double s = 0.0;
+      bool e = false;
+      for (int q = w; q <= t; q += 4 * ENW) {
+        EnfWord v[4];
+        bool wait;
+        do {
+          wait = false;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int c = q + ENW * u;
+            v[u] = c < t && c != I ? agent_load(slot(iters, I, c)) : 0;
+            wait |= v[u] == ENF_EMPTY;
+          }
+        } while (__ballot(wait) != 0);
+        __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int c = q + ENW * u;
+          if (c < t && c != I) agent_store(slot(iters, I, c), ENF_EMPTY);
+          e |= v[u] == ENF_ERROR;
+          if (c <= t) s += c == I ? rowc[4][l] : c == t ? rowc[5][l] : enf_value(v[u]);
+        }
+      }
+      sB[2 + 2 * ENW + w][l] = s;
+      if (__ballot(e) != 0 && l == 0) error = 1;
+      __syncthreads();
+      if (w == 0) {
+        const double(*p)[ETP] = sB + 2 + 2 * ENW;
+        s = ((p[0][l] + p[1][l]) + (p[2][l] + p[3][l])) + ((p[4][l] + p[5][l]) + (p[6][l] + p[7][l]));
+        const bool row = !EDGE || ig < n;
+        const bool failed = error != 0;
+        const bool zero = row && !(s > 0.0) && !failed;  // after an input error a sum means nothing
+        if (zero) raise_status(&in.ctrl->status, RAD_EZEROROW);
+        d = row ? fabs(s - 1.0) : 0.0;
+        const double sc = row && s > 0.0 ? 1.0 / s : 1.0;
+        const EnfWord state = failed || __ballot(zero) != 0 ? ENF_FAILED
+                              : __ballot(!(d <= tol)) == 0  ? ENF_CLOSED
+                                                            : ENF_OPEN;
+        __builtin_amdgcn_s_waitcnt(0);
+        agent_store(xscale + ((iters & 3) * static_cast<long>(t) + I) * ET + l, enf_word(sc));
+        if (l == 0) agent_store(xstate + (iters & 3) * static_cast<long>(t) + I, state);
+        const int e2 = (iters + 2) & 3;
+        agent_store(xscale + (e2 * static_cast<long>(t) + I) * ET + l, ENF_EMPTY);
+        if (l == 0) agent_store(xstate + e2 * static_cast<long>(t) + I, ENF_EMPTY);
+        rowc[3][l] = sc;
+      }
+    } else if (w < 2) {
+      const long r = (iters & 3) * static_cast<long>(t) + (w == 0 ? I : J);
+      rowc[w == 0 ? 3 : 7][l] = enf_value(enf_await(xscale + r * ET + l));
+    }
+    if (w == 2) {
+      const EnfWord st = enf_await(xstate + (iters & 3) * static_cast<long>(t) + min(l, t - 1));
+      const bool all = __ballot(st != ENF_CLOSED) == 0, any = __ballot(st == ENF_FAILED) != 0;
+      if (l == 0) {
+        dec[0] = all;
+        dec[1] = any;
+      }
     }
     __syncthreads();
-    if (last[0]) enf_resident_finalize(in, I, finred, sB);
-    if (!DIAG && last[1]) enf_resident_finalize(in, J, finred, sB);
-    if (tid == 0)
-      while (agent_load(&in.arr->done) < t * epoch) __builtin_amdgcn_s_sleep(1);
-    __syncthreads();
-    // every wave of every workgroup takes the same decision from the same values
-#pragma unroll
-    for (int c = 0; c < 4; ++c) x[c] = l < t ? agent_load(finred + 4 * l + c) : 0.0;
-    if (tid < (DIAG ? ET : 2 * ET)) rowc[cq + 3][l] = agent_load(in.scale + crc);
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-      for (int off = 32; off > 0; off >>= 1) x[c] = fmax(x[c], __shfl_xor(x[c], off));
-    __syncthreads();
-    stop = x[3] > 0.0;
+    stop = dec[1];
     if (stop) break;
     ++iters;
-    converged = tol > 0.0 && x[0] <= tol;
+    converged = tol > 0.0 && dec[0];
   }
-  if (pair == 0 && tid == 0) {
+  // the last iteration's maxima; the workgroup that adds its own last reports
+  for (int off = 32; off > 0; off >>= 1) {
+    d = fmax(d, __shfl_xor(d, off));
+    rmax = fmax(rmax, __shfl_xor(rmax, off));
+    emax = fmax(emax, __shfl_xor(emax, off));
+  }
+  __syncthreads();
+  if (l == 0) {
+    sB[0][w] = d;
+    sB[1][w] = rmax;
+    sB[2][w] = emax;
+  }
+  __syncthreads();
+  if (tid < 3) {
+    double x = 0.0;
+    for (int q = 0; q < ENW; ++q) x = fmax(x, sB[tid][q]);
+    atomicMax(xmax + tid, static_cast<EnfWord>(__double_as_longlong(x)));
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  if (tid == 0 && atomicAdd(xmax + 3, 1ull) + 1 == static_cast<EnfWord>(in.pairs)) {
+    const double em = enf_value(agent_load(xmax + 2));
     in.ctrl->iters = iters;
     in.ctrl->converged = converged;
-    in.ctrl->last_defect = x[0];
-    in.ctrl->last_recip = x[2] > 0.0 ? x[1] / x[2] : 0.0;
+    in.ctrl->last_defect = enf_value(agent_load(xmax));
+    in.ctrl->last_recip = em > 0.0 ? enf_value(agent_load(xmax + 1)) / em : 0.0;
   }
   if (stop || iters == 0) return;
   // F once, with the last closure scale (rowc[3], rowc[7])
@@ -924,12 +982,6 @@ __global__ void __launch_bounds__(ENF_THREADS, 2) enf_single(EnfInst in, double 
     enf_single_body<false>(in, tol, max_iter, sF, part, rowc, flags);
 }
 
-__global__ void __launch_bounds__(64) enf_arrivals_init(EnfArrivals* arr) {
-  arr->block[threadIdx.x][0] = 0;
-  if (threadIdx.x == 0) arr->done = 0;
-}
-static_assert(ENF_RES_TILES == 64, "one counter per thread, one finred entry per lane");
-
 __device__ __forceinline__ void enf_apply_scale_body(const EnfInst& in, long row) {
   if (in.ctrl->status < 0 || in.ctrl->iters == 0) return;
   const double s = in.scale[row];  // 1 / row sum
@@ -955,6 +1007,15 @@ __device__ __forceinline__ void enf_inv_area_body(const EnfInst& in, int i) {
 
 __global__ void __launch_bounds__(256) enf_inv_area(EnfInst in) {
   enf_inv_area_body(in, blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// the same, and an empty exchange, ahead of the resident kernel
+__global__ void __launch_bounds__(256) enf_resident_init(EnfInst in) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  enf_inv_area_body(in, i);
+  const long words = enf_xch_words(in.t);
+  for (long k = i; k < words; k += static_cast<long>(gridDim.x) * blockDim.x)
+    in.xch[k] = k < words - 4 ? ENF_EMPTY : 0;
 }
 
 // blocks [blk_start[k], blk_start[k+1]) cover the faces of instance k (256 per block)
