@@ -32,10 +32,18 @@ struct rad_batch_plan {
   size_t work_bytes = 0;
   void* prepared_for = nullptr;
   // filled by layout()
-  struct InstOff { size_t ctrl, scale, inv_area, blkmax, finred, partial; int t; long pairs; };
+  struct InstOff { size_t ctrl, scale, inv_area, blkmax, finred, partial, xch; int t; long pairs; };
   struct ProbOff { int inst, band, n, np, P2; long ldk, ldy, ldx, ldp, ldw, ldt; size_t kf, dinv, y, x, r, p, sc, w, v, scr;
                    size_t da, db, xa, xb, pa, pb; };
   std::vector<InstOff> io;
+  // enforcement order of the instances: the groups that fit the chip at once,
+  // then those that are always streamed (positions from streamed on)
+  struct Group { long first_pair, pairs; };
+  std::vector<int> order;
+  std::vector<Group> groups;
+  int streamed = 0;
+  long streamed_pair = 0, streamed_fin = 0, streamed_row = 0;  // of position streamed
+  double streamed_bytes = 0.0;
   std::vector<ProbOff> po;
   size_t tables_off = 0;
   // launch schedule (table offsets relative to the tables block)
@@ -723,6 +731,48 @@ struct Sched {
 
 size_t elem(int prec) { return prec == RAD_PREC_FP32_IR ? 4 : 8; }
 
+// Instances whose tile pairs fit the chip together form a group: all their
+// iterations are one cooperative launch, F on chip (see enf_resident_tile).
+// An iteration of a group costs 4.5 to 9 us however many of its workgroups are
+// used; streamed, a batch costs about 12 us an iteration for its two launches
+// and 14 us for every 512 tile pairs.  So the instances that are small enough
+// are packed into as few groups as first fit finds, largest first, and a group
+// that is less than half full is streamed if others are streamed anyway.
+constexpr long RES_PAIRS = 512;  // two workgroups on each of 256 CUs
+
+void group_instances(rad_batch_plan* P) {
+  std::vector<int> small, large;
+  for (int i = 0; i < P->count; ++i)
+    (P->io[i].t <= ENF_RES_TILES && P->io[i].pairs <= RES_PAIRS ? small : large).push_back(i);
+  std::stable_sort(small.begin(), small.end(), [&](int a, int b) { return P->io[a].pairs > P->io[b].pairs; });
+  std::vector<std::vector<int>> bins;
+  std::vector<long> fill;
+  for (int i : small) {
+    size_t g = bins.size() > 64 ? bins.size() - 64 : 0;  // of the latest groups
+    while (g < bins.size() && fill[g] + P->io[i].pairs > RES_PAIRS) ++g;
+    if (g == bins.size()) {
+      bins.emplace_back();
+      fill.push_back(0);
+    }
+    bins[g].push_back(i);
+    fill[g] += P->io[i].pairs;
+  }
+  P->order.clear();
+  P->groups.clear();
+  long first = 0;
+  for (size_t g = 0; g < bins.size(); ++g) {
+    if (!large.empty() && 2 * fill[g] < RES_PAIRS) {
+      large.insert(large.end(), bins[g].begin(), bins[g].end());
+      continue;
+    }
+    P->order.insert(P->order.end(), bins[g].begin(), bins[g].end());
+    P->groups.push_back({first, fill[g]});
+    first += fill[g];
+  }
+  P->streamed = static_cast<int>(P->order.size());
+  P->order.insert(P->order.end(), large.begin(), large.end());
+}
+
 // buffer layout of the workspace (tables come last, see build_tables)
 void layout(rad_batch_plan* P) {
   size_t used = 0;
@@ -745,6 +795,11 @@ void layout(rad_batch_plan* P) {
     o.finred = take(3 * static_cast<size_t>(fin_blocks(static_cast<int64_t>(n))) * sizeof(double));
     o.partial = take(static_cast<size_t>(o.t + 1) * n * sizeof(double));
     P->io.push_back(o);
+  }
+  group_instances(P);
+  for (int k = 0; k < P->streamed; ++k) {
+    auto& o = P->io[P->order[k]];
+    o.xch = take(static_cast<size_t>(enf_xch_words(o.t)) * sizeof(EnfWord));
   }
   const size_t es = elem(P->precision);
   for (int i = 0; i < P->count; ++i) {
@@ -802,9 +857,10 @@ void build_tables(rad_batch_plan* P, char* base, TableBuilder& tb) {
   for (int i = 0; i < P->count; ++i) f_bytes += 8.0 * static_cast<double>(P->inst[i].n) * (P->inst[i].n + 1);
   std::vector<EnfInst> ei;
   std::vector<long> pair_start(1, 0), fblk_start(1, 0), fin_start(1, 0), row_start(1, 0);
-  for (int i = 0; i < P->count; ++i) {
-    const rad_instance& s = P->inst[i];
-    const auto& o = P->io[i];
+  P->streamed_bytes = 0.0;
+  for (int k = 0; k < P->count; ++k) {
+    const rad_instance& s = P->inst[P->order[k]];
+    const auto& o = P->io[P->order[k]];
     EnfInst e{};
     e.F = s.F;
     e.ldf = static_cast<long>(s.ldf);
@@ -821,13 +877,18 @@ void build_tables(rad_batch_plan* P, char* base, TableBuilder& tb) {
     e.blkmax = reinterpret_cast<double*>(base + o.blkmax);
     e.finred = reinterpret_cast<double*>(base + o.finred);
     e.ctrl = reinterpret_cast<EnfCtrl*>(base + o.ctrl);
+    if (k < P->streamed) e.xch = reinterpret_cast<EnfWord*>(base + o.xch);
     ei.push_back(e);
     pair_start.push_back(pair_start.back() + o.pairs);
     fblk_start.push_back(fblk_start.back() + ceil_div(s.n, 256));
     fin_start.push_back(fin_start.back() + fin_blocks(s.n));
     row_start.push_back(row_start.back() + s.n);
     P->sweep_bytes += 16.0 * static_cast<double>(s.n) * (s.n + 1);
+    if (k >= P->streamed) P->streamed_bytes += 16.0 * static_cast<double>(s.n) * (s.n + 1);
   }
+  P->streamed_pair = pair_start[P->streamed];
+  P->streamed_fin = fin_start[P->streamed];
+  P->streamed_row = row_start[P->streamed];
   P->total_pairs = pair_start.back();
   P->total_fblk = fblk_start.back();
   P->total_fin = fin_start.back();
@@ -1035,17 +1096,47 @@ extern "C" int32_t rad_batch_run(const rad_batch_plan* P, void* work, double enf
   if (enforce_iters > 0) {
     hipLaunchKernelGGL(enf_inv_area_batched, dim3(static_cast<unsigned>(P->total_fblk)), dim3(256), 0, s, ei,
                        fblk_start, C);
-    for (int it = 0; it < enforce_iters; ++it) {
-      {
-        ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, P->sweep_bytes);
-        hipLaunchKernelGGL(enf_sweep_batched, dim3(static_cast<unsigned>(P->total_pairs)), dim3(ENF_THREADS), 0, s,
-                           ei, pair_map, it == 0 ? 1 : 0);
+    // a capture records no cooperative launch: everything is streamed then
+    static std::atomic<long> limit[64];
+    const void* resident = reinterpret_cast<const void*>(enf_resident_batched);
+    long first_pair = 0, first_fin = 0, first_row = 0;
+    int first = 0;
+    double bytes = P->sweep_bytes;
+    if (P->streamed > 0 && !stream_capturing(s) && resident_workgroups(resident, 2, limit) >= RES_PAIRS) {
+      hipLaunchKernelGGL(enf_exchange_init_batched, dim3(static_cast<unsigned>(P->streamed) * ENF_XCH_BLOCKS), dim3(256),
+                         0, s, ei);
+      ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, P->sweep_bytes - P->streamed_bytes);
+      hipError_t e = hipSuccess;
+      for (const auto& g : P->groups) {
+        const EnfBlk* map = pair_map + g.first_pair;
+        void* args[] = {&ei, &map, &enforce_tol, &enforce_iters};
+        e = hipLaunchCooperativeKernel(resident, dim3(static_cast<unsigned>(g.pairs)), dim3(ENF_THREADS), args, 0, s);
+        if (e != hipSuccess) break;
+        first = P->streamed;
       }
-      hipLaunchKernelGGL(enf_finalize_batched, dim3(static_cast<unsigned>(P->total_fin)), dim3(256), 0, s, ei,
-                         fin_map, enforce_tol);
+      if (first > 0) {
+        RAD_HIP_CHECK(e);
+        first_pair = P->streamed_pair;
+        first_fin = P->streamed_fin;
+        first_row = P->streamed_row;
+        bytes = P->streamed_bytes;
+      } else {
+        (void)hipGetLastError();  // nothing was enqueued: everything is streamed
+      }
     }
-    hipLaunchKernelGGL(enf_apply_scale_batched, dim3(static_cast<unsigned>(P->total_rows)), dim3(256), 0, s, ei,
-                       row_start, C);
+    if (first < C) {
+      for (int it = 0; it < enforce_iters; ++it) {
+        {
+          ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, bytes);
+          hipLaunchKernelGGL(enf_sweep_batched, dim3(static_cast<unsigned>(P->total_pairs - first_pair)),
+                             dim3(ENF_THREADS), 0, s, ei, pair_map + first_pair, it == 0 ? 1 : 0);
+        }
+        hipLaunchKernelGGL(enf_finalize_batched, dim3(static_cast<unsigned>(P->total_fin - first_fin)), dim3(256), 0,
+                           s, ei, fin_map + first_fin, enforce_tol);
+      }
+      hipLaunchKernelGGL(enf_apply_scale_batched, dim3(static_cast<unsigned>(P->total_rows - first_row)), dim3(256),
+                         0, s, ei + first, row_start + first, C - first);
+    }
   }
   // ---- Gebhart solves of every (instance, band)
   hipLaunchKernelGGL(b_scalars_init, dim3(qb), dim3(64), 0, s, pd, Q, 1);

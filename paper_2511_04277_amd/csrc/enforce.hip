@@ -89,35 +89,11 @@ int32_t enforce_check_args(const char* who, double* F, int64_t n, int64_t ldf, c
 }
 
 // Tile pairs that the current device holds at once with per_cu = 1 or 2
-// workgroups per CU (0: no cooperative launches), looked up once per device.
+// workgroups per CU.
 long resident_limit(int per_cu) {
-  static std::atomic<long> limit[64][2];  // limit + 1; 0: not looked up yet
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  long v = limit[dev][per_cu - 1].load(std::memory_order_relaxed);
-  if (v == 0) {
-    int coop = 0, cus = 0, per = 0;
-    const bool ok =
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        (per_cu == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, enf_resident<1>, ENF_THREADS, 0)
-                     : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, enf_resident<2>, ENF_THREADS, 0)) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-    v = 1 + (ok ? static_cast<long>(cus) * std::min(per, per_cu) : 0L);
-    limit[dev][per_cu - 1].store(v, std::memory_order_relaxed);
-  }
-  return v - 1;
-}
-
-// Whether the stream is being captured (or cannot be asked): a cooperative
-// launch is not recorded into graphs.
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;
-  }
-  return st != hipStreamCaptureStatusNone;
+  static std::atomic<long> one[64], two[64];
+  return per_cu == 1 ? resident_workgroups(reinterpret_cast<const void*>(enf_resident<1>), 1, one)
+                     : resident_workgroups(reinterpret_cast<const void*>(enf_resident<2>), 2, two);
 }
 
 // One sweep and one finalize launch per iteration, F streamed through.
@@ -180,7 +156,7 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.xch = l.xch;
   // one tile needs no co-operation; a resident grid does, which a capture does
   // not record
-  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(2) && !capturing(s));
+  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(2) && !stream_capturing(s));
   if (pairs > 1) {
     hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
     const long words = resident ? enf_xch_words(t) : 0;

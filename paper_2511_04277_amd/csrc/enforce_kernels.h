@@ -2,6 +2,9 @@
 // batched entry points.  See enforce.hip for the algorithm.
 #pragma once
 
+#include <algorithm>
+#include <atomic>
+
 #include "common.h"
 
 namespace rad {
@@ -812,6 +815,22 @@ __global__ void __launch_bounds__(ENF_THREADS, 2 * PER_CU) enf_resident(EnfInst 
   else enf_resident_pair<false, PER_CU == 1>(in, I, J, tol, max_iter, sB, rowc);
 }
 
+// Several models in one cooperative launch, each with an exchange of its own:
+// map[b] names the instance and the tile pair of workgroup b.
+__global__ void __launch_bounds__(ENF_THREADS, 4)
+enf_resident_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__ map, double tol, int max_iter) {
+  __shared__ double sB[ET][ETP];
+  __shared__ double rowc[8][ET];
+  const EnfBlk m = map[blockIdx.x];
+  const EnfInst in = ins[m.inst];
+  int I, J;
+  pair_from_index(m.local, in.t, I, J);
+  I = __builtin_amdgcn_readfirstlane(I);
+  J = __builtin_amdgcn_readfirstlane(J);
+  if (in.mode == RAD_KAPPA_HALF) enf_resident_pair<true, false>(in, I, J, tol, max_iter, sB, rowc);
+  else enf_resident_pair<false, false>(in, I, J, tol, max_iter, sB, rowc);
+}
+
 __device__ __forceinline__ void enf_init_body(EnfCtrl* ctrl) {
   {
     ctrl->status = 0;
@@ -991,11 +1010,12 @@ __device__ __forceinline__ void enf_apply_scale_body(const EnfInst& in, long row
 
 __global__ void __launch_bounds__(256) enf_apply_scale(EnfInst in) { enf_apply_scale_body(in, blockIdx.x); }
 
-// blocks [row_start[k], row_start[k+1]) are the rows of instance k
+// rows [row_start[k], row_start[k+1]) are instance k's
 __global__ void __launch_bounds__(256)
 enf_apply_scale_batched(const EnfInst* __restrict__ ins, const long* __restrict__ row_start, int count) {
-  const int k = find_segment(row_start, count, blockIdx.x);
-  enf_apply_scale_body(ins[k], blockIdx.x - row_start[k]);
+  const long row = row_start[0] + blockIdx.x;
+  const int k = find_segment(row_start, count, row);
+  enf_apply_scale_body(ins[k], row - row_start[k]);
 }
 
 __device__ __forceinline__ void enf_inv_area_body(const EnfInst& in, int i) {
@@ -1009,13 +1029,19 @@ __global__ void __launch_bounds__(256) enf_inv_area(EnfInst in) {
   enf_inv_area_body(in, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-// the same, and an empty exchange, ahead of the resident kernel
-__global__ void __launch_bounds__(256) enf_resident_init(EnfInst in) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  enf_inv_area_body(in, i);
+// an empty exchange, ahead of the resident kernel
+__device__ __forceinline__ void enf_exchange_init(const EnfInst& in, long block, long blocks) {
   const long words = enf_xch_words(in.t);
-  for (long k = i; k < words; k += static_cast<long>(gridDim.x) * blockDim.x)
+  for (long k = block * blockDim.x + threadIdx.x; k < words; k += blocks * blockDim.x)
     in.xch[k] = k < words - 4 ? ENF_EMPTY : 0;
+}
+__global__ void __launch_bounds__(256) enf_resident_init(EnfInst in) {
+  enf_inv_area_body(in, blockIdx.x * blockDim.x + threadIdx.x);
+  enf_exchange_init(in, blockIdx.x, gridDim.x);
+}
+constexpr int ENF_XCH_BLOCKS = 16;  // per instance
+__global__ void __launch_bounds__(256) enf_exchange_init_batched(const EnfInst* __restrict__ ins) {
+  enf_exchange_init(ins[blockIdx.x / ENF_XCH_BLOCKS], blockIdx.x % ENF_XCH_BLOCKS, ENF_XCH_BLOCKS);
 }
 
 // blocks [blk_start[k], blk_start[k+1]) cover the faces of instance k (256 per block)
@@ -1032,6 +1058,36 @@ __global__ void enf_init(EnfCtrl* ctrl) {
 __global__ void enf_init_batched(const EnfInst* __restrict__ ins, int count) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k < count) enf_init_body(ins[k].ctrl);
+}
+
+// Workgroups of a cooperative kernel that the current device holds at once, at
+// most per_cu on a CU (0: no cooperative launches); cache: one slot per device.
+inline long resident_workgroups(const void* kernel, int per_cu, std::atomic<long> (&cache)[64]) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  long v = cache[dev].load(std::memory_order_relaxed);  // count + 1; 0: not looked up yet
+  if (v == 0) {
+    int coop = 0, cus = 0, per = 0;
+    const bool ok =
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, ENF_THREADS, 0) == hipSuccess;
+    if (!ok) (void)hipGetLastError();
+    v = 1 + (ok ? static_cast<long>(cus) * std::min(per, per_cu) : 0L);
+    cache[dev].store(v, std::memory_order_relaxed);
+  }
+  return v - 1;
+}
+
+// Whether the stream is being captured (or cannot be asked): a cooperative
+// launch is not recorded into graphs.
+inline bool stream_capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
 }
 
 }  // namespace
