@@ -733,12 +733,12 @@ size_t elem(int prec) { return prec == RAD_PREC_FP32_IR ? 4 : 8; }
 
 // Instances whose tile pairs fit the chip together form a group: all their
 // iterations are one cooperative launch, F on chip (see enf_resident_tile).
-// An iteration of a group costs 4.5 to 9 us however many of its workgroups are
-// used; streamed, a batch costs about 12 us an iteration for its two launches
-// and 14 us for every 512 tile pairs.  So the instances that are small enough
+// An iteration of a group costs 4.5 to 11 us however many of its workgroups are
+// used; streamed, a batch costs about 10 us an iteration for its two launches
+// and 20 us for every 768 tile pairs.  So the instances that are small enough
 // are packed into as few groups as first fit finds, largest first, and a group
 // that is less than half full is streamed if others are streamed anyway.
-constexpr long RES_PAIRS = 512;  // two workgroups on each of 256 CUs
+constexpr long RES_PAIRS = ENF_RES_PER_CU * 256;  // the workgroups of 256 CUs
 
 void group_instances(rad_batch_plan* P) {
   std::vector<int> small, large;
@@ -1102,7 +1102,7 @@ extern "C" int32_t rad_batch_run(const rad_batch_plan* P, void* work, double enf
     long first_pair = 0, first_fin = 0, first_row = 0;
     int first = 0;
     double bytes = P->sweep_bytes;
-    if (P->streamed > 0 && !stream_capturing(s) && resident_workgroups(resident, 2, limit) >= RES_PAIRS) {
+    if (P->streamed > 0 && !stream_capturing(s) && resident_workgroups(resident, ENF_RES_PER_CU, limit) >= RES_PAIRS) {
       hipLaunchKernelGGL(enf_exchange_init_batched, dim3(static_cast<unsigned>(P->streamed) * ENF_XCH_BLOCKS), dim3(256),
                          0, s, ei);
       ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, P->sweep_bytes - P->streamed_bytes);

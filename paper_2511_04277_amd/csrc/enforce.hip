@@ -88,12 +88,12 @@ int32_t enforce_check_args(const char* who, double* F, int64_t n, int64_t ldf, c
   return RAD_OK;
 }
 
-// Tile pairs that the current device holds at once with per_cu = 1 or 2
-// workgroups per CU.
-long resident_limit(int per_cu) {
-  static std::atomic<long> one[64], two[64];
-  return per_cu == 1 ? resident_workgroups(reinterpret_cast<const void*>(enf_resident<1>), 1, one)
-                     : resident_workgroups(reinterpret_cast<const void*>(enf_resident<2>), 2, two);
+// Tile pairs that the current device holds at once, with one workgroup per CU
+// or with as many as fit.
+long resident_limit(bool alone) {
+  static std::atomic<long> one[64], all[64];
+  return alone ? resident_workgroups(reinterpret_cast<const void*>(enf_resident<1>), 1, one)
+               : resident_workgroups(reinterpret_cast<const void*>(enf_resident<ENF_RES_PER_CU>), ENF_RES_PER_CU, all);
 }
 
 // One sweep and one finalize launch per iteration, F streamed through.
@@ -156,7 +156,7 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.xch = l.xch;
   // one tile needs no co-operation; a resident grid does, which a capture does
   // not record
-  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(2) && !stream_capturing(s));
+  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(false) && !stream_capturing(s));
   if (pairs > 1) {
     hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
     const long words = resident ? enf_xch_words(t) : 0;
@@ -172,8 +172,8 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
       hipLaunchKernelGGL(enf_single, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
     } else {
       void* args[] = {&in, &tol, &max_iter};
-      const void* k = pairs <= resident_limit(1) ? reinterpret_cast<const void*>(enf_resident<1>)
-                                                 : reinterpret_cast<const void*>(enf_resident<2>);
+      const void* k = pairs <= resident_limit(true) ? reinterpret_cast<const void*>(enf_resident<1>)
+                                                    : reinterpret_cast<const void*>(enf_resident<ENF_RES_PER_CU>);
       const hipError_t e = hipLaunchCooperativeKernel(k,
                                                       dim3(static_cast<unsigned>(pairs)), dim3(ENF_THREADS), args, 0, s);
       if (e != hipSuccess) {  // nothing was enqueued: one launch per step instead

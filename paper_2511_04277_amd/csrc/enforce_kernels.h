@@ -29,7 +29,8 @@ struct EnfCtrl {
 // What the workgroups of the resident kernel exchange, in words: row sums
 // (two iterations in turn x row block x column block x 64), closure scales and
 // row blocks' states (four iterations in turn), then three maxima and a counter.
-constexpr int ENF_RES_TILES = 32;  // most 64-row blocks of a resident model
+constexpr int ENF_RES_TILES = 39;  // most 64-row blocks of a resident model
+constexpr int ENF_RES_PER_CU = 3;  // its workgroups per CU: 80 registers and 37 KB of LDS each
 typedef unsigned long long EnfWord;
 __host__ __device__ constexpr long enf_xch_words(long t) { return 2 * t * t * ET + 4 * t * ET + 4 * t + 4; }
 
@@ -568,7 +569,7 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 
 // ---- all iterations in one launch, F on chip ---------------------------------
 // A pair's two tiles fit the registers of its workgroup, so a model whose tile
-// pairs are all resident at once (two workgroups per CU: n <= 1984 on 256
+// pairs are all resident at once (three workgroups per CU: n <= 2432 on 256
 // CUs) is read and written once, and between iterations only row sums travel:
 // a workgroup stores its rows' partial sums, the diagonal workgroup of a row
 // block adds the block's t + 1 sums and stores the closure scales and the
@@ -577,7 +578,8 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 // that all XCDs share, so the data are their own signal: a word holds ENF_EMPTY
 // until its value is stored, and a reader loads until it is not.  Two one-way
 // trips an iteration; with counters that announce the data there were five
-// dependent round trips (n = 1081: 10.5 us an iteration, now 6; n = 1900: 16.5, now 8.8).
+// dependent round trips (n = 1081: 10.5 us an iteration, now 6; n = 1900: 16.5, now 9.0;
+// n = 2304 streamed: 27.7, now 10.4).
 //
 // Buffers are used in turn and emptied by the diagonal workgroup of their row
 // block.  Row sums (two in turn): it empties what it has read at iteration k, and
@@ -685,26 +687,25 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
       static_assert(ENW == FIN_LANES, "wave w sums part w of every row");
       double s = 0.0;
       bool e = false;
-      for (int q = w; q <= t; q += 4 * ENW) {
-        EnfWord v[4];
-        bool wait;
-        do {
-          wait = false;
+      constexpr int NU = ENF_RES_TILES / ENW + 1;  // all sums of a part at once: t <= ENF_RES_TILES
+      EnfWord v[NU];
+      bool wait;
+      do {
+        wait = false;
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int c = q + ENW * u;
-            v[u] = c < t && c != I ? agent_load(slot(iters, I, c)) : 0;
-            wait |= v[u] == ENF_EMPTY;
-          }
-        } while (__ballot(wait) != 0);
-        __builtin_amdgcn_s_waitcnt(0);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int c = q + ENW * u;
-          if (c < t && c != I) agent_store(slot(iters, I, c), ENF_EMPTY);
-          e |= v[u] == ENF_ERROR;
-          if (c <= t) s += c == I ? rowc[4][l] : c == t ? rowc[5][l] : enf_value(v[u]);
+        for (int u = 0; u < NU; ++u) {
+          const int c = w + ENW * u;
+          v[u] = c < t && c != I ? agent_load(slot(iters, I, c)) : 0;
+          wait |= v[u] == ENF_EMPTY;
         }
+      } while (__ballot(wait) != 0);
+      __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int c = w + ENW * u;
+        if (c < t && c != I) agent_store(slot(iters, I, c), ENF_EMPTY);
+        e |= v[u] == ENF_ERROR;
+        if (c <= t) s += c == I ? rowc[4][l] : c == t ? rowc[5][l] : enf_value(v[u]);
       }
       sB[2 + 2 * ENW + w][l] = s;
       if (__ballot(e) != 0 && l == 0) error = 1;
@@ -802,7 +803,7 @@ __device__ __forceinline__ void enf_resident_pair(const EnfInst& in, int I, int 
   }
 }
 
-// PER_CU: workgroups per CU the registers allow, 1 or 2
+// PER_CU: workgroups per CU the registers allow, 1 or ENF_RES_PER_CU
 template <int PER_CU>
 __global__ void __launch_bounds__(ENF_THREADS, 2 * PER_CU) enf_resident(EnfInst in, double tol, int max_iter) {
   __shared__ double sB[ET][ETP];
@@ -817,7 +818,7 @@ __global__ void __launch_bounds__(ENF_THREADS, 2 * PER_CU) enf_resident(EnfInst 
 
 // Several models in one cooperative launch, each with an exchange of its own:
 // map[b] names the instance and the tile pair of workgroup b.
-__global__ void __launch_bounds__(ENF_THREADS, 4)
+__global__ void __launch_bounds__(ENF_THREADS, 2 * ENF_RES_PER_CU)
 enf_resident_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__ map, double tol, int max_iter) {
   __shared__ double sB[ET][ETP];
   __shared__ double rowc[8][ET];
