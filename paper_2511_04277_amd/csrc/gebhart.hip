@@ -181,17 +181,23 @@ hipError_t factor_update_emu(const EmuWork& ew, const Fact<double>& f, int c0, i
   return hipSuccess;
 }
 
-// W_p = U_pp^-1 and V_p = L_pp^-1 of every panel (at most seven launches).
+// W_p = U_pp^-1 and V_p = L_pp^-1 of nb diagonal blocks from block b0 on (part
+// of one panel, or whole panels; at most seven launches): the blocks' own
+// inverses, then the joins of b-wide inverses from b = NB on.  halves: only the
+// join of a panel's two halves, formed before.
 template <class T>
-hipError_t panel_inverses(const Fact<T>& f, T* tmp, long ldt, hipStream_t s) {
-  TriJob<T> j{f.kf, f.ldk, f.dinv, f.np, f.W, f.V, f.ldw, tmp, ldt};
-  hipLaunchKernelGGL(tri_init<T>, dim3(tri_init_blocks(f.np)), dim3(256), 0, s, j);
-  for (int b = NB; b < NB2 && b < f.np; b *= 2)  // pairs of b-wide blocks exist
+hipError_t panel_inverses(const Fact<T>& f, int b0, int nb, bool halves, T* tmp, long ldt, hipStream_t s) {
+  const long r = static_cast<long>(b0) * NB, w = r * f.ldw + r % NB2;  // panels are NB2 rows each
+  const TriJob<T> j{f.kf + r * (f.ldk + 1), f.ldk, f.dinv + r * NB, nb * NB, f.W + w, f.V + w, f.ldw, tmp + r * ldt,
+                    ldt};
+  const int P2 = static_cast<int>(ceil_div(j.np, NB2));
+  if (!halves) hipLaunchKernelGGL(tri_init<T>, dim3(tri_init_blocks(j.np)), dim3(256), 0, s, j);
+  for (int b = halves ? NB2 / 2 : NB; b < NB2 && b < j.np; b *= 2)  // pairs of b-wide blocks exist
     for (int stage = 0; stage < 2; ++stage) {
-      if (tri_level_blocks(f.P2, b, 64) < GEMM_TILE32_BELOW)
-        hipLaunchKernelGGL((tri_level<T, 32>), dim3(tri_level_blocks(f.P2, b, 32)), dim3(256), 0, s, j, b, stage);
+      if (tri_level_blocks(P2, b, 64) < GEMM_TILE32_BELOW)
+        hipLaunchKernelGGL((tri_level<T, 32>), dim3(tri_level_blocks(P2, b, 32)), dim3(256), 0, s, j, b, stage);
       else
-        hipLaunchKernelGGL((tri_level<T, 64>), dim3(tri_level_blocks(f.P2, b, 64)), dim3(256), 0, s, j, b, stage);
+        hipLaunchKernelGGL((tri_level<T, 64>), dim3(tri_level_blocks(P2, b, 64)), dim3(256), 0, s, j, b, stage);
     }
   return hipGetLastError();
 }
@@ -204,10 +210,13 @@ hipError_t panel_inverses(const Fact<T>& f, T* tmp, long ldt, hipStream_t s) {
 // p+1's chain of diagonal inverses and narrow updates can start at once; the
 // rest of the trailing matrix and the right-hand sides are updated on the
 // side stream s2 meanwhile.  Panel p+1's row-block forward substitution waits
-// for that part (event).  Past the last panel only the right-hand sides are
-// left, up to seven short products in a row: they run on s2 beside the panel
-// inverses (as many short launches), and the call joins s2 back into s at the
-// end.  The arithmetic and its order per element are the same as without the
+// for that part (event).  s2 also takes the last panel's right-hand sides, up to
+// seven short products in a row, and with up to EARLY_PANELS panels, whose far
+// updates leave it idle, the inverse of a panel, which only the solves read: its
+// upper half once those blocks are done, the rest after the far update (the last
+// panel's rest on s).  The inverses at the end, all panels in a launch, against
+// early: n = 591 308 and 292 us, 2048 1040 and 1024, 4096 alike, 8192 with int8
+// products 17.07 and 17.55 ms.  The call joins s2 back into s at the end.  The arithmetic and its order per element are the same as without the
 // split.  A single diagonal block has no side work: no events.
 template <class T>
 hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc, T* tmp, long ldt, hipStream_t s,
@@ -223,6 +232,17 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
     e = stream_wait(s2, s, ss->ev[0]);  // s2 starts after the caller's earlier work
     if (e != hipSuccess) return e;
   }
+  constexpr int HALF = NB2 / NB / 2, EARLY_PANELS = 4;  // HALF: blocks
+  const bool early = s2 != s && f.P2 <= EARLY_PANELS;
+  // a panel's inverse but for the half that is on s2 already
+  auto rest_of_inverse = [&](int c0, int c1, hipStream_t st) {
+    const int b0 = c0 / NB, nb = (c1 - c0) / NB;
+    if (nb <= HALF) return panel_inverses<T>(f, b0, nb, false, tmp, ldt, st);
+    hipError_t er = panel_inverses<T>(f, b0 + HALF, nb - HALF, false, tmp, ldt, st);
+    if (er == hipSuccess && st != s2) er = hipStreamWaitEvent(st, ss->ev[4], 0);
+    if (er == hipSuccess) er = panel_inverses<T>(f, b0, nb, true, tmp, ldt, st);
+    return er;
+  };
   for (int c0 = 0; c0 < f.np; c0 += NB2) {
     const int c1 = std::min(c0 + NB2, f.np);
     const int c2 = std::min(c1 + NB2, f.np);
@@ -233,6 +253,16 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
         ProfScope prof(s, RAD_PROF_DIAG_INVERSE, 2.0 * NB * NB * NB, 0.0);
         hipLaunchKernelGGL(gj_inverse<T>, dim3(1), dim3(GJ_THREADS), 0, s,
                            kf + static_cast<long>(k0) * ldk + k0, ldk, dk, sc);
+      }
+      if (early && k0 - c0 == (HALF - 1) * NB && c1 - c0 > HALF * NB) {
+        e = stream_wait(s2, s, ss->ev[0]);
+        if (e != hipSuccess) return e;
+        e = panel_inverses<T>(f, c0 / NB, HALF, false, tmp, ldt, s2);
+        if (e != hipSuccess) return e;
+        if (c1 == f.np) {
+          e = hipEventRecord(ss->ev[4], s2);
+          if (e != hipSuccess) return e;
+        }
       }
       const int r1 = k0 + NB;
       if (r1 >= f.np) break;
@@ -331,8 +361,12 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
         if (e != hipSuccess) return e;
       }
     }
+    if (early) {
+      e = rest_of_inverse(c0, c1, s2);
+      if (e != hipSuccess) return e;
+    }
   }
-  e = panel_inverses<T>(f, tmp, ldt, s);
+  e = early ? rest_of_inverse((f.np - 1) / NB2 * NB2, f.np, s) : panel_inverses<T>(f, 0, f.P, false, tmp, ldt, s);
   if (e != hipSuccess) return e;
   if (s2 != s) {
     e = stream_wait(s, s2, ss->ev[1]);  // join
