@@ -805,9 +805,6 @@ extern "C" int32_t rad_steady_temperature(const double* Y, int64_t n, int64_t ld
               "rad_steady_temperature: workspace too small or not 256-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int ni = static_cast<int>(n), mi = static_cast<int>(m);
-  // the right-hand sides occupy one full 64-column tile (zero past m)
-  constexpr int SS_RHS = 64;
-  static_assert(SS_RHS >= RAD_STEADY_MAX_CASES, "right-hand side tile narrower than the case limit");
   const EmuWork* ew = precision == RAD_PREC_FP64_I8 ? &w.emu : nullptr;
   Fact<double> f = make_fact<double>(factors, factor_layout<double>(n));
   double* X = static_cast<double*>(w.y);
@@ -815,8 +812,8 @@ extern "C" int32_t rad_steady_temperature(const double* Y, int64_t n, int64_t ld
   hipLaunchKernelGGL(scalars_init, dim3(1), dim3(64), 0, s, w.sc);
   hipLaunchKernelGGL(ss_form, dim3(f.np), dim3(256), 0, s, Y, static_cast<long>(ldy), ni, weight, Q,
                      static_cast<long>(ldq), mi, t_fixed, xs, sigma, f.kf, f.ldk, f.np, X, w.ldy, w.sc);
-  RAD_HIP_CHECK(factor_forward<double>(f, X, w.ldy, SS_RHS, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
-  RAD_HIP_CHECK(back_solve<double>(f, X, w.ldy, SS_RHS, static_cast<double*>(w.scr), w.ldy, s, ew));
+  RAD_HIP_CHECK(factor_forward<double>(f, X, w.ldy, mi, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
+  RAD_HIP_CHECK(back_solve<double>(f, X, w.ldy, mi, static_cast<double*>(w.scr), w.ldy, s, ew));
   hipLaunchKernelGGL(ss_output, dim3(static_cast<unsigned>(ceil_div(n * m, 256))), dim3(256), 0, s, X, w.ldy, ni,
                      mi, t_fixed, T, static_cast<long>(ldt), w.sc);
   RAD_HIP_CHECK(hipGetLastError());
@@ -888,7 +885,7 @@ extern "C" int32_t rad_enforce_lsq(const double* F, int64_t n, int64_t ldf, cons
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int ni = static_cast<int>(n);
   const int nnr = (flags & RAD_LSQ_NNR) != 0;
-  constexpr int LSQ_RHS = 64;
+  constexpr int LSQ_RHS = 1;
   const GebWork& w = l.geb;
   const EmuWork* ew = precision == RAD_PREC_FP64_I8 ? &w.emu : nullptr;
   Fact<double> f = make_fact<double>(factors, factor_layout<double>(n));

@@ -469,6 +469,57 @@ __global__ void __launch_bounds__(256, 2) gemm_lds32(GemmArgs<T> g) {
   gemm_tile32<T, TRANS_A>(g, bx, by, sh);
 }
 
+// C (N <= 16 columns) of a few right-hand sides: a handful of tiles, so the
+// chain of a deep K binds (eight 128-deep stages of a tile, 18-20 us at K =
+// 1024).  A workgroup takes 16 rows and its eight waves an eighth of K each,
+// with all operands (up to 128 k a wave) in flight at once straight to
+// registers; the eight partial sums are added in wave order: 8.8 us.
+constexpr int GEMM_NARROW = 16, GEMM_NARROW_K = 1024;
+
+template <class T>
+__global__ void __launch_bounds__(512) gemm_narrow(GemmArgs<T> g) {
+  typedef typename Mfma<T>::v4 v4;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int PV = 16 / sizeof(T), STEPS = GEMM_NARROW_K / 8 / 16;
+  __shared__ T part[8][16][GEMM_NARROW + 1];
+  const int t = threadIdx.x, l = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), li = l & 15, lg = l >> 4;
+  const int m0 = blockIdx.x * 16, N = g.N[0], M = g.M;
+  const int mb = (m0 / GEMM_TILE) * GEMM_TILE;
+  const int kbeg = g.tri == 1 ? mb : 0, kend = g.tri == 2 ? min(g.K, mb + GEMM_TILE) : g.K;
+  const int steps = (kend - kbeg) / 128;  // of 16 k, per wave
+  const int k0 = kbeg + 16 * steps * w + 4 * lg;
+  const T* a = g.A + static_cast<long>(m0 + li) * g.lda + k0;
+  const T* b = g.B[0] + static_cast<long>(k0) * g.ldb[0] + min(li, N - 1);
+  vec fa[STEPS][4 / PV];
+  T fb[STEPS][4];
+#pragma unroll
+  for (int q = 0; q < STEPS; ++q)
+    if (q < steps) {
+#pragma unroll
+      for (int u = 0; u < 4 / PV; ++u) fa[q][u] = *reinterpret_cast<const vec*>(a + 16 * q + PV * u);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) fb[q][s] = b[static_cast<long>(16 * q + s) * g.ldb[0]];
+    }
+  const int i = m0 + t / 16, j = t % 16;
+  T* c = g.C[0] + static_cast<long>(min(i, M - 1)) * g.ldc[0] + min(j, N - 1);
+  const T cv = t < 256 && g.beta != T(0) ? *c : T(0);
+  v4 acc = v4{0, 0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < STEPS; ++q)
+    if (q < steps)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) acc = Mfma<T>::mma(fa[q][s / PV][s % PV], fb[q][s], acc);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) part[w][Mfma<T>::orow(l, r)][li] = acc[r];
+  __syncthreads();
+  if (t >= 256 || i >= M || j >= N) return;
+  T x = part[0][t / 16][j];
+#pragma unroll
+  for (int q = 1; q < 8; ++q) x += part[q][t / 16][j];
+  const T ax = g.alpha * x;
+  *c = g.beta != T(0) ? fma(g.beta, cv, ax) : ax;
+}
+
 // Runtime choice of the tile: a product with fewer than small_tile_below
 // 128 x 128 tiles (precision index 0 = FP64, 1 = FP32) runs with 64 x 64
 // tiles.  Set by rad_tuning_set (tuning.cpp), chosen by the autotuner.
@@ -548,6 +599,13 @@ inline hipError_t launch_gemm(const GemmArgs<T>& a0, bool trans_a, hipStream_t s
   const int big = gemm_tiles<T>(a);
   if (big == 0) return hipSuccess;
   ProfScope prof(s, gemm_prof_kind<T>(trans_a), gemm_flops(a), gemm_bytes(a));
+  // K = 128: one stage is no chain, and the products of small models keep the
+  // tiles' order of accumulation, as their batched ones do
+  if (!trans_a && a.nseg == 1 && a.N[0] <= GEMM_NARROW && a.K % GEMM_KS == 0 && a.K > GEMM_KS &&
+      a.K <= GEMM_NARROW_K && a.btri == 0) {
+    hipLaunchKernelGGL(gemm_narrow<T>, dim3(static_cast<unsigned>((a.M + 15) / 16)), dim3(512), 0, s, a);
+    return hipGetLastError();
+  }
   const int tiles64 = tiles_x<T, 64>(a) * ((a.M + 63) / 64);
   if (a.K % GEMM_KS == 0 && tiles64 < GEMM_TILE32_BELOW) {
     const unsigned grid = static_cast<unsigned>(tiles_x<T, 32>(a)) * static_cast<unsigned>((a.M + 31) / 32);
