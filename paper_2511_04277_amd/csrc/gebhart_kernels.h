@@ -167,11 +167,18 @@ ss_form(const double* __restrict__ Y, long ldy, int n, const double* __restrict_
   const double* yrow = Y + static_cast<long>(i) * ldy;
   int bad = 0;
   double s = 0.0;
+  constexpr int U = 8;  // loads of a thread in flight; the sum stays in order
   if (row)
-    for (long j = threadIdx.x; j <= n; j += blockDim.x) {
-      const double v = yrow[j];
-      bad |= !(v >= 0.0 && v <= 1.0e300);
-      s += v;
+    for (int j0 = threadIdx.x; j0 <= n; j0 += 256 * U) {
+      double v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = yrow[min(j0 + 256 * u, n)];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + 256 * u <= n) {
+          bad |= !(v[u] >= 0.0 && v[u] <= 1.0e300);
+          s += v[u];
+        }
     }
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -183,19 +190,22 @@ ss_form(const double* __restrict__ Y, long ldy, int n, const double* __restrict_
     bad |= !(t >= 0.0 && t <= 1.0e300);
   }
   double* krow = KF + static_cast<long>(i) * ldk;
-  for (long j = threadIdx.x; j < ldk; j += blockDim.x) {
-    double kv = (i == j) ? 1.0 : 0.0;
-    if (row && j < n) {
-      const double v = yrow[j];
-      kv = (i == j) ? s - v : -v;
+  for (int j0 = threadIdx.x; j0 < ldk; j0 += 256 * U) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = row ? yrow[min(j0 + 256 * u, n)] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 256 * u;
+      const double kv = row && j < n ? (i == j ? s - v[u] : -v[u]) : (i == j ? 1.0 : 0.0);
+      if (j < ldk) krow[j] = j < np ? kv : 0.0;
     }
-    krow[j] = j < np ? kv : 0.0;
   }
   double* rrow = R + static_cast<long>(i) * ldr;
   const double ysp = row ? yrow[n] : 0.0;
-  for (long c = threadIdx.x; c < ldr; c += blockDim.x) {
+  for (int c = threadIdx.x; c < m; c += 256) {  // the solve carries m columns
     double rv = 0.0;
-    if (real && c < m) {
+    if (real) {
       if (fixed) {
         rv = (t * t) * (t * t);
       } else {
@@ -299,24 +309,54 @@ lsq_schur(const double* __restrict__ F, long ldf, int n, const double* __restric
     wi[j] = i < n ? W[i] : 0.0;
   }
   if (i0 < n) {
+    // a chunk's entries (the rows' own, and the partners' as in
+    // lsq_stage_partner) are in flight while the chunk before it is summed, for
+    // there is less than one workgroup per CU to cover them; addresses clamped
+    // into the matrix (n = 2845: 140 -> 78 us, of which 10 for columns of Y
+    // that no solve reads)
+    constexpr int NP = LSQ_KC * LSQ_RB / 256;
+    double fn[4], pn[NP], wn;
+    uint8_t an[4], qn[NP];
+    auto load = [&](int k0) {
+      const int k = min(k0 + l, n);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const long i = min(i0 + w + 4 * j, n - 1);
+        an[j] = mask[i * ldm + k];
+        fn[j] = F[i * ldf + k];
+      }
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const int e = t + 256 * q;
+        const long kk = min(k0 + e / LSQ_RB, n - 1);
+        const int i = min(i0 + e % LSQ_RB, n - 1);
+        pn[q] = F[kk * ldf + i];
+        qn[q] = mask[kk * ldm + i];
+      }
+      wn = W[min(k, n - 1)];
+    };
+    load(0);
     for (int k0 = 0; k0 <= n; k0 += LSQ_KC) {
-      // the rows' own entries of the chunk, loaded before the partner tile
-      // so that both sets of loads are in flight together
       const int k = k0 + l;
       int am[4];
       double fv[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int i = i0 + w + 4 * j;
-        const bool in = i < n && k <= n;
-        am[j] = in ? mask[static_cast<long>(i) * ldm + k] : 0;
-        fv[j] = in ? F[static_cast<long>(i) * ldf + k] : 0.0;
+        am[j] = an[j];
+        fv[j] = fn[j];
       }
+      const double wk = k < n ? wn : 0.0;
       __syncthreads();  // the previous chunk's partner reads are done
-      lsq_stage_partner(F, ldf, mask, ldm, n, i0, k0, pf, pm);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) {
+        const int e = t + 256 * q;
+        const bool in = k0 + e / LSQ_RB < n && i0 + e % LSQ_RB < n;
+        pf[e / LSQ_RB][e % LSQ_RB] = in ? pn[q] : 0.0;
+        pm[e / LSQ_RB][e % LSQ_RB] = in ? qn[q] : 0;
+      }
       __syncthreads();
+      if (k0 + LSQ_KC <= n) load(k0 + LSQ_KC);
       if (k > n) continue;
-      const double wk = k < n ? W[k] : 0.0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int ii = w + 4 * j, i = i0 + ii;
@@ -364,11 +404,10 @@ lsq_schur(const double* __restrict__ F, long ldf, int n, const double* __restric
         krow[i] = cnt[j] > 0.0 ? cnt[j] - sub[j] : 1.0;
         yrow[0] = cnt[j] > 0.0 ? (rsum[j] - 1.0) - tt[j] : 0.0;
       }
-      for (long c = 1 + l; c < ldy; c += 64) yrow[c] = 0.0;
     } else {
       // padding rows: identity
       for (long k = l; k < ldk; k += 64) krow[k] = k == i ? 1.0 : 0.0;
-      for (long c = l; c < ldy; c += 64) yrow[c] = 0.0;
+      if (l == 0) yrow[0] = 0.0;
     }
   }
 }
