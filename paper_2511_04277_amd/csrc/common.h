@@ -110,6 +110,17 @@ inline hipError_t stream_wait(hipStream_t dst, hipStream_t src, hipEvent_t ev) {
   return hipStreamWaitEvent(dst, ev, 0);
 }
 
+// Loads and stores at the level that all XCDs share (no cache of one XCD
+// holds the value), for what workgroups of one launch exchange.
+template <class T>
+__device__ __forceinline__ T agent_load(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T>
+__device__ __forceinline__ void agent_store(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Device status codes raised by kernels (stored in an int32 flag; the
 // smallest (most negative) code wins via atomicMin).
 __device__ inline void raise_status(int* flag, int code) { atomicMin(flag, code); }

@@ -114,17 +114,6 @@ __device__ __forceinline__ double kappa_c(double fij, double fji, double ci, dou
   return s > 0.0 ? b * r : 0.5;
 }
 
-// Loads and stores at the level that all XCDs share (no cache of one XCD
-// holds the value), for what workgroups of one launch exchange.
-template <class T>
-__device__ __forceinline__ T agent_load(const T* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class T>
-__device__ __forceinline__ void agent_store(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // One iteration of a tile pair held in registers: own tile (I, J) in a, partner
 // tile (J, I) in b (see enf_sweep_tile); rowc holds the rows' constants and the
 // previous closure scale.  put() is called once the new own tile is in a and

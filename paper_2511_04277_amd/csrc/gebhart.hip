@@ -234,6 +234,11 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
   }
   constexpr int HALF = NB2 / NB / 2, EARLY_PANELS = 4;  // HALF: blocks
   const bool early = s2 != s && f.P2 <= EARLY_PANELS;
+  // Tiles that s2 updates beside a panel.  A workgroup of update_invert needs
+  // most of a CU, and waits until so much is free: beside more tiles than the
+  // chip holds at once (four a CU), separate small workgroups get there first.
+  constexpr long FUSE_BESIDE = 4 * 256;
+  long beside = 0;
   // a panel's inverse but for the half that is on s2 already
   auto rest_of_inverse = [&](int c0, int c1, hipStream_t st) {
     const int b0 = c0 / NB, nb = (c1 - c0) / NB;
@@ -247,9 +252,10 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
     const int c1 = std::min(c0 + NB2, f.np);
     const int c2 = std::min(c1 + NB2, f.np);
     // (1) panel: 128-wide blocks; updates stay inside the panel's columns
+    bool inverted = false;  // the block, with the update before it
     for (int k0 = c0; k0 < c1; k0 += NB) {
       T* dk = f.dinv + static_cast<long>(k0) * NB;
-      {
+      if (!inverted) {
         ProfScope prof(s, RAD_PROF_DIAG_INVERSE, 2.0 * NB * NB * NB, 0.0);
         hipLaunchKernelGGL(gj_inverse<T>, dim3(1), dim3(GJ_THREADS), 0, s,
                            kf + static_cast<long>(k0) * ldk + k0, ldk, dk, sc);
@@ -273,7 +279,14 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
         GemmArgs<T> u = update_args<T>(x, ldk, f.np - r1, NB);
         gemm_add_segment<T>(u, kf + static_cast<long>(k0) * ldk + r1, ldk, kf + static_cast<long>(r1) * ldk + r1,
                             ldk, c1 - r1);
-        RAD_GEMM(u, false);
+        inverted = beside <= FUSE_BESIDE;
+        if (inverted) {
+          ProfScope prof(s, gemm_prof_kind<T>(false), gemm_flops(u) + 2.0 * NB * NB * NB, gemm_bytes(u));
+          hipLaunchKernelGGL(update_invert<T>, dim3(update_invert_blocks(u)), dim3(GJ_THREADS), 0, s, u, dk + NB * NB,
+                             sc);
+        } else {
+          RAD_GEMM(u, false);
+        }
       }
     }
     if (c1 == f.np) {
@@ -361,6 +374,7 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
         if (e != hipSuccess) return e;
       }
     }
+    if (s2 != s) beside = ceil_div(f.np - c1, 64) * ceil_div(f.np - c2 + (Y ? wy : 0), 64);
     if (early) {
       e = rest_of_inverse(c0, c1, s2);
       if (e != hipSuccess) return e;

@@ -57,7 +57,7 @@ inline long rhs_ld(int64_t n, long pad) { return static_cast<long>(ceil_div(n + 
 
 struct Scalars {
   int status;
-  int pad;
+  int arrivals;      // corner tiles of update_invert launches (a multiple of their number between them)
   double max_r;      // max |residual|
   double max_d;      // max |correction|
   double red[2];     // REF check outputs
@@ -95,6 +95,7 @@ Fact<T> make_fact(void* base, const FactorLayout& l) {
 __global__ void scalars_init(Scalars* sc) {
   if (threadIdx.x == 0) {
     sc->status = 0;
+    sc->arrivals = 0;
     sc->max_r = 0.0;
     sc->max_d = 0.0;
     sc->red[0] = sc->red[1] = 0.0;
@@ -625,7 +626,13 @@ struct GjShared {
 };
 
 // The pivot wave: inverts pivot tile s, and forms tile s + 1 from the tiles of step s.
-template <class T>
+// AGENT: A was stored by other workgroups of the launch.
+template <bool AGENT, class T>
+__device__ __forceinline__ T gj_load(const T* p) {
+  if constexpr (AGENT) return agent_load(p);
+  else return *p;
+}
+template <class T, bool AGENT>
 __device__ __forceinline__ void gj_pivots(const T* __restrict__ A, long lda, Scalars* sc, GjShared<T>& sh) {
   typedef typename Mfma<T>::v4 v4;
   constexpr int BT = 16, NT = NB / BT;
@@ -635,7 +642,7 @@ __device__ __forceinline__ void gj_pivots(const T* __restrict__ A, long lda, Sca
   int singular = 0;
   T v[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = A[static_cast<long>(Mfma<T>::orow(l, r)) * lda + li];
+  for (int r = 0; r < 4; ++r) v[r] = gj_load<AGENT>(A + static_cast<long>(Mfma<T>::orow(l, r)) * lda + li);
 #pragma unroll 1
   for (int s = 0;; ++s) {
     T pivots = T(1);
@@ -666,7 +673,7 @@ __device__ __forceinline__ void gj_pivots(const T* __restrict__ A, long lda, Sca
 }
 
 // Tile row w, of the upper or the lower half, through the eight steps.
-template <class T, bool UPPER>
+template <class T, bool UPPER, bool AGENT>
 __device__ __forceinline__ void gj_row(const T* __restrict__ A, long lda, T* __restrict__ out, int w,
                                        GjShared<T>& sh) {
   typedef typename Mfma<T>::v4 v4;
@@ -676,7 +683,8 @@ __device__ __forceinline__ void gj_row(const T* __restrict__ A, long lda, T* __r
 #pragma unroll
   for (int bj = 0; bj < NT; ++bj)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) m[bj][r] = A[static_cast<long>(w * BT + Mfma<T>::orow(l, r)) * lda + bj * BT + li];
+    for (int r = 0; r < 4; ++r)
+      m[bj][r] = gj_load<AGENT>(A + static_cast<long>(w * BT + Mfma<T>::orow(l, r)) * lda + bj * BT + li);
   auto put = [&](T* d, int ld, const v4& x) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) d[Mfma<T>::orow(l, r) * ld + li] = x[r];
@@ -789,21 +797,21 @@ __device__ __forceinline__ void gj_row(const T* __restrict__ A, long lda, T* __r
   }
 }
 
-template <class T>
+template <class T, bool AGENT = false>
 __device__ __forceinline__ void gj_body(const T* __restrict__ A, long lda, T* __restrict__ out, Scalars* sc,
                                         GjShared<T>& sh) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (wave == 0) {
-    gj_pivots<T>(A, lda, sc, sh);
+    gj_pivots<T, AGENT>(A, lda, sc, sh);
   } else if ((wave & 3) == 0) {  // on the pivot wave's SIMD: no work
     for (int s = 0; s < 2 * (NB / 16); ++s) __syncthreads();
   } else {
     // tile rows of waves 1, 2, 3, 5, 6, 7, 9, 10, so that the three SIMDs share the updates
     const int w = (0x64753210 >> (4 * (wave - 1 - wave / 4))) & 15;
     if (w < NB / 32)
-      gj_row<T, true>(A, lda, out, w, sh);
+      gj_row<T, true, AGENT>(A, lda, out, w, sh);
     else
-      gj_row<T, false>(A, lda, out, w, sh);
+      gj_row<T, false, AGENT>(A, lda, out, w, sh);
   }
 }
 template <class T>
@@ -811,6 +819,146 @@ __global__ void __launch_bounds__(GJ_THREADS)
 gj_inverse(const T* __restrict__ A, long lda, T* __restrict__ out, Scalars* sc) {
   __shared__ GjShared<T> sh;
   gj_body<T>(A, lda, out, sc, sh);
+}
+
+// The update of the panel's remaining columns by one block and the half inverses
+// of the next diagonal block, in one launch: C -= X U with X (M x NB) and U (NB x
+// N) at K = NB, C's first NB x NB corner the next block.  The corner's sixteen
+// 32 x 32 tiles come first; the workgroup that stores the last of them inverts
+// the corner (nobody waits), while the others form the rest in 64 x 128 tiles.
+// Each gives the bits of gemm_tile.  Workgroups have the inversion's eleven
+// waves and LDS, one per CU, and eight waves with 32 x 32 of C each; a tile takes K
+// in two stages, the second in flight under the first's products.  28 us for up
+// to one round of tiles (M x N = 1920 x 896 and less: 19 us of update, then 21 of
+// inversion as launches of their own), 30 us at M = 2816.
+template <class T>
+struct UpdateStage {
+  static constexpr int KS = NB / 2;
+  T a[64][KS + 2];
+  T b[KS][NB + 4];
+};
+template <class T>
+union UpdateShared {
+  GjShared<T> gj;
+  Tile32<T, false> corner;
+  UpdateStage<T> tile;
+};
+
+template <class T>
+__device__ __forceinline__ void update_tile(const T* __restrict__ X, const T* __restrict__ U, T* __restrict__ C,
+                                            long ld, UpdateStage<T>& sh) {
+  typedef typename Mfma<T>::v4 v4;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int PV = 16 / sizeof(T), KS = UpdateStage<T>::KS, KC = GemmCfg<T>::KC;
+  constexpr int NA = 64 * KS / PV / 512, NBV = KS * NB / PV / 512;
+  const int t = threadIdx.x, l = t & 63, li = l & 15, lg = l >> 4, w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const bool work = w < 8;  // the other waves only keep step
+  const int wr = (w & 1) * 32, wc = (w >> 1) * 32;
+  vec ra[NA], rb[NBV];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const int p = t + 512 * q;
+      ra[q] = *reinterpret_cast<const vec*>(X + static_cast<long>(p / (KS / PV)) * ld + k0 + (p % (KS / PV)) * PV);
+    }
+#pragma unroll
+    for (int q = 0; q < NBV; ++q) {
+      const int p = t + 512 * q;
+      rb[q] = *reinterpret_cast<const vec*>(U + static_cast<long>(k0 + p / (NB / PV)) * ld + (p % (NB / PV)) * PV);
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const int p = t + 512 * q;
+      *reinterpret_cast<vec*>(&sh.a[p / (KS / PV)][(p % (KS / PV)) * PV]) = ra[q];
+    }
+#pragma unroll
+    for (int q = 0; q < NBV; ++q) {
+      const int p = t + 512 * q;
+      *reinterpret_cast<vec*>(&sh.b[p / (NB / PV)][(p % (NB / PV)) * PV]) = rb[q];
+    }
+  };
+  T cv[2][2][4];
+  v4 acc[2][2];
+  if (work) {
+    load(0);
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        acc[x][y] = v4{0, 0, 0, 0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          cv[x][y][r] = C[static_cast<long>(wr + 16 * x + Mfma<T>::orow(l, r)) * ld + wc + 16 * y + li];
+      }
+  }
+#pragma unroll
+  for (int k0 = 0; k0 < NB; k0 += KS) {
+    if (k0 > 0) __syncthreads();  // the first stage has been read
+    if (work) store();
+    __syncthreads();
+    if (!work) continue;
+    if (k0 + KS < NB) load(k0 + KS);
+#pragma unroll
+    for (int c = 0; c < KS / KC; ++c)
+#pragma unroll
+      for (int s = 0; s < KC / 4; ++s) {
+        const int k = c * KC + lg * (KC / 4) + s;
+        T fa[2], fb[2];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          fa[x] = sh.a[wr + 16 * x + li][k];
+          fb[x] = sh.b[k][wc + 16 * x + li];
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 2; ++y) acc[x][y] = Mfma<T>::mma(fa[x], fb[y], acc[x][y]);
+      }
+  }
+  if (!work) return;
+#pragma unroll
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        C[static_cast<long>(wr + 16 * x + Mfma<T>::orow(l, r)) * ld + wc + 16 * y + li] =
+            fma(T(1), cv[x][y][r], T(-1) * acc[x][y][r]);
+}
+
+// u: the update (update_args, one segment, M and N multiples of NB); out: the
+// next block's place in dinv; sc->arrivals counts the corner's tiles
+template <class T>
+__global__ void __launch_bounds__(GJ_THREADS)
+update_invert(GemmArgs<T> u, T* __restrict__ out, Scalars* sc) {
+  __shared__ UpdateShared<T> sh;
+  __shared__ int last;
+  constexpr int CORNER = (NB / 32) * (NB / 32);
+  const int b = blockIdx.x;
+  if (b >= CORNER) {
+    const int nty = u.M / 64, i = b - CORNER;
+    // column by column; the first without the corner's two row tiles
+    const int bx = i < nty - 2 ? 0 : 1 + (i - (nty - 2)) / nty;
+    const int by = i < nty - 2 ? i + 2 : (i - (nty - 2)) % nty;
+    update_tile<T>(u.A + static_cast<long>(by) * 64 * u.lda, u.B[0] + bx * NB,
+                   u.C[0] + static_cast<long>(by) * 64 * u.ldc[0] + bx * NB, u.lda, sh.tile);
+    return;
+  }
+  if (threadIdx.x < 256)
+    gemm_tile32<T, false, true>(u, b % (NB / 32), b / (NB / 32), sh.corner);
+  else
+    __syncthreads();  // the tile's one stage
+  __builtin_amdgcn_s_waitcnt(0);  // this wave's part of C is stored
+  __syncthreads();
+  if (threadIdx.x == 0) last = (atomicAdd(&sc->arrivals, 1) + 1) % CORNER == 0;
+  __syncthreads();
+  if (last) gj_body<T, true>(u.C[0], u.ldc[0], out, sc, sh.gj);
+}
+template <class T>
+inline unsigned update_invert_blocks(const GemmArgs<T>& u) {
+  return static_cast<unsigned>((NB / 32) * (NB / 32) + (u.M / 64) * (u.N[0] / NB) - 2);
 }
 
 // many diagonal blocks (of different problems) in one launch

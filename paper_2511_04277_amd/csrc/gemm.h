@@ -326,7 +326,8 @@ struct Tile32 {
   T b[KS][LB];
 };
 
-template <class T, bool TRANS_A>
+// AGENT: C is stored where workgroups on other XCDs of the launch can read it.
+template <class T, bool TRANS_A, bool AGENT = false>
 __device__ __forceinline__ void gemm_tile32(const GemmArgs<T>& g, int bx, int by, Tile32<T, TRANS_A>& sh) {
   typedef typename Mfma<T>::v4 v4;
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
@@ -402,7 +403,9 @@ __device__ __forceinline__ void gemm_tile32(const GemmArgs<T>& g, int bx, int by
     const int i = m0 + wr + Mfma<T>::orow(l, r), j = n0 + wc + li;
     if (i < M && j < N) {
       const T ax = g.alpha * acc[r];
-      Cm[static_cast<long>(i) * ldc + j] = g.beta != T(0) ? fma(g.beta, cv[r], ax) : ax;
+      const T x = g.beta != T(0) ? fma(g.beta, cv[r], ax) : ax;
+      if constexpr (AGENT) agent_store(Cm + static_cast<long>(i) * ldc + j, x);
+      else Cm[static_cast<long>(i) * ldc + j] = x;
     }
   }
 }
