@@ -129,6 +129,59 @@ csr_scatter(const int* __restrict__ group, int n, int g, const int* __restrict__
   members[offs[gi] + cnt[static_cast<long>(c) * g + gi] + rank[i]] = i;
 }
 
+// The whole sort in one workgroup for up to 1024 indices and groups: thread i
+// ranks index i, and the group counts are scanned in place.  Small calls are
+// bound by their launches (four as above).
+constexpr int CSR_SMALL = 1024;
+__global__ void __launch_bounds__(CSR_SMALL)
+csr_small(const int* __restrict__ group, int n, int g, int* __restrict__ offs, int* __restrict__ members,
+          int* __restrict__ status) {
+  __shared__ __align__(16) int ids[CSR_SMALL];
+  __shared__ int first[CSR_SMALL], wsum[16], error;
+  const int i = threadIdx.x, lane = i & 63, wv = i >> 6;
+  int gi = i < n ? group[i] : -1;
+  const bool bad = i < n && (gi < 0 || gi >= g);
+  if (bad) gi = -1;
+  ids[i] = gi;
+  first[i] = 0;
+  if (i == 0) error = 0;
+  __syncthreads();
+  int r = 0;  // equal ids before index i
+  for (int q0 = 0; q0 < min(64 * (wv + 1), n); q0 += 16) {
+    int4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const int4*>(&ids[q0 + 4 * u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int q = q0 + 4 * u;
+      r += (v[u].x == gi && q < i) + (v[u].y == gi && q + 1 < i) + (v[u].z == gi && q + 2 < i) +
+           (v[u].w == gi && q + 3 < i);
+    }
+  }
+  if (gi >= 0) atomicAdd(&first[gi], 1);
+  __syncthreads();
+  const int count = first[i];
+  int x = count;  // inclusive scan over the groups
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int y = __shfl_up(x, off);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) wsum[wv] = x;
+  if (bad || (i < g && count == 0)) error = RAD_EINVAL;  // an id out of range, an empty group
+  __syncthreads();
+  int before = 0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) before += q < wv ? wsum[q] : 0;
+  x += before;
+  first[i] = x - count;
+  if (i < g) offs[i] = x - count;
+  if (i == g - 1) offs[g] = x;
+  if (i == 0) *status = error;
+  __syncthreads();
+  if (gi >= 0) members[first[gi] + r] = i;
+}
+
 __global__ void __launch_bounds__(AGG_THREADS)
 agg_reduce(const double* __restrict__ X, long ldx, int n, const double* __restrict__ w,
            const int* __restrict__ offs, const int* __restrict__ members, int g,
@@ -484,6 +537,10 @@ __global__ void __launch_bounds__(256) fill_ones(double* __restrict__ p, int n) 
 
 // CSR of the group map (members of each group in index order), shared by the reductions of one call
 void agg_build(const int32_t* group, int n, int g, const AggLayout& l, hipStream_t s) {
+  if (n <= CSR_SMALL && g <= CSR_SMALL) {
+    hipLaunchKernelGGL(csr_small, dim3(1), dim3(CSR_SMALL), 0, s, group, n, g, l.offs, l.members, l.status);
+    return;
+  }
   const long ncnt = static_cast<long>(l.nch) * g;
   hipLaunchKernelGGL(csr_init, dim3(static_cast<unsigned>(std::min<long>(ceil_div(ncnt, 256), 4096))), dim3(256), 0,
                      s, l.status, l.cnt, ncnt);

@@ -444,15 +444,19 @@ struct PanelSweep {
     }
     cur = S[idx & 1];
     ++idx;
+    return product(Mp, ldm, trans, tri, L, Y + static_cast<long>(c0) * ldy, ldy, cur, lds, wy);
+  }
+  hipError_t product(const T* Mp, long ldm, bool trans, int tri, int L, const T* src, long ldsrc, T* dst, long lddst,
+                     int wy) {
     GemmArgs<T> a = gemm_args<T>(Mp, ldm, L, L, T(1), T(0));
     a.tri = tri;
-    gemm_add_segment<T>(a, Y + static_cast<long>(c0) * ldy, ldy, cur, lds, wy);
+    gemm_add_segment<T>(a, src, ldsrc, dst, lddst, wy);
     return launch_gemm(a, trans, s);
   }
-  // copy of the current product into Y_p, on the side stream; after the last
-  // product of a sweep there is nothing beside it, and it stays on s
-  hipError_t copy_back(int c0, int L, T* Y, long ldy, int wy, bool last) {
-    hipStream_t st = last ? s : s2;
+  // copy of the current product into Y_p, on the side stream; a solve's last
+  // has nothing beside it, and stays on s
+  hipError_t copy_back(int c0, int L, T* Y, long ldy, int wy) {
+    hipStream_t st = c0 == 0 ? s : s2;
     if (st != s) {
       hipError_t e = stream_wait(st, s, ss->ev[0]);
       if (e != hipSuccess) return e;
@@ -504,7 +508,7 @@ hipError_t emu_sweep_update(const EmuWork& ew, const EmuOperand& oa, bool akc, b
 // in one K = panel-width product.
 template <class T>
 hipError_t back_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, long lds, hipStream_t s,
-                      const EmuWork* ew = nullptr) {
+                      const EmuWork* ew = nullptr, const T** top = nullptr) {
   const long ldk = f.ldk;
   PanelSweep<T> ps;
   hipError_t e = ps.init(scr, lds, s);
@@ -521,8 +525,10 @@ hipError_t back_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, long lds
     }
     e = ps.product(Wp, f.ldw, false, 1, c0, c1 - c0, Y, ldy, wy);
     if (e != hipSuccess) return e;
-    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy, c0 == 0);
-    if (e != hipSuccess) return e;
+    if (c0 > 0 || !top) {
+      e = ps.copy_back(c0, c1 - c0, Y, ldy, wy);
+      if (e != hipSuccess) return e;
+    }
     if (c0 > 0 && ew) {
       if constexpr (std::is_same<T, double>::value) {
         e = emu_sweep_update(*ew, emu_operand(f.kf + c0, ldk, 1, c0, c1 - c0), true, a_ready,
@@ -535,6 +541,7 @@ hipError_t back_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, long lds
       RAD_GEMM(u, false);
     }
   }
+  if (top) *top = ps.cur;
   return ps.join();
 }
 
@@ -560,8 +567,10 @@ hipError_t transposed_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, lo
     }
     e = ps.product(Wp, f.ldw, true, 2, c0, c1 - c0, Y, ldy, wy);
     if (e != hipSuccess) return e;
-    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy, c1 == f.np);
-    if (e != hipSuccess) return e;
+    if (c1 < f.np) {
+      e = ps.copy_back(c0, c1 - c0, Y, ldy, wy);
+      if (e != hipSuccess) return e;
+    }
     if (c1 < f.np && ew) {
       if constexpr (std::is_same<T, double>::value) {
         e = emu_sweep_update(*ew, emu_operand(f.kf + static_cast<long>(c0) * ldk + c1, 1, ldk, f.np - c1, c1 - c0),
@@ -575,7 +584,8 @@ hipError_t transposed_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, lo
       RAD_GEMM(u, true);
     }
   }
-  // the second pass reads every panel of Z, so the copies must have landed
+  // the second pass starts from the last panel's product where it is, and
+  // reads the other panels of Z, so the copies must have landed
   e = ps.join();
   if (e != hipSuccess) return e;
   // L^T Lambda = Z: backward over panels (op(V_p) = V_p^T is upper triangular)
@@ -590,19 +600,28 @@ hipError_t transposed_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, lo
                          &a_ready);
       if (e != hipSuccess) return e;
     }
-    e = ps.product(Vp, f.ldw, true, 1, c0, c1 - c0, Y, ldy, wy);
-    if (e != hipSuccess) return e;
-    e = ps.copy_back(c0, c1 - c0, Y, ldy, wy, c0 == 0);
-    if (e != hipSuccess) return e;
+    const T* prod = Y + static_cast<long>(c0) * ldy;
+    long ldp = ldy;
+    if (c0 == last_c0) {
+      e = ps.product(Vp, f.ldw, true, 1, c1 - c0, ps.cur, lds, Y + static_cast<long>(c0) * ldy, ldy, wy);
+      if (e != hipSuccess) return e;
+    } else {
+      e = ps.product(Vp, f.ldw, true, 1, c0, c1 - c0, Y, ldy, wy);
+      if (e != hipSuccess) return e;
+      e = ps.copy_back(c0, c1 - c0, Y, ldy, wy);
+      if (e != hipSuccess) return e;
+      prod = ps.cur;
+      ldp = lds;
+    }
     if (c0 > 0 && ew) {
       if constexpr (std::is_same<T, double>::value) {
         e = emu_sweep_update(*ew, emu_operand(f.kf + static_cast<long>(c0) * ldk, 1, ldk, c0, c1 - c0), false,
-                             a_ready, emu_operand(ps.cur, 1, lds, wy, c1 - c0), c0, wy, Y, ldy, ps);
+                             a_ready, emu_operand(prod, 1, ldp, wy, c1 - c0), c0, wy, Y, ldy, ps);
         if (e != hipSuccess) return e;
       }
     } else if (c0 > 0) {  // rows above the panel: (X_{panel, 0..c0})^T Lambda_panel
       GemmArgs<T> u = update_args<T>(f.kf + static_cast<long>(c0) * ldk, ldk, c0, c1 - c0);
-      gemm_add_segment<T>(u, ps.cur, lds, Y, ldy, wy);
+      gemm_add_segment<T>(u, prod, ldp, Y, ldy, wy);
       RAD_GEMM(u, true);
     }
   }
@@ -720,9 +739,7 @@ extern "C" int32_t rad_gebhart_ref(const double* F, int64_t n, int64_t ldf, cons
               "rad_gebhart_ref: workspace too small or not 256-byte aligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int ni = static_cast<int>(n);
-  hipLaunchKernelGGL(scalars_init, dim3(1), dim3(64), 0, s, w.sc);
-  hipLaunchKernelGGL(check_optical, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s,
-                     eps, rho, ni, w.sc);
+  hipLaunchKernelGGL(check_optical, dim3(1), dim3(1024), 0, s, eps, rho, ni, w.sc);
   int ir_steps = 0;
   Scalars h{};
   if (precision != RAD_PREC_FP32_IR) {
@@ -732,8 +749,9 @@ extern "C" int32_t rad_gebhart_ref(const double* F, int64_t n, int64_t ldf, cons
     hipLaunchKernelGGL(geb_form<double>, dim3(f.np), dim3(256), 0, s, F, static_cast<long>(ldf), ni, eps,
                        rho, f.kf, f.ldk, f.np, Y, w.ldy, w.sc);
     RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, ni + 1, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
-    RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, ni + 1, static_cast<double*>(w.scr), w.ldy, s, ew));
-    hipLaunchKernelGGL((copy_block<double, double>), dim3(ni), dim3(256), 0, s, Y, w.ldy, ni, B,
+    const double* top = nullptr;
+    RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, ni + 1, static_cast<double*>(w.scr), w.ldy, s, ew, &top));
+    hipLaunchKernelGGL(copy_solution<double>, dim3(ni), dim3(256), 0, s, top, w.ldy, Y, w.ldy, ni, B,
                        static_cast<long>(ldb));
   } else {
     Fact<float> f = make_fact<float>(factors, factor_layout<float>(n));
@@ -827,8 +845,9 @@ extern "C" int32_t rad_steady_temperature(const double* Y, int64_t n, int64_t ld
   hipLaunchKernelGGL(ss_form, dim3(f.np), dim3(256), 0, s, Y, static_cast<long>(ldy), ni, weight, Q,
                      static_cast<long>(ldq), mi, t_fixed, xs, sigma, f.kf, f.ldk, f.np, X, w.ldy, w.sc);
   RAD_HIP_CHECK(factor_forward<double>(f, X, w.ldy, mi, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
-  RAD_HIP_CHECK(back_solve<double>(f, X, w.ldy, mi, static_cast<double*>(w.scr), w.ldy, s, ew));
-  hipLaunchKernelGGL(ss_output, dim3(static_cast<unsigned>(ceil_div(n * m, 256))), dim3(256), 0, s, X, w.ldy, ni,
+  const double* top = nullptr;
+  RAD_HIP_CHECK(back_solve<double>(f, X, w.ldy, mi, static_cast<double*>(w.scr), w.ldy, s, ew, &top));
+  hipLaunchKernelGGL(ss_output, dim3(static_cast<unsigned>(ceil_div(n * m, 256))), dim3(256), 0, s, top, w.ldy, X, w.ldy, ni,
                      mi, t_fixed, T, static_cast<long>(ldt), w.sc);
   RAD_HIP_CHECK(hipGetLastError());
   if (!stats) return RAD_OK;

@@ -109,12 +109,33 @@ __global__ void scalars_init_partial(Scalars* sc) {
   }
 }
 
-__global__ void check_optical(const double* __restrict__ eps, const double* __restrict__ rho,
-                              int n, Scalars* sc) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double e = eps ? eps[i] : 0.5, r = rho[i];
-  if (!(e >= 0.0 && e <= 1.0 && r >= 0.0 && r <= 1.0)) raise_status(&sc->status, RAD_ENONFINITE);
+// the same reset, then the range checks of a call's optical properties (one
+// workgroup; the reset is at the level where the checks' atomics act)
+__global__ void __launch_bounds__(1024)
+check_optical(const double* __restrict__ eps, const double* __restrict__ rho, int n, Scalars* sc) {
+  if (threadIdx.x == 0) {
+    agent_store(&sc->status, 0);
+    sc->arrivals = 0;
+    sc->max_r = 0.0;
+    sc->max_d = 0.0;
+    sc->red[0] = sc->red[1] = 0.0;
+    __builtin_amdgcn_s_waitcnt(0);
+  }
+  __syncthreads();
+  constexpr int U = 4;
+  bool bad = false;
+  for (int i0 = threadIdx.x; i0 < n; i0 += 1024 * U) {
+    double e[U], r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + 1024 * u, n - 1);
+      e[u] = eps ? eps[i] : 0.5;
+      r[u] = rho[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) bad |= !(e[u] >= 0.0 && e[u] <= 1.0 && r[u] >= 0.0 && r[u] <= 1.0);
+  }
+  if (bad) raise_status(&sc->status, RAD_ENONFINITE);
 }
 
 // K (padded with identity) and E (padded with zeros) in precision T.
@@ -223,7 +244,8 @@ ss_form(const double* __restrict__ Y, long ldy, int n, const double* __restrict_
 // T = x^(1/4) for free nodes (x <= 0: no real temperature balances the
 // given heat input, reported as RAD_ENONFINITE), the prescribed T otherwise.
 __global__ void __launch_bounds__(256)
-ss_output(const double* __restrict__ X, long ldx, int n, int m, const double* __restrict__ tfix,
+ss_output(const double* __restrict__ top, long ldtop, const double* __restrict__ X, long ldx, int n, int m,
+          const double* __restrict__ tfix,
           double* __restrict__ T, long ldt, Scalars* sc) {
   const long q = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (q >= static_cast<long>(n) * m) return;
@@ -231,7 +253,7 @@ ss_output(const double* __restrict__ X, long ldx, int n, int m, const double* __
   const double tf = tfix ? tfix[i] : 0.0;
   double out = tf;
   if (!(tf > 0.0)) {
-    const double x = X[static_cast<long>(i) * ldx + c];
+    const double x = i < NB2 ? top[static_cast<long>(i) * ldtop + c] : X[static_cast<long>(i) * ldx + c];
     if (x > 0.0 && x <= 1.0e300) {
       out = sqrt(sqrt(x));
     } else {
@@ -1021,10 +1043,6 @@ __device__ __forceinline__ void tri_init_block(const TriJob<T>& j, int b) {
   const int rl = k * NB % NB2;
   const long diag = (static_cast<long>(k * NB / NB2) * NB2 + rl) * j.ldw + rl;
   T* W = j.W + diag;
-  for (int e = threadIdx.x; e < NB * NB / TRI_STRIPS; e += 256) {
-    const int i = NB / TRI_STRIPS * (b % TRI_STRIPS) + e / NB, c = e % NB;
-    j.V[diag + static_cast<long>(i) * j.ldw + c] = i == c ? T(1) : T(0);
-  }
   // this wave's rows of T, A21 and I2, and the strips of I1 and I2
   T ft[KK], fa[KK], fi[KK], s1[KK], s2[KK];
 #pragma unroll
@@ -1068,6 +1086,10 @@ __device__ __forceinline__ void tri_init_block(const TriJob<T>& j, int b) {
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) i1 = Mfma<T>::mma(-ft[kk], x[4 * kk + lg][li], i1);
   put(0, 0, i1);
+  for (int e = threadIdx.x; e < NB * NB / TRI_STRIPS; e += 256) {
+    const int i = NB / TRI_STRIPS * (b % TRI_STRIPS) + e / NB, c = e % NB;
+    j.V[diag + static_cast<long>(i) * j.ldw + c] = i == c ? T(1) : T(0);
+  }
 }
 
 template <class T>
@@ -1281,9 +1303,8 @@ copy_rows(const T* __restrict__ src, long lds, T* __restrict__ dst, long ldd, in
 
 // dst (D, rows < n, cols <= n) <- src (S)
 template <class S, class D>
-__global__ void __launch_bounds__(256)
-copy_block(const S* __restrict__ src, long lds, int n, D* __restrict__ dst, long ldd) {
-  const int i = blockIdx.x;
+__device__ __forceinline__ void copy_block_row(const S* __restrict__ src, long lds, int n, D* __restrict__ dst,
+                                               long ldd, int i) {
   for (int j0 = threadIdx.x; j0 <= n; j0 += 8 * blockDim.x) {  // eight loads per thread in flight
     S v[8];
 #pragma unroll
@@ -1294,6 +1315,19 @@ copy_block(const S* __restrict__ src, long lds, int n, D* __restrict__ dst, long
       if (j <= n) dst[static_cast<long>(i) * ldd + j] = static_cast<D>(v[u]);
     }
   }
+}
+template <class S, class D>
+__global__ void __launch_bounds__(256)
+copy_block(const S* __restrict__ src, long lds, int n, D* __restrict__ dst, long ldd) {
+  copy_block_row(src, lds, n, dst, ldd, blockIdx.x);
+}
+// the same of a solution whose first NB2 rows are still in the last product's scratch panel
+template <class T>
+__global__ void __launch_bounds__(256)
+copy_solution(const T* __restrict__ top, long ldt, const T* __restrict__ src, long lds, int n, double* __restrict__ dst,
+              long ldd) {
+  const int i = blockIdx.x;
+  copy_block_row(i < NB2 ? top : src, i < NB2 ? ldt : lds, n, dst, ldd, i);
 }
 
 // max of v over a 256-thread block, merged into *target with one atomic per
