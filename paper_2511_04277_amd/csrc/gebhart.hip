@@ -505,10 +505,13 @@ hipError_t emu_sweep_update(const EmuWork& ew, const EmuOperand& oa, bool akc, b
 
 // Y <- U^{-1} Y in place (all np rows; padded rows stay zero): per panel from
 // the last, Y_p <- W_p Y_p, then the rows above take the panel's contribution
-// in one K = panel-width product.
+// in one K = panel-width product.  With out (n rows) the products go there
+// instead of into Y; with top the last product, of the first NB2 rows, stays in
+// the scratch panel *top.
 template <class T>
 hipError_t back_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, long lds, hipStream_t s,
-                      const EmuWork* ew = nullptr, const T** top = nullptr) {
+                      const EmuWork* ew = nullptr, const T** top = nullptr, T* out = nullptr, long ldo = 0,
+                      int n = 0) {
   const long ldk = f.ldk;
   PanelSweep<T> ps;
   hipError_t e = ps.init(scr, lds, s);
@@ -526,7 +529,7 @@ hipError_t back_solve(const Fact<T>& f, T* Y, long ldy, int wy, T* scr, long lds
     e = ps.product(Wp, f.ldw, false, 1, c0, c1 - c0, Y, ldy, wy);
     if (e != hipSuccess) return e;
     if (c0 > 0 || !top) {
-      e = ps.copy_back(c0, c1 - c0, Y, ldy, wy);
+      e = out ? ps.copy_back(c0, std::min(c1, n) - c0, out, ldo, wy) : ps.copy_back(c0, c1 - c0, Y, ldy, wy);
       if (e != hipSuccess) return e;
     }
     if (c0 > 0 && ew) {
@@ -749,10 +752,8 @@ extern "C" int32_t rad_gebhart_ref(const double* F, int64_t n, int64_t ldf, cons
     hipLaunchKernelGGL(geb_form<double>, dim3(f.np), dim3(256), 0, s, F, static_cast<long>(ldf), ni, eps,
                        rho, f.kf, f.ldk, f.np, Y, w.ldy, w.sc);
     RAD_HIP_CHECK(factor_forward<double>(f, Y, w.ldy, ni + 1, w.sc, static_cast<double*>(w.scr), w.ldt, s, ew));
-    const double* top = nullptr;
-    RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, ni + 1, static_cast<double*>(w.scr), w.ldy, s, ew, &top));
-    hipLaunchKernelGGL(copy_solution<double>, dim3(ni), dim3(256), 0, s, top, w.ldy, Y, w.ldy, ni, B,
-                       static_cast<long>(ldb));
+    RAD_HIP_CHECK(back_solve<double>(f, Y, w.ldy, ni + 1, static_cast<double*>(w.scr), w.ldy, s, ew, nullptr, B,
+                                     static_cast<long>(ldb), ni));
   } else {
     Fact<float> f = make_fact<float>(factors, factor_layout<float>(n));
     float* Y = static_cast<float*>(w.y);

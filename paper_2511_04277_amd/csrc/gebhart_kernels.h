@@ -1303,8 +1303,9 @@ copy_rows(const T* __restrict__ src, long lds, T* __restrict__ dst, long ldd, in
 
 // dst (D, rows < n, cols <= n) <- src (S)
 template <class S, class D>
-__device__ __forceinline__ void copy_block_row(const S* __restrict__ src, long lds, int n, D* __restrict__ dst,
-                                               long ldd, int i) {
+__global__ void __launch_bounds__(256)
+copy_block(const S* __restrict__ src, long lds, int n, D* __restrict__ dst, long ldd) {
+  const int i = blockIdx.x;
   for (int j0 = threadIdx.x; j0 <= n; j0 += 8 * blockDim.x) {  // eight loads per thread in flight
     S v[8];
 #pragma unroll
@@ -1316,20 +1317,6 @@ __device__ __forceinline__ void copy_block_row(const S* __restrict__ src, long l
     }
   }
 }
-template <class S, class D>
-__global__ void __launch_bounds__(256)
-copy_block(const S* __restrict__ src, long lds, int n, D* __restrict__ dst, long ldd) {
-  copy_block_row(src, lds, n, dst, ldd, blockIdx.x);
-}
-// the same of a solution whose first NB2 rows are still in the last product's scratch panel
-template <class T>
-__global__ void __launch_bounds__(256)
-copy_solution(const T* __restrict__ top, long ldt, const T* __restrict__ src, long lds, int n, double* __restrict__ dst,
-              long ldd) {
-  const int i = blockIdx.x;
-  copy_block_row(i < NB2 ? top : src, i < NB2 ? ldt : lds, n, dst, ldd, i);
-}
-
 // max of v over a 256-thread block, merged into *target with one atomic per
 // block (every thread of the block must call it)
 __device__ inline void block_max(double v, double* target) {
