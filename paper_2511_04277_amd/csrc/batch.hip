@@ -117,7 +117,14 @@ b_copy_jobs(const CopyJob<T>* __restrict__ jobs, const long* __restrict__ start,
   const int q = find_segment(start, count, blockIdx.x);
   const CopyJob<T> j = jobs[q];
   const long i = blockIdx.x - start[q];
-  for (int c = threadIdx.x; c < j.cols; c += blockDim.x) j.dst[i * j.ldd + c] = j.src[i * j.lds + c];
+  for (int c0 = threadIdx.x; c0 < j.cols; c0 += 8 * 256) {  // eight loads of a thread in flight
+    T v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = j.src[i * j.lds + min(c0 + 256 * u, j.cols - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (c0 + 256 * u < j.cols) j.dst[i * j.ldd + c0 + 256 * u] = v[u];
+  }
 }
 
 // the L blocks of one step of many problems: start[q] = first workgroup of job q
@@ -670,8 +677,15 @@ struct Sched {
         a.tri = 1;
         gemm_add_segment<T>(a, y(q) + static_cast<long>(c0) * o.ldy, o.ldy, scr(q), o.ldy, o.n + 1);
         g.push_back(a);
-        cj.push_back(CopyJob<T>{scr(q), o.ldy, y(q) + static_cast<long>(c0) * o.ldy, o.ldy, o.n + 1});
-        rs.push_back(rs.back() + L);
+        if constexpr (std::is_same<T, double>::value) {  // nothing reads the solution before the result
+          const rad_instance& in = P->inst[o.inst];
+          const long ldb = static_cast<long>(in.ldb[o.band]);
+          cj.push_back(CopyJob<T>{scr(q), o.ldy, in.B[o.band] + c0 * ldb, ldb, o.n + 1});
+          rs.push_back(rs.back() + std::min(L, o.n - c0));
+        } else {
+          cj.push_back(CopyJob<T>{scr(q), o.ldy, y(q) + static_cast<long>(c0) * o.ldy, o.ldy, o.n + 1});
+          rs.push_back(rs.back() + L);
+        }
       }
       emit_gemm(P->back, g, false);
       if (!cj.empty()) emit_rows(P->back, L_COPY, tb->add(cj.data(), cj.size()), rs, static_cast<int>(cj.size()));
@@ -686,8 +700,7 @@ struct Sched {
             if (pan <= 0) continue;
             const int c0 = pan * NB2, c1 = std::min(c0 + NB2, o.np), K = c1 - c0;
             const EmuOperand oa{{kf(q) + c0, nullptr}, {o.ldk, 0}, {1, 0}, c0, c0, K};
-            const EmuOperand ob{{y(q) + static_cast<long>(c0) * o.ldy, nullptr}, {1, 0}, {o.ldy, 0}, o.n + 1,
-                                o.n + 1, K};
+            const EmuOperand ob{{scr(q), nullptr}, {1, 0}, {o.ldy, 0}, o.n + 1, o.n + 1, K};
             const EmuJob ja = emu_job(oa, true, q), jb = emu_job(ob, false, q);
             kc.push_back(ja);
             rc.push_back(jb);
@@ -705,7 +718,7 @@ struct Sched {
         if (pan <= 0) continue;
         const int c0 = pan * NB2, c1 = std::min(c0 + NB2, o.np);
         GemmArgs<T> a = gemm_args<T>(kf(q) + c0, o.ldk, c0, c1 - c0, T(-1), T(1));
-        gemm_add_segment<T>(a, y(q) + static_cast<long>(c0) * o.ldy, o.ldy, y(q), o.ldy, o.n + 1);
+        gemm_add_segment<T>(a, scr(q), o.ldy, y(q), o.ldy, o.n + 1);
         g.push_back(a);
       }
       emit_gemm(P->back, g, false);
@@ -1145,7 +1158,6 @@ extern "C" int32_t rad_batch_run(const rad_batch_plan* P, void* work, double enf
     hipLaunchKernelGGL(b_form<double>, dim3(npr), dim3(256), 0, s, pd, nprow, Q);
     RAD_HIP_CHECK(run_launches<double>(P->factor, tables, s));
     RAD_HIP_CHECK(run_launches<double>(P->back, tables, s));
-    hipLaunchKernelGGL(b_copy<double>, dim3(nr), dim3(256), 0, s, pd, nrow, Q, 0);
   } else {
     hipLaunchKernelGGL(b_form<float>, dim3(npr), dim3(256), 0, s, pd, nprow, Q);
     RAD_HIP_CHECK(run_launches<float>(P->factor, tables, s));
