@@ -566,20 +566,19 @@ struct Sched {
   // K = panel-width update below it; with_k = false updates Y only
   void rows_and_outer(std::vector<rad_batch_plan::Launch>& out, int pan, bool with_k) {
     std::vector<GemmArgs<T>> g;
-    for (int kk = 0; kk + 1 < NB2 / NB; ++kk) {
+    for (int k = 1; k < NB2 / NB; ++k) {
       for (int q = 0; q < P->nprob; ++q) {
         const auto& o = P->po[q];
         const int c0 = pan * NB2;
         if (c0 >= o.np) continue;
-        const int c1 = std::min(c0 + NB2, o.np), k0 = c0 + kk * NB, r1 = k0 + NB;
-        if (r1 >= c1) continue;
-        GemmArgs<T> a =
-            gemm_args<T>(kf(q) + static_cast<long>(r1) * o.ldk + k0, o.ldk, c1 - r1, NB, T(-1), T(1));
+        const int c1 = std::min(c0 + NB2, o.np), nb = (c1 - c0) / NB;
+        if (k >= nb) continue;
+        const ForwardStep st = forward_step(k, nb);
+        const long r = c0 + st.row, c = c0 + st.col;
+        GemmArgs<T> a = gemm_args<T>(kf(q) + r * o.ldk + c, o.ldk, st.rows, st.cols, T(-1), T(1));
         if (with_k && c1 < o.np)
-          gemm_add_segment<T>(a, kf(q) + static_cast<long>(k0) * o.ldk + c1, o.ldk,
-                              kf(q) + static_cast<long>(r1) * o.ldk + c1, o.ldk, o.np - c1);
-        gemm_add_segment<T>(a, y(q) + static_cast<long>(k0) * o.ldy, o.ldy, y(q) + static_cast<long>(r1) * o.ldy,
-                            o.ldy, o.n + 1);
+          gemm_add_segment<T>(a, kf(q) + c * o.ldk + c1, o.ldk, kf(q) + r * o.ldk + c1, o.ldk, o.np - c1);
+        gemm_add_segment<T>(a, y(q) + c * o.ldy, o.ldy, y(q) + r * o.ldy, o.ldy, o.n + 1);
         g.push_back(a);
       }
       emit_gemm(out, g, false);

@@ -294,10 +294,11 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
         e = stream_wait(s2, s, ss->ev[0]);
         if (e != hipSuccess) return e;
       }
-      for (int k0 = c0; Y && k0 + NB < c1; k0 += NB) {
-        const int r1 = k0 + NB;
-        GemmArgs<T> u = update_args<T>(kf + static_cast<long>(r1) * ldk + k0, ldk, c1 - r1, NB);
-        gemm_add_segment<T>(u, Y + static_cast<long>(k0) * ldy, ldy, Y + static_cast<long>(r1) * ldy, ldy, wy);
+      for (int k = 1; Y && k < (c1 - c0) / NB; ++k) {
+        const ForwardStep st = forward_step(k, (c1 - c0) / NB);
+        const long r = c0 + st.row, c = c0 + st.col;
+        GemmArgs<T> u = update_args<T>(kf + r * ldk + c, ldk, st.rows, st.cols);
+        gemm_add_segment<T>(u, Y + c * ldy, ldy, Y + r * ldy, ldy, wy);
         e = launch_gemm(u, false, s2);
         if (e != hipSuccess) return e;
       }
@@ -310,12 +311,12 @@ hipError_t factor_forward(const Fact<T>& f, T* Y, long ldy, int wy, Scalars* sc,
       if (e != hipSuccess) return e;
     }
     // (2) the panel's rows to the right of the panel: block forward substitution
-    for (int k0 = c0; k0 + NB < c1; k0 += NB) {
-      const int r1 = k0 + NB;
-      GemmArgs<T> u = update_args<T>(kf + static_cast<long>(r1) * ldk + k0, ldk, c1 - r1, NB);
-      gemm_add_segment<T>(u, kf + static_cast<long>(k0) * ldk + c1, ldk, kf + static_cast<long>(r1) * ldk + c1,
-                          ldk, f.np - c1);
-      if (Y) gemm_add_segment<T>(u, Y + static_cast<long>(k0) * ldy, ldy, Y + static_cast<long>(r1) * ldy, ldy, wy);
+    for (int k = 1; k < (c1 - c0) / NB; ++k) {
+      const ForwardStep st = forward_step(k, (c1 - c0) / NB);
+      const long r = c0 + st.row, c = c0 + st.col;
+      GemmArgs<T> u = update_args<T>(kf + r * ldk + c, ldk, st.rows, st.cols);
+      gemm_add_segment<T>(u, kf + c * ldk + c1, ldk, kf + r * ldk + c1, ldk, f.np - c1);
+      if (Y) gemm_add_segment<T>(u, Y + c * ldy, ldy, Y + r * ldy, ldy, wy);
       RAD_GEMM(u, false);
     }
     // the rest of the previous panel's far update must be done before the
@@ -395,10 +396,11 @@ hipError_t forward_only(const Fact<T>& f, T* Y, long ldy, int wy, hipStream_t s)
   const long ldk = f.ldk;
   for (int c0 = 0; c0 < f.np; c0 += NB2) {
     const int c1 = std::min(c0 + NB2, f.np);
-    for (int k0 = c0; k0 + NB < c1; k0 += NB) {
-      const int r1 = k0 + NB;
-      GemmArgs<T> u = update_args<T>(f.kf + static_cast<long>(r1) * ldk + k0, ldk, c1 - r1, NB);
-      gemm_add_segment<T>(u, Y + static_cast<long>(k0) * ldy, ldy, Y + static_cast<long>(r1) * ldy, ldy, wy);
+    for (int k = 1; k < (c1 - c0) / NB; ++k) {
+      const ForwardStep st = forward_step(k, (c1 - c0) / NB);
+      const long r = c0 + st.row, c = c0 + st.col;
+      GemmArgs<T> u = update_args<T>(f.kf + r * ldk + c, ldk, st.rows, st.cols);
+      gemm_add_segment<T>(u, Y + c * ldy, ldy, Y + r * ldy, ldy, wy);
       RAD_GEMM(u, false);
     }
     if (c1 < f.np) {

@@ -55,6 +55,20 @@ inline size_t tri_tmp_elems(int P2, long pad) { return static_cast<size_t>(P2) *
 // right-hand-side buffers: columns padded to a multiple of 128 plus 128 bytes
 inline long rhs_ld(int64_t n, long pad) { return static_cast<long>(ceil_div(n + 1, 128) * 128 + pad); }
 
+// Block forward substitution over a panel's nb diagonal blocks, step k = 1 ..
+// nb - 1: with p the largest power of two that divides k, the p block rows from
+// k on take the p blocks before k.  Every block row meets all blocks above it, in
+// products of K = p NB: as many as with one block at a time, but half the block
+// rows are read and written (12 for 28 of a whole panel), which is what a wide
+// product with K = NB is bound by.
+struct ForwardStep {
+  int row, rows, col, cols;  // rows [row, row + rows) -= L[rows][col, col + cols) times rows [col, col + cols)
+};
+inline ForwardStep forward_step(int k, int nb) {
+  const int p = k & -k;
+  return ForwardStep{k * NB, std::min(p, nb - k) * NB, (k - p) * NB, p * NB};
+}
+
 struct Scalars {
   int status;
   int arrivals;      // corner tiles of update_invert launches (a multiple of their number between them)
