@@ -3,8 +3,11 @@
 //
 //   csr_rank, csr_offsets, csr_scatter: stable counting sort of the group map
 //               into member lists (each group's members in increasing index
-//               order), so every later sum runs in a fixed order.
-//   agg_reduce: workgroup = (row group G, chunk of 256 column groups H); each
+//               order), so every later sum runs in a fixed order (csr_small:
+//               in one launch for small maps).
+//   agg_reduce_lds: workgroup = row group G; member rows staged in LDS, each
+//               thread owns output columns (the same sums as agg_reduce).
+//   agg_reduce: for rows beyond the LDS; workgroup = (row group G, chunk of 256 column groups H); each
 //               thread owns one output Y_GH and sums w_i X_ij over i in G,
 //               j in H in member order, then divides by W_G.
 #include <algorithm>

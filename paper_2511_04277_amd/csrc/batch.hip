@@ -1,21 +1,23 @@
 // Batched radiative pipeline: many open models of uneven size, one or two
 // spectral bands each, enforced and solved together.
 //
-// Enforcement (thesis Sec. 3.5.5) runs all instances in the same grids: the
-// tile pairs, row blocks and rows of every instance are concatenated and each
-// block finds its instance by a binary search over prefix sums; per-instance
-// device flags stop converged instances without host synchronisation.
+// Enforcement (thesis Sec. 3.5.5): the instances that fit the chip together run
+// all their iterations in one cooperative launch per group, with F on chip; the
+// others, and everything in a captured run, share grids of one launch per step,
+// in which the tile pairs, row blocks and rows of every instance are
+// concatenated and a block finds its instance through a map or by a binary
+// search over prefix sums.  Per-instance device flags stop converged instances
+// without host synchronisation.
 //
 // The Gebhart solves (App. B.2) of all (instance, band) problems advance in
 // lockstep through the same two-level block LDU schedule as the single solve;
 // at every schedule step one grouped launch carries the diagonal-block
-// inverses, or the MFMA GEMM tiles, of every problem that has that step.
-// The grouped GEMM is persistent: its grid is capped near the number of
-// resident workgroups and each workgroup walks the tile list.
+// inverses, the L blocks or the MFMA GEMM tiles of every problem that has that
+// step.
 //
 // rad_batch_prepare builds the schedule and uploads its descriptor tables
-// once; rad_batch_run only launches kernels, so it can be captured in a HIP
-// graph and replayed.
+// once; rad_batch_run only launches kernels (plain ones under capture), so it can
+// be captured in a HIP graph and replayed.
 #include <cstring>
 #include <vector>
 

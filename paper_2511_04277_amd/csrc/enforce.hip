@@ -16,6 +16,9 @@
 //   decide   : convergence flag and statistics (device-side, no host sync),
 //              by the finalize block that finishes last.
 // The last closure scale is applied by a final streaming pass.
+// Models whose tile pairs the chip holds at once run all iterations in one
+// launch with F in registers (enf_single up to 64 faces, enf_resident up to 2432
+// on 256 CUs), with the same arithmetic; larger ones, and captured calls, stream.
 #include "enforce_kernels.h"
 
 #include <algorithm>

@@ -7,7 +7,8 @@
 // so block Gaussian elimination needs no pivoting and every Schur complement
 // stays dominant.  The factorization is a block LDU with 128 x 128 blocks that
 // never splits a diagonal block:  for block k,
-//   D_k^{-1}        Gauss-Jordan inverse of the diagonal block (one workgroup)
+//   D_k^{-1}        in the form that products with it need (Gauss-Jordan on its
+//                   halves, one workgroup)
 //   X  = A21 D^{-1} (block column of L, in place)
 //   A22 -= X A12,   Y2 -= X Y1    (trailing matrix and the n+1 right-hand sides)
 // so K = L U with L block-unit-lower (blocks X) and U block-upper (diagonal

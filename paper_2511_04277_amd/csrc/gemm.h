@@ -7,8 +7,10 @@
 // own base pointers (used to update a factor matrix and its right-hand sides
 // in one launch).
 //
-// Tiling: a 256-thread workgroup computes a 128 x 128 tile; each of its four
-// waves owns 64 x 64 = 4 x 4 blocks of v_mfma_{f64,f32}_16x16x4.
+// Tiling: a 256-thread workgroup computes a 128 x 128, 64 x 64 or 32 x 32 tile;
+// its four waves own a quarter each, in 16 x 16 blocks of
+// v_mfma_{f64,f32}_16x16x4.  Every tile shape accumulates an output in the same
+// order.  Products with at most 16 columns split K over a workgroup's waves.
 #pragma once
 
 #include <hip/hip_runtime.h>
