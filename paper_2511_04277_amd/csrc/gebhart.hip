@@ -1079,14 +1079,14 @@ extern "C" int32_t rad_gebhart_ref_adjoint(const void* factors, size_t fbytes, i
     hipLaunchKernelGGL((copy_block<double, double>), dim3(ni), dim3(256), 0, s, lam, ldlam, ni, Lambda,
                        static_cast<long>(ldl));
   const int chunks = static_cast<int>(ceil_div(n, GE_ROWS));
+  // one chunk's sums are the gradient
   hipLaunchKernelGGL(adj_grad_eps_partial, dim3(static_cast<unsigned>(ceil_div(n, 256)), chunks), dim3(256), 0, s,
-                     lam, ldlam, F, static_cast<long>(ldf), ni, w.part);
-  hipLaunchKernelGGL(adj_grad_eps_final, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, w.part,
-                     ni, chunks, grad_eps);
-  hipLaunchKernelGGL(adj_grad_rho, dim3(static_cast<unsigned>(ceil_div(n, 4))), dim3(256), 0, s, lam, ldlam,
-                     G, static_cast<long>(ldg), B, static_cast<long>(ldb), rho, ni, grad_rho);
-  hipLaunchKernelGGL(adj_grad_rho_direct, dim3(ni), dim3(256), 0, s, lam, ldlam, F, static_cast<long>(ldf),
-                     B, static_cast<long>(ldb), rho, ni, grad_rho);
+                     lam, ldlam, F, static_cast<long>(ldf), ni, chunks == 1 ? grad_eps : w.part);
+  if (chunks > 1)
+    hipLaunchKernelGGL(adj_grad_eps_final, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, w.part,
+                       ni, chunks, grad_eps);
+  hipLaunchKernelGGL(adj_grad_rho, dim3(ni), dim3(256), 0, s, lam, ldlam, F, static_cast<long>(ldf), G,
+                     static_cast<long>(ldg), B, static_cast<long>(ldb), rho, ni, grad_rho);
   RAD_HIP_CHECK(hipGetLastError());
   if (!stats) return RAD_OK;
   int rc = read_scalars(w.sc, &h, s);

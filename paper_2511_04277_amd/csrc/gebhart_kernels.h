@@ -1530,7 +1530,19 @@ adj_grad_eps_partial(const double* __restrict__ L, long ldl, const double* __res
   if (k >= n) return;
   const int i0 = c * GE_ROWS, i1 = min(n, i0 + GE_ROWS);
   double s = 0.0;
-  for (int i = i0; i < i1; ++i) s += L[static_cast<long>(i) * ldl + k] * F[static_cast<long>(i) * ldf + k];
+  constexpr int U = 8;  // rows in flight; the sum stays in row order
+  for (int a = i0; a < i1; a += U) {
+    double x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long i = min(a + u, i1 - 1);
+      x[u] = L[i * ldl + k];
+      y[u] = F[i * ldf + k];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (a + u < i1) s += x[u] * y[u];
+  }
   part[static_cast<long>(c) * n + k] = s;
 }
 
@@ -1543,40 +1555,47 @@ adj_grad_eps_final(const double* __restrict__ part, int n, int chunks, double* _
   ge[k] = s;
 }
 
-// grad_rho[k] = (1/rho_k) sum_j B_kj (Lambda_kj - G_kj)   (one wave per row)
+// grad_rho[k] = (1/rho_k) sum_j B_kj (Lambda_kj - G_kj), for small rho_k in the
+// direct form sum_j B_kj sum_i F_ik Lambda_ij; one workgroup per row
 __global__ void __launch_bounds__(256)
-adj_grad_rho(const double* __restrict__ L, long ldl, const double* __restrict__ G, long ldg,
-             const double* __restrict__ B, long ldb, const double* __restrict__ rho, int n,
-             double* __restrict__ gr) {
-  const int k = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int l = threadIdx.x & 63;
-  if (k >= n) return;
-  double s = 0.0;
-  for (int j = l; j <= n; j += 64)
-    s += B[static_cast<long>(k) * ldb + j] *
-         (L[static_cast<long>(k) * ldl + j] - G[static_cast<long>(k) * ldg + j]);
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-  if (l == 0 && rho[k] >= 1e-3) gr[k] = s / rho[k];
-}
-
-// direct form for small rho_k: sum_j B_kj sum_i F_ik Lambda_ij
-__global__ void __launch_bounds__(256)
-adj_grad_rho_direct(const double* __restrict__ L, long ldl, const double* __restrict__ F, long ldf,
-                    const double* __restrict__ B, long ldb, const double* __restrict__ rho, int n,
-                    double* __restrict__ gr) {
+adj_grad_rho(const double* __restrict__ L, long ldl, const double* __restrict__ F, long ldf,
+             const double* __restrict__ G, long ldg, const double* __restrict__ B, long ldb,
+             const double* __restrict__ rho, int n, double* __restrict__ gr) {
   const int k = blockIdx.x;
-  if (rho[k] >= 1e-3) return;
   __shared__ double red[4];
+  const double r = rho[k];
+  const double* bk = B + static_cast<long>(k) * ldb;
   double acc = 0.0;
-  for (int j = threadIdx.x; j <= n; j += blockDim.x) {
-    double t = 0.0;
-    for (int i = 0; i < n; ++i) t += F[static_cast<long>(i) * ldf + k] * L[static_cast<long>(i) * ldl + j];
-    acc += B[static_cast<long>(k) * ldb + j] * t;
+  if (r >= 1e-3) {
+    const double *lk = L + static_cast<long>(k) * ldl, *gk = G + static_cast<long>(k) * ldg;
+    constexpr int U = 4;
+    for (int j0 = threadIdx.x; j0 <= n; j0 += 256 * U) {
+      double x[U], y[U], z[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = min(j0 + 256 * u, n);
+        x[u] = bk[j];
+        y[u] = lk[j];
+        z[u] = gk[j];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + 256 * u <= n) acc += x[u] * (y[u] - z[u]);
+    }
+  } else {
+    for (int j = threadIdx.x; j <= n; j += 256) {
+      double t = 0.0;
+      for (int i = 0; i < n; ++i) t += F[static_cast<long>(i) * ldf + k] * L[static_cast<long>(i) * ldl + j];
+      acc += bk[j] * t;
+    }
   }
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
-  if (threadIdx.x == 0) gr[k] = red[0] + red[1] + red[2] + red[3];
+  if (threadIdx.x == 0) {
+    const double s = red[0] + red[1] + red[2] + red[3];
+    gr[k] = r >= 1e-3 ? s / r : s;
+  }
 }
 
 }  // namespace
