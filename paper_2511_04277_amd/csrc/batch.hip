@@ -180,29 +180,8 @@ b_form(const ProbDesc* __restrict__ pd, const long* __restrict__ start, int coun
   const int q = find_segment(start, count, blockIdx.x);
   const ProbDesc& d = pd[q];
   const int i = static_cast<int>(blockIdx.x - start[q]);
-  const int n = d.n, np = d.np;
-  const double* frow = d.F + static_cast<long>(i) * d.ldf;
-  T* krow = static_cast<T*>(d.kf) + static_cast<long>(i) * d.ldk;
-  T* yrow = static_cast<T*>(d.y) + static_cast<long>(i) * d.ldy;
-  int bad = 0;
-  const long jend = d.ldk > d.ldy ? d.ldk : d.ldy;
-  for (long j = threadIdx.x; j < jend; j += blockDim.x) {
-    double kv = (i == j) ? 1.0 : 0.0;
-    double yv = 0.0;
-    if (i < n && j <= n) {
-      const double f = frow[j];
-      bad |= !(f >= 0.0 && f <= 1.0e300);
-      if (j < n) {
-        kv = kv - f * d.rho[j];
-        yv = f * d.eps[j];
-      } else {
-        yv = f;  // space column: no emissivity factor (eq. B.6)
-      }
-    }
-    if (j < d.ldk) krow[j] = (j < np) ? static_cast<T>(kv) : T(0);
-    if (j < d.ldy) yrow[j] = static_cast<T>(yv);
-  }
-  if (i < n && threadIdx.x == 0) {
+  bool bad = geb_form_row(d.F, d.ldf, d.n, d.eps, d.rho, static_cast<T*>(d.kf), d.ldk, d.np, static_cast<T*>(d.y), d.ldy, i);
+  if (i < d.n && threadIdx.x == 0) {
     const double e = d.eps[i], r = d.rho[i];
     bad |= !(e >= 0.0 && e <= 1.0 && r >= 0.0 && r <= 1.0);
   }

@@ -152,36 +152,56 @@ check_optical(const double* __restrict__ eps, const double* __restrict__ rho, in
   if (bad) raise_status(&sc->status, RAD_ENONFINITE);
 }
 
-// K (padded with identity) and E (padded with zeros) in precision T.
-// Row i of both, one workgroup per row of the padded size.
+// Row i of K (padded with identity) and of E (padded with zeros) in precision
+// T; returns whether the row has a bad entry.  Bound by memory; six columns of a
+// thread are in flight (n = 4096: 111 -> 87 us for 0.4 GB; 8192: 355 us, 4.5 TB/s).
+template <class T>
+__device__ __forceinline__ bool geb_form_row(const double* __restrict__ F, long ldf, int n,
+                                             const double* __restrict__ eps, const double* __restrict__ rho,
+                                             T* __restrict__ KF, long ldk, int np, T* __restrict__ Y, long ldy, int i) {
+  constexpr int U = 6;
+  const double* frow = F + static_cast<long>(min(i, n - 1)) * ldf;
+  T* krow = KF + static_cast<long>(i) * ldk;
+  T* yrow = Y + static_cast<long>(i) * ldy;
+  bool bad = false;
+  const int jend = static_cast<int>(ldk > ldy ? ldk : ldy);
+  for (int j0 = threadIdx.x; j0 < jend; j0 += 256 * U) {
+    double f[U], r[U], e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 256 * u, jr = min(j, n - 1);
+      f[u] = frow[min(j, n)];
+      r[u] = rho[jr];
+      e[u] = eps[jr];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 256 * u;
+      double kv = (i == j) ? 1.0 : 0.0;
+      double yv = 0.0;
+      if (i < n && j <= n) {
+        bad |= !(f[u] >= 0.0 && f[u] <= 1.0e300);
+        if (j < n) {
+          kv = kv - f[u] * r[u];
+          yv = f[u] * e[u];
+        } else {
+          yv = f[u];  // space column: no emissivity factor (eq. B.6)
+        }
+      }
+      if (j < ldk) krow[j] = (j < np) ? static_cast<T>(kv) : T(0);
+      if (j < ldy) yrow[j] = static_cast<T>(yv);
+    }
+  }
+  return bad;
+}
+
+// one workgroup per row of the padded size
 template <class T>
 __global__ void __launch_bounds__(256)
 geb_form(const double* __restrict__ F, long ldf, int n, const double* __restrict__ eps,
          const double* __restrict__ rho, T* __restrict__ KF, long ldk, int np,
          T* __restrict__ Y, long ldy, Scalars* sc) {
-  const int i = blockIdx.x;
-  const double* frow = F + static_cast<long>(i) * ldf;
-  T* krow = KF + static_cast<long>(i) * ldk;
-  T* yrow = Y + static_cast<long>(i) * ldy;
-  int bad = 0;
-  const long jend = ldk > ldy ? ldk : ldy;
-  for (long j = threadIdx.x; j < jend; j += blockDim.x) {
-    double kv = (i == j) ? 1.0 : 0.0;
-    double yv = 0.0;
-    if (i < n && j <= n) {
-      double f = frow[j];
-      bad |= !(f >= 0.0 && f <= 1.0e300);
-      if (j < n) {
-        kv = kv - f * rho[j];
-        yv = f * eps[j];
-      } else {
-        yv = f;  // space column: no emissivity factor (eq. B.6)
-      }
-    }
-    if (j < ldk) krow[j] = (j < np) ? static_cast<T>(kv) : T(0);
-    if (j < ldy) yrow[j] = static_cast<T>(yv);
-  }
-  if (bad) raise_status(&sc->status, RAD_ENONFINITE);
+  if (geb_form_row(F, ldf, n, eps, rho, KF, ldk, np, Y, ldy, blockIdx.x)) raise_status(&sc->status, RAD_ENONFINITE);
 }
 
 // Radiation-only steady balance (eq. 3.12-3.14 with GR_ij = sigma w_i Y_ij,
