@@ -101,39 +101,30 @@ long resident_limit(bool alone) {
 
 // One sweep and one finalize launch per iteration, F streamed through.
 int32_t enforce_streamed(const EnfInst& in, double tol, int32_t max_iter, hipStream_t s) {
+  // tol mode: launch iterations in batches; a converged flag makes the rest
+  // of a batch exit at once, so the stop is exact without a sync per step.
+  const int batch = tol > 0.0 ? 8 : max_iter;
   int launched = 0;
-  auto launch = [&](int count) {
-    for (count = std::min(count, max_iter - launched); count > 0; --count, ++launched) {
+  while (launched < max_iter) {
+    int nb = std::min(batch, max_iter - launched);
+    for (int k = 0; k < nb; ++k) {
+      int it = launched + k;
       {
         ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, 16.0 * static_cast<double>(in.n) * (in.n + 1));
         hipLaunchKernelGGL(enf_sweep, dim3(static_cast<unsigned>(in.pairs)), dim3(ENF_THREADS), 0, s, in,
-                           launched == 0 ? 1 : 0);
+                           it == 0 ? 1 : 0);
       }
       hipLaunchKernelGGL(enf_finalize, dim3(static_cast<unsigned>(fin_blocks(in.n))), dim3(256), 0, s, in, tol);
     }
-  };
-  if (tol > 0.0) {
-    // tol mode: a converged flag makes later iterations exit at once, so the
-    // stop is exact without a sync per step.  The flag is read every eight
-    // iterations, on the side stream as it is after five of them, so the caller's
-    // stream has three to run while the host waits and launches more (a read on
-    // it left the chip idle for about 70 us each: n = 8192 15.0 -> 14.8 ms, 2640 2.1 -> 1.9 ms).
-    SideStream* ss = nullptr;
-    RAD_HIP_CHECK(side_stream(&ss));
-    while (launched < max_iter) {
-      launch(5);
-      if (launched == max_iter) break;
-      RAD_HIP_CHECK(stream_wait(ss->s2, s, ss->ev[0]));
-      launch(3);
-      RAD_HIP_CHECK(hipGetLastError());
+    RAD_HIP_CHECK(hipGetLastError());
+    launched += nb;
+    if (tol > 0.0 && launched < max_iter) {
       int conv = 0, st = 0;
-      RAD_HIP_CHECK(hipMemcpyAsync(&conv, &in.ctrl->converged, sizeof(int), hipMemcpyDeviceToHost, ss->s2));
-      RAD_HIP_CHECK(hipMemcpyAsync(&st, &in.ctrl->status, sizeof(int), hipMemcpyDeviceToHost, ss->s2));
-      RAD_HIP_CHECK(hipStreamSynchronize(ss->s2));
+      RAD_HIP_CHECK(hipMemcpyAsync(&conv, &in.ctrl->converged, sizeof(int), hipMemcpyDeviceToHost, s));
+      RAD_HIP_CHECK(hipMemcpyAsync(&st, &in.ctrl->status, sizeof(int), hipMemcpyDeviceToHost, s));
+      RAD_HIP_CHECK(hipStreamSynchronize(s));
       if (conv || st < 0) break;
     }
-  } else {
-    launch(max_iter);
   }
   hipLaunchKernelGGL(enf_apply_scale, dim3(static_cast<unsigned>(in.n)), dim3(256), 0, s, in);
   RAD_HIP_CHECK(hipGetLastError());
