@@ -726,7 +726,7 @@ size_t elem(int prec) { return prec == RAD_PREC_FP32_IR ? 4 : 8; }
 
 // Instances whose tile pairs fit the chip together form a group: all their
 // iterations are one cooperative launch, F on chip (see enf_resident_tile).
-// An iteration of a group costs 4.5 to 11 us however many of its workgroups are
+// An iteration of a group costs 4.5 to 10 us however many of its workgroups are
 // used; streamed, a batch costs about 10 us an iteration for its two launches
 // and 20 us for every 768 tile pairs.  So the instances that are small enough
 // are packed into as few groups as first fit finds, largest first, and a group

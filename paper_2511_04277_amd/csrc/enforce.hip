@@ -17,7 +17,7 @@
 //              by the finalize block that finishes last.
 // The last closure scale is applied by a final streaming pass.
 // Models whose tile pairs the chip holds at once run all iterations in one
-// launch with F in registers (enf_single up to 64 faces, enf_resident up to 2432
+// launch with F in registers (enf_single up to 64 faces, enf_resident up to 1984
 // on 256 CUs), with the same arithmetic; larger ones, and captured calls, stream.
 #include "enforce_kernels.h"
 
@@ -92,11 +92,11 @@ int32_t enforce_check_args(const char* who, double* F, int64_t n, int64_t ldf, c
 }
 
 // Tile pairs that the current device holds at once, with one workgroup per CU
-// or with as many as fit.
+// or with ENF_RES_PER_CU.
 long resident_limit(bool alone) {
   static std::atomic<long> one[64], all[64];
-  return alone ? resident_workgroups(reinterpret_cast<const void*>(enf_resident<1>), 1, one)
-               : resident_workgroups(reinterpret_cast<const void*>(enf_resident<ENF_RES_PER_CU>), ENF_RES_PER_CU, all);
+  return alone ? resident_workgroups(reinterpret_cast<const void*>(enf_resident_wide), 1, one)
+               : resident_workgroups(reinterpret_cast<const void*>(enf_resident), ENF_RES_PER_CU, all);
 }
 
 // One sweep and one finalize launch per iteration, F streamed through.
@@ -175,8 +175,8 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
       hipLaunchKernelGGL(enf_single, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
     } else {
       void* args[] = {&in, &tol, &max_iter};
-      const void* k = pairs <= resident_limit(true) ? reinterpret_cast<const void*>(enf_resident<1>)
-                                                    : reinterpret_cast<const void*>(enf_resident<ENF_RES_PER_CU>);
+      const void* k = pairs <= resident_limit(true) ? reinterpret_cast<const void*>(enf_resident_wide)
+                                                    : reinterpret_cast<const void*>(enf_resident);
       const hipError_t e = hipLaunchCooperativeKernel(k,
                                                       dim3(static_cast<unsigned>(pairs)), dim3(ENF_THREADS), args, 0, s);
       if (e != hipSuccess) {  // nothing was enqueued: one launch per step instead

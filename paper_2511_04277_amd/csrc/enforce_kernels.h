@@ -29,8 +29,20 @@ struct EnfCtrl {
 // What the workgroups of the resident kernel exchange, in words: row sums
 // (two iterations in turn x row block x column block x 64), closure scales and
 // row blocks' states (four iterations in turn), then three maxima and a counter.
-constexpr int ENF_RES_TILES = 39;  // most 64-row blocks of a resident model
-constexpr int ENF_RES_PER_CU = 3;  // its workgroups per CU: 80 registers and 37 KB of LDS each
+constexpr int ENF_RES_TILES = 31;  // most 64-row blocks of a resident model: 496 tile pairs
+// Workgroups of a resident kernel on a CU, and the waves per SIMD that its
+// registers are held to (72 each).  All its workgroups have to find a place
+// beside whatever other streams run, and the waves that are placed first stay
+// where they were put, between waves that end: registers (512 a SIMD) and LDS
+// come in contiguous pieces of 8 and 1280, so what is free may be in holes.
+// A workgroup's two waves on a SIMD fit beside any one other of its kind: three
+// waves with a hole of less than 72 on either side of each are 3 x 72 + 4 x 64 =
+// 472 < 512 (with 80 registers 3 x 80 + 4 x 72 = 528: not so), and 38 KB of LDS
+// beside another 38 KB anywhere in 160.  A third does not: a CU that ran two
+// workgroups of 152 registers and 70 KB (gemm_lds32 in FP64) keeps two, and a
+// grid that needs a third on some CUs then waits for ever.
+constexpr int ENF_RES_PER_CU = 2;
+constexpr int ENF_RES_WAVES = 7;
 typedef unsigned long long EnfWord;
 __host__ __device__ constexpr long enf_xch_words(long t) { return 2 * t * t * ET + 4 * t * ET + 4 * t + 4; }
 
@@ -114,6 +126,14 @@ __device__ __forceinline__ double kappa_c(double fij, double fji, double ci, dou
   return s > 0.0 ? b * r : 0.5;
 }
 
+// This thread's lane, formed anew: what is made from it stays out of registers
+// until it is needed (made from threadIdx it would be hoisted out of a loop).
+__device__ __forceinline__ int fresh_lane() {
+  unsigned z = 0;
+  __asm__ volatile("" : "+v"(z));
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, z)));
+}
+
 // One iteration of a tile pair held in registers: own tile (I, J) in a, partner
 // tile (J, I) in b (see enf_sweep_tile); rowc holds the rows' constants and the
 // previous closure scale.  put() is called once the new own tile is in a and
@@ -124,15 +144,14 @@ __device__ __forceinline__ double kappa_c(double fij, double fji, double ci, dou
 // MAXIMA: the workgroup's maxima go to sums; otherwise rmax and emax are left
 // per thread.
 template <bool DIAG, bool EDGE, bool HALF, bool WIDE, bool MAXIMA, class Put, class Sums>
-__device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, double (&a)[ERW],
+__device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, int w, double (&a)[ERW],
                                               const double (&b)[ERW], double (*sB)[ETP], double (*rowc)[ET], int& bad,
                                               double& rmax, double& emax, Put put, Sums sums) {
 #pragma clang fp contract(off)
   const int n = in.n;
   const bool half = HALF;
   const int r0 = I * ET, c0 = J * ET;
-  const int tid = threadIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int l = WIDE || MAXIMA ? threadIdx.x & 63 : fresh_lane();
   const int jg = c0 + l;
   const int ig = r0 + l;
   // scaled by the positive finite 1 / s (1 on the first sweep); negative or
@@ -163,11 +182,17 @@ __device__ __forceinline__ void enf_pair_step(const EnfInst& in, int I, int J, d
   double sb = 0.0;
   rmax = emax = 0.0;
   // constants of row c0 + l (the partner's row; on a diagonal tile the own rows)
-  const double aj = rowc[DIAG ? 0 : 4][l], iaj = rowc[DIAG ? 1 : 5][l];
-  const double cj = rowc[DIAG ? 2 : 6][l];
+  double aj = rowc[DIAG ? 0 : 4][l], iaj = rowc[DIAG ? 1 : 5][l];
+  double cj = rowc[DIAG ? 2 : 6][l];
 #pragma unroll
   for (int k = 0; k < ERW; ++k) {
     const int il = w + ENW * k;
+    if (!WIDE && !MAXIMA) {  // read for every pair: no registers to keep them
+      const int lj = fresh_lane();
+      aj = rowc[DIAG ? 0 : 4][lj];
+      iaj = rowc[DIAG ? 1 : 5][lj];
+      cj = rowc[DIAG ? 2 : 6][lj];
+    }
     const double ai = rowc[0][il];
     if (DIAG) {
       if (l == il) {                               // the diagonal keeps its value
@@ -319,7 +344,7 @@ __device__ __forceinline__ void enf_sweep_tile(const EnfInst& in, long pair, int
   __syncthreads();
   double rmax, emax;
   enf_pair_step<DIAG, EDGE, HALF, false, true>(
-      in, I, J, a, b, sB, rowc, bad, rmax, emax,
+      in, I, J, w, a, b, sB, rowc, bad, rmax, emax,
       [&]() {
         // own tile back to F
 #pragma unroll
@@ -558,7 +583,7 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 
 // ---- all iterations in one launch, F on chip ---------------------------------
 // A pair's two tiles fit the registers of its workgroup, so a model whose tile
-// pairs are all resident at once (three workgroups per CU: n <= 2432 on 256
+// pairs are all resident at once (two workgroups per CU: n <= 1984 on 256
 // CUs) is read and written once, and between iterations only row sums travel:
 // a workgroup stores its rows' partial sums, the diagonal workgroup of a row
 // block adds the block's t + 1 sums and stores the closure scales and the
@@ -567,8 +592,8 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 // that all XCDs share, so the data are their own signal: a word holds ENF_EMPTY
 // until its value is stored, and a reader loads until it is not.  Two one-way
 // trips an iteration; with counters that announce the data there were five
-// dependent round trips (n = 1081: 10.5 us an iteration, now 6; n = 1900: 16.5, now 9.0;
-// n = 2304 streamed: 27.7, now 10.4).
+// dependent round trips (n = 1081: 10.5 us an iteration, now 6.1; n = 1900: 16.5, now
+// 9.5; n = 1985 streamed: 21).
 //
 // Buffers are used in turn and emptied by the diagonal workgroup of their row
 // block.  Row sums (two in turn): it empties what it has read at iteration k, and
@@ -580,7 +605,11 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 //
 // Needs a cooperative launch: a workgroup that waits holds its place, and every
 // word that it waits for is stored by a workgroup that is resident too, in the
-// same iteration, whether or not an error was seen.  Same operations in the
+// same iteration, whether or not an error was seen.  Such launches run one after
+// another (four streams with 15 workgroups each take four times as long as
+// one), so a workgroup shares its CU with others of its own launch and with
+// kernels that end by themselves; why every one gets a place beside those is at
+// ENF_RES_PER_CU.  Same operations in the
 // same order as enf_sweep, enf_finalize and enf_apply_scale, so the same bits.
 constexpr EnfWord ENF_NAN = 0x7ff8000000000000ull;    // any NaN that is stored
 constexpr EnfWord ENF_EMPTY = 0x7ff8c0ffee000001ull;  // so no sum or scale is one of these
@@ -602,26 +631,49 @@ __device__ __forceinline__ EnfWord enf_await(const EnfWord* p) {
   return v;
 }
 
+// the maximum over the 16 lanes of a row, by rotations within the row (lane
+// permutations of the vector pipe; through the LDS, six steps of both maxima of a
+// step took 0.45 us of an iteration)
+template <int R>
+__device__ __forceinline__ double max_rotated(double x) {
+  const unsigned long long v = static_cast<unsigned long long>(__double_as_longlong(x));
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, static_cast<unsigned>(v), 0x120 + R, 0xf, 0xf, true);  // row_ror:R
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, static_cast<unsigned>(v >> 32), 0x120 + R, 0xf, 0xf, true);
+  return fmax(x, __longlong_as_double(static_cast<long long>(static_cast<unsigned long long>(hi) << 32 | lo)));
+}
+__device__ __forceinline__ double max_of_16(double x) {
+  return max_rotated<1>(max_rotated<2>(max_rotated<4>(max_rotated<8>(x))));
+}
+
+// What lives on between iterations is here, but for the tiles: the kernel is
+// held to 72 registers.
+struct ResidentShared {
+  double sB[ET][ETP];
+  double rowc[8][ET];   // see enf_pair_step; of a diagonal tile [4]: its own row sums, [5]: the space column,
+                        // [6]: the rows' closure defects
+  double most[2][ENW][4];  // maxima of 16 threads each, of the last iteration
+  int error, dec[2];    // an input error in this workgroup; all row blocks closed, any failed
+};
+
 template <bool DIAG, bool EDGE, bool HALF, bool WIDE>
-__device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int J, double tol, int max_iter,
-                                                  double (*sB)[ETP], double (*rowc)[ET]) {
+__device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int J, int w, double tol, int max_iter,
+                                                  ResidentShared& sh) {
 #pragma clang fp contract(off)
-  __shared__ int error, dec[2];  // an input error in this workgroup; all closed, any failed
+  double(*const sB)[ETP] = sh.sB;
+  double(*const rowc)[ET] = sh.rowc;
   const long ldf = in.ldf;
   const int n = in.n, t = in.t;
   const int r0 = I * ET, c0 = J * ET;
-  const int tid = threadIdx.x;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
-  const int jg = c0 + l, ig = r0 + l;
-  const int jgc = (EDGE && jg >= n) ? n - 1 : jg, igc = (EDGE && ig >= n) ? n - 1 : ig;
+  const int lane = fresh_lane();
+  const int jgc = EDGE ? min(c0 + lane, n - 1) : c0 + lane, igc = EDGE ? min(r0 + lane, n - 1) : r0 + lane;
   EnfWord* const xpart = in.xch;
   EnfWord* const xscale = xpart + 2L * t * t * ET;
   EnfWord* const xstate = xscale + 4L * t * ET;
   EnfWord* const xmax = xstate + 4L * t;
   // slot of row block r, column block c in iteration k
-  auto slot = [&](int k, int r, int c) { return xpart + ((static_cast<long>(k & 1) * t + r) * t + c) * ET + l; };
+  auto slot = [&](int k, int r, int c) { return xpart + ((static_cast<long>(k & 1) * t + r) * t + c) * ET; };
   if (agent_load(&in.ctrl->status) < 0) return;  // a bad area, found by an earlier launch: for every workgroup alike
-  double a[ERW], b[ERW], space = 0.0;
+  double a[ERW], b[ERW];
 #pragma unroll
   for (int k = 0; k < ERW; ++k) {
     const int i = r0 + w + ENW * k;
@@ -632,44 +684,53 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
     const int jr = c0 + w + ENW * k;
     b[k] = DIAG ? 0.0 : row_ld(in.F + static_cast<long>((EDGE && jr >= n) ? n - 1 : jr) * ldf, igc);
   }
-  if (DIAG && w == 0) space = in.F[static_cast<long>(igc) * ldf + n];
-  const int crow = (tid < ET ? r0 : c0) + l, cq = tid < ET ? 0 : 4;  // the row of this thread's constants
+  if (DIAG && w == 0) rowc[5][lane] = in.F[static_cast<long>(igc) * ldf + n];  // the space column's entries
+  const int crow = (w == 0 ? r0 : c0) + lane, cq = w == 0 ? 0 : 4;  // the row of this thread's constants
   const int crc = (EDGE && crow >= n) ? n - 1 : crow;
-  if (tid < (DIAG ? ET : 2 * ET)) {
+  if (w < (DIAG ? 1 : 2)) {
     const double ai = in.area[crc];
-    rowc[cq + 0][l] = ai;
-    rowc[cq + 1][l] = in.inv_area[crc];
-    rowc[cq + 2][l] = HALF ? 0.0 : ai * ai / in.nrays[crc];
-    rowc[cq + 3][l] = 1.0;
+    rowc[cq + 0][lane] = ai;
+    rowc[cq + 1][lane] = in.inv_area[crc];
+    rowc[cq + 2][lane] = HALF ? 0.0 : ai * ai / in.nrays[crc];
+    rowc[cq + 3][lane] = 1.0;
   }
-  if (tid == 0) error = 0;
+  if (w == 0 && lane == 0) sh.error = 0;
   __syncthreads();
   int iters = 0, converged = 0, stop = 0;
-  double rmax = 0.0, emax = 0.0, d = 0.0;
   while (iters < max_iter && !converged) {
     int bad = 0;
+    double rmax, emax;
     enf_pair_step<DIAG, EDGE, HALF, WIDE, false>(
-        in, I, J, a, b, sB, rowc, bad, rmax, emax,
+        in, I, J, w, a, b, sB, rowc, bad, rmax, emax,
         [&]() {
+          const int l = fresh_lane();
           if (!DIAG)
 #pragma unroll
             for (int k = 0; k < ERW; ++k) b[k] = sB[w + ENW * k][l];
-          if (__ballot(bad) != 0 && l == 0) error = 1;
+          if (__ballot(bad) != 0 && l == 0) sh.error = 1;
         },
         [&](double s_own, double s_par) {
+          const int l = fresh_lane(), ig = r0 + l;
           if (DIAG) {
+            const double space = rowc[5][l];
             if (!EDGE || ig < n) bad |= !(space >= 0.0) || !(space <= 1.0e300);
-            space *= rowc[3][l];
-            if (__ballot(bad) != 0 && l == 0) error = 1;
+            if (__ballot(bad) != 0 && l == 0) sh.error = 1;
             rowc[4][l] = s_own;
-            rowc[5][l] = space;
+            rowc[5][l] = space * rowc[3][l];
           } else {
-            const bool e = error != 0;
-            agent_store(slot(iters, I, J), e ? ENF_ERROR : enf_word(s_own));
-            agent_store(slot(iters, J, I), e ? ENF_ERROR : enf_word(s_par));
+            const bool e = sh.error != 0;
+            agent_store(slot(iters, I, J) + l, e ? ENF_ERROR : enf_word(s_own));
+            agent_store(slot(iters, J, I) + l, e ? ENF_ERROR : enf_word(s_par));
           }
         });
     if (bad) raise_status(&in.ctrl->status, RAD_ENONFINITE);
+    const int l = fresh_lane(), ig = r0 + l;
+    rmax = max_of_16(rmax);
+    emax = max_of_16(emax);
+    if (l % 16 == 0) {
+      sh.most[0][w][l / 16] = rmax;
+      sh.most[1][w][l / 16] = emax;
+    }
     if (DIAG) {
       // wave w sums every 8th partial sum of row l, the last one the space column's
       __syncthreads();
@@ -684,7 +745,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
           const int c = w + ENW * u;
-          v[u] = c < t && c != I ? agent_load(slot(iters, I, c)) : 0;
+          v[u] = c < t && c != I ? agent_load(slot(iters, I, c) + l) : 0;
           wait |= v[u] == ENF_EMPTY;
         }
       } while (__ballot(wait) != 0);
@@ -692,21 +753,22 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
         const int c = w + ENW * u;
-        if (c < t && c != I) agent_store(slot(iters, I, c), ENF_EMPTY);
+        if (c < t && c != I) agent_store(slot(iters, I, c) + l, ENF_EMPTY);
         e |= v[u] == ENF_ERROR;
         if (c <= t) s += c == I ? rowc[4][l] : c == t ? rowc[5][l] : enf_value(v[u]);
       }
       sB[2 + 2 * ENW + w][l] = s;
-      if (__ballot(e) != 0 && l == 0) error = 1;
+      if (__ballot(e) != 0 && l == 0) sh.error = 1;
       __syncthreads();
       if (w == 0) {
         const double(*p)[ETP] = sB + 2 + 2 * ENW;
         s = ((p[0][l] + p[1][l]) + (p[2][l] + p[3][l])) + ((p[4][l] + p[5][l]) + (p[6][l] + p[7][l]));
         const bool row = !EDGE || ig < n;
-        const bool failed = error != 0;
+        const bool failed = sh.error != 0;
         const bool zero = row && !(s > 0.0) && !failed;  // after an input error a sum means nothing
         if (zero) raise_status(&in.ctrl->status, RAD_EZEROROW);
-        d = row ? fabs(s - 1.0) : 0.0;
+        const double d = row ? fabs(s - 1.0) : 0.0;
+        rowc[6][l] = d;
         const double sc = row && s > 0.0 ? 1.0 / s : 1.0;
         const EnfWord state = failed || __ballot(zero) != 0 ? ENF_FAILED
                               : __ballot(!(d <= tol)) == 0  ? ENF_CLOSED
@@ -727,36 +789,30 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
       const EnfWord st = enf_await(xstate + (iters & 3) * static_cast<long>(t) + min(l, t - 1));
       const bool all = __ballot(st != ENF_CLOSED) == 0, any = __ballot(st == ENF_FAILED) != 0;
       if (l == 0) {
-        dec[0] = all;
-        dec[1] = any;
+        sh.dec[0] = all;
+        sh.dec[1] = any;
       }
     }
     __syncthreads();
-    stop = dec[1];
+    stop = sh.dec[1];
     if (stop) break;
     ++iters;
-    converged = tol > 0.0 && dec[0];
+    converged = tol > 0.0 && sh.dec[0];
   }
+  const int l = fresh_lane(), jg = c0 + l, ig = r0 + l;
   // the last iteration's maxima; the workgroup that adds its own last reports
-  for (int off = 32; off > 0; off >>= 1) {
-    d = fmax(d, __shfl_xor(d, off));
-    rmax = fmax(rmax, __shfl_xor(rmax, off));
-    emax = fmax(emax, __shfl_xor(emax, off));
-  }
-  __syncthreads();
-  if (l == 0) {
-    sB[0][w] = d;
-    sB[1][w] = rmax;
-    sB[2][w] = emax;
-  }
-  __syncthreads();
-  if (tid < 3) {
-    double x = 0.0;
-    for (int q = 0; q < ENW; ++q) x = fmax(x, sB[tid][q]);
-    atomicMax(xmax + tid, static_cast<EnfWord>(__double_as_longlong(x)));
+  if (w == 0) {
+    double x = DIAG ? rowc[6][l] : 0.0;
+    for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
+    if (l == 1 || l == 2) {
+      x = 0.0;
+      for (int q = 0; q < ENW; ++q)
+        for (int g = 0; g < 4; ++g) x = fmax(x, sh.most[l - 1][q][g]);
+    }
+    if (l < 3 && iters + stop > 0) atomicMax(xmax + l, static_cast<EnfWord>(__double_as_longlong(x)));
   }
   __builtin_amdgcn_s_waitcnt(0);
-  if (tid == 0 && atomicAdd(xmax + 3, 1ull) + 1 == static_cast<EnfWord>(in.pairs)) {
+  if (w == 0 && l == 0 && atomicAdd(xmax + 3, 1ull) + 1 == static_cast<EnfWord>(in.pairs)) {
     const double em = enf_value(agent_load(xmax + 2));
     in.ctrl->iters = iters;
     in.ctrl->converged = converged;
@@ -776,49 +832,52 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
       const int jr = c0 + w + ENW * k;
       if (!EDGE || (jr < n && ig < n)) row_st(in.F + static_cast<long>(jr) * ldf, ig, b[k] * rowc[7][w + ENW * k]);
     }
-  if (DIAG && w == 0 && (!EDGE || ig < n)) in.F[static_cast<long>(ig) * ldf + n] = space * rowc[3][l];
+  if (DIAG && w == 0 && (!EDGE || ig < n)) in.F[static_cast<long>(ig) * ldf + n] = rowc[5][l] * rowc[3][l];
 }
 
 template <bool HALF, bool WIDE>
-__device__ __forceinline__ void enf_resident_pair(const EnfInst& in, int I, int J, double tol, int max_iter,
-                                                  double (*sB)[ETP], double (*rowc)[ET]) {
+__device__ __forceinline__ void enf_resident_pair(const EnfInst& in, int I, int J, int w, double tol, int max_iter,
+                                                  ResidentShared& sh) {
   const bool edge = (J + 1) * ET > in.n;
   if (I == J) {
-    if (edge) enf_resident_tile<true, true, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
-    else enf_resident_tile<true, false, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
+    if (edge) enf_resident_tile<true, true, HALF, WIDE>(in, I, J, w, tol, max_iter, sh);
+    else enf_resident_tile<true, false, HALF, WIDE>(in, I, J, w, tol, max_iter, sh);
   } else {
-    if (edge) enf_resident_tile<false, true, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
-    else enf_resident_tile<false, false, HALF, WIDE>(in, I, J, tol, max_iter, sB, rowc);
+    if (edge) enf_resident_tile<false, true, HALF, WIDE>(in, I, J, w, tol, max_iter, sh);
+    else enf_resident_tile<false, false, HALF, WIDE>(in, I, J, w, tol, max_iter, sh);
   }
 }
 
-// PER_CU: workgroups per CU the registers allow, 1 or ENF_RES_PER_CU
-template <int PER_CU>
-__global__ void __launch_bounds__(ENF_THREADS, 2 * PER_CU) enf_resident(EnfInst in, double tol, int max_iter) {
-  __shared__ double sB[ET][ETP];
-  __shared__ double rowc[8][ET];
+template <bool WIDE>
+__device__ __forceinline__ void enf_resident_body(const EnfInst& in, long pair, double tol, int max_iter,
+                                                  ResidentShared& sh) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int I, J;
-  pair_from_index(blockIdx.x, in.t, I, J);
+  pair_from_index(pair, in.t, I, J);
   I = __builtin_amdgcn_readfirstlane(I);
   J = __builtin_amdgcn_readfirstlane(J);
-  if (in.mode == RAD_KAPPA_HALF) enf_resident_pair<true, PER_CU == 1>(in, I, J, tol, max_iter, sB, rowc);
-  else enf_resident_pair<false, PER_CU == 1>(in, I, J, tol, max_iter, sB, rowc);
+  if (in.mode == RAD_KAPPA_HALF) enf_resident_pair<true, WIDE>(in, I, J, w, tol, max_iter, sh);
+  else enf_resident_pair<false, WIDE>(in, I, J, w, tol, max_iter, sh);
+}
+// one workgroup per CU
+__global__ void __launch_bounds__(ENF_THREADS, 2) enf_resident_wide(EnfInst in, double tol, int max_iter) {
+  __shared__ ResidentShared sh;
+  enf_resident_body<true>(in, blockIdx.x, tol, max_iter, sh);
+}
+// ENF_RES_PER_CU workgroups per CU
+__global__ void __launch_bounds__(ENF_THREADS, ENF_RES_WAVES) enf_resident(EnfInst in, double tol, int max_iter) {
+  __shared__ ResidentShared sh;
+  enf_resident_body<false>(in, blockIdx.x, tol, max_iter, sh);
 }
 
 // Several models in one cooperative launch, each with an exchange of its own:
 // map[b] names the instance and the tile pair of workgroup b.
-__global__ void __launch_bounds__(ENF_THREADS, 2 * ENF_RES_PER_CU)
+__global__ void __launch_bounds__(ENF_THREADS, ENF_RES_WAVES)
 enf_resident_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__ map, double tol, int max_iter) {
-  __shared__ double sB[ET][ETP];
-  __shared__ double rowc[8][ET];
+  __shared__ ResidentShared sh;
   const EnfBlk m = map[blockIdx.x];
   const EnfInst in = ins[m.inst];
-  int I, J;
-  pair_from_index(m.local, in.t, I, J);
-  I = __builtin_amdgcn_readfirstlane(I);
-  J = __builtin_amdgcn_readfirstlane(J);
-  if (in.mode == RAD_KAPPA_HALF) enf_resident_pair<true, false>(in, I, J, tol, max_iter, sB, rowc);
-  else enf_resident_pair<false, false>(in, I, J, tol, max_iter, sB, rowc);
+  enf_resident_body<false>(in, m.local, tol, max_iter, sh);
 }
 
 __device__ __forceinline__ void enf_init_body(EnfCtrl* ctrl) {
