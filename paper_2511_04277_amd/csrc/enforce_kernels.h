@@ -605,7 +605,13 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 //
 // Needs a cooperative launch: a workgroup that waits holds its place, and every
 // word that it waits for is stored by a workgroup that is resident too, in the
-// same iteration, whether or not an error was seen.  Such launches run one after
+// same iteration, whether or not an error was seen.  The workgroups may start at
+// very different times, so nothing but those words ends one: each takes part in
+// every iteration that any of them enters.  An error, of the input or a bad area
+// found by an earlier launch, travels in the words (ENF_ERROR, ENF_FAILED), every
+// workgroup leaves after the same iteration, and the status is raised only then
+// (a workgroup that left on a status raised in this launch would leave the
+// others waiting).  Such launches run one after
 // another (four streams with 15 workgroups each take four times as long as
 // one), so a workgroup shares its CU with others of its own launch and with
 // kernels that end by themselves; why every one gets a place beside those is at
@@ -652,7 +658,9 @@ struct ResidentShared {
   double rowc[8][ET];   // see enf_pair_step; of a diagonal tile [4]: its own row sums, [5]: the space column,
                         // [6]: the rows' closure defects
   double most[2][ENW][4];  // maxima of 16 threads each, of the last iteration
-  int error, dec[2];    // an input error in this workgroup; all row blocks closed, any failed
+  int refused, error;   // a bad area; that, or an input error that this workgroup has seen
+  int zero;             // a row of this row block sums to zero
+  int dec[2];           // all row blocks closed, any failed
 };
 
 template <bool DIAG, bool EDGE, bool HALF, bool WIDE>
@@ -672,7 +680,6 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
   EnfWord* const xmax = xstate + 4L * t;
   // slot of row block r, column block c in iteration k
   auto slot = [&](int k, int r, int c) { return xpart + ((static_cast<long>(k & 1) * t + r) * t + c) * ET; };
-  if (agent_load(&in.ctrl->status) < 0) return;  // a bad area, found by an earlier launch: for every workgroup alike
   double a[ERW], b[ERW];
 #pragma unroll
   for (int k = 0; k < ERW; ++k) {
@@ -694,7 +701,11 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
     rowc[cq + 2][lane] = HALF ? 0.0 : ai * ai / in.nrays[crc];
     rowc[cq + 3][lane] = 1.0;
   }
-  if (w == 0 && lane == 0) sh.error = 0;
+  if (w == 0 && lane == 0) {
+    sh.refused = agent_load(&in.ctrl->status) < 0;  // a bad area, found by an earlier launch
+    sh.error = sh.refused;
+    sh.zero = 0;
+  }
   __syncthreads();
   int iters = 0, converged = 0, stop = 0;
   while (iters < max_iter && !converged) {
@@ -766,7 +777,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
         const bool row = !EDGE || ig < n;
         const bool failed = sh.error != 0;
         const bool zero = row && !(s > 0.0) && !failed;  // after an input error a sum means nothing
-        if (zero) raise_status(&in.ctrl->status, RAD_EZEROROW);
+        if (zero) sh.zero = 1;
         const double d = row ? fabs(s - 1.0) : 0.0;
         rowc[6][l] = d;
         const double sc = row && s > 0.0 ? 1.0 / s : 1.0;
@@ -800,6 +811,11 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
     converged = tol > 0.0 && sh.dec[0];
   }
   const int l = fresh_lane(), jg = c0 + l, ig = r0 + l;
+  if (sh.refused) return;
+  if (stop && w == 0 && fresh_lane() == 0) {
+    if (sh.error) raise_status(&in.ctrl->status, RAD_ENONFINITE);
+    if (sh.zero) raise_status(&in.ctrl->status, RAD_EZEROROW);
+  }
   // the last iteration's maxima; the workgroup that adds its own last reports
   if (w == 0) {
     double x = DIAG ? rowc[6][l] : 0.0;
