@@ -608,7 +608,7 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 // same iteration, whether or not an error was seen.  The workgroups may start at
 // very different times, so nothing but those words ends one: each takes part in
 // every iteration that any of them enters.  An error, of the input or a bad area
-// found by an earlier launch, travels in the words (ENF_ERROR, ENF_FAILED), every
+// found by an earlier launch, travels in the words (ENF_ERROR and the states), every
 // workgroup leaves after the same iteration, and the status is raised only then
 // (a workgroup that left on a status raised in this launch would leave the
 // others waiting).  Such launches run one after
@@ -620,7 +620,8 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 constexpr EnfWord ENF_NAN = 0x7ff8000000000000ull;    // any NaN that is stored
 constexpr EnfWord ENF_EMPTY = 0x7ff8c0ffee000001ull;  // so no sum or scale is one of these
 constexpr EnfWord ENF_ERROR = 0x7ff8c0ffee000002ull;  // in place of a sum: an input error was seen
-enum : EnfWord { ENF_OPEN = 0, ENF_CLOSED = 1, ENF_FAILED = 2 };  // state of a row block
+// state of a row block; ENF_FAILED: ENF_ERROR in its sums, ENF_NOSUM: a row sums to zero
+enum : EnfWord { ENF_OPEN = 0, ENF_CLOSED = 1, ENF_FAILED = 2, ENF_NOSUM = 3 };
 
 __device__ __forceinline__ EnfWord enf_word(double x) {
   return x == x ? static_cast<EnfWord>(__double_as_longlong(x)) : ENF_NAN;
@@ -659,8 +660,7 @@ struct ResidentShared {
                         // [6]: the rows' closure defects
   double most[2][ENW][4];  // maxima of 16 threads each, of the last iteration
   int refused, error;   // a bad area; that, or an input error that this workgroup has seen
-  int zero;             // a row of this row block sums to zero
-  int dec[2];           // all row blocks closed, any failed
+  int dec[2];           // all row blocks closed; the code if any failed
 };
 
 template <bool DIAG, bool EDGE, bool HALF, bool WIDE>
@@ -704,7 +704,6 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
   if (w == 0 && lane == 0) {
     sh.refused = agent_load(&in.ctrl->status) < 0;  // a bad area, found by an earlier launch
     sh.error = sh.refused;
-    sh.zero = 0;
   }
   __syncthreads();
   int iters = 0, converged = 0, stop = 0;
@@ -777,13 +776,13 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
         const bool row = !EDGE || ig < n;
         const bool failed = sh.error != 0;
         const bool zero = row && !(s > 0.0) && !failed;  // after an input error a sum means nothing
-        if (zero) sh.zero = 1;
         const double d = row ? fabs(s - 1.0) : 0.0;
         rowc[6][l] = d;
         const double sc = row && s > 0.0 ? 1.0 / s : 1.0;
-        const EnfWord state = failed || __ballot(zero) != 0 ? ENF_FAILED
-                              : __ballot(!(d <= tol)) == 0  ? ENF_CLOSED
-                                                            : ENF_OPEN;
+        const EnfWord state = failed                       ? ENF_FAILED
+                              : __ballot(zero) != 0        ? ENF_NOSUM
+                              : __ballot(!(d <= tol)) == 0 ? ENF_CLOSED
+                                                           : ENF_OPEN;
         __builtin_amdgcn_s_waitcnt(0);
         agent_store(xscale + ((iters & 3) * static_cast<long>(t) + I) * ET + l, enf_word(sc));
         if (l == 0) agent_store(xstate + (iters & 3) * static_cast<long>(t) + I, state);
@@ -798,10 +797,12 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
     }
     if (w == 2) {
       const EnfWord st = enf_await(xstate + (iters & 3) * static_cast<long>(t) + min(l, t - 1));
-      const bool all = __ballot(st != ENF_CLOSED) == 0, any = __ballot(st == ENF_FAILED) != 0;
+      // the streamed sweep sees a bad entry anywhere before any row's sum
+      const bool all = __ballot(st != ENF_CLOSED) == 0, bad_entry = __ballot(st == ENF_FAILED) != 0;
+      const bool no_sum = __ballot(st == ENF_NOSUM) != 0;
       if (l == 0) {
         sh.dec[0] = all;
-        sh.dec[1] = any;
+        sh.dec[1] = bad_entry ? RAD_ENONFINITE : no_sum ? RAD_EZEROROW : 0;
       }
     }
     __syncthreads();
@@ -812,10 +813,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
   }
   const int l = fresh_lane(), jg = c0 + l, ig = r0 + l;
   if (sh.refused) return;
-  if (stop && w == 0 && fresh_lane() == 0) {
-    if (sh.error) raise_status(&in.ctrl->status, RAD_ENONFINITE);
-    if (sh.zero) raise_status(&in.ctrl->status, RAD_EZEROROW);
-  }
+  if (stop && w == 0 && fresh_lane() == 0) raise_status(&in.ctrl->status, stop);
   // the last iteration's maxima; the workgroup that adds its own last reports
   if (w == 0) {
     double x = DIAG ? rowc[6][l] : 0.0;
@@ -825,7 +823,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
       for (int q = 0; q < ENW; ++q)
         for (int g = 0; g < 4; ++g) x = fmax(x, sh.most[l - 1][q][g]);
     }
-    if (l < 3 && iters + stop > 0) atomicMax(xmax + l, static_cast<EnfWord>(__double_as_longlong(x)));
+    if (l < 3 && (iters > 0 || stop)) atomicMax(xmax + l, static_cast<EnfWord>(__double_as_longlong(x)));
   }
   __builtin_amdgcn_s_waitcnt(0);
   if (w == 0 && l == 0 && atomicAdd(xmax + 3, 1ull) + 1 == static_cast<EnfWord>(in.pairs)) {

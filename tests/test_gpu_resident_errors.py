@@ -37,8 +37,14 @@ def _bad_area(F, area):
     area[-1] = 0.0
 
 
+def _empty_row_and_bad_entry(F, area):
+    """The entry belongs to row blocks other than the row's: a bad entry counts first."""
+    _empty_row(F, area)
+    F[-2, -3] = -1.0
+
+
 SPOILS = [(_nan_first, -2), (_nan_corner, -2), (_negative_last, -2), (_negative_space, -2), (_empty_row, -3),
-          (_bad_area, -1)]
+          (_empty_row_and_bad_entry, -2), (_bad_area, -1)]
 
 
 def _model(n, seed):
