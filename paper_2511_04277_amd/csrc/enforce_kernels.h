@@ -657,8 +657,8 @@ __device__ __forceinline__ double max_of_16(double x) {
 struct ResidentShared {
   double sB[ET][ETP];
   double rowc[8][ET];   // see enf_pair_step; of a diagonal tile [4]: its own row sums, [5]: the space column,
-                        // [6]: the rows' closure defects
-  double most[2][ENW][4];  // maxima of 16 threads each, of the last iteration
+                        // [6] and [7]: the rows' closure defects, of two iterations in turn
+  double most[2][2][ENW][4];  // of two iterations in turn: both maxima, of 16 threads each
   int refused, error;   // a bad area; that, or an input error that this workgroup has seen
   int dec[2];           // all row blocks closed; the code if any failed
 };
@@ -738,8 +738,8 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
     rmax = max_of_16(rmax);
     emax = max_of_16(emax);
     if (l % 16 == 0) {
-      sh.most[0][w][l / 16] = rmax;
-      sh.most[1][w][l / 16] = emax;
+      sh.most[iters & 1][0][w][l / 16] = rmax;
+      sh.most[iters & 1][1][w][l / 16] = emax;
     }
     if (DIAG) {
       // wave w sums every 8th partial sum of row l, the last one the space column's
@@ -777,7 +777,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
         const bool failed = sh.error != 0;
         const bool zero = row && !(s > 0.0) && !failed;  // after an input error a sum means nothing
         const double d = row ? fabs(s - 1.0) : 0.0;
-        rowc[6][l] = d;
+        rowc[6 + (iters & 1)][l] = d;
         const double sc = row && s > 0.0 ? 1.0 / s : 1.0;
         const EnfWord state = failed                       ? ENF_FAILED
                               : __ballot(zero) != 0        ? ENF_NOSUM
@@ -814,16 +814,18 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
   const int l = fresh_lane(), jg = c0 + l, ig = r0 + l;
   if (sh.refused) return;
   if (stop && w == 0 && fresh_lane() == 0) raise_status(&in.ctrl->status, stop);
-  // the last iteration's maxima; the workgroup that adds its own last reports
+  // the maxima of the last iteration that was completed (an error ends one
+  // without); the workgroup that adds its own last reports
+  const int last = (iters - 1) & 1;
   if (w == 0) {
-    double x = DIAG ? rowc[6][l] : 0.0;
+    double x = DIAG ? rowc[6 + last][l] : 0.0;
     for (int off = 32; off > 0; off >>= 1) x = fmax(x, __shfl_xor(x, off));
     if (l == 1 || l == 2) {
       x = 0.0;
       for (int q = 0; q < ENW; ++q)
-        for (int g = 0; g < 4; ++g) x = fmax(x, sh.most[l - 1][q][g]);
+        for (int g = 0; g < 4; ++g) x = fmax(x, sh.most[last][l - 1][q][g]);
     }
-    if (l < 3 && (iters > 0 || stop)) atomicMax(xmax + l, static_cast<EnfWord>(__double_as_longlong(x)));
+    if (l < 3 && iters > 0) atomicMax(xmax + l, static_cast<EnfWord>(__double_as_longlong(x)));
   }
   __builtin_amdgcn_s_waitcnt(0);
   if (w == 0 && l == 0 && atomicAdd(xmax + 3, 1ull) + 1 == static_cast<EnfWord>(in.pairs)) {
@@ -962,6 +964,7 @@ __device__ __forceinline__ void enf_single_body(const EnfInst& in, double tol, i
   const double area = own ? rowc[0][tid] : 0.0;
   int iters = 0, converged = 0, stop = 0;
   double rmax = 0.0, emax = 0.0, d = 0.0;
+  double rlast = 0.0, elast = 0.0, dlast = 0.0;  // of the last iteration without an error
   while (iters < max_iter && !converged) {
     // of this iteration: a wave ahead may be in the next while another reads it
     int* error = flags + 1 + (iters & 1);
@@ -1019,27 +1022,30 @@ __device__ __forceinline__ void enf_single_body(const EnfInst& in, double tol, i
     }
     ++iters;
     converged = flags[0];
+    rlast = rmax;
+    elast = emax;
+    dlast = d;
   }
   for (int off = 32; off > 0; off >>= 1) {
-    rmax = fmax(rmax, __shfl_xor(rmax, off));
-    emax = fmax(emax, __shfl_xor(emax, off));
-    d = fmax(d, __shfl_xor(d, off));
+    rlast = fmax(rlast, __shfl_xor(rlast, off));
+    elast = fmax(elast, __shfl_xor(elast, off));
+    dlast = fmax(dlast, __shfl_xor(dlast, off));
   }
   __syncthreads();  // part has been read
   if (l == 0) {
-    part[0][w] = rmax;
-    part[1][w] = emax;
+    part[0][w] = rlast;
+    part[1][w] = elast;
   }
   __syncthreads();
   if (tid == 0 && iters > 0) {
     for (int q = 1; q < ENW; ++q) {
-      rmax = fmax(rmax, part[0][q]);
-      emax = fmax(emax, part[1][q]);
+      rlast = fmax(rlast, part[0][q]);
+      elast = fmax(elast, part[1][q]);
     }
     in.ctrl->iters = iters;
     in.ctrl->converged = converged;
-    in.ctrl->last_defect = d;
-    in.ctrl->last_recip = emax > 0.0 ? rmax / emax : 0.0;
+    in.ctrl->last_defect = dlast;
+    in.ctrl->last_recip = elast > 0.0 ? rlast / elast : 0.0;
   }
   if (stop != 0 || iters == 0) return;
 #pragma unroll

@@ -142,3 +142,53 @@ def test_model_of_a_batch(spoil, code):
         batch.run(enforce_iters=5)
     g.replay()
     assert _device_status(batch) == got
+
+
+def _overflow(F, area):
+    """Finite at first, beyond the range after one iteration."""
+    area[0], area[-1] = 1e200, 1e-200
+    F[0, F.shape[0] - 1] = 0.5
+
+
+def _stats(s):
+    return [s.iters, s.converged, s.closure_defect, s.recip_err]
+
+
+@pytest.mark.parametrize("n", [2, 40, 64, 300, 1300, 1984])
+@pytest.mark.parametrize("spoil", [f for f, _ in SPOILS] + [_overflow])
+def test_statistics_of_a_refused_call(n, spoil):
+    """Of the last iteration that was completed, as of the streamed enforcement (a captured run)."""
+    need_gpu()
+    import paper_2511_04277_amd as rad
+    from paper_2511_04277_amd import _lib as L
+    if n < 6 and spoil in (_empty_row, _empty_row_and_bad_entry):
+        pytest.skip("too few rows")
+    lib, stream = L.lib(), torch.cuda.current_stream().cuda_stream
+    F, area, rays = _model(n, 3)
+    spoil(F, area)
+    start, a, r, half = dev(F), dev(area), dev(rays), dev(np.full(n, 0.5))
+    f = start.clone()
+    batch = rad.Batch([{"F": f, "area": a, "n_rays": r, "eps": [half], "rho": [half]}], precision="fp64",
+                      kappa="half")
+
+    def batch_stats():
+        out = (L.RadStats * 1)()
+        lib.rad_batch_stats(batch._plan, batch.work.data_ptr(), out, stream)
+        return _stats(out[0])
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        batch.run(enforce_iters=5)
+    g.replay()
+    want = batch_stats()
+    f.copy_(start)
+    batch.run(enforce_iters=5)
+    assert batch_stats() == want
+    f.copy_(start)
+    work = torch.empty(lib.rad_enforce_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    st = L.RadStats()
+    code = lib.rad_enforce_vf(f.data_ptr(), n, f.stride(0), a.data_ptr(), r.data_ptr(), L.RAD_KAPPA_HALF, 0.0, 5,
+                              work.data_ptr(), work.numel(), st, stream)
+    assert code == st.device_status < 0
+    assert _stats(st) == want
+    assert want[0] == (1 if spoil is _overflow else 0)
