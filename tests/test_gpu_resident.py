@@ -1,5 +1,5 @@
-"""Enforcement with F held on chip (one tile; all tile pairs resident) against the oracle and,
-bitwise, against the batch path, which streams F through once per iteration."""
+"""Enforcement with F held on chip (one tile; all tile pairs resident) against the oracle and, bitwise,
+against the batch path (from 65 faces on the same tile code, from 1985 on streamed in both)."""
 import numpy as np
 import pytest
 

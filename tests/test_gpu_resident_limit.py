@@ -1,5 +1,5 @@
-"""Enforcement at the largest model whose tile pairs the chip holds at once (38 blocks of 64 rows
-on 256 CUs) and just past it: an eager call against a captured one, which streams F through memory
+"""Enforcement at the largest model whose tile pairs the chip holds at once (31 blocks of 64 rows
+on 256 CUs) and past it: an eager call against a captured one, which streams F through memory
 once per iteration, bit for bit; alone and in batches with smaller models."""
 import numpy as np
 import pytest

@@ -1,6 +1,6 @@
 """The resident enforcement exchanges sums, scales and states through buffers that are used in
 turn (two and four iterations): every iteration count over two rounds of them, and a long run,
-bitwise against the batch path, which streams F through once per iteration."""
+bitwise against the batch path, whose group launch has an exchange of the same kind."""
 import numpy as np
 import pytest
 

@@ -1,5 +1,5 @@
 """Small models' products run in 32 x 32 tiles (and the L blocks in place): the batch path keeps
-64 x 64 and 128 x 128 tiles, and every tile shape accumulates in the same order, so the REF matrices
+64 x 64 tiles, and every tile shape accumulates in the same order, so the REF matrices
 agree bitwise.  The transposed products are compared with the oracle's adjoint (K's condition number
 is below 19; n eps cond = 1100 * 1.1e-16 * 19 = 2.3e-12 relative to the gradients' scale)."""
 import numpy as np
