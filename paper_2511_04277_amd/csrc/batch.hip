@@ -1095,7 +1095,9 @@ extern "C" int32_t rad_batch_run(const rad_batch_plan* P, void* work, double enf
     long first_pair = 0, first_fin = 0, first_row = 0;
     int first = 0;
     double bytes = P->sweep_bytes;
-    if (P->streamed > 0 && !stream_capturing(s) && resident_workgroups(resident, ENF_RES_PER_CU, limit) >= RES_PAIRS) {
+    const long min_iters = ENF_RES_ITERS * (1 + static_cast<long>(P->groups.size())) / 2;
+    if (P->streamed > 0 && enforce_iters >= min_iters && !stream_capturing(s) &&
+        resident_workgroups(resident, ENF_RES_PER_CU, limit) >= RES_PAIRS) {
       hipLaunchKernelGGL(enf_exchange_init_batched, dim3(static_cast<unsigned>(P->streamed) * ENF_XCH_BLOCKS), dim3(256),
                          0, s, ei);
       ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, P->sweep_bytes - P->streamed_bytes);

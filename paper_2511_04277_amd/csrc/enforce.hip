@@ -159,7 +159,8 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.xch = l.xch;
   // one tile needs no co-operation; a resident grid does, which a capture does
   // not record
-  bool resident = pairs == 1 || (t <= ENF_RES_TILES && pairs <= resident_limit(false) && !stream_capturing(s));
+  bool resident = pairs == 1 || (t <= ENF_RES_TILES && max_iter >= ENF_RES_ITERS &&
+                                 pairs <= resident_limit(false) && !stream_capturing(s));
   if (pairs > 1) {
     hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
     const long words = resident ? enf_xch_words(t) : 0;

@@ -43,6 +43,13 @@ constexpr int ENF_RES_TILES = 31;  // most 64-row blocks of a resident model: 49
 // grid that needs a third on some CUs then waits for ever.
 constexpr int ENF_RES_PER_CU = 2;
 constexpr int ENF_RES_WAVES = 7;
+// Fewer iterations are streamed: the exchange's set-up and the cooperative launch
+// cost about 15 us, and an iteration saves 7 to 9.  84 faces, one and two
+// iterations: 21.7 and 32.3 us streamed, 35.5 and 40.7 on chip; 1984 faces: 37.3
+// and 55.5, 56.0 and 66.0; three: alike.  In a batch the groups are launched one
+// after another: three for one group, half as many for each one more (16 models
+// in five groups: 112 us and 60 an iteration more, 245 us and 40).
+constexpr int ENF_RES_ITERS = 3;
 typedef unsigned long long EnfWord;
 __host__ __device__ constexpr long enf_xch_words(long t) { return 2 * t * t * ET + 4 * t * ET + 4 * t + 4; }
 
