@@ -224,7 +224,12 @@ agg_reduce(const double* __restrict__ X, long ldx, int n, const double* __restri
 // to row, so the column groups' ranges and (up to eight outputs per thread)
 // their first members stay in registers, and the next row's loads run under
 // the gathers: 8192 faces to 2048 (537 MB) 187 -> 108 us against loading the
-// ranges and members again for every row and output.  Used when a row of X fits in
+// ranges and members again for every row and output.  With more outputs the
+// gathers load their members, which come back after all that was asked for
+// before, so the next row waits until they are done (12000 faces to 3000 in 547 us
+// with its loads ahead, 493 without prefetch or ranges in registers, 414 as it is;
+// 8192 faces to 8192 458, 529 and 310).  Outputs past g have no members (few
+// groups: 3000 faces to 64 417 -> 259 us).  Used when a row of X fits in
 // AGGL_MAX_LDS.
 // MODE: what becomes of the sums.
 constexpr int AGG_SUMS = 0;        // Y = sums (divided by the group weight if divide)
@@ -245,12 +250,14 @@ struct AggOut {
 };
 
 template <int HPT, int NWT, int MODE>
-__global__ void __launch_bounds__(AGGL_THREADS, HPT <= 8 ? 4 : 2)
+__global__ void __launch_bounds__(AGGL_THREADS, HPT <= 8 || (HPT == 16 && NWT == 1) ? 4 : 2)
 agg_reduce_lds(const double* __restrict__ X, long ldx, int n, const int* __restrict__ group,
                const int* __restrict__ offs, const int* __restrict__ members, int g, AggOut o, long ldy, int divide) {
   extern __shared__ double xrow[];  // n + 1
   constexpr int CM = HPT <= 2 ? 16 : HPT <= 4 ? 4 : HPT <= 8 ? 2 : 0;  // members kept per output
-  constexpr int PF = HPT >= 8 && NWT == 2 ? (HPT > 16 ? 4 : 12) : 16;  // entries of the next row in flight per thread
+  // entries of the next row in flight per thread (none if the gathers load their
+  // members: those loads would wait for the row's, which are before them)
+  constexpr int PF = CM == 0 ? 0 : HPT == 8 && NWT == 2 ? 12 : 16;
   const int G = blockIdx.x, tid = threadIdx.x;
   const int rb = offs[G], re = offs[G + 1];
   // column groups of the thread's outputs: first member index and count, and
@@ -265,6 +272,12 @@ agg_reduce_lds(const double* __restrict__ X, long ldx, int n, const int* __restr
   }
 #pragma unroll
   for (int k = 0; k < HPT; ++k) {
+    // no members for outputs past g (opaque, or the loads above move into a
+    // branch here and run one after another)
+    if (HPT <= 2 || HPT >= 16) {
+      __asm__ volatile("" : "+v"(rc[k]));
+      if (tid + k * AGGL_THREADS >= g) rc[k] &= 0xffff;
+    }
     const int cb = rc[k] & 0xffff, cn = rc[k] >> 16;
 #pragma unroll
     for (int u = 0; u < CM; u += 2) {
@@ -283,7 +296,7 @@ agg_reduce_lds(const double* __restrict__ X, long ldx, int n, const int* __restr
   // entries of a row in pieces of AGGL_THREADS; the last piece of a row ends
   // with it (overlapping the one before), so no lane needs a bounds test
   const int lane = min(tid, n), last = max(0, n + 1 - AGGL_THREADS);
-  double v[PF];
+  double v[PF + 1];
   auto load = [&](int i) {
     const double* row = X + static_cast<long>(i) * ldx;
 #pragma unroll
@@ -339,6 +352,7 @@ agg_reduce_lds(const double* __restrict__ X, long ldx, int n, const int* __restr
         int m[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) m[u] = members[cb + min(b0 + u, cn - 1)];
+        __asm__ volatile("" : "+v"(m[0]), "+v"(m[1]), "+v"(m[2]), "+v"(m[3]));  // (or the loads move to their uses)
 #pragma unroll
         for (int u = 0; u < 4; ++u)
           if (b0 + u < cn) sv += xrow[m[u]];
@@ -430,7 +444,10 @@ bool launch_agg_lds(const double* X, long ldx, int n, const int* group, const Ag
   if (static_cast<size_t>(n + 1) * sizeof(double) > AGGL_MAX_LDS || hpt > 32) return false;
   if (hpt <= 2) return launch_agg_hpt<2, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
   if (hpt <= 4) return launch_agg_hpt<4, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
-  if (hpt <= 8) return launch_agg_hpt<8, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
+  // eight outputs per thread compute all eight, and with rows past half of the LDS
+  // there is one workgroup per CU whatever the registers: 16, which skip those
+  // past g (12000 faces to 3000: 537 against 414 us; 8192 faces fit twice)
+  if (hpt <= 8 && n < 10240) return launch_agg_hpt<8, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
   if (hpt <= 16) return launch_agg_hpt<16, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
   return launch_agg_hpt<32, NWT, MODE>(X, ldx, n, group, o, offs, members, g, ldy, divide, s);
 }
