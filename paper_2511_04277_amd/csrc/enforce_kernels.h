@@ -740,7 +740,6 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
             agent_store(slot(iters, J, I) + l, e ? ENF_ERROR : enf_word(s_par));
           }
         });
-    if (bad) raise_status(&in.ctrl->status, RAD_ENONFINITE);
     const int l = fresh_lane(), ig = r0 + l;
     rmax = max_of_16(rmax);
     emax = max_of_16(emax);

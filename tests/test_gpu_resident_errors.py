@@ -37,6 +37,12 @@ def _bad_area(F, area):
     area[-1] = 0.0
 
 
+def _bad_area_and_entry(F, area):
+    """The areas are checked before the first sweep."""
+    _bad_area(F, area)
+    _negative_last(F, area)
+
+
 def _empty_row_and_bad_entry(F, area):
     """The entry belongs to row blocks other than the row's: a bad entry counts first."""
     _empty_row(F, area)
@@ -44,7 +50,7 @@ def _empty_row_and_bad_entry(F, area):
 
 
 SPOILS = [(_nan_first, -2), (_nan_corner, -2), (_negative_last, -2), (_negative_space, -2), (_empty_row, -3),
-          (_empty_row_and_bad_entry, -2), (_bad_area, -1)]
+          (_empty_row_and_bad_entry, -2), (_bad_area, -1), (_bad_area_and_entry, -1)]
 
 
 def _model(n, seed):
