@@ -871,6 +871,7 @@ void build_tables(rad_batch_plan* P, char* base, TableBuilder& tb) {
     e.finred = reinterpret_cast<double*>(base + o.finred);
     e.ctrl = reinterpret_cast<EnfCtrl*>(base + o.ctrl);
     if (k < P->streamed) e.xch = reinterpret_cast<EnfWord*>(base + o.xch);
+    e.patience = resident_patience();
     ei.push_back(e);
     pair_start.push_back(pair_start.back() + o.pairs);
     fblk_start.push_back(fblk_start.back() + ceil_div(s.n, 256));
@@ -1111,6 +1112,8 @@ extern "C" int32_t rad_batch_run(const rad_batch_plan* P, void* work, double enf
       }
       if (first > 0) {
         RAD_HIP_CHECK(e);
+        hipLaunchKernelGGL(enf_alone_batched, dim3(static_cast<unsigned>(P->streamed)), dim3(ENF_THREADS), 0, s, ei,
+                           enforce_tol, enforce_iters);
         first_pair = P->streamed_pair;
         first_fin = P->streamed_fin;
         first_row = P->streamed_row;

@@ -157,6 +157,7 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.finred = l.finred;
   in.ctrl = l.ctrl;
   in.xch = l.xch;
+  in.patience = resident_patience();
   // one tile needs no co-operation; a resident grid does, which a capture does
   // not record
   bool resident = pairs == 1 || (t <= ENF_RES_TILES && max_iter >= ENF_RES_ITERS &&
@@ -183,6 +184,8 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
       if (e != hipSuccess) {  // nothing was enqueued: one launch per step instead
         (void)hipGetLastError();
         resident = false;
+      } else {
+        hipLaunchKernelGGL(enf_alone, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
       }
     }
   }

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cstdlib>
 
 #include "common.h"
 
@@ -28,7 +29,8 @@ struct EnfCtrl {
 
 // What the workgroups of the resident kernel exchange, in words: row sums
 // (two iterations in turn x row block x column block x 64), closure scales and
-// row blocks' states (four iterations in turn), then three maxima and a counter.
+// row blocks' states (four iterations in turn), then three maxima, a counter and
+// the verdict.
 constexpr int ENF_RES_TILES = 31;  // most 64-row blocks of a resident model: 496 tile pairs
 // Workgroups of a resident kernel on a CU, and the waves per SIMD that its
 // registers are held to (72 each).  All its workgroups have to find a place
@@ -50,8 +52,10 @@ constexpr int ENF_RES_WAVES = 7;
 // after another: three for one group, half as many for each one more (16 models
 // in five groups: 112 us and 60 an iteration more, 245 us and 40).
 constexpr int ENF_RES_ITERS = 3;
+// Polls (about a microsecond each) until a waiting wave gives up.
+constexpr int ENF_PATIENCE = 1 << 20;
 typedef unsigned long long EnfWord;
-__host__ __device__ constexpr long enf_xch_words(long t) { return 2 * t * t * ET + 4 * t * ET + 4 * t + 4; }
+__host__ __device__ constexpr long enf_xch_words(long t) { return 2 * t * t * ET + 4 * t * ET + 4 * t + 5; }
 
 // One enforcement problem as the kernels see it.
 struct EnfInst {
@@ -70,6 +74,7 @@ struct EnfInst {
   double* finred;           // 3 per finalize block: closure defect, the two maxima
   EnfCtrl* ctrl;
   EnfWord* xch;             // resident kernel only: enf_xch_words(t)
+  int patience;             // and how often a wave asks for a word before it gives up
 };
 
 constexpr int ERW = ET / ENW;  // tile rows per wave
@@ -610,20 +615,25 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 // have all seen every state of k - 1 and so every workgroup those of k - 2, it
 // empties those of k - 2 for iteration k + 2, before it stores those of k + 1.
 //
-// Needs a cooperative launch: a workgroup that waits holds its place, and every
-// word that it waits for is stored by a workgroup that is resident too, in the
-// same iteration, whether or not an error was seen.  The workgroups may start at
-// very different times, so nothing but those words ends one: each takes part in
-// every iteration that any of them enters.  An error, of the input or a bad area
-// found by an earlier launch, travels in the words (ENF_ERROR and the states), every
-// workgroup leaves after the same iteration, and the status is raised only then
-// (a workgroup that left on a status raised in this launch would leave the
-// others waiting).  Such launches run one after
-// another (four streams with 15 workgroups each take four times as long as
-// one), so a workgroup shares its CU with others of its own launch and with
-// kernels that end by themselves; why every one gets a place beside those is at
-// ENF_RES_PER_CU.  Same operations in the
-// same order as enf_sweep, enf_finalize and enf_apply_scale, so the same bits.
+// A workgroup that waits holds its place, and every word that it waits for is
+// stored by a workgroup of the same launch, in the same iteration, whether or not
+// an error was seen.  The workgroups may start at very different times, so nothing
+// but those words ends one: each takes part in every iteration that any of them
+// enters.  An error, of the input or a bad area found by an earlier launch, travels
+// in the words (ENF_ERROR and the states), every workgroup leaves after the same
+// iteration, and the status is raised only then (a workgroup that left on a status
+// raised in this launch would leave the others waiting).  Cooperative launches run one after
+// another (four streams with 15 workgroups each take four times as long as one),
+// so a workgroup shares its CU with others of its own launch and with kernels that
+// end by themselves; why every one gets a place beside those is at ENF_RES_PER_CU.
+//
+// Should some not get a place all the same (another process on the GPU), every
+// wait ends: a wave whose patience is out declares the launch given up, unless it
+// is done.  It is done once a workgroup is through with its last iteration: then
+// all sums, scales and states of that have been stored, so the waits for them
+// end too.  Nothing outside the exchange is written before that verdict, and
+// enf_alone after it does what was given up.  Same operations in the same order
+// as enf_sweep, enf_finalize and enf_apply_scale, so the same bits.
 constexpr EnfWord ENF_NAN = 0x7ff8000000000000ull;    // any NaN that is stored
 constexpr EnfWord ENF_EMPTY = 0x7ff8c0ffee000001ull;  // so no sum or scale is one of these
 constexpr EnfWord ENF_ERROR = 0x7ff8c0ffee000002ull;  // in place of a sum: an input error was seen
@@ -635,14 +645,31 @@ __device__ __forceinline__ EnfWord enf_word(double x) {
 }
 __device__ __forceinline__ double enf_value(EnfWord v) { return __longlong_as_double(static_cast<long long>(v)); }
 
-// One word per lane of an active wave, once no active lane's is empty.
-__device__ __forceinline__ EnfWord enf_await(const EnfWord* p) {
-  EnfWord v = agent_load(p);
-  while (__ballot(v == ENF_EMPTY) != 0) {
+// The verdict of a launch: whether its workgroups write their results.
+enum : EnfWord { ENF_RUNNING = 0, ENF_DONE = 1, ENF_GIVEN_UP = 2 };
+constexpr int ENF_GAVE_UP = 1;  // why a workgroup stops; otherwise an error code
+
+// A whole wave asks after each poll in vain whether to leave.
+__device__ __forceinline__ bool enf_gives_up(EnfWord* verdict, int polls, int patience) {
+  if (polls < patience && (polls & 63) != 63) return false;
+  EnfWord v = ENF_RUNNING;
+  if (polls < patience)
+    v = agent_load(verdict);
+  else if (fresh_lane() == 0)
+    v = atomicCAS(verdict, ENF_RUNNING, ENF_GIVEN_UP);
+  const int old = __builtin_amdgcn_readfirstlane(static_cast<int>(v));
+  return polls < patience ? old == static_cast<int>(ENF_GIVEN_UP) : old != static_cast<int>(ENF_DONE);
+}
+
+// One word per lane of a whole wave, once no lane's is empty; false: given up.
+__device__ __forceinline__ bool enf_await(const EnfWord* p, EnfWord& v, EnfWord* verdict, int patience) {
+  v = agent_load(p);
+  for (int polls = 0; __ballot(v == ENF_EMPTY) != 0; ++polls) {
+    if (enf_gives_up(verdict, polls, patience)) return false;
     __builtin_amdgcn_s_sleep(1);
     v = agent_load(p);
   }
-  return v;
+  return true;
 }
 
 // the maximum over the 16 lanes of a row, by rotations within the row (lane
@@ -666,8 +693,10 @@ struct ResidentShared {
   double rowc[8][ET];   // see enf_pair_step; of a diagonal tile [4]: its own row sums, [5]: the space column,
                         // [6] and [7]: the rows' closure defects, of two iterations in turn
   double most[2][2][ENW][4];  // of two iterations in turn: both maxima, of 16 threads each
-  int refused, error;   // a bad area; that, or an input error that this workgroup has seen
-  int dec[2];           // all row blocks closed; the code if any failed
+  struct alignas(16) {
+    int closed, code, gave_up;  // all row blocks closed; the code if any failed; this workgroup gave up
+  } now;
+  int refused, error;  // a bad area; that, or an input error that this workgroup has seen
 };
 
 template <bool DIAG, bool EDGE, bool HALF, bool WIDE>
@@ -711,6 +740,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
   if (w == 0 && lane == 0) {
     sh.refused = agent_load(&in.ctrl->status) < 0;  // a bad area, found by an earlier launch
     sh.error = sh.refused;
+    sh.now.gave_up = 0;
   }
   __syncthreads();
   int iters = 0, converged = 0, stop = 0;
@@ -755,16 +785,20 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
       bool e = false;
       constexpr int NU = ENF_RES_TILES / ENW + 1;  // all sums of a part at once: t <= ENF_RES_TILES
       EnfWord v[NU];
-      bool wait;
-      do {
-        wait = false;
+      for (int polls = 0;; ++polls) {
+        bool wait = false;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
           const int c = w + ENW * u;
           v[u] = c < t && c != I ? agent_load(slot(iters, I, c) + l) : 0;
           wait |= v[u] == ENF_EMPTY;
         }
-      } while (__ballot(wait) != 0);
+        if (__ballot(wait) == 0) break;
+        if (enf_gives_up(xmax + 4, polls, in.patience)) {
+          if (l == 0) sh.now.gave_up = 1;
+          break;
+        }
+      }
       __builtin_amdgcn_s_waitcnt(0);
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
@@ -776,7 +810,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
       sB[2 + 2 * ENW + w][l] = s;
       if (__ballot(e) != 0 && l == 0) sh.error = 1;
       __syncthreads();
-      if (w == 0) {
+      if (w == 0) {  // (after giving up these mean nothing, and are not used)
         const double(*p)[ETP] = sB + 2 + 2 * ENW;
         s = ((p[0][l] + p[1][l]) + (p[2][l] + p[3][l])) + ((p[4][l] + p[5][l]) + (p[6][l] + p[7][l]));
         const bool row = !EDGE || ig < n;
@@ -799,26 +833,34 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
       }
     } else if (w < 2) {
       const long r = (iters & 3) * static_cast<long>(t) + (w == 0 ? I : J);
-      rowc[w == 0 ? 3 : 7][l] = enf_value(enf_await(xscale + r * ET + l));
+      EnfWord v;
+      if (!enf_await(xscale + r * ET + l, v, xmax + 4, in.patience) && l == 0) sh.now.gave_up = 1;
+      rowc[w == 0 ? 3 : 7][l] = enf_value(v);
     }
     if (w == 2) {
-      const EnfWord st = enf_await(xstate + (iters & 3) * static_cast<long>(t) + min(l, t - 1));
+      EnfWord st;
+      if (!enf_await(xstate + (iters & 3) * static_cast<long>(t) + min(l, t - 1), st, xmax + 4, in.patience) && l == 0)
+        sh.now.gave_up = 1;
       // the streamed sweep sees a bad entry anywhere before any row's sum
       const bool all = __ballot(st != ENF_CLOSED) == 0, bad_entry = __ballot(st == ENF_FAILED) != 0;
       const bool no_sum = __ballot(st == ENF_NOSUM) != 0;
       if (l == 0) {
-        sh.dec[0] = all;
-        sh.dec[1] = bad_entry ? RAD_ENONFINITE : no_sum ? RAD_EZEROROW : 0;
+        sh.now.closed = all;
+        sh.now.code = bad_entry ? RAD_ENONFINITE : no_sum ? RAD_EZEROROW : 0;
       }
     }
     __syncthreads();
-    stop = sh.dec[1];
+    const auto now = sh.now;
+    stop = __builtin_amdgcn_readfirstlane(now.gave_up) ? ENF_GAVE_UP : __builtin_amdgcn_readfirstlane(now.code);
     if (stop) break;
     ++iters;
-    converged = tol > 0.0 && sh.dec[0];
+    converged = tol > 0.0 && __builtin_amdgcn_readfirstlane(now.closed);
   }
   const int l = fresh_lane(), jg = c0 + l, ig = r0 + l;
-  if (sh.refused) return;
+  if (stop == ENF_GAVE_UP || __builtin_amdgcn_readfirstlane(sh.refused)) return;
+  if (w == 0 && l == 0) sh.now.gave_up = atomicCAS(xmax + 4, ENF_RUNNING, ENF_DONE) == ENF_GIVEN_UP;
+  __syncthreads();
+  if (__builtin_amdgcn_readfirstlane(sh.now.gave_up)) return;
   if (stop && w == 0 && fresh_lane() == 0) raise_status(&in.ctrl->status, stop);
   // the maxima of the last iteration that was completed (an error ends one
   // without); the workgroup that adds its own last reports
@@ -1085,6 +1127,88 @@ __device__ __forceinline__ void enf_apply_scale_body(const EnfInst& in, long row
 
 __global__ void __launch_bounds__(256) enf_apply_scale(EnfInst in) { enf_apply_scale_body(in, blockIdx.x); }
 
+// An enforcement that a resident launch gave up: the streamed steps one after
+// another in one workgroup, which waits for nobody.  Reached when the GPU is
+// shared with something that holds places for ever; otherwise a launch that
+// leaves at once.
+template <bool HALF>
+__device__ __forceinline__ void enf_alone_body(const EnfInst& in, double tol, int max_iter, ResidentShared& sh,
+                                               double (*red)[3]) {
+  EnfCtrl* ctrl = in.ctrl;
+  const int n = in.n, t = in.t, tid = threadIdx.x;
+  auto status = [&]() {
+    __threadfence();
+    __syncthreads();
+    const int st = agent_load(&ctrl->status);
+    __syncthreads();
+    return st;
+  };
+  if (status() < 0) return;
+  for (int it = 0; it < max_iter; ++it) {
+    for (long p = 0; p < in.pairs; ++p) {
+      int I, J;
+      pair_from_index(p, t, I, J);
+      I = __builtin_amdgcn_readfirstlane(I);
+      J = __builtin_amdgcn_readfirstlane(J);
+      enf_sweep_pair<HALF, false>(in, p, I, J, it == 0, sh.sB, sh.rowc);
+      __syncthreads();
+    }
+    if (status() < 0) return;
+    double d = 0.0, rm = 0.0, em = 0.0;
+    for (int i = tid; i < n; i += ENF_THREADS) {
+      double s[FIN_LANES];
+#pragma unroll
+      for (int p = 0; p < FIN_LANES; ++p) {
+        s[p] = 0.0;
+        for (int q = p; q <= t; q += FIN_LANES) s[p] += in.partial[static_cast<long>(q) * n + i];
+      }
+      const double sum = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+      if (!(sum > 0.0)) raise_status(&ctrl->status, RAD_EZEROROW);
+      in.scale[i] = 1.0 / sum;
+      d = fmax(d, fabs(sum - 1.0));
+    }
+    for (long b = tid; b < in.pairs; b += ENF_THREADS) {
+      rm = fmax(rm, in.blkmax[2 * b]);
+      em = fmax(em, in.blkmax[2 * b + 1]);
+    }
+    red[tid][0] = d;
+    red[tid][1] = rm;
+    red[tid][2] = em;
+    if (status() < 0) return;
+    for (int half = ENF_THREADS / 2; half > 0; half /= 2) {
+      if (tid < half)
+        for (int c = 0; c < 3; ++c) red[tid][c] = fmax(red[tid][c], red[tid + half][c]);
+      __syncthreads();
+    }
+    const bool converged = tol > 0.0 && red[0][0] <= tol;
+    if (tid == 0) {
+      ctrl->iters = it + 1;
+      ctrl->last_defect = red[0][0];
+      ctrl->last_recip = red[0][2] > 0.0 ? red[0][1] / red[0][2] : 0.0;
+      ctrl->converged = converged;
+    }
+    __syncthreads();
+    if (converged) break;
+  }
+  __threadfence();
+  __syncthreads();
+  for (int row = 0; row < n; ++row) enf_apply_scale_body(in, row);
+}
+__device__ __forceinline__ void enf_alone_instance(const EnfInst& in, double tol, int max_iter) {
+  __shared__ ResidentShared sh;
+  __shared__ double red[ENF_THREADS][3];
+  if (agent_load(in.xch + enf_xch_words(in.t) - 1) != ENF_GIVEN_UP) return;
+  if (in.mode == RAD_KAPPA_HALF) enf_alone_body<true>(in, tol, max_iter, sh, red);
+  else enf_alone_body<false>(in, tol, max_iter, sh, red);
+}
+__global__ void __launch_bounds__(ENF_THREADS) enf_alone(EnfInst in, double tol, int max_iter) {
+  enf_alone_instance(in, tol, max_iter);
+}
+__global__ void __launch_bounds__(ENF_THREADS)
+enf_alone_batched(const EnfInst* __restrict__ ins, double tol, int max_iter) {
+  enf_alone_instance(ins[blockIdx.x], tol, max_iter);
+}
+
 // rows [row_start[k], row_start[k+1]) are instance k's
 __global__ void __launch_bounds__(256)
 enf_apply_scale_batched(const EnfInst* __restrict__ ins, const long* __restrict__ row_start, int count) {
@@ -1108,7 +1232,7 @@ __global__ void __launch_bounds__(256) enf_inv_area(EnfInst in) {
 __device__ __forceinline__ void enf_exchange_init(const EnfInst& in, long block, long blocks) {
   const long words = enf_xch_words(in.t);
   for (long k = block * blockDim.x + threadIdx.x; k < words; k += blocks * blockDim.x)
-    in.xch[k] = k < words - 4 ? ENF_EMPTY : 0;
+    in.xch[k] = k < words - 5 ? ENF_EMPTY : 0;
 }
 __global__ void __launch_bounds__(256) enf_resident_init(EnfInst in) {
   enf_inv_area_body(in, blockIdx.x * blockDim.x + threadIdx.x);
@@ -1152,6 +1276,12 @@ inline long resident_workgroups(const void* kernel, int per_cu, std::atomic<long
     cache[dev].store(v, std::memory_order_relaxed);
   }
   return v - 1;
+}
+
+// ENF_PATIENCE, or what the environment says (the tests: nobody is waited for).
+inline int resident_patience() {
+  const char* e = std::getenv("RAD_RESIDENT_PATIENCE");
+  return e ? std::atoi(e) : ENF_PATIENCE;
 }
 
 // Whether the stream is being captured (or cannot be asked): a cooperative
