@@ -2,7 +2,7 @@
 // spectral bands each, enforced and solved together.
 //
 // Enforcement (thesis Sec. 3.5.5): the instances that fit the chip together run
-// all their iterations in one cooperative launch per group, with F on chip; the
+// all their iterations in one launch per group, with F on chip; the
 // others, and everything in a captured run, share grids of one launch per step,
 // in which the tile pairs, row blocks and rows of every instance are
 // concatenated and a block finds its instance through a map or by a binary
@@ -16,8 +16,8 @@
 // step.
 //
 // rad_batch_prepare builds the schedule and uploads its descriptor tables
-// once; rad_batch_run only launches kernels (plain ones under capture), so it can
-// be captured in a HIP graph and replayed.
+// once; rad_batch_run only launches kernels (streamed enforcement under capture),
+// so it can be captured in a HIP graph and replayed.
 #include <cstring>
 #include <vector>
 
@@ -725,7 +725,7 @@ struct Sched {
 size_t elem(int prec) { return prec == RAD_PREC_FP32_IR ? 4 : 8; }
 
 // Instances whose tile pairs fit the chip together form a group: all their
-// iterations are one cooperative launch, F on chip (see enf_resident_tile).
+// iterations are one launch, F on chip (see enf_resident_tile).
 // An iteration of a group costs 4.5 to 10 us however many of its workgroups are
 // used; streamed, a batch costs about 10 us an iteration for its two launches
 // and 20 us for every 768 tile pairs.  So the instances that are small enough
@@ -1090,36 +1090,33 @@ extern "C" int32_t rad_batch_run(const rad_batch_plan* P, void* work, double enf
   if (enforce_iters > 0) {
     hipLaunchKernelGGL(enf_inv_area_batched, dim3(static_cast<unsigned>(P->total_fblk)), dim3(256), 0, s, ei,
                        fblk_start, C);
-    // a capture records no cooperative launch: everything is streamed then
+    // the groups take turns with other resident grids, which the replays of a
+    // capture could not: everything is streamed then
     static std::atomic<long> limit[64];
     const void* resident = reinterpret_cast<const void*>(enf_resident_batched);
     long first_pair = 0, first_fin = 0, first_row = 0;
     int first = 0;
     double bytes = P->sweep_bytes;
-    const long min_iters = ENF_RES_ITERS * (1 + static_cast<long>(P->groups.size())) / 2;
+    const long min_iters = ENF_RES_ITERS + static_cast<long>(P->groups.size()) / 4;
     if (P->streamed > 0 && enforce_iters >= min_iters && !stream_capturing(s) &&
         resident_workgroups(resident, ENF_RES_PER_CU, limit) >= RES_PAIRS) {
-      hipLaunchKernelGGL(enf_exchange_init_batched, dim3(static_cast<unsigned>(P->streamed) * ENF_XCH_BLOCKS), dim3(256),
-                         0, s, ei);
-      ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, P->sweep_bytes - P->streamed_bytes);
-      hipError_t e = hipSuccess;
-      for (const auto& g : P->groups) {
-        const EnfBlk* map = pair_map + g.first_pair;
-        void* args[] = {&ei, &map, &enforce_tol, &enforce_iters};
-        e = hipLaunchCooperativeKernel(resident, dim3(static_cast<unsigned>(g.pairs)), dim3(ENF_THREADS), args, 0, s);
-        if (e != hipSuccess) break;
-        first = P->streamed;
-      }
-      if (first > 0) {
-        RAD_HIP_CHECK(e);
+      ResidentTurn turn(s);
+      if (turn.ok()) {
+        hipLaunchKernelGGL(enf_exchange_init_batched, dim3(static_cast<unsigned>(P->streamed) * ENF_XCH_BLOCKS),
+                           dim3(256), 0, s, ei);
+        {
+          ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, P->sweep_bytes - P->streamed_bytes);
+          for (const auto& g : P->groups)
+            hipLaunchKernelGGL(enf_resident_batched, dim3(static_cast<unsigned>(g.pairs)), dim3(ENF_THREADS), 0, s, ei,
+                               pair_map + g.first_pair, enforce_tol, enforce_iters);
+        }
         hipLaunchKernelGGL(enf_alone_batched, dim3(static_cast<unsigned>(P->streamed)), dim3(ENF_THREADS), 0, s, ei,
                            enforce_tol, enforce_iters);
+        first = P->streamed;
         first_pair = P->streamed_pair;
         first_fin = P->streamed_fin;
         first_row = P->streamed_row;
         bytes = P->streamed_bytes;
-      } else {
-        (void)hipGetLastError();  // nothing was enqueued: everything is streamed
       }
     }
     if (first < C) {

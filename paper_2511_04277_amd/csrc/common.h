@@ -6,6 +6,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 #include <cstdio>
 #include <string>
 
@@ -109,6 +110,25 @@ inline hipError_t stream_wait(hipStream_t dst, hipStream_t src, hipEvent_t ev) {
   if (e != hipSuccess) return e;
   return hipStreamWaitEvent(dst, ev, 0);
 }
+
+// Held while a resident grid (one whose workgroups wait for each other) is
+// enqueued on s: such grids of a device run one after another, whatever their
+// streams, for two at once could each hold the places that the other waits for.
+// ok() is false if that cannot be arranged.
+class ResidentTurn {
+ public:
+  explicit ResidentTurn(hipStream_t s);
+  ~ResidentTurn();
+  ResidentTurn(const ResidentTurn&) = delete;
+  ResidentTurn& operator=(const ResidentTurn&) = delete;
+  bool ok() const { return ok_; }
+
+ private:
+  std::unique_lock<std::mutex> lock_;
+  hipStream_t s_;
+  int dev_ = -1;
+  bool ok_ = false;
+};
 
 // Loads and stores at the level that all XCDs share (no cache of one XCD
 // holds the value), for what workgroups of one launch exchange.

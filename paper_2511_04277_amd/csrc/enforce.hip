@@ -131,6 +131,26 @@ int32_t enforce_streamed(const EnfInst& in, double tol, int32_t max_iter, hipStr
   return RAD_OK;
 }
 
+// All iterations in one launch; false if the grid cannot have its turn (nothing
+// is enqueued then).
+bool enforce_resident(const EnfInst& in, double tol, int32_t max_iter, hipStream_t s) {
+  ResidentTurn turn(s);
+  if (!turn.ok()) return false;
+  hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, in.ctrl);
+  const long blocks = ceil_div(std::max<long>(in.n, enf_xch_words(in.t) / 8), 256);
+  hipLaunchKernelGGL(enf_resident_init, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, in);
+  const dim3 grid(static_cast<unsigned>(in.pairs));
+  {
+    ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, 16.0 * static_cast<double>(in.n) * (in.n + 1));
+    if (in.pairs <= resident_limit(true))
+      hipLaunchKernelGGL(enf_resident_wide, grid, dim3(ENF_THREADS), 0, s, in, tol, max_iter);
+    else
+      hipLaunchKernelGGL(enf_resident, grid, dim3(ENF_THREADS), 0, s, in, tol, max_iter);
+  }
+  hipLaunchKernelGGL(enf_alone, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
+  return true;
+}
+
 // The iteration itself, on scratch laid out by enf_layout (either the
 // caller's workspace or the library's static scratch).
 int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const double* area,
@@ -158,35 +178,18 @@ int32_t enforce_run(const char* who, double* F, int64_t n, int64_t ldf, const do
   in.ctrl = l.ctrl;
   in.xch = l.xch;
   in.patience = resident_patience();
-  // one tile needs no co-operation; a resident grid does, which a capture does
-  // not record
+  // one tile's workgroup waits for nobody; the others take turns, which the
+  // replays of a captured call could not
   bool resident = pairs == 1 || (t <= ENF_RES_TILES && max_iter >= ENF_RES_ITERS &&
                                  pairs <= resident_limit(false) && !stream_capturing(s));
-  if (pairs > 1) {
-    hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
-    const long words = resident ? enf_xch_words(t) : 0;
-    if (resident)
-      hipLaunchKernelGGL(enf_resident_init, dim3(static_cast<unsigned>(ceil_div(std::max<long>(n, words / 8), 256))),
-                         dim3(256), 0, s, in);
-    else
-      hipLaunchKernelGGL(enf_inv_area, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, in);
-  }
-  if (resident) {
+  if (pairs == 1) {
     ProfScope prof(s, RAD_PROF_ENFORCE_SWEEP, 0.0, 16.0 * static_cast<double>(n) * (n + 1));
-    if (pairs == 1) {
-      hipLaunchKernelGGL(enf_single, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
-    } else {
-      void* args[] = {&in, &tol, &max_iter};
-      const void* k = pairs <= resident_limit(true) ? reinterpret_cast<const void*>(enf_resident_wide)
-                                                    : reinterpret_cast<const void*>(enf_resident);
-      const hipError_t e = hipLaunchCooperativeKernel(k,
-                                                      dim3(static_cast<unsigned>(pairs)), dim3(ENF_THREADS), args, 0, s);
-      if (e != hipSuccess) {  // nothing was enqueued: one launch per step instead
-        (void)hipGetLastError();
-        resident = false;
-      } else {
-        hipLaunchKernelGGL(enf_alone, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
-      }
+    hipLaunchKernelGGL(enf_single, dim3(1), dim3(ENF_THREADS), 0, s, in, tol, max_iter);
+  } else {
+    if (resident) resident = enforce_resident(in, tol, max_iter, s);
+    if (!resident) {
+      hipLaunchKernelGGL(enf_init, dim3(1), dim3(64), 0, s, l.ctrl);
+      hipLaunchKernelGGL(enf_inv_area, dim3(static_cast<unsigned>(ceil_div(n, 256))), dim3(256), 0, s, in);
     }
   }
   if (!resident) {

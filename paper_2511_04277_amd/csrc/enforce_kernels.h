@@ -45,13 +45,12 @@ constexpr int ENF_RES_TILES = 31;  // most 64-row blocks of a resident model: 49
 // grid that needs a third on some CUs then waits for ever.
 constexpr int ENF_RES_PER_CU = 2;
 constexpr int ENF_RES_WAVES = 7;
-// Fewer iterations are streamed: the exchange's set-up and the cooperative launch
-// cost about 15 us, and an iteration saves 7 to 9.  84 faces, one and two
-// iterations: 21.7 and 32.3 us streamed, 35.5 and 40.7 on chip; 1984 faces: 37.3
-// and 55.5, 56.0 and 66.0; three: alike.  In a batch the groups are launched one
-// after another: three for one group, half as many for each one more (16 models
-// in five groups: 112 us and 60 an iteration more, 245 us and 40).
-constexpr int ENF_RES_ITERS = 3;
+// One iteration is streamed: it saves nothing that would pay for the exchange's
+// set-up.  84 faces, one and two iterations: 22 and 33 us streamed, 23 and 28 on
+// chip; 1984 faces: 38 and 57, 46 and 56.  A batch's groups are launched one after
+// another, and four more of them take an iteration more to win (16 models in five
+// groups, two and three iterations: 164 and 225 us streamed, 183 and 220 on chip).
+constexpr int ENF_RES_ITERS = 2;
 // Polls (about a microsecond each) until a waiting wave gives up.
 constexpr int ENF_PATIENCE = 1 << 20;
 typedef unsigned long long EnfWord;
@@ -622,10 +621,14 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 // enters.  An error, of the input or a bad area found by an earlier launch, travels
 // in the words (ENF_ERROR and the states), every workgroup leaves after the same
 // iteration, and the status is raised only then (a workgroup that left on a status
-// raised in this launch would leave the others waiting).  Cooperative launches run one after
-// another (four streams with 15 workgroups each take four times as long as one),
-// so a workgroup shares its CU with others of its own launch and with kernels that
-// end by themselves; why every one gets a place beside those is at ENF_RES_PER_CU.
+// raised in this launch would leave the others waiting).
+//
+// Resident grids of a process take turns (ResidentTurn), so a workgroup shares its
+// CU with others of its own launch and with kernels that end by themselves; why
+// every one gets a place beside those is at ENF_RES_PER_CU.  Ordinary launches:
+// the runtime gives cooperative ones a hardware queue beside the four of a process,
+// after which everything in several streams is slower (two streams of solves at
+// 2000 faces 757 -> 1320 us a call, four at 900 faces 248 -> 616).
 //
 // Should some not get a place all the same (another process on the GPU), every
 // wait ends: a wave whose patience is out declares the launch given up, unless it
@@ -934,7 +937,7 @@ __global__ void __launch_bounds__(ENF_THREADS, ENF_RES_WAVES) enf_resident(EnfIn
   enf_resident_body<false>(in, blockIdx.x, tol, max_iter, sh);
 }
 
-// Several models in one cooperative launch, each with an exchange of its own:
+// Several models in one launch, each with an exchange of its own:
 // map[b] names the instance and the tile pair of workgroup b.
 __global__ void __launch_bounds__(ENF_THREADS, ENF_RES_WAVES)
 enf_resident_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__ map, double tol, int max_iter) {
@@ -1259,16 +1262,15 @@ __global__ void enf_init_batched(const EnfInst* __restrict__ ins, int count) {
   if (k < count) enf_init_body(ins[k].ctrl);
 }
 
-// Workgroups of a cooperative kernel that the current device holds at once, at
-// most per_cu on a CU (0: no cooperative launches); cache: one slot per device.
+// Workgroups of a kernel that the current device holds at once, at most per_cu on
+// a CU (0: unknown); cache: one slot per device.
 inline long resident_workgroups(const void* kernel, int per_cu, std::atomic<long> (&cache)[64]) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
   long v = cache[dev].load(std::memory_order_relaxed);  // count + 1; 0: not looked up yet
   if (v == 0) {
-    int coop = 0, cus = 0, per = 0;
+    int cus = 0, per = 0;
     const bool ok =
-        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && coop &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, ENF_THREADS, 0) == hipSuccess;
     if (!ok) (void)hipGetLastError();
@@ -1284,8 +1286,8 @@ inline int resident_patience() {
   return e ? std::atoi(e) : ENF_PATIENCE;
 }
 
-// Whether the stream is being captured (or cannot be asked): a cooperative
-// launch is not recorded into graphs.
+// Whether the stream is being captured (or cannot be asked): replays would not
+// take turns with other resident grids.
 inline bool stream_capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &st) != hipSuccess) {

@@ -81,3 +81,38 @@ def test_batch_beside_solves():
     assert torch.equal(B, want_b)
     for a, w in zip([m[0] for m in models] + [b for bs in batch.B for b in bs], want):
         assert torch.equal(a, w)
+
+
+def test_grids_of_two_threads_take_turns():
+    """Enforcement with statistics (the host waits) from two threads, each with a stream of its own."""
+    import threading
+
+    need_gpu()
+    import paper_2511_04277_amd as rad
+    models = [_model(n, 5) for n in (1984, 1700)]
+    want, got, failed = [], [[], []], []
+    for m in models:
+        f = m[0].clone()
+        want.append((f, rad.enforce_vf_(f, m[1], m[2], tol=1e-6, max_iter=40)))
+    torch.cuda.synchronize()
+
+    def work(k):
+        try:
+            m = models[k]
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(8):
+                    f = m[0].clone()
+                    got[k].append((f, rad.enforce_vf_(f, m[1], m[2], tol=1e-6, max_iter=40)))
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:  # noqa: BLE001
+            failed.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
+    for k in (0, 1):
+        for f, st in got[k]:
+            assert torch.equal(f, want[k][0]) and st == want[k][1]
