@@ -131,7 +131,11 @@ class ResidentTurn {
 };
 
 // Loads and stores at the level that all XCDs share (no cache of one XCD
-// holds the value), for what workgroups of one launch exchange.
+// holds the value), for what workgroups of one launch exchange.  They are relaxed:
+// agent_settle between two of them orders them, for the wave (its earlier loads
+// have returned and its earlier stores have arrived) and for the compiler (no
+// access moves across it).  A release at agent scope would do the same and write
+// back the XCD's L2 as well.
 template <class T>
 __device__ __forceinline__ T agent_load(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -140,6 +144,7 @@ template <class T>
 __device__ __forceinline__ void agent_store(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void agent_settle() { __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
 // Device status codes raised by kernels (stored in an int32 flag; the
 // smallest (most negative) code wins via atomicMin).

@@ -567,7 +567,7 @@ __device__ __forceinline__ void enf_finalize_body(const EnfInst& in, int blk, in
       for (int q = 1; q < 4; ++q) x = fmax(x, fr[c][q]);
       agent_store(in.finred + 3 * static_cast<long>(blk) + c, x);
     }
-    __builtin_amdgcn_s_waitcnt(0);  // the maxima are there before the block counts itself done
+    agent_settle();  // the maxima are there before the block counts itself done
     last = atomicAdd(&ctrl->done, 1) == nblocks - 1;
   }
   __syncthreads();
@@ -802,7 +802,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
           break;
         }
       }
-      __builtin_amdgcn_s_waitcnt(0);
+      agent_settle();
 #pragma unroll
       for (int u = 0; u < NU; ++u) {
         const int c = w + ENW * u;
@@ -826,7 +826,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
                               : __ballot(zero) != 0        ? ENF_NOSUM
                               : __ballot(!(d <= tol)) == 0 ? ENF_CLOSED
                                                            : ENF_OPEN;
-        __builtin_amdgcn_s_waitcnt(0);
+        agent_settle();
         agent_store(xscale + ((iters & 3) * static_cast<long>(t) + I) * ET + l, enf_word(sc));
         if (l == 0) agent_store(xstate + (iters & 3) * static_cast<long>(t) + I, state);
         const int e2 = (iters + 2) & 3;
@@ -878,7 +878,7 @@ __device__ __forceinline__ void enf_resident_tile(const EnfInst& in, int I, int 
     }
     if (l < 3 && iters > 0) atomicMax(xmax + l, static_cast<EnfWord>(__double_as_longlong(x)));
   }
-  __builtin_amdgcn_s_waitcnt(0);
+  agent_settle();
   if (w == 0 && l == 0 && atomicAdd(xmax + 3, 1ull) + 1 == static_cast<EnfWord>(in.pairs)) {
     const double em = enf_value(agent_load(xmax + 2));
     in.ctrl->iters = iters;

@@ -133,7 +133,7 @@ check_optical(const double* __restrict__ eps, const double* __restrict__ rho, in
     sc->max_r = 0.0;
     sc->max_d = 0.0;
     sc->red[0] = sc->red[1] = 0.0;
-    __builtin_amdgcn_s_waitcnt(0);
+    agent_settle();
   }
   __syncthreads();
   constexpr int U = 4;
@@ -1006,7 +1006,7 @@ update_invert(GemmArgs<T> u, T* __restrict__ out, Scalars* sc) {
     gemm_tile32<T, false, true>(u, b % (NB / 32), b / (NB / 32), sh.corner);
   else
     __syncthreads();  // the tile's one stage
-  __builtin_amdgcn_s_waitcnt(0);  // this wave's part of C is stored
+  agent_settle();  // this wave's part of C is stored
   __syncthreads();
   if (threadIdx.x == 0) last = (atomicAdd(&sc->arrivals, 1) + 1) % CORNER == 0;
   __syncthreads();
