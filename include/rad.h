@@ -103,6 +103,9 @@ int32_t rad_version(void);
  * area:   n face areas A_i > 0.
  * n_rays: n rays emitted per face (> 0); may be NULL for RAD_KAPPA_HALF.
  * work:   >= rad_enforce_workspace_bytes(n).
+ * Up to 1984 faces all iterations run in one launch with F on chip, but for a
+ * captured call.  From 65 faces on its workgroups wait for each other, so such
+ * launches of one device run one after another, whatever their streams.
  * Device checks: F entries finite and >= 0 (RAD_ENONFINITE), zero rows
  * (RAD_EZEROROW).
  */
@@ -124,8 +127,9 @@ int32_t rad_enforce_vf(double* F, int64_t n, int64_t ldf, const double* area,
  * The call allocates nothing; the caller passes F, area, n_rays as for
  * rad_enforce_vf.  Every call on one GPU uses that GPU's single scratch
  * array: calls that overlap on one GPU (on different streams, or from
- * different threads) race; serialise them.  The device of ``stream`` must
- * be the current HIP device.
+ * different threads, or with the replay of a graph that holds one) race and
+ * their results are undefined, though every call ends; serialise them.  The
+ * device of ``stream`` must be the current HIP device.
  */
 #define RAD_ENFORCE_NOALLOC_BYTES ((size_t)36 << 20)
 int32_t rad_enforce_vf_noalloc(double* F, int64_t n, int64_t ldf,

@@ -116,3 +116,33 @@ def test_grids_of_two_threads_take_turns():
     for k in (0, 1):
         for f, st in got[k]:
             assert torch.equal(f, want[k][0]) and st == want[k][1]
+
+
+def test_calls_in_the_shared_scratch_end():
+    """rad_enforce_vf_noalloc from two streams at once: undefined results, but every call ends, and the
+    next ones are right."""
+    need_gpu()
+    from paper_2511_04277_amd import _lib as L
+    lib = L.lib()
+    models = [_model(n, 6) for n in (1200, 700)]
+
+    def call(f, m, stream):
+        assert lib.rad_enforce_vf_noalloc(f.data_ptr(), f.shape[0], f.stride(0), m[1].data_ptr(), m[2].data_ptr(),
+                                          L.RAD_KAPPA_FRACVAR, 0.0, 30, None, stream.cuda_stream) == 0
+
+    alone = []
+    for m in models:
+        alone.append(m[0].clone())
+        call(alone[-1], m, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+    streams = _streams(2)
+    for _ in range(6):
+        for s, m in zip(streams, models):
+            with torch.cuda.stream(s):
+                call(m[0].clone(), m, s)
+    torch.cuda.synchronize()
+    for m, want in zip(models, alone):
+        f = m[0].clone()
+        call(f, m, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert torch.equal(f, want)
