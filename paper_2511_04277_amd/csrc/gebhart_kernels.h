@@ -721,7 +721,7 @@ __device__ __forceinline__ void gj_pivots(const T* __restrict__ A, long lda, Sca
       for (int r = 0; r < 4; ++r) v[r] = d[r];
     }
     const double ap = fabs(static_cast<double>(pivots));
-    singular |= !(ap > tiny && ap < 1e300);
+    singular |= !(ap > tiny && ap <= 1.7976931348623157e308);  // too small, infinite or NaN
     __syncthreads();  // the new tile row s is complete; the old row and column have been read
     if (s + 1 == NT) break;
   }
