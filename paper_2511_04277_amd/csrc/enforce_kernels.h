@@ -603,7 +603,7 @@ enf_finalize_batched(const EnfInst* __restrict__ ins, const EnfBlk* __restrict__
 // that all XCDs share, so the data are their own signal: a word holds ENF_EMPTY
 // until its value is stored, and a reader loads until it is not.  Two one-way
 // trips an iteration; with counters that announce the data there were five
-// dependent round trips (n = 1081: 10.5 us an iteration, now 6.1; n = 1900: 16.5, now
+// dependent round trips (n = 1081: 10.5 us an iteration, now 6.4; n = 1900: 16.5, now
 // 9.5; n = 1985 streamed: 21).
 //
 // Buffers are used in turn and emptied by the diagonal workgroup of their row
